@@ -94,8 +94,7 @@ __device__ __forceinline__ double v_elem(const GArgs& g, int64_t vo, int64_t j, 
 // Column-major n x n matrices (V with ld = lda, V_bar with ld = ldb; a
 // batch's problems lda * n and ldb * n apart; X row-major with ld = n).
 // EPI_X computes op(A) = A^T (A = V),
-// EPI_D op(A) = A.  The linear block index is mapped so that all tiles of a
-// problem run on one XCD and share its L2.
+// EPI_D op(A) = A.
 // RV: V is not passed in; its elements are rebuilt by v_elem (a separate
 // instance, so that the path with V keeps its plain loads).
 // Two blocks per CU (66.5 KB of LDS each, 68 KB where V^T is rebuilt) are 4
@@ -106,11 +105,15 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
   const int64_t n = g.n;
   const int tiles = (int)((n + BM - 1) / BM);
   const int T = tiles * tiles;
-  const int B_ = blockIdx.x;
-  const int xcd = B_ % NXCD, slot = B_ / NXCD;
-  const int t = slot % T;
-  const int pb = NXCD * (slot / T) + xcd;
-  if (pb >= g.nb) return;
+  // (problem, tile) pairs in one list, cut into NXCD consecutive pieces of
+  // equal length, one per XCD: a problem's tiles still share an XCD's L2, and
+  // few problems fill all XCDs (a whole problem per XCD left 7 of 8 idle for
+  // one problem: n = 2000, 2.25 ms a product against 0.33)
+  const int64_t total = (int64_t)g.nb * T;
+  const int64_t piece = (total + NXCD - 1) / NXCD;
+  const int64_t it = (int64_t)(blockIdx.x % NXCD) * piece + blockIdx.x / NXCD;
+  if (blockIdx.x / NXCD >= piece || it >= total) return;
+  const int pb = (int)(it / T), t = (int)(it % T);
   const int tm = t % tiles, tn = t / tiles;
   const int64_t mo = (int64_t)pb * n * n;
   const int64_t vo = (int64_t)pb * n;
@@ -522,8 +525,7 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
   double* pd = (double*)(w + L.pd);
   double* pz = (double*)(w + L.pz);
   const int tiles = (int)((n + BM - 1) / BM);
-  const int64_t nbpad = (nbatch + NXCD - 1) / NXCD * NXCD;
-  const unsigned ggrid = (unsigned)(nbpad * tiles * tiles);
+  const unsigned ggrid = (unsigned)((nbatch * tiles * tiles + NXCD - 1) / NXCD * NXCD);
 
   double* sig = V ? nullptr : (double*)(w + L.sig);
   double* ixn = V ? nullptr : (double*)(w + L.ixn);
