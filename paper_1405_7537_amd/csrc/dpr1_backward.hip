@@ -445,18 +445,30 @@ __global__ void __launch_bounds__(256) k_bwd_final(int64_t n, int64_t nb, int nt
 // Without V_bar only the eigenvalue part remains, in closed form (O(n^2) per
 // problem instead of two n^3 products): d_bar_j = sum_k lam_bar_k v_jk^2,
 // z_bar_j = -2 sum_k lam_bar_k v_jk / ||x_k|| (from v_k^T z = -1/(rho ||x_k||)),
-// rho_bar = sum_k lam_bar_k / (rho ||x_k||)^2.  Grid (row blocks, problems);
-// the first row block of a problem also forms rho_bar.
+// rho_bar = sum_k lam_bar_k / (rho ||x_k||)^2.  Grid (row blocks, problems,
+// pieces of k); the constants of EIG_K eigenvalues at a time are staged in
+// LDS and read by every row of the block.  With one piece per row block the
+// sum over k is one serial chain on few CUs (n = 4096, V rebuilt: 16 blocks,
+// 967 us); eigonly_pieces cuts it until about 1024 blocks run, and
+// k_bwd_eigsum adds the pieces in order.  More than one piece: row sums to
+// part_d, part_z [problem][piece][n].
+constexpr int EIG_K = 64;
+static int64_t eigonly_pieces(int64_t n, int64_t nb) {
+  const int64_t rows = (n + 255) / 256 * nb;
+  return std::max<int64_t>(1, std::min<int64_t>((1024 + rows - 1) / rows, n / 128));
+}
 __global__ void __launch_bounds__(256) k_bwd_eigonly(GArgs g, const double* __restrict__ lam_bar,
                                                      const double* __restrict__ xnorm,
                                                      const double* __restrict__ rho, double* __restrict__ d_bar,
                                                      double* __restrict__ z_bar, double* __restrict__ rho_bar) {
+  __shared__ double red[256];
+  __shared__ double c_lb[EIG_K], c_lx[EIG_K], c_sig[EIG_K], c_mu[EIG_K], c_ix[EIG_K];
   const int64_t n = g.n;
   const int64_t p = blockIdx.y;
   const int64_t vo = p * n;
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (blockIdx.x == 0) {
-    __shared__ double red[256];
+  const int pieces = gridDim.z;
+  if (blockIdx.x == 0 && blockIdx.z == 0) {
     double acc = 0.0;
     for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
       const double lb = lam_bar ? lam_bar[vo + k] : 0.0;
@@ -471,17 +483,69 @@ __global__ void __launch_bounds__(256) k_bwd_eigonly(GArgs g, const double* __re
     }
     if (threadIdx.x == 0) rho_bar[p] = red[0];
   }
-  if (j >= n) return;
+  const int64_t chunk = (n + pieces - 1) / pieces;
+  const int64_t ka = min(n, (int64_t)blockIdx.z * chunk), kb = min(n, ka + chunk);
+  const bool ok = j < n;
+  const double dj = ok && !g.A ? g.d[vo + j] : 0.0, zj = ok && !g.A ? g.z[vo + j] : 0.0;
   double sd = 0.0, sz = 0.0;
-  for (int64_t k = 0; k < n; ++k) {
-    const double lb = lam_bar ? lam_bar[vo + k] : 0.0;
-    const double v = g.A ? g.A[p * g.lda * n + j + k * g.lda] : v_elem(g, vo, j, k);
-    const double t = lb * v;
-    sd = __builtin_fma(t, v, sd);
-    sz += t / xnorm[vo + k];
+  for (int64_t k0 = ka; k0 < kb; k0 += EIG_K) {
+    const int nk = (int)min((int64_t)EIG_K, kb - k0);
+    __syncthreads();  // the previous constants are no longer read
+    if ((int)threadIdx.x < nk) {
+      const int64_t k = vo + k0 + threadIdx.x;
+      const double lb = lam_bar ? lam_bar[k] : 0.0;
+      c_lb[threadIdx.x] = lb;
+      c_lx[threadIdx.x] = lb / xnorm[k];
+      if (!g.A) {
+        c_sig[threadIdx.x] = g.sig[k];
+        c_mu[threadIdx.x] = g.mu[k];
+        c_ix[threadIdx.x] = g.ixn[k];
+      }
+    }
+    __syncthreads();
+    if (!ok) continue;
+    if (g.A) {
+      const double* col = g.A + p * g.lda * n + j + k0 * g.lda;
+#pragma unroll 8
+      for (int q = 0; q < nk; ++q) {
+        const double v = col[q * g.lda];
+        sd = __builtin_fma(c_lb[q] * v, v, sd);
+        sz = __builtin_fma(c_lx[q], v, sz);
+      }
+    } else {
+#pragma unroll 4
+      for (int q = 0; q < nk; ++q) {
+        const double v = v_from(dj, zj, c_sig[q], c_mu[q], c_ix[q]);
+        sd = __builtin_fma(c_lb[q] * v, v, sd);
+        sz = __builtin_fma(c_lx[q], v, sz);
+      }
+    }
   }
-  d_bar[vo + j] = sd;
-  z_bar[vo + j] = -2.0 * sz;
+  if (!ok) return;
+  if (pieces == 1) {
+    d_bar[vo + j] = sd;
+    z_bar[vo + j] = -2.0 * sz;
+  } else {
+    const int64_t a = (p * pieces + blockIdx.z) * n + j;
+    g.part_d[a] = sd;
+    g.part_z[a] = sz;
+  }
+}
+__global__ void __launch_bounds__(256) k_bwd_eigsum(int64_t n, int64_t nb, int pieces,
+                                                    const double* __restrict__ part_d,
+                                                    const double* __restrict__ part_z, double* __restrict__ d_bar,
+                                                    double* __restrict__ z_bar) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= n * nb) return;
+  const int64_t p = t / n, j = t % n;
+  double sd = 0.0, sz = 0.0;
+  for (int q = 0; q < pieces; ++q) {
+    const int64_t a = (p * pieces + q) * n + j;
+    sd += part_d[a];
+    sz += part_z[a];
+  }
+  d_bar[t] = sd;
+  z_bar[t] = -2.0 * sz;
 }
 
 // rho of the single-problem call, moved to the device as a kernel argument
@@ -554,8 +618,14 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
   g.lda = lda;
   g.ldb = ldb;
   if (!V_bar) {
-    hipLaunchKernelGGL(k_bwd_eigonly, dim3((unsigned)((n + 255) / 256), (unsigned)nbatch), dim3(256), 0, st, g,
-                       lambda_bar, xnorm, rho, d_bar, z_bar, rho_bar);
+    const int64_t pieces = eigonly_pieces(n, nbatch);  // <= tiles, the capacity of the partials
+    g.part_d = pd;
+    g.part_z = pz;
+    hipLaunchKernelGGL(k_bwd_eigonly, dim3((unsigned)((n + 255) / 256), (unsigned)nbatch, (unsigned)pieces),
+                       dim3(256), 0, st, g, lambda_bar, xnorm, rho, d_bar, z_bar, rho_bar);
+    if (pieces > 1)
+      hipLaunchKernelGGL(k_bwd_eigsum, dim3((unsigned)((n * nbatch + 255) / 256)), dim3(256), 0, st, n, nbatch,
+                         (int)pieces, pd, pz, d_bar, z_bar);
     if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
     return DPR1_OK;
   }
