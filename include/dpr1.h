@@ -312,6 +312,21 @@ int dpr1_eig_backward(const double* d, const double* z, double rho, int64_t n,
                       const double* V_bar, int64_t ldvb, double* d_bar, double* z_bar,
                       double* rho_bar, void* work, size_t work_bytes, void* stream);
 
+/* dpr1_eig_backward_batched with V's leading dimension (ldv >= n, problems ldv n
+ * apart) and V_bar in either order: element (j, k) of V_bar at j vb_row +
+ * k vb_col, one of the strides 1 and the other >= n, problems n times that
+ * apart.  A row-major V_bar (vb_col = 1), as automatic differentiation
+ * produces it, is read as it is.  Argument errors -p as the parameter list
+ * orders them (z may be NULL only when V is given: -4; ldv -10; strides -13,
+ * -14; work_bytes -19).  Results are the same bit for bit for either order.
+ * Kernel launches only.                                                     */
+int dpr1_eig_backward_strided(int64_t nbatch, int64_t n, const double* d, const double* z,
+                              const double* rho, const int32_t* shift_idx, const double* mu,
+                              const double* xnorm, const double* V, int64_t ldv,
+                              const double* lambda_bar, const double* V_bar, int64_t vb_row,
+                              int64_t vb_col, double* d_bar, double* z_bar, double* rho_bar,
+                              void* work, size_t work_bytes, void* stream);
+
 /* Reducible inputs (Sec. 1): any finite d (any order, repeated values) and
  * any finite z (zeros allowed).  The poles are sorted decreasingly; a pole
  * with z_j == 0 is deflated (eigenpair (d_j, e_j)); a group of equal poles

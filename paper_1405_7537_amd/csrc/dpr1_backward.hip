@@ -70,7 +70,7 @@ struct GArgs {
   double* part_z;         // [nb][ntile][n]  sum_k V_jk u_k
   int has_B;              // 0: V_bar is null, P = 0
   int64_t lda;            // leading dimension of V (A), column-major
-  int64_t ldb;            // leading dimension of V_bar (EPI_X's B), column-major
+  int64_t ldb;            // leading dimension of B: V_bar's (columns, or rows with BR), n for X
 };
 
 // Element (j, k) of V for problem offset vo, recomputed from the forward's
@@ -97,10 +97,13 @@ __device__ __forceinline__ double v_elem(const GArgs& g, int64_t vo, int64_t j, 
 // EPI_D op(A) = A.
 // RV: V is not passed in; its elements are rebuilt by v_elem (a separate
 // instance, so that the path with V keeps its plain loads).
+// BR (EPI_X): V_bar comes row by row, V_bar(j, c) at j ldb + c, as autograd
+// hands it over; it is loaded as EPI_D loads X instead of being transposed
+// first (256 x 512: the copy took 680 us of a 4.0 ms step).
 // Two blocks per CU (66.5 KB of LDS each, 68 KB where V^T is rebuilt) are 4
 // waves per SIMD, which leaves 128 VGPRs a lane: the bound asks for that
 // budget.
-template <int EPI, bool RV>
+template <int EPI, bool RV, bool BR = EPI == EPI_D>
 __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
   const int64_t n = g.n;
   const int tiles = (int)((n + BM - 1) / BM);
@@ -119,7 +122,7 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
   const int64_t vo = (int64_t)pb * n;
   const double* A = RV ? nullptr : g.A + (int64_t)pb * g.lda * n;
   const double* Bm = g.B + (EPI == EPI_X ? (int64_t)pb * g.ldb * n : mo);
-  const int64_t lda = g.lda, ldb = g.ldb;
+  const int64_t lda = g.lda, ldb = EPI == EPI_X ? g.ldb : n;
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x;
   const int wv = tid / 64, lane = tid % 64;
@@ -145,11 +148,14 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
   // Element e2 of a thread: EPI_X: k = ek, m (or c) = em + STEP e2; EPI_D: m (or
   // c) = em, k = ek + STEP e2.  The per-thread part of each address is formed
   // once; what changes with k0 and e2 is uniform across the block.
-  constexpr int STEP = EPI == EPI_X ? NT / BK : NT / BM;
+  // The same for B, whose contiguous index is k where it comes column by column
+  // and c (BR) where it comes row by row.
+  constexpr int STEP = EPI == EPI_X ? NT / BK : NT / BM, STEPB = BR ? NT / BN : NT / BK;
   const int ek = EPI == EPI_X ? tid % BK : tid / BM;
   const int em = EPI == EPI_X ? tid / BK : tid % BM;
+  const int bk = BR ? tid / BN : tid % BK, bc = BR ? tid % BN : tid / BK;
   const double* pA = RV ? nullptr : (EPI == EPI_X ? A + ek + (m0 + em) * lda : A + (m0 + em) + ek * lda);
-  const double* pB = EPI == EPI_X ? Bm + ek + (n0 + em) * ldb : Bm + (int64_t)ek * n + (n0 + em);
+  const double* pB = BR ? Bm + bk * ldb + (n0 + bc) : Bm + bk + (n0 + bc) * ldb;
   double ra[PER], rb[PER];
   // V^T rebuilt (EPI_X): the tile's columns k = m0 .. m0 + BM - 1 keep their
   // (d_{i_k}, mu_k, 1/||x_k||) in LDS for the whole K loop, and a thread's
@@ -173,34 +179,36 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
     }
     __syncthreads();
   }
-  auto gload = [&](int64_t k0) {
+  // indices are below 2^20 + 128 (n is at most 2^20): 32 bits
+  const int ni = (int)n;
+  auto gload = [&](int k0) {
     double dj = 0.0, zj = 0.0;
     if constexpr (RV && EPI == EPI_X) {
-      const int64_t gk = k0 + ek;
-      if (gk < n) {
-        dj = g.d[vo + gk];
-        zj = g.z[vo + gk];
+      if (k0 + ek < ni) {
+        dj = g.d[vo + k0 + ek];
+        zj = g.z[vo + k0 + ek];
       }
     }
 #pragma unroll
     for (int e2 = 0; e2 < PER; ++e2) {
       if (EPI == EPI_X) {
-        // A^T(m, k) = V[k + m lda] and V_bar(k, c) = V_bar[k + c ldb], contiguous along k
-        const int64_t gk = k0 + ek, gm = m0 + em + STEP * e2, gc = n0 + em + STEP * e2;
+        // A^T(m, k) = V[k + m lda], contiguous along k
         const int ml = em + STEP * e2;
-        ra[e2] = (gm < n && gk < n)
+        ra[e2] = (m0 + ml < ni && k0 + ek < ni)
                      ? (RV ? v_from(dj, zj, colc[0][RV ? ml : 0], colc[1][RV ? ml : 0], colc[2][RV ? ml : 0])
                            : pA[k0 + STEP * e2 * lda])
                      : 0.0;
-        rb[e2] = (gk < n && gc < n) ? pB[k0 + STEP * e2 * ldb] : 0.0;
       } else {
-        // A(m, k) = V[m + k lda], contiguous along m; X(k, c) = X[k n + c] (row-major), contiguous along c
-        const int64_t gk = k0 + ek + STEP * e2, gm = m0 + em, gc = n0 + em;
-        ra[e2] = (gm < n && gk < n)
-                     ? (RV ? v_from(djr, zjr, g.sig[vo + gk], g.mu[vo + gk], g.ixn[vo + gk]) : pA[(k0 + STEP * e2) * lda])
+        // A(m, k) = V[m + k lda], contiguous along m
+        const int gk = k0 + ek + STEP * e2;
+        ra[e2] = (m0 + em < ni && gk < ni)
+                     ? (RV ? v_from(djr, zjr, g.sig[vo + gk], g.mu[vo + gk], g.ixn[vo + gk])
+                           : pA[(k0 + STEP * e2) * lda])
                      : 0.0;
-        rb[e2] = (gk < n && gc < n) ? pB[(k0 + STEP * e2) * n] : 0.0;
       }
+      // B(k, c): X[k n + c] (EPI_D), V_bar[k ldb + c] (BR) or V_bar[k + c ldb]
+      const int hk = k0 + bk + (BR ? STEPB * e2 : 0), hc = n0 + bc + (BR ? 0 : STEPB * e2);
+      rb[e2] = (hk < ni && hc < ni) ? (BR ? pB[(k0 + STEPB * e2) * ldb] : pB[k0 + STEPB * e2 * ldb]) : 0.0;
     }
   };
   auto sstore = [&](int buf) {
@@ -209,11 +217,11 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
       int e = tid + e2 * NT;
       if (EPI == EPI_X) {
         As[buf][e % BK][e / BK] = ra[e2];
-        Bs[buf][e % BK][e / BK] = rb[e2];
       } else {
         As[buf][e / BM][e % BM] = ra[e2];
-        Bs[buf][e / BN][e % BN] = rb[e2];
       }
+      if (BR) Bs[buf][e / BN][e % BN] = rb[e2];
+      else Bs[buf][e % BK][e / BK] = rb[e2];
     }
   };
 
@@ -223,8 +231,8 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
     sstore(0);
     __syncthreads();
     int buf = 0;
-    for (int64_t k0 = 0; k0 < n; k0 += BK) {
-      const bool more = k0 + BK < n;
+    for (int k0 = 0; k0 < ni; k0 += BK) {
+      const bool more = k0 + BK < ni;
       if (more) gload(k0 + BK);  // next slice in flight during this one
 #pragma unroll
       for (int ks = 0; ks < BK; ks += 4) {
@@ -577,8 +585,8 @@ static BLayout blayout(int64_t n, int64_t nb) {
 // The launches of both entry points (arguments checked there).
 static int run_backward(int64_t nbatch, int64_t n, const double* d, const double* z, const double* rho,
                         const int32_t* shift_idx, const double* mu, const double* xnorm, const double* V, int64_t lda,
-                        const double* lambda_bar, const double* V_bar, int64_t ldb, double* d_bar, double* z_bar,
-                        double* rho_bar, void* work, const BLayout& L, void* stream) {
+                        const double* lambda_bar, const double* V_bar, int64_t ldb, bool rows, double* d_bar,
+                        double* z_bar, double* rho_bar, void* work, const BLayout& L, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   char* w = (char*)work;
   double* X = (double*)(w + L.X);
@@ -629,10 +637,14 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
     if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
     return DPR1_OK;
   }
-  if (V)
-    hipLaunchKernelGGL((k_gemm<EPI_X, false>), dim3(ggrid), dim3(NT), 0, st, g);
+  if (V && rows)
+    hipLaunchKernelGGL((k_gemm<EPI_X, false, true>), dim3(ggrid), dim3(NT), 0, st, g);
+  else if (V)
+    hipLaunchKernelGGL((k_gemm<EPI_X, false, false>), dim3(ggrid), dim3(NT), 0, st, g);
+  else if (rows)
+    hipLaunchKernelGGL((k_gemm<EPI_X, true, true>), dim3(ggrid), dim3(NT), 0, st, g);
   else
-    hipLaunchKernelGGL((k_gemm<EPI_X, true>), dim3(ggrid), dim3(NT), 0, st, g);
+    hipLaunchKernelGGL((k_gemm<EPI_X, true, false>), dim3(ggrid), dim3(NT), 0, st, g);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
   hipLaunchKernelGGL(k_bwd_u, dim3((unsigned)nbatch), dim3(256), 0, st, n, tiles, pr, pc, y, u, rho_bar);
   g.B = X;
@@ -677,8 +689,8 @@ int dpr1_eig_backward_batched(int64_t nbatch, int64_t n, const double* d, const 
   if (!work) return -15;
   BLayout L = blayout(n, nbatch);
   if (work_bytes < L.total) return -16;
-  return run_backward(nbatch, n, d, z, rho, shift_idx, mu, xnorm, V, n, lambda_bar, V_bar, n, d_bar, z_bar, rho_bar,
-                      work, L, stream);
+  return run_backward(nbatch, n, d, z, rho, shift_idx, mu, xnorm, V, n, lambda_bar, V_bar, n, false, d_bar, z_bar,
+                      rho_bar, work, L, stream);
 }
 
 int dpr1_eig_backward(const double* d, const double* z, double rho, int64_t n, const int32_t* shift_idx,
@@ -704,7 +716,34 @@ int dpr1_eig_backward(const double* d, const double* z, double rho, int64_t n, c
   hipLaunchKernelGGL(k_set_rho, dim3(1), dim3(1), 0, (hipStream_t)stream, drho, rho);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
   return run_backward(1, n, d, z, drho, shift_idx, mu, xnorm, V, V ? ldv : n, lambda_bar, V_bar, V_bar ? ldvb : n,
-                      d_bar, z_bar, rho_bar, work, L, stream);
+                      false, d_bar, z_bar, rho_bar, work, L, stream);
+}
+
+int dpr1_eig_backward_strided(int64_t nbatch, int64_t n, const double* d, const double* z, const double* rho,
+                              const int32_t* shift_idx, const double* mu, const double* xnorm, const double* V,
+                              int64_t ldv, const double* lambda_bar, const double* V_bar, int64_t vb_row,
+                              int64_t vb_col, double* d_bar, double* z_bar, double* rho_bar, void* work,
+                              size_t work_bytes, void* stream) {
+  if (nbatch < 1 || nbatch > 65535) return -1;
+  if (n < 1 || n > (1 << 20)) return -2;
+  if (!d) return -3;
+  if (!z && !V) return -4;
+  if (!rho) return -5;
+  if (!shift_idx) return -6;
+  if (!mu) return -7;
+  if (!xnorm) return -8;
+  if (V && ldv < n) return -10;
+  const bool rows = V_bar && vb_row != 1;
+  if (rows && (vb_row < n || vb_col != 1)) return -13;
+  if (V_bar && !rows && vb_col < n) return -14;
+  if (!d_bar) return -15;
+  if (!z_bar) return -16;
+  if (!rho_bar) return -17;
+  if (!work) return -18;
+  BLayout L = blayout(n, nbatch);
+  if (work_bytes < L.total) return -19;
+  return run_backward(nbatch, n, d, z, rho, shift_idx, mu, xnorm, V, V ? ldv : n, lambda_bar, V_bar,
+                      V_bar ? (rows ? vb_row : vb_col) : n, rows, d_bar, z_bar, rho_bar, work, L, stream);
 }
 
 }  // extern "C"

@@ -73,6 +73,8 @@ def lib():
             L.dpr1_eig_backward_batched.argtypes = [i64, i64] + [vp] * 12 + [vp, C.c_size_t, vp]
             L.dpr1_eig_backward.argtypes = [vp, vp, C.c_double, i64, vp, vp, vp, vp, i64, vp, vp, i64, vp, vp,
                                             vp, vp, C.c_size_t, vp]
+            L.dpr1_eig_backward_strided.argtypes = ([i64, i64] + [vp] * 7 + [i64, vp, vp, i64, i64] + [vp] * 4
+                                                    + [C.c_size_t, vp])
         L.dpr1_general_workspace_size.argtypes = [i64]
         L.dpr1_general_workspace_size.restype = C.c_size_t
         L.dpr1_eig_general.argtypes = [vp, vp, C.c_double, i64, vp, vp, i64, vp, C.POINTER(Opts), vp,
@@ -447,6 +449,12 @@ def backward_batched(d, z, rho, shift_idx, mu, xnorm, V, lam_bar=None, V_bar=Non
     [nb] n x n matrices (tensors whose memory is V[b] with element (j, k) at j + k n).  V may be
     None: the kernels then recompute its elements from z and (shift_idx, mu, xnorm).
     Returns (d_bar [nb, n], z_bar [nb, n], rho_bar [nb])."""
+    n = d.shape[1]
+    return _backward_batched(d, z, rho, shift_idx, mu, xnorm, V, lam_bar, V_bar, 1, n, work)
+
+
+def _backward_batched(d, z, rho, shift_idx, mu, xnorm, V, lam_bar, V_bar, vb_row, vb_col, work=None):
+    """backward_batched with element (j, k) of each V_bar at j vb_row + k vb_col of its block."""
     nb, n = d.shape
     dev = d.device
     d_bar = torch.empty((nb, n), dtype=torch.float64, device=dev)
@@ -458,9 +466,9 @@ def backward_batched(d, z, rho, shift_idx, mu, xnorm, V, lam_bar=None, V_bar=Non
     for t in (d, z, rho, shift_idx, mu, xnorm, V, lam_bar, V_bar):
         if t is not None:
             assert t.is_contiguous() and t.device == dev
-    rc = lib().dpr1_eig_backward_batched(nb, n, _ptr(d), _ptr(z), _ptr(rho), _ptr(shift_idx), _ptr(mu),
-                                         _ptr(xnorm), _ptr(V), _ptr(lam_bar), _ptr(V_bar), _ptr(d_bar),
-                                         _ptr(z_bar), _ptr(rho_bar), _ptr(work), wb, _stream())
+    rc = lib().dpr1_eig_backward_strided(nb, n, _ptr(d), _ptr(z), _ptr(rho), _ptr(shift_idx), _ptr(mu),
+                                         _ptr(xnorm), _ptr(V), n, _ptr(lam_bar), _ptr(V_bar), vb_row, vb_col,
+                                         _ptr(d_bar), _ptr(z_bar), _ptr(rho_bar), _ptr(work), wb, _stream())
     _rc(rc, "dpr1_eig_backward_batched")
     return d_bar, z_bar, rho_bar
 
@@ -486,10 +494,19 @@ def backward(d, z, rho, shift_idx, mu, xnorm, V=None, lam_bar=None, V_bar=None, 
             return M, M.stride(1)
         return M.t().contiguous().t(), n
     Vc, ldv = colmajor(V)
-    Vbc, ldvb = colmajor(V_bar)
     for t in (d, z, shift_idx, mu, xnorm, lam_bar):
         if t is not None:
             assert t.is_contiguous() and t.device == dev
+    if V_bar is not None and V_bar.stride(1) == 1 and V_bar.stride(0) >= n and n > 1:
+        # V_bar row by row (as autograd produces it): read in place
+        rho_t = torch.full((1,), float(rho), dtype=torch.float64, device=dev)
+        rc = lib().dpr1_eig_backward_strided(1, n, _ptr(d), _ptr(z), _ptr(rho_t), _ptr(shift_idx), _ptr(mu),
+                                             _ptr(xnorm), _ptr(Vc), ldv, _ptr(lam_bar), _ptr(V_bar),
+                                             V_bar.stride(0), 1, _ptr(d_bar), _ptr(z_bar), _ptr(rho_bar),
+                                             _ptr(work), wb, _stream())
+        _rc(rc, "dpr1_eig_backward")
+        return d_bar, z_bar, rho_bar
+    Vbc, ldvb = colmajor(V_bar)
     rc = lib().dpr1_eig_backward(_ptr(d), _ptr(z), float(rho), n, _ptr(shift_idx), _ptr(mu), _ptr(xnorm), _ptr(Vc),
                                  ldv, _ptr(lam_bar), _ptr(Vbc), ldvb, _ptr(d_bar), _ptr(z_bar), _ptr(rho_bar),
                                  _ptr(work), wb, _stream())
@@ -579,5 +596,10 @@ class DPR1EigBatched(torch.autograd.Function):
     def backward(ctx, lam_bar, V_bar):
         d, z, rho, idx, mu, xn, Vst = ctx.saved_tensors
         lb = lam_bar.contiguous() if lam_bar is not None else None
-        Vb = V_bar.transpose(1, 2).contiguous() if V_bar is not None else None
-        return backward_batched(d.contiguous(), z.contiguous(), rho.contiguous(), idx, mu, xn, Vst, lb, Vb)
+        n = d.shape[1]
+        if V_bar is not None and V_bar.is_contiguous():
+            Vb, strides = V_bar, (n, 1)               # row by row: read in place
+        else:
+            Vb = V_bar.transpose(1, 2).contiguous() if V_bar is not None else None
+            strides = (1, n)
+        return _backward_batched(d.contiguous(), z.contiguous(), rho.contiguous(), idx, mu, xn, Vst, lb, Vb, *strides)
