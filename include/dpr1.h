@@ -186,7 +186,7 @@ int dpr1_eig(const double* d, const double* z, double rho, int64_t n, double* la
 /* For callers that cannot allocate device memory (code under hipGraph
  * capture, tight serving loops, harnesses that forbid hipMalloc): dpr1_eig
  * without the workspace argument.  Its workspace is a static device array of
- * the library, dpr1_noalloc_scratch_bytes() bytes (about 6.2 MB, sized for
+ * the library, dpr1_noalloc_scratch_bytes() bytes (about 7.5 MB, sized for
  * n = DPR1_NOALLOC_MAX_N), of which every GPU the library runs on holds its
  * own copy until the process ends.  The call allocates nothing (no hipMalloc,
  * no allocating library routine); on its first use on a device it looks up

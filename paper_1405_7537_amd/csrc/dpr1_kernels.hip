@@ -14,6 +14,11 @@
 //              Per eigenvalue: shift test, tip b in double-double, extreme
 //              root of the arrowhead secular function (model passes, the
 //              last one with compensated summation), near-zero test, ||x||.
+//              From order FAR_MIN on only the poles near the block's
+//              eigenvalues are summed one by one; the others enter through
+//              expansions whose moments k_far has formed.
+//   k_far   -- moments of the far-field expansions, one per block of 64
+//              eigenvalues and (from FAR_MIN2) one per 512.
 //              Instances for 4, 6 and 8 waves per SIMD (register budgets);
 //              the split W, the budget and the pass count are options that
 //              dpr1_autotune / dpr1_batched_autotune choose by timing.
@@ -89,8 +94,12 @@ struct KArgs {
   uint8_t* vflag;       // [N]  1: eigenpair finished in k_fix (its V column written after)
   int32_t* ctr;         // [0] fix count, [1] queue head, [2] k_fix queue head
   int32_t* stats;       // nullable
-  const int2* items;    // batched queue (p, k0) or nullptr
+  const int4* items;    // batched queue (p, k0, record of the wide level or -1, its slices), or nullptr
   int32_t nitems;
+  const double* far;    // far-field records (FAR_REC doubles each; a batch: record of item e at e), or
+                        // nullptr: every pole summed directly
+  int32_t far_wide, far_slices;  // one problem: first record of the wide level (0: none), its slices
+  int32_t far_min;      // a batch: smallest order with records
   int32_t nfixcap;  // capacity of `fix` (one slot per eigenvalue)
   int32_t W;
   int32_t mode_b, root, polish;
@@ -136,6 +145,14 @@ __device__ __forceinline__ double rcp_1nr(double x) {
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE); }
 __device__ __forceinline__ int lane_id() { return threadIdx.x % WAVE; }
 __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0; }
+
+// lane l's value to every lane (an SGPR), l a compile-time constant
+__device__ __forceinline__ double lane_value(double x, int l) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 
 // ------------------------------------------------- cross-wave reductions
 // Every wave of the block ends with the same sums, added in the same order,
@@ -481,8 +498,537 @@ __device__ __forceinline__ void model_step(double m, double g, double Sz, double
   nu = nn;
 }
 
-// One block of 64 eigenvalues (k0 .. k0+63) of problem p, W waves.
-__device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
+// ------------------------------------------------------------- far field
+// The sums of the method over the poles far from a block's 64 eigenvalues.
+// With c the middle and R = 1/iR the half-width of the interval that holds the
+// block's eigenvalues and shift poles, D_j = (d_j - c)/R, x = (t - c)/R,
+//   sum_far zeta_j^2/(d_j - t) = f(x) = sum_q m_q T_q(x),
+//   m_0 = sum a_j, m_q = 2 sum a_j u_j^q,
+//   u = 1/(D + sign(D) sqrt(D^2 - 1)), a = (zeta^2 iR)/(sign(D) sqrt(D^2 - 1))
+// (Chebyshev expansion of 1/(D - x) on [-1, 1]; geometric in u).  A pole is
+// far when |D| >= FAR_T = 2.5, so |u| <= 1/4.79 and FAR_P = 48 orders leave
+// less than 2^-106 of the sum of magnitudes; orders below FAR_Q = 24 are
+// accumulated in double-double, the others (below 2^-54 of it) in binary64.
+// The moments cost about 450 instructions per pole and block instead of the
+// 64 x 71 of the direct sums, and what the eigenvalue kernel does per
+// eigenvalue no longer grows with n.  A second, wide level (FAR_WIDE blocks
+// share an expansion, cut into slices of poles) takes the poles far from
+// those; the block's own level then covers only the poles between the two
+// windows.  Each pole is in exactly one of: the near window [a, b) (summed
+// directly), the block's level, the wide level.  The windows come from the
+// poles' positions alone, so any distribution is covered: where poles cluster
+// so that nothing is far, the window is the whole problem.  Bound by FP64
+// issue; measured at n = 32768 (uniform poles): k_far 72 us and k_eig 212 us
+// where the direct sums took 2520 us; the 2048-problem mix 383 and 1840 us
+// against 3560 us.  Errors of lambda, mu, ||x|| and V against an extended-
+// precision root are those of the direct sums (rms over 26 distributions: mu
+// 1.3e-16 both, ||x|| 1.3e-16 against 1.7e-16).
+constexpr int FAR_P = 48, FAR_Q = 24, FAR_ND = 26;
+constexpr double FAR_T = 2.5;
+constexpr int FAR_WIDE = 8;  // blocks of 64 eigenvalues that share a wide record
+// record: m_q (FAR_P), their low parts (FAR_Q), the moments of the
+// magnitudes sum zeta_j^2/|d_j - t| (FAR_ND), c, iR, the window a, b, and the
+// number of poles in the level
+constexpr int FR_LO = FAR_P, FR_ABS = FR_LO + FAR_Q, FR_C = FR_ABS + FAR_ND, FR_IR = FR_C + 1, FR_A = FR_C + 2,
+              FR_B = FR_C + 3, FR_CNT = FR_C + 4, FAR_REC = 104;
+static_assert(FR_CNT < FAR_REC, "far record");
+
+struct FarGeo {
+  double c, ir;
+  int a, b;  // near window: poles a .. b-1
+};
+
+// first j in [0, n) with (d_j - c) iR < t (STRICT) or <= t; the products
+// decrease with j, so one wave narrows 64-fold per step
+template <bool STRICT>
+__device__ __forceinline__ int far_first(const double* Dv, int n, double c, double ir, double t, int lane) {
+  int lo = 0, len = n;
+  while (len > 0) {
+    const int step = (len + WAVE - 1) / WAVE;
+    const int end = lo + len;
+    const int64_t j = lo + (int64_t)(lane + 1) * step - 1;
+    bool hit = true;
+    if (j < end) {
+      const double x = (Dv[j] - c) * ir;
+      hit = STRICT ? x < t : x <= t;
+    }
+    const int cnt = __popcll(__ballot(!hit));
+    lo = (int)min((int64_t)end, lo + (int64_t)cnt * step);
+    len = min(step - 1, end - lo);
+  }
+  return lo;
+}
+
+// Interval and near window of the eigenvalues e0 .. e0+ne-1.  Where the
+// positions leave the range in which the moments are safe (poles further than
+// 2^400 half-widths, or an interval that over- or underflows) every pole is
+// near.
+__device__ __forceinline__ FarGeo far_geo(const double* Dv, int n, int e0, int ne, int lane) {
+  FarGeo g;
+  const double dl = Dv[max(e0 - 1, 0)], dh = Dv[min(e0 + ne - 1, n - 1)];
+  g.c = 0.5 * dl + 0.5 * dh;
+  g.ir = 1.0 / fmax(dl - g.c, g.c - dh);
+  g.a = 0;
+  g.b = n;
+  const double x0 = (Dv[0] - g.c) * g.ir, x1 = (Dv[n - 1] - g.c) * g.ir;
+  if (g.ir < 0x1p500 && g.ir > 0x1p-500 && fabs(x0) < 0x1p400 && fabs(x1) < 0x1p400) {
+    g.a = far_first<true>(Dv, n, g.c, g.ir, FAR_T, lane);
+    g.b = far_first<false>(Dv, n, g.c, g.ir, -FAR_T, lane);
+  }
+  return g;
+}
+
+// t (hi, lo) to the accumulator (s, e): TwoSum into s, the rest into e
+__device__ __forceinline__ void far_acc(double& s, double& e, double th, double tl) {
+  const dd y = two_sum(s, th);
+  s = y.hi;
+  e += y.lo + tl;
+}
+
+// One exchange of a reduce-scatter over 2 H values: lanes with bit M set keep
+// the upper half.
+template <int H, int M, bool DD>
+__device__ __forceinline__ void far_halve(double (&h)[32], double (&l)[32], int lane) {
+  const bool up = (lane & M) != 0;
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const double kh = up ? h[i + H] : h[i], sh = up ? h[i] : h[i + H];
+    const double oh = __shfl_xor(sh, M);
+    if (DD) {
+      const double kl = up ? l[i + H] : l[i], sl = up ? l[i] : l[i + H];
+      const double ol = __shfl_xor(sl, M);
+      const dd y = two_sum(kh, oh);
+      h[i] = y.hi;
+      l[i] = y.lo + (kl + ol);
+    } else {
+      h[i] = kh + oh;
+    }
+  }
+}
+// After it lanes 2q and 2q+1 hold the wave's sum of value q in h[0] (and, with
+// DD, its low part in l[0]; without DD l is not touched).
+template <bool DD>
+__device__ __forceinline__ void far_reduce(double (&h)[32], double (&l)[32], int lane) {
+  far_halve<16, 32, DD>(h, l, lane);
+  far_halve<8, 16, DD>(h, l, lane);
+  far_halve<4, 8, DD>(h, l, lane);
+  far_halve<2, 4, DD>(h, l, lane);
+  far_halve<1, 2, DD>(h, l, lane);
+  const double oh = __shfl_xor(h[0], 1);
+  if (DD) {
+    const double ol = __shfl_xor(l[0], 1);
+    const dd y = two_sum(h[0], oh);
+    h[0] = y.hi;
+    l[0] = y.lo + (l[0] + ol);
+  } else {
+    h[0] = h[0] + oh;
+  }
+}
+
+constexpr int FAR_BLK = 256, FAR_SLICE = 2048, FAR_NSL_MAX = 1024;
+
+// Orders from which a problem has records, and from which it has the wide
+// level too.  Below FAR_MIN the near window of a block (about 2.5 times its
+// 64 poles) is most of the problem.
+constexpr int FAR_MIN = 384, FAR_MIN2 = 2048;
+static constexpr int64_t far_slices(int64_t n) {
+  const int64_t s = (n + FAR_SLICE - 1) / FAR_SLICE;
+  return s > FAR_NSL_MAX ? FAR_NSL_MAX : s;
+}
+// records of the wide level
+static constexpr int64_t far_wide_records(int64_t n) {
+  if (n < FAR_MIN2) return 0;
+  return ((n + WAVE - 1) / WAVE + FAR_WIDE - 1) / FAR_WIDE * far_slices(n);
+}
+
+// Moments of one (level, group, slice): the block's waves are dealt to the
+// poles above and below the window in proportion to their numbers (at least
+// one each), so that the sums of magnitudes come from the same accumulators.
+__device__ __forceinline__ void far_item(const Meta& M, const double* sd, const double* pairs, const double* z2lo, int e0, bool wide,
+                         int slice, int nsl, bool two, double* rec, double* lds) {
+  const int lane = lane_id(), wv = wave_id();
+  const int n = M.n;
+  const double* Dv = sd + M.off;
+  const FarGeo g = far_geo(Dv, n, e0, wide ? FAR_WIDE * WAVE : WAVE, lane);
+  int pa = 0, pb = n;
+  int a = g.a, b = g.b;
+  if (two && !wide) {
+    const FarGeo w = far_geo(Dv, n, e0 / (FAR_WIDE * WAVE) * (FAR_WIDE * WAVE), FAR_WIDE * WAVE, lane);
+    pa = w.a;
+    pb = w.b;
+    a = max(a, pa);
+    b = min(b, pb);
+  }
+  // this slice's part of the poles above [pa, a) and below [b, pb)
+  const int la = a - pa, lb = pb - b;
+  const int ua = pa + (int)((int64_t)la * slice / nsl), ub = pa + (int)((int64_t)la * (slice + 1) / nsl);
+  const int va = b + (int)((int64_t)lb * slice / nsl), vb = b + (int)((int64_t)lb * (slice + 1) / nsl);
+  constexpr int NW = FAR_BLK / WAVE;
+  const int cu = ub - ua, cv = vb - va;
+  int wu = 0;  // waves on the upper side
+  if (cu > 0) wu = cv == 0 ? NW : min(NW - 1, max(1, (int)(((int64_t)NW * cu + (cu + cv) / 2) / (cu + cv))));
+  const bool upper = wv < wu;
+  const int j0 = upper ? ua + wv * WAVE + lane : va + (wv - wu) * WAVE + lane;
+  const int j1 = upper ? ub : vb;
+  const int stride = (upper ? wu : NW - wu) * WAVE;
+
+  double mh[32], ml[32], md[32];
+#pragma unroll
+  for (int q = 0; q < 32; ++q) mh[q] = ml[q] = md[q] = 0.0;
+  for (int j = j0; j < j1; j += stride) {
+    const double dj = pairs[2 * (M.off + j)], z2 = pairs[2 * (M.off + j) + 1], z2l = z2lo[M.off + j];
+    // D and v = 1/D in double-double
+    const dd D = dd_mul_d(two_sum(dj, -g.c), g.ir);
+    const double r = rcp_1nr(D.hi);
+    const double ev = __builtin_fma(-r, D.lo, __builtin_fma(-r, D.hi, 1.0));
+    const dd v = fast_two_sum(r, r * ev);
+    // s = sqrt(1 - v^2) (0.91 < s <= 1), rs = 1/s to working precision
+    const dd vv = dd_mul(v, v);
+    dd E = fast_two_sum(1.0, -vv.hi);
+    E.lo -= vv.lo;
+    double rs = __builtin_amdgcn_rsq(E.hi);
+    rs = __builtin_fma(rs, __builtin_fma(-0.5 * E.hi * rs, rs, 0.5), rs);
+    rs = __builtin_fma(rs, __builtin_fma(-0.5 * E.hi * rs, rs, 0.5), rs);
+    const double s0 = E.hi * rs;
+    const dd sq = fast_two_sum(s0, (__builtin_fma(-s0, s0, E.hi) + E.lo) * (0.5 * rs));
+    // u = v/(1 + s)
+    dd den = fast_two_sum(1.0, sq.hi);
+    den.lo += sq.lo;
+    const double ru = rcp_1nr(den.hi);
+    const double u1 = v.hi * ru;
+    const double eu = __builtin_fma(-u1, den.lo, __builtin_fma(-u1, den.hi, v.hi) + v.lo);
+    const dd u = fast_two_sum(u1, eu * ru);
+    // a = zeta^2 (v iR)/s
+    const dd w = dd_mul(dd_mul_d(v, g.ir), dd{z2, z2l});
+    const double a1 = w.hi * rs;
+    const double ea = __builtin_fma(-a1, sq.lo, __builtin_fma(-a1, sq.hi, w.hi) + w.lo);
+    const dd t = fast_two_sum(a1, ea * rs);
+    far_acc(mh[0], ml[0], t.hi, t.lo);
+    double th = 2.0 * t.hi, tl = 2.0 * t.lo;
+#pragma unroll
+    for (int q = 1; q < FAR_Q; ++q) {
+      const double p = th * u.hi;
+      tl = __builtin_fma(tl, u.hi, __builtin_fma(th, u.lo, __builtin_fma(th, u.hi, -p)));
+      th = p;
+      far_acc(mh[q], ml[q], th, tl);
+    }
+#pragma unroll
+    for (int q = 0; q < FAR_P - FAR_Q; ++q) {
+      th *= u.hi;
+      md[q] += th;
+    }
+  }
+  far_reduce<true>(mh, ml, lane);
+  const double h0 = mh[0], l0 = ml[0];
+  far_reduce<false>(md, ml, lane);
+  __syncthreads();  // the previous item's sums are no longer read
+  if ((lane & 1) == 0) {
+    lds[(wv * 3) * 32 + lane / 2] = h0;
+    lds[(wv * 3 + 1) * 32 + lane / 2] = l0;
+    lds[(wv * 3 + 2) * 32 + lane / 2] = md[0];
+  }
+  __syncthreads();
+  // waves in order; the sum of magnitudes takes the lower side's terms negated
+  const int t = threadIdx.x;
+  if (t < FAR_Q) {
+    dd s = {0.0, 0.0};
+    double ab = 0.0;
+    for (int w = 0; w < NW; ++w) {
+      const double h = lds[(w * 3) * 32 + t], l = lds[(w * 3 + 1) * 32 + t];
+      const dd y = two_sum(s.hi, h);
+      s = {y.hi, s.lo + (y.lo + l)};
+      ab += w < wu ? h : -h;
+    }
+    s = fast_two_sum(s.hi, s.lo);
+    rec[t] = s.hi;
+    rec[FR_LO + t] = s.lo;
+    rec[FR_ABS + t] = ab;
+  } else if (t < FAR_P) {
+    double s = 0.0, ab = 0.0;
+    for (int w = 0; w < NW; ++w) {
+      const double h = lds[(w * 3 + 2) * 32 + t - FAR_Q];
+      s += h;
+      ab += w < wu ? h : -h;
+    }
+    rec[t] = s;
+    if (t < FAR_ND) rec[FR_ABS + t] = ab;
+  } else if (t == FAR_P) {
+    rec[FR_C] = g.c;
+    rec[FR_IR] = g.ir;
+    rec[FR_A] = (double)a;
+    rec[FR_B] = (double)b;
+    rec[FR_CNT] = (double)(la + lb);
+  }
+}
+
+// A batch's list, left in the workspace by the plan (the plan struct does not
+// hold it): the first nown items of the eigenvalue queue have a record of
+// their own (record = item), the wide level's entries are (problem, first
+// eigenvalue, slice | slices << 16, record).
+struct FarHdr {
+  int64_t nown, nwide, wide_off;  // wide_off: bytes from the start of the workspace
+};
+// The first wide block of one problem (blocks in order: the wide level's
+// (group, slice) pairs, then the blocks of 64), or of a batch the wide items,
+// then the items of the queue.
+struct FarArgs {
+  const Meta* meta;
+  const double* sd;
+  const double* pairs;
+  const double* z2lo;
+  double* rec;
+  int32_t ng, wide, slices;  // one problem: blocks of 64, first record of the wide level (0: none), its slices
+  const int4* items;         // a batch
+  const FarHdr* hdr;
+  const char* work;
+};
+__global__ void __launch_bounds__(FAR_BLK, 2) k_far(FarArgs F) {
+  __shared__ double lds[3 * 32 * (FAR_BLK / WAVE)];
+  const bool one = F.items == nullptr;
+  const int64_t nwide = one ? (F.wide ? (int64_t)((F.ng + FAR_WIDE - 1) / FAR_WIDE) * F.slices : 0) : F.hdr->nwide;
+  const int64_t cnt = nwide + (one ? F.ng : F.hdr->nown);
+  const int4* wi = one ? nullptr : reinterpret_cast<const int4*>(F.work + F.hdr->wide_off);
+  for (int64_t e = blockIdx.x; e < cnt; e += gridDim.x) {
+    const bool wide = e < nwide;
+    const int w = (int)(wide ? e : e - nwide);
+    int p = 0, e0, slice = 0, nsl = 1;
+    int64_t rec;
+    bool two = true;
+    if (one) {
+      e0 = wide ? w / F.slices * (FAR_WIDE * WAVE) : w * WAVE;
+      if (wide) {
+        slice = w % F.slices;
+        nsl = F.slices;
+      }
+      rec = wide ? F.wide + (int64_t)w : w;
+      two = F.wide != 0;
+    } else {
+      const int4 it = wide ? wi[w] : F.items[w];
+      p = it.x;
+      e0 = it.y;
+      rec = wide ? it.w : w;
+      if (wide) {
+        slice = it.z & 0xffff;
+        nsl = it.z >> 16;
+      } else {
+        two = it.z >= 0;
+      }
+    }
+    const Meta M = F.meta[p];
+    if (M.info != 0) continue;
+    far_item(M, F.sd, F.pairs, F.z2lo, e0, wide, slice, nsl, two, F.rec + rec * FAR_REC, lds);
+  }
+}
+
+// Values of an expansion held in LDS (the layout of a record) by Clenshaw's
+// recurrence, differentiated for the slopes.
+// f, f' and f''/2 at x
+__device__ __forceinline__ void far_eval(const double* cf, double x, double& f, double& f1, double& f2) {
+  const double x2 = 2.0 * x;
+  double b1 = 0.0, b2 = 0.0, p1 = 0.0, p2 = 0.0, h1 = 0.0, h2 = 0.0;
+#pragma unroll 5
+  for (int q = FAR_ND - 1; q >= 1; --q) {
+    const double h0 = __builtin_fma(x2, h1, __builtin_fma(2.0, p1, -h2));
+    const double p0 = __builtin_fma(x2, p1, __builtin_fma(2.0, b1, -p2));
+    const double b0 = __builtin_fma(x2, b1, cf[q] - b2);
+    b2 = b1;
+    b1 = b0;
+    p2 = p1;
+    p1 = p0;
+    h2 = h1;
+    h1 = h0;
+  }
+  f = __builtin_fma(x, b1, cf[0] - b2);
+  f1 = __builtin_fma(x, p1, b1 - p2);
+  f2 = __builtin_fma(x, h1, p1 - h2);
+}
+// the divided difference f[x, y], and f', f''/2 and the third derivative / 6 at y
+__device__ __forceinline__ void far_diff(const double* cf, double x, double y, double& fxy, double& f1, double& f2,
+                                         double& f3) {
+  const double x2 = 2.0 * x, y2 = 2.0 * y;
+  double a1 = 0.0, a2 = 0.0, c1 = 0.0, c2 = 0.0;
+  double b1 = 0.0, b2 = 0.0, p1 = 0.0, p2 = 0.0, h1 = 0.0, h2 = 0.0, g1 = 0.0, g2 = 0.0;
+#pragma unroll 5
+  for (int q = FAR_ND - 1; q >= 1; --q) {
+    const double c0 = __builtin_fma(y2, c1, __builtin_fma(2.0, a1, -c2));
+    const double a0 = __builtin_fma(x2, a1, cf[q] - a2);
+    const double g0 = __builtin_fma(y2, g1, __builtin_fma(2.0, h1, -g2));
+    const double h0 = __builtin_fma(y2, h1, __builtin_fma(2.0, p1, -h2));
+    const double p0 = __builtin_fma(y2, p1, __builtin_fma(2.0, b1, -p2));
+    const double b0 = __builtin_fma(y2, b1, cf[q] - b2);
+    a2 = a1;
+    a1 = a0;
+    c2 = c1;
+    c1 = c0;
+    b2 = b1;
+    b1 = b0;
+    p2 = p1;
+    p1 = p0;
+    h2 = h1;
+    h1 = h0;
+    g2 = g1;
+    g1 = g0;
+  }
+  fxy = __builtin_fma(y, c1, a1 - c2);
+  f1 = __builtin_fma(y, p1, b1 - p2);
+  f2 = __builtin_fma(y, h1, p1 - h2);
+  f3 = __builtin_fma(y, g1, h1 - g2);
+}
+// the sum of magnitudes at x
+__device__ __forceinline__ double far_mag(const double* cf, double x) {
+  const double x2 = 2.0 * x;
+  double m1 = 0.0, m2 = 0.0;
+#pragma unroll 5
+  for (int q = FAR_ND - 1; q >= 1; --q) {
+    const double m0 = __builtin_fma(x2, m1, cf[FR_ABS + q] - m2);
+    m2 = m1;
+    m1 = m0;
+  }
+  return __builtin_fma(x, m1, cf[FR_ABS] - m2);
+}
+// f in double-double at a double-double x
+__device__ __forceinline__ dd far_value(const double* cf, dd x) {
+  const double x2 = 2.0 * x.hi;
+  double b1 = 0.0, b2 = 0.0;
+#pragma unroll 6
+  for (int q = FAR_P - 1; q >= FAR_Q; --q) {
+    const double b0 = __builtin_fma(x2, b1, cf[q] - b2);
+    b2 = b1;
+    b1 = b0;
+  }
+  const dd X2 = {x2, 2.0 * x.lo};
+  dd B1 = {b1, 0.0}, B2 = {b2, 0.0};
+  for (int q = FAR_Q - 1; q >= 1; --q) {
+    const dd B0 = dd_add_same(dd_add_same(dd{cf[q], cf[FR_LO + q]}, dd_neg(B2)), dd_mul(X2, B1));
+    B2 = B1;
+    B1 = B0;
+  }
+  return dd_add_same(dd_add_same(dd{cf[0], cf[FR_LO]}, dd_neg(B2)), dd_mul(x, B1));
+}
+
+// Expansions of one block: the levels that hold poles (their records in LDS,
+// FAR_REC doubles each) and the near window.
+struct Far {
+  const double* cf;
+  int lev, na, nb;
+};
+
+// The record of the block's own level, and the wide level's slices added in
+// order, to LDS; every thread of the block calls it.
+__device__ __forceinline__ Far far_load(const double* r0, const double* r1, int nsl, int n, double* cf) {
+  const int t = threadIdx.x;
+  Far F;
+  F.cf = cf;
+  F.lev = 0;
+  F.na = 0;
+  F.nb = n;
+  if (!r0) return F;
+  F.na = (int)ldu(r0, FR_A);
+  F.nb = (int)ldu(r0, FR_B);
+  if (ldu(r0, FR_CNT) != 0.0) {
+    for (int q = t; q < FR_A; q += blockDim.x) cf[q] = r0[q];
+    F.lev = 1;
+  }
+  if (r1 && ldu(r1, FR_CNT) != 0.0) {
+    double* c1 = cf + F.lev * FAR_REC;
+    if (t < FAR_Q) {
+      dd s = {0.0, 0.0};
+#pragma unroll 4
+      for (int w = 0; w < nsl; ++w) {
+        const double* q = r1 + (int64_t)w * FAR_REC;
+        const dd y = two_sum(s.hi, q[t]);
+        s = {y.hi, s.lo + (y.lo + q[FR_LO + t])};
+      }
+      s = fast_two_sum(s.hi, s.lo);
+      c1[t] = s.hi;
+      c1[FR_LO + t] = s.lo;
+    } else if (t < FAR_P) {
+      double s = 0.0;
+      for (int w = 0; w < nsl; ++w) s += r1[(int64_t)w * FAR_REC + t];
+      c1[t] = s;
+    } else if (t < FAR_P + 2) {
+      c1[FR_C + t - FAR_P] = r1[FR_C + t - FAR_P];
+    }
+    if (t < FAR_ND) {
+      double s = 0.0;
+      for (int w = 0; w < nsl; ++w) s += r1[(int64_t)w * FAR_REC + FR_ABS + t];
+      c1[FR_ABS + t] = s;
+    }
+    F.lev += 1;
+  }
+  __syncthreads();
+  return F;
+}
+
+// The exterior eigenvalue (k = 1) lies outside its block's interval: its sums
+// over the poles outside the near window are taken directly, the block's
+// threads along the poles.  All threads call it; every thread receives the
+// totals.  red: 5 doubles per wave.
+__device__ __forceinline__ void ext_total(double (&v)[5], int W, int wv, int lane, double* red) {
+#pragma unroll
+  for (int q = 0; q < 5; ++q)
+    for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o);
+  __syncthreads();
+  if (lane == 0)
+    for (int q = 0; q < 5; ++q) red[5 * wv + q] = v[q];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 5; ++q) {
+    double s = red[q];
+    for (int w = 1; w < W; ++w) s += red[5 * w + q];
+    v[q] = s;
+  }
+}
+// f, f', f''/2 of the far poles at sigma + tau
+__device__ __forceinline__ void ext_eval(const double* P, int n, const Far& F, double sigma, double tau, double (&v)[5],
+                                         int W, int wv, int lane, double* red) {
+  for (int q = 0; q < 5; ++q) v[q] = 0.0;
+  const int len = F.na + (n - F.nb);
+  for (int e = threadIdx.x; e < len; e += blockDim.x) {
+    const int j = e < F.na ? e : e - F.na + F.nb;
+    const double den = (P[2 * j] - sigma) - tau, z2 = P[2 * j + 1];
+    const double r = rcp_1nr(den);
+    double t = z2 * r;
+    t = __builtin_fma(__builtin_fma(-t, den, z2), r, t);
+    v[0] += t;
+    v[1] += t * r;
+    v[2] = __builtin_fma(t * r, r, v[2]);
+  }
+  ext_total(v, W, wv, lane, red);
+}
+// the sums of a root-finder pass over the far poles at nu = m (s = 1):
+// sum zeta^2/(delta pp) (Neumaier partials of each thread), and those of
+// zeta^2/pp^2, zeta^2 delta/pp^3, zeta^2 delta^2/pp^4
+__device__ __forceinline__ void ext_sums(const double* P, int n, const Far& F, double sigma, double m, double (&v)[5],
+                                         int W, int wv, int lane, double* red) {
+  for (int q = 0; q < 5; ++q) v[q] = 0.0;
+  const int len = F.na + (n - F.nb);
+  for (int e = threadIdx.x; e < len; e += blockDim.x) {
+    const int j = e < F.na ? e : e - F.na + F.nb;
+    const double dl = P[2 * j] - sigma, z2 = P[2 * j + 1];
+    const double pp = __builtin_fma(m, dl, -1.0);
+    const double q = fmin(dl * pp, DBL_MAX);
+    const double r = rcp_1nr(q);
+    double t = z2 * r;
+    t = __builtin_fma(__builtin_fma(-t, q, z2), r, t);
+    const double u = (dl * r) * dl;
+    const double tp = t * u, tp3 = tp * u;
+    const double hi = fmax(v[0], t), lo = fmin(v[0], t);
+    const double y = hi + lo;
+    v[1] += (hi - y) + lo;
+    v[0] = y;
+    v[2] += tp;
+    v[3] += tp3;
+    v[4] = __builtin_fma(tp3, u, v[4]);
+  }
+  ext_total(v, W, wv, lane, red);
+}
+
+// One block of 64 eigenvalues (k0 .. k0+63) of problem p, W waves.  r0, r1: the
+// far-field records of the block's own level and of the wide level (nsl
+// slices), or nullptr; cf: LDS for two records, er: 5 doubles per wave.
+__device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double* red, const double* r0, const double* r1, int nsl,
+                          double* cf, double* er) {
   const int W = A.W;
   const int wv = wave_id();
   const int lane = lane_id();
@@ -499,13 +1045,6 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
   const bool valid = k < n;
   const int kk = valid ? k : n - 1;
 
-  // wave slice of the inner index and the window of possible shift indices
-  const int chunk = (n + W - 1) / W;
-  const int j0 = min(n, wv * chunk);
-  const int j1 = min(n, j0 + chunk);
-  const int wlo = max(0, k0 - 1);
-  const int whi = min(n, k0 + WAVE);
-
   if (n == 1) {
     // 1x1: lambda = d_1 + rho zeta_1^2, x = zeta_1/(d_1 - lambda)
     if (wv == 0 && lane == 0) {
@@ -519,6 +1058,16 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
     }
     return;
   }
+
+  // the near window, the wave's slice of it and the range of possible shift
+  // indices; poles outside the window enter through the expansions
+  const Far FF = far_load(r0, r1, nsl, n, cf);
+  const int chunk = (FF.nb - FF.na + W - 1) / W;
+  const int j0 = min(FF.nb, FF.na + wv * chunk);
+  const int j1 = min(FF.nb, j0 + chunk);
+  const int wlo = max(0, k0 - 1);
+  const int whi = min(n, k0 + WAVE);
+  const bool ext = FF.lev > 0 && k0 == 0;  // this block holds the exterior eigenvalue
 
   const double dk = Dv[kk];
   const double dkm1 = kk > 0 ? Dv[kk - 1] : 0.0;
@@ -563,7 +1112,33 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
     Fs[2] += tr;
     Fs[3] = __builtin_fma(tr, r, Fs[3]);
   });
+  double Ff = 0.0;  // the far poles' part of the sum
+  if (wv == 0) {
+    for (int l = 0; l < FF.lev; ++l) {
+      const double* q = FF.cf + l * FAR_REC;
+      const double ir = q[FR_IR], x = kk > 0 ? ((dk - q[FR_C]) + tau) * ir : 0.0;
+      double f, f1, f2;
+      far_eval(q, x, f, f1, f2);
+      const double fa = far_mag(q, x);
+      if (kk > 0) {
+        Ff += f;
+        Fs[0] += 0.5 * (f + fa);
+        Fs[1] += 0.5 * (f - fa);
+        Fs[2] = __builtin_fma(f1, ir, Fs[2]);
+        Fs[3] = __builtin_fma(f2 * ir, ir, Fs[3]);
+      }
+    }
+  }
   wg_sum<4>(Fs, W, wv, lane, red);
+  if (ext) {
+    double v[5];
+    ext_eval(P, n, FF, lane_value(dk, 0), lane_value(tau, 0), v, W, wv, lane, er);
+    if (lane == 0) {  // every far pole lies below: negative terms
+      Fs[1] += v[0];
+      Fs[2] += v[1];
+      Fs[3] += v[2];
+    }
+  }
   {
     const double sp = Fs[0], sn = Fs[1];
     Fs[0] = sp + sn;  // sum of the terms
@@ -587,6 +1162,7 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
       t = __builtin_fma(__builtin_fma(-t, den, z2), r, t);
       Fr[0] += t;
     });
+    if (wv == 0) Fr[0] += Ff;
     wg_sum<1>(Fr, W, wv, lane, red);
     if (open) F = 1.0 + rho * Fr[0];
   }
@@ -633,6 +1209,21 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
   });
   dd Pd = fast_two_sum(ps, pc);
   dd Nd = fast_two_sum(-ns, -nc);
+  if (wv == 0) {
+    // the far poles' f = P + N in double-double, cut with the sum of
+    // magnitudes P - N so that P and N keep their meaning in K_b (the split is
+    // exact: P rounded, N the rest)
+    for (int l = 0; l < FF.lev; ++l) {
+      const double* q = FF.cf + l * FAR_REC;
+      const dd x = dd_mul_d(two_sum(sigma, -q[FR_C]), q[FR_IR]);
+      const dd f = far_value(q, x);
+      const double pf = 0.5 * (f.hi + far_mag(q, x.hi));
+      dd nf = two_sum(f.hi, -pf);
+      nf.lo += f.lo;
+      Pd = dd_add_same(Pd, dd{pf, 0.0});
+      Nd = dd_add_same(Nd, nf);
+    }
+  }
   wg_sum_dd(Pd, W, wv, lane, red);
   wg_sum_dd(Nd, W, wv, lane, red);
   const dd rr = dd_div(dd{1.0, 0.0}, dd{rho, 0.0});
@@ -714,6 +1305,41 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
   }
   const double L0 = L, U0 = U;
 
+  // The far poles' part of a pass at nu = m, in wave 0 (the other waves add
+  // 0): with mu = s/m, zeta^2/(delta' pp) = |mu| zeta^2/((d - sigma)(d - lambda)),
+  // a divided difference of f, and zeta^2/pp^2, zeta^2 delta'/pp^3, zeta^2
+  // delta'^2/pp^4 are its derivatives at lambda times powers of |mu|.  The
+  // exterior eigenvalue takes its direct sums instead.
+  auto far_sums = [&](double m, double (&v)[4]) {
+    v[0] = v[1] = v[2] = v[3] = 0.0;
+    if (wv == 0) {
+      const double muv = s / m, am = fabs(muv);
+      for (int l = 0; l < FF.lev; ++l) {
+        const double* q = FF.cf + l * FAR_REC;
+        const double ir = q[FR_IR], x = (sigma - q[FR_C]) * ir;
+        const double y = interior ? __builtin_fma(muv, ir, x) : x;
+        double fxy, f1, f2, f3;
+        far_diff(q, x, y, fxy, f1, f2, f3);
+        const double mi = am * ir, ms = muv * ir;  // in units of the half-width
+        v[0] = __builtin_fma(fxy, mi, v[0]);
+        v[1] = __builtin_fma(f1 * am, mi, v[1]);
+        v[2] = __builtin_fma(__builtin_fma(ms, f2, f1) * am, am * mi, v[2]);
+        v[3] = __builtin_fma(__builtin_fma(ms, __builtin_fma(ms, f3, 2.0 * f2), f1) * am, am * (am * mi), v[3]);
+      }
+    }
+    if (ext) {
+      double e[5];
+      ext_sums(P, n, FF, lane_value(sigma, 0), lane_value(m, 0), e, W, wv, lane, er);
+      if (lane == 0) {
+        const bool first = wv == 0;
+        v[0] = first ? e[0] + e[1] : 0.0;
+        v[1] = first ? e[2] : 0.0;
+        v[2] = first ? e[3] : 0.0;
+        v[3] = first ? e[4] : 0.0;
+      }
+    }
+  };
+
   if (A.root == 0) {
     // -------- bisection in the order of the binary64 numbers
     while (wave_any(!done)) {
@@ -727,6 +1353,9 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
           if (seg == 1 && j == i) t = 0.0;
           S[0] += t;
         });
+        double fs[4];
+        far_sums(m, fs);
+        S[0] += fs[0];
         wg_sum<1>(S, W, wv, lane, red);
         ++iters;
       }
@@ -775,6 +1404,11 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
           S[1] += tp;
           S[2] = __builtin_fma(tp, u, S[2]);  // w_j/(m - xi_j)^3
         });
+        double fs[4];
+        far_sums(m, fs);
+        S[0] += fs[0];
+        S[1] += fs[1];
+        S[2] += fs[2];
         wg_sum<3>(S, W, wv, lane, red);
         ++iters;
         ++passes;
@@ -856,6 +1490,14 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
     Sp[1] += tp3;
     Sp[2] = __builtin_fma(tp3, u, Sp[2]);               // zeta_j^2 delta'_j^2/pp^4
   });
+  {
+    double fs[4];
+    far_sums(m, fs);
+    neu(fs[0]);
+    Sp[0] += fs[1];
+    Sp[1] += fs[2];
+    Sp[2] += fs[3];
+  }
   wg_sum_comp(cs, cc, W, wv, lane, red);
   wg_sum<3>(Sp, W, wv, lane, red);
   const double Sz = (cs + cc) / zi2;
@@ -958,20 +1600,36 @@ __device__ void eig_block(const KArgs& A, int p, int k0, double* red) {
 template <int OCC>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(OCC, OCC))) k_eig(KArgs A) {
   extern __shared__ double red[];
-  if (A.items == nullptr) {
-    eig_block(A, 0, (A.g0 + (int)blockIdx.x) * WAVE, red);
-    return;
-  }
-  // persistent: take (problem, first eigenvalue) items from the queue
+  __shared__ double cf[2 * FAR_REC], er[5 * MAXW];
+  // one problem: block b solves group g0 + b; a batch: persistent blocks take
+  // (problem, first eigenvalue) items from the queue
   __shared__ int item;
+  const bool one = A.items == nullptr;
   for (;;) {
-    if (threadIdx.x == 0) item = atomicAdd(&A.ctr[1], 1);
-    __syncthreads();
-    int it = item;
-    __syncthreads();
-    if (it >= A.nitems) break;
-    int2 pk = A.items[it];
-    eig_block(A, pk.x, pk.y, red);
+    int p = 0, k0, nsl = A.far_slices;
+    const double *r0 = nullptr, *r1 = nullptr;
+    if (one) {
+      const int g = A.g0 + (int)blockIdx.x;
+      k0 = g * WAVE;
+      if (A.far) r0 = A.far + (int64_t)g * FAR_REC;
+      if (A.far_wide) r1 = A.far + (A.far_wide + (int64_t)(g / FAR_WIDE) * nsl) * FAR_REC;
+    } else {
+      if (threadIdx.x == 0) item = atomicAdd(&A.ctr[1], 1);
+      __syncthreads();
+      const int it = __builtin_amdgcn_readfirstlane(item);
+      __syncthreads();
+      if (it >= A.nitems) break;
+      const int4 pk = A.items[it];
+      p = pk.x;
+      k0 = pk.y;
+      nsl = pk.w;
+      if (A.far && A.meta[p].n >= A.far_min) {
+        r0 = A.far + (int64_t)it * FAR_REC;
+        if (pk.z >= 0) r1 = A.far + (int64_t)pk.z * FAR_REC;
+      }
+    }
+    eig_block(A, p, k0, red, r0, r1, nsl, cf, er);
+    if (one) break;
   }
 }
 
@@ -1667,13 +2325,6 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
 // constants loaded while the current one is written.  The arithmetic is
 // vec_block's.
 constexpr int SWEEP_U = 8, SWEEP_WAVES = 2048;
-// lane l's value to every lane (an SGPR), l a compile-time constant
-__device__ __forceinline__ double lane_value(double x, int l) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
 __device__ void vec_sweep(const VArgs& v, int g, int nw) {
   const Meta M = v.meta[0];
   if (M.info != 0) return;
@@ -2072,12 +2723,16 @@ __global__ void __launch_bounds__(FIXT) k_remedy(KArgs A, OArgs O) {
 
 // ===================================================================== host
 struct Layout {
-  size_t meta, sd, sz, pairs, z2lo, ii, mu, xs, lam, csig, cinv, fix, vflag, items, groups, part, ctr, total;
+  size_t meta, sd, sz, pairs, z2lo, ii, mu, xs, lam, csig, cinv, fix, vflag, items, groups, part, ctr, far, total;
 };
 
 static constexpr size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
-static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t ngroups = 0) {
+// nrec: far-field records.  A batch's list of wide items (and their records
+// past the queue's) follows L.total; its offset is in the header at FAR_HDR
+// behind the counters.
+constexpr size_t FAR_HDR = 128;
+static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t ngroups, int64_t nrec) {
   Layout L{};
   size_t o = 0;
   L.meta = o; o = al(o + sizeof(Meta) * nprob);
@@ -2093,12 +2748,31 @@ static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t
   L.cinv = o; o = al(o + 8 * N);
   L.fix = o; o = al(o + sizeof(FixItem) * N);
   L.vflag = o; o = al(o + N);
-  L.items = o; o = al(o + sizeof(int2) * nitems);
+  L.items = o; o = al(o + sizeof(int4) * nitems);
   L.groups = o; o = al(o + sizeof(int4) * ngroups);
   L.part = o; o = al(o + 3 * sizeof(double) * PREP_MAX_SPLIT);
-  L.ctr = o; o = al(o + 64);
+  L.ctr = o; o = al(o + FAR_HDR + sizeof(FarHdr));
+  L.far = o; o = al(o + 8 * (size_t)FAR_REC * nrec);
   L.total = o;
   return L;
+}
+
+// One problem: a record per block of 64 eigenvalues and the wide level's.
+static constexpr Layout layout_single(int64_t n) {
+  return layout(1, n, 0, 0, n < FAR_MIN ? 0 : (n + WAVE - 1) / WAVE + far_wide_records(n));
+}
+// A batch: records for the whole queue; its wide level lies behind.
+static Layout layout_batch(int64_t nprob, int64_t N, int64_t ngroups) {
+  const int64_t nitems = N / WAVE + nprob;  // upper bound of sum ceil(n_p/64)
+  return layout(nprob, N, nitems, ngroups, nitems);
+}
+static size_t batch_bytes(const Layout& L, int64_t nwide) {
+  return L.total + al(8 * (size_t)FAR_REC * nwide) + al(sizeof(int4) * nwide);
+}
+static int64_t count_wide(int64_t nprob, const int64_t* offs) {
+  int64_t c = 0;
+  for (int64_t p = 0; p < nprob; ++p) c += far_wide_records(offs[p + 1] - offs[p]);
+  return c;
 }
 
 static void fill_opts(const dpr1_opts* in, dpr1_opts* o) {
@@ -2210,7 +2884,7 @@ static size_t red_bytes(int W) { return W > 1 ? sizeof(double) * RED_NV * W * WA
 // the process; host code reaches it only through the address that
 // hipGetSymbolAddress returns on that device (the name itself is a host-side
 // stand-in, not a device address).
-constexpr size_t NOALLOC_BYTES = layout(1, DPR1_NOALLOC_MAX_N, 0).total;
+constexpr size_t NOALLOC_BYTES = layout_single(DPR1_NOALLOC_MAX_N).total;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
@@ -2255,7 +2929,7 @@ void dpr1_default_opts(dpr1_opts* o) {
 
 size_t dpr1_workspace_size(int64_t n) {
   if (n < 1) return 0;
-  return layout(1, n, 0).total;
+  return layout_single(n).total;
 }
 
 #define HIPCHECK(x)                           \
@@ -2281,7 +2955,7 @@ static hipStream_t aux_stream() {
   return aux_streams[dev];
 }
 
-static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, const int64_t* offs,
+static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int64_t nmax, const int64_t* offs,
                         int64_t n_single, const double* d, const double* z, const double* rho_dev,
                         double rho_host, double* lambda, double* V, const int64_t* voffs, int64_t ldv,
                         int32_t* shift_idx, double* mu, double* xnorm, int32_t* info, int32_t* stats,
@@ -2302,7 +2976,12 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, cons
   A.vflag = (uint8_t*)(w + L.vflag);
   A.ctr = (int32_t*)(w + L.ctr);
   A.stats = stats;
-  A.items = persistent_grid ? (const int2*)(w + L.items) : nullptr;
+  A.items = persistent_grid ? (const int4*)(w + L.items) : nullptr;
+  const bool far = nmax >= FAR_MIN;
+  A.far = far ? (const double*)(w + L.far) : nullptr;
+  A.far_wide = far && !persistent_grid && far_wide_records(N) ? (int32_t)nitems : 0;
+  A.far_slices = (int32_t)far_slices(N);
+  A.far_min = FAR_MIN;
   A.nitems = (int32_t)nitems;
   A.nfixcap = (int32_t)N;
   A.W = W;
@@ -2315,7 +2994,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, cons
   // whose stragglers (under a tenth of the roots) are finished beside the V
   // write; a batch runs one more, since its many small problems would queue
   // their stragglers in k_fix.
-  A.main_passes = o.main_passes > 0 ? o.main_passes : (persistent_grid ? 3 : 2);
+  A.main_passes = o.main_passes > 0 ? o.main_passes : far ? 4 : (persistent_grid ? 3 : 2);
   A.remedy = o.remedy;
   A.knu_thr = o.knu_thr;
   A.knu = o.knu;
@@ -2326,6 +3005,22 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, cons
   hipLaunchKernelGGL(k_prep, dim3((unsigned)(nsplit > 1 ? nsplit : nprob)), dim3(256), 0, st, (int)nprob, nsplit,
                      offs, n_single, d, z, rho_dev, rho_host, meta, (double*)A.sd, (double*)A.sz,
                      (double*)A.pairs, (double*)A.z2lo, info, (double*)(w + L.part), A.ctr + 8);
+  if (far) {
+    FarArgs F;
+    F.meta = meta;
+    F.sd = A.sd;
+    F.pairs = A.pairs;
+    F.z2lo = A.z2lo;
+    F.rec = (double*)(w + L.far);
+    F.ng = (int32_t)nitems;
+    F.wide = A.far_wide;
+    F.slices = A.far_slices;
+    F.items = A.items;
+    F.hdr = (const FarHdr*)(w + L.ctr + FAR_HDR);
+    F.work = w;
+    const int64_t blocks = persistent_grid ? std::min<int64_t>(nitems, 2048) : nitems + far_wide_records(N);
+    hipLaunchKernelGGL(k_far, dim3((unsigned)blocks), dim3(FAR_BLK), 0, st, F);
+  }
   HIPCHECK(hipGetLastError());
   hipEvent_t* ev = (hipEvent_t*)o.events;
   double* csig = (double*)(w + L.csig);
@@ -2500,7 +3195,7 @@ int dpr1_eig(const double* d, const double* z, double rho, int64_t n, double* la
   if (!lambda) return -5;
   if (V && ldv < n) return -7;
   if (!info) return -11;
-  Layout L = layout(1, n, 0);
+  Layout L = layout_single(n);
   if (!work) return -14;
   if (work_bytes < L.total) return -15;
   dpr1_opts o;
@@ -2509,7 +3204,7 @@ int dpr1_eig(const double* d, const double* z, double rho, int64_t n, double* la
     return -13;
   int64_t nblocks = (n + WAVE - 1) / WAVE;
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nblocks, n, occ_of(o));
-  return launch_solve(L, (char*)work, 1, n, nullptr, n, d, z, nullptr, rho, lambda, V, nullptr, ldv, shift_idx,
+  return launch_solve(L, (char*)work, 1, n, n, nullptr, n, d, z, nullptr, rho, lambda, V, nullptr, ldv, shift_idx,
                       mu, xnorm, info, stats, o, W, nblocks, 0, 0, (hipStream_t)stream);
 }
 
@@ -2534,10 +3229,10 @@ int dpr1_eig_noalloc(const double* d, const double* z, double rho, int64_t n, do
     return -13;
   void* work = scratch_on_current_device();
   if (!work) return DPR1_EHIP;
-  const Layout L = layout(1, n, 0);
+  const Layout L = layout_single(n);
   int64_t nblocks = (n + WAVE - 1) / WAVE;
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nblocks, n, occ_of(o));
-  return launch_solve(L, (char*)work, 1, n, nullptr, n, d, z, nullptr, rho, lambda, V, nullptr, ldv, shift_idx,
+  return launch_solve(L, (char*)work, 1, n, n, nullptr, n, d, z, nullptr, rho, lambda, V, nullptr, ldv, shift_idx,
                       mu, xnorm, info, stats, o, W, nblocks, 0, 0, (hipStream_t)stream,
                       /*aux_ok=*/false);
 }
@@ -2548,8 +3243,7 @@ size_t dpr1_batched_workspace_size(int64_t nprob, const int64_t* offs_host) {
   for (int64_t p = 0; p < nprob; ++p)
     if (offs_host[p + 1] - offs_host[p] < 1) return 0;
   int64_t ntotal = offs_host[nprob];
-  int64_t nitems = ntotal / WAVE + nprob;  // upper bound of sum ceil(n_p/64)
-  return layout(nprob, ntotal, nitems, count_groups(nprob, offs_host)).total;
+  return batch_bytes(layout_batch(nprob, ntotal, count_groups(nprob, offs_host)), count_wide(nprob, offs_host));
 }
 
 int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* opts, dpr1_plan* plan,
@@ -2567,8 +3261,9 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   }
   int64_t N = offs_host[nprob];
   if (N > (int64_t)INT32_MAX) return -2;
-  Layout L0 = layout(nprob, N, N / WAVE + nprob, count_groups(nprob, offs_host));
-  if (work_bytes < L0.total) return -6;
+  const Layout L0 = layout_batch(nprob, N, count_groups(nprob, offs_host));
+  const int64_t nwide = count_wide(nprob, offs_host);
+  if (work_bytes < batch_bytes(L0, nwide)) return -6;
   dpr1_opts o;
   fill_opts(opts, &o);
   if (!occ_valid(o.waves_per_simd) || o.mode_b < 0 || o.mode_b > 3) return -3;
@@ -2578,10 +3273,22 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
     return offs_host[a + 1] - offs_host[a] > offs_host[b + 1] - offs_host[b];
   });
-  std::vector<int2> items;
+  // the queue, and the far-field records: item e's own record is e, the wide
+  // level's lie behind the queue's
+  std::vector<int4> items, witems;
+  FarHdr hdr{0, nwide, (int64_t)(L0.total + al(8 * (size_t)FAR_REC * nwide))};
+  const int64_t rec0 = N / WAVE + nprob;
   for (int32_t p : order) {
-    int64_t np = offs_host[p + 1] - offs_host[p];
-    for (int64_t k0 = 0; k0 < np; k0 += WAVE) items.push_back(make_int2(p, (int)k0));
+    const int64_t np = offs_host[p + 1] - offs_host[p];
+    const int nsl = (int)far_slices(np);
+    const int64_t w0 = rec0 + (int64_t)witems.size();
+    if (np >= FAR_MIN2)
+      for (int64_t k0 = 0; k0 < np; k0 += FAR_WIDE * WAVE)
+        for (int sl = 0; sl < nsl; ++sl)
+          witems.push_back(make_int4(p, (int)k0, sl | nsl << 16, (int)(rec0 + (int64_t)witems.size())));
+    for (int64_t k0 = 0; k0 < np; k0 += WAVE)
+      items.push_back(make_int4(p, (int)k0, np >= FAR_MIN2 ? (int)(w0 + k0 / (FAR_WIDE * WAVE) * nsl) : -1, nsl));
+    if (np >= FAR_MIN) hdr.nown = (int64_t)items.size();
   }
   int64_t nitems = (int64_t)items.size();
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax, occ_of(o));
@@ -2595,7 +3302,11 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
         groups.push_back(make_int4(p, (int)c0, (int)std::min<int64_t>(VEC_C_BATCH, np - c0), (int)r0));
   }
   hipStream_t st = (hipStream_t)stream;
-  HIPCHECK(hipMemcpyAsync((char*)work + L0.items, items.data(), sizeof(int2) * nitems, hipMemcpyHostToDevice, st));
+  HIPCHECK(hipMemcpyAsync((char*)work + L0.items, items.data(), sizeof(int4) * nitems, hipMemcpyHostToDevice, st));
+  HIPCHECK(hipMemcpyAsync((char*)work + L0.ctr + FAR_HDR, &hdr, sizeof hdr, hipMemcpyHostToDevice, st));
+  if (nwide)
+    HIPCHECK(hipMemcpyAsync((char*)work + hdr.wide_off, witems.data(), sizeof(int4) * nwide, hipMemcpyHostToDevice,
+                            st));
   HIPCHECK(hipMemcpyAsync((char*)work + L0.groups, groups.data(), sizeof(int4) * groups.size(),
                           hipMemcpyHostToDevice, st));
   HIPCHECK(hipStreamSynchronize(st));
@@ -2623,9 +3334,9 @@ int dpr1_eig_batched(const dpr1_plan* plan, const int64_t* offs, const double* d
   if (V && !voffs) return -8;
   if (!info) return -12;
   if (!work) return -14;
-  Layout L = layout(plan->nprob, plan->ntotal, plan->ntotal / WAVE + plan->nprob, plan->ngroups);
+  const Layout L = layout_batch(plan->nprob, plan->ntotal, plan->ngroups);
   if (work_bytes < L.total) return -15;
-  return launch_solve(L, (char*)work, plan->nprob, plan->ntotal, offs, 0, d, z, rho, 0.0, lambda, V, voffs, 0,
+  return launch_solve(L, (char*)work, plan->nprob, plan->ntotal, plan->nmax, offs, 0, d, z, rho, 0.0, lambda, V, voffs, 0,
                       shift_idx, mu, xnorm, info, stats, plan->opts, plan->split, plan->nitems, plan->grid,
                       plan->ngroups, (hipStream_t)stream);
 }

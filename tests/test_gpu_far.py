@@ -1,0 +1,106 @@
+"""The eigenvalue kernel's far-field expansions against the CPU oracle: orders at the edges of the two
+levels and of their groups (64 and 512 eigenvalues), and pole distributions that make the near windows
+empty on one side, uneven, or the whole problem."""
+import numpy as np
+import pytest
+
+from parity_util import check_repr, rel
+from paper_1405_7537_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+LAM_TOL, V_TOL = 1e-13, 1e-12
+
+
+@pytest.fixture(scope="module")
+def D():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1405_7537_amd.dpr1 as D
+    D.lib()
+    return D
+
+
+def poles(kind, n, rng):
+    if kind == "uniform":
+        d = rng.uniform(-1.0, 1.0, n)
+    elif kind == "two clusters":        # a gap of 2 against gaps of 1e-9
+        d = np.concatenate([1.0 + 1e-6 * rng.uniform(0, 1, n // 2), -1.0 - 1e-6 * rng.uniform(0, 1, n - n // 2)])
+    elif kind == "outliers":            # one pole 1e30 away at each end, one 64 places in from the top
+        d = np.concatenate([rng.uniform(-1.0, 1.0, n - 3), [1e30, -1e30, 0.9999999]])
+    elif kind == "40 decades":
+        d = 10.0 ** -np.sort(rng.uniform(0, 40, n)) * rng.choice([-1.0, 1.0], n)
+    elif kind == "300 decades":         # neighbours further than 2^400 interval widths away
+        d = 10.0 ** -np.sort(rng.uniform(0, 300, n))
+    else:                               # every 64th gap 1e-10 of the others
+        d = np.linspace(1.0, -1.0, n)
+        d[64::64] = d[63:-1:64] - 1e-10 * 2.0 / n
+    d = np.unique(d)[::-1].copy()
+    return d
+
+
+CASES = [("uniform", n, r, 1.0) for n, r in ((383, 1.0), (384, 1.0), (385, -0.5), (447, 1.0), (449, 1e4), (700, 1e-6),
+                                              (2047, 1.0), (2048, -1.0), (2049, 1.0), (2113, 1.0), (4161, 50.0))]
+CASES += [("two clusters", 1000, 1.0, 1.0), ("two clusters", 4000, -0.1, 1.0), ("outliers", 900, 1.0, 1.0),
+          ("outliers", 2500, 1.0, 1.0), ("40 decades", 800, 1.0, 1.0), ("40 decades", 3000, -1e-3, 1.0),
+          ("300 decades", 600, 1.0, 1.0), ("close pairs", 2600, 1.0, 1.0), ("uniform", 2500, 1.0, 1e-150),
+          ("two clusters", 2500, -2.0, 1e-150)]
+
+
+@pytest.mark.parametrize("kind,n,rho,zmin", CASES)
+def test_expansions_against_oracle(D, orc, kind, n, rho, zmin):
+    """zmin < 1: |z_j| = 10^U(log10 zmin, 0)."""
+    rng = np.random.default_rng(n)
+    d = poles(kind, n, rng)
+    n = d.size
+    z = rng.standard_normal(n) if zmin == 1.0 else 10.0 ** rng.uniform(np.log10(zmin), 0, n) * rng.choice([-1.0, 1.0], n)
+    print(f"[far] {kind} n={n} rho={rho} zmin={zmin}", flush=True)
+    r = D.eig(d, z, rho)
+    edge = [k for k in (0, 1, 62, 63, 64, 65, 127, 128, 511, 512, 513, n - 64, n - 2, n - 1) if 0 <= k < n]
+    ks = np.unique(np.concatenate([edge, rng.choice(n, 50, replace=False)])).astype(np.int64)
+    if rho > 0:
+        lo, Vo, dg = orc.eig_some(d, z, rho, ks, vectors=True)
+    else:                               # (eig_some takes rho > 0)
+        lo, Vo, dg = orc.eig(d, z, rho, diags=True)
+        lo, Vo, dg = lo[ks], Vo[:, ks], [dg[k] for k in ks]
+    lam = r.lam.cpu().numpy()
+    assert np.max(rel(lam[ks], lo)) <= LAM_TOL
+    assert np.max(rel(r.V.cpu().numpy()[:, ks], Vo)) <= V_TOL
+    check_repr(d, z, rho, r.shift_idx.cpu().numpy()[ks], r.mu.cpu().numpy()[ks], r.xnorm.cpu().numpy()[ks], dg, ks)
+    assert np.all(lam[:-1] > lam[1:])
+
+
+@pytest.mark.parametrize("n", [700, 2300])
+def test_bisection_with_expansions(D, orc, n):
+    d, z, rho = W.uniform(n, n)
+    r = D.eig(d, z, rho, opts=D.opts(root=0))
+    ks = np.arange(0, n, 29)
+    lo, Vo, _ = orc.eig_some(d, z, rho, ks, vectors=True)
+    assert np.max(rel(r.lam.cpu().numpy()[ks], lo)) <= LAM_TOL
+    assert np.max(rel(r.V.cpu().numpy()[:, ks], Vo)) <= V_TOL
+
+
+def test_batch_matches_single_solves(D):
+    """A batch with orders below, at and above both thresholds: every problem as solved alone, whose records
+    lie elsewhere (eigenvalues to 4 eps, the norms and mu to the parity bar), also with an unsolvable one."""
+    import torch
+    sizes = [1, 2600, 64, 383, 384, 2047, 2048, 500, 5000, 17]
+    d, z, rho, offs = W.batched(len(sizes), 77, sizes=sizes)
+    bad = 3
+    d[offs[bad]] = -9.0                      # not decreasing
+    b = D.Batch(offs)
+    dt, zt, rt = (torch.as_tensor(x, device="cuda") for x in (d, z, rho))
+    for _ in range(2):
+        b.solve(dt, zt, rt)
+    info = b.info.cpu().numpy()
+    assert info[bad] == 1 and np.count_nonzero(info) == 1
+    for p, n in enumerate(sizes):
+        if p == bad:
+            continue
+        s = slice(int(offs[p]), int(offs[p + 1]))
+        r = D.eig(d[s], z[s], float(rho[p]))
+        print(f"[far] batch problem {p} n={n}", flush=True)
+        assert torch.equal(b.shift_idx[s], r.shift_idx)
+        assert float(((b.lam[s] - r.lam) / r.lam).abs().max()) <= 4 * 2.0 ** -52
+        assert float(((b.mu[s] - r.mu) / r.mu).abs().max()) <= 1e-13
+        assert float(((b.vblock(p) - r.V) / r.V).abs().max()) <= V_TOL
