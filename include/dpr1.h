@@ -109,7 +109,8 @@ typedef struct dpr1_opts {
   int32_t polish;      /* 1 (default): double-double Newton polish of roots
                           whose rounding amplification is large; 0 off     */
   int32_t split;       /* waves that share one block of 64 eigenvalues by
-                          splitting the inner sum; 0 = chosen from n        */
+                          splitting the inner sum; 0 = chosen from the
+                          number of blocks and n                            */
   double kappa_polish; /* polish threshold on kappa_g*max(1,|mu/lambda|);
                           default 16                                        */
   double nearzero;     /* near-zero rule factor: recompute lambda from
@@ -118,8 +119,7 @@ typedef struct dpr1_opts {
   int32_t main_passes; /* model solver: passes the eigenvalue kernel runs
                           (the last one with compensated summation) before
                           it hands an unconverged eigenpair to the
-                          cooperative kernel; 0 = default (2 for dpr1_eig,
-                          3 for dpr1_eig_batched)                          */
+                          cooperative kernel; 0 = default (3)              */
   int32_t waves_per_simd; /* register budget of the eigenvalue kernel: 4
                           (default, 0) waves per SIMD with up to 128 VGPRs,
                           6 (80) or 8 (64); more waves hide more latency,

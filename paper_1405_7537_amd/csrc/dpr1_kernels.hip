@@ -390,61 +390,103 @@ __global__ void k_zero(int32_t* __restrict__ a, int n) {
 }
 
 // ------------------------------------------------------------------- eig
-// Root of the model of g at the current iterate m.  Written in poles,
-// g(t) = b' - t + sum_j w_j/(t - xi_j) with xi_j = 1/delta'_j and
+// Step from the current iterate m to the root of the model of g.  Written in
+// poles, g(t) = b' - t + sum_j w_j/(t - xi_j) with xi_j = 1/delta'_j and
 // w_j = zeta_j^2/(delta'_j^2 zeta_i^2); the wanted root lies right of every
 // pole.  The model keeps the nearest pole xm with its exact weight sw^2 and
-// replaces the rest of the sum, R(t), by sa^2/(t - p) + B fitted to R's
-// value, slope and curvature at m (Sz, Spz, Sppz are the moments of the whole
-// sum: S/zeta_i^2, sum w/(m - xi)^2, sum w/(m - xi)^3).  Every other pole
-// lies left of xm, so the fitted pole does too; the model is then convex and
-// decreasing right of its poles and its root is found by Newton's method
-// inside the bracket (L, U).  The model matches g to second order at m, so
-// the outer iteration converges cubically.  Both weights are carried as
-// square roots: with zeta_i near 1e-148 beside a pole 1e-13 away a weight
-// reaches 1e322 while every term weight/(t - pole) of the model is finite.
-__device__ __forceinline__ double model_root(double m, double Sz, double Spz, double Sppz, double bp, double xm,
-                                             double sw, double L, double U) {
-  double Rs = Sz, Rp = Spz, Rpp = Sppz;
-  if (sw > 0.0) {
-    const double ie = 1.0 / (m - xm);
-    const double a = sw * ie;
-    Rs -= sw * a;
-    Rp -= a * a;
-    Rpp -= (a * a) * ie;
-  }
-  double p = xm, sa = 0.0, B = Rs;
-  if (Rp > 0.0 && Rpp > 0.0) {
-    p = fmin(m - Rp / Rpp, xm);
-    const double x = m - p;
-    sa = sqrt(Rp) * x;
-    B = Rs - Rp * x;
-  }
-  // a model whose parameters are not finite says nothing: NaN makes the
-  // caller take a bisection step instead of reading a zero step as
-  // convergence
-  if (!(sa < INFINITY) || !(fabs(B) < INFINITY) || !(sw < INFINITY)) return NAN;
-  double lo = fmax(L, fmax(xm, p)), hi = U;
-  double t = m;
+// replaces the rest of the sum by one pole p fitted to value, slope and
+// curvature at m (Spz, Sppz are the moments sum w/(m - xi)^2, sum
+// w/(m - xi)^3).  Every other pole lies left of xm, so the fitted pole does
+// too.  With D = t - m and g the value at m the model's root satisfies
+//   D (1 + a^2/(1 + D e) + r/(1 + D f)) = g,
+// e = 1/(m - xm), a = sw e, r the rest of the slope, f = 1/(m - p): D comes
+// with the relative accuracy of g whatever its size, so refined reciprocal
+// estimates serve.  Solved in steps x from the residual h at the current D:
+// one quotient of the slope and curvature there, x (1 + sl/(1 + x be)) = -h, a
+// quadratic in x; inside the bracket (L, U), until a step is below 2^-20 of D,
+// which leaves less than 2^-40 of it.  Two to five steps where Newton's method
+// doubles D step by step beside a small zeta_i.  (Newton's method for t itself to 2^-52 with IEEE quotients
+// took up to 20 us a call: single lanes ran 40 steps at the rounding level,
+// and the wave waits for the last.)  The model matches g to second order at m,
+// so the outer iteration converges cubically.  The weight enters as its square
+// root: with zeta_i near 1e-148 beside a pole 1e-13 away a weight reaches
+// 1e322 while weight/(t - pole) is finite.  A model whose parameters are not
+// finite says nothing: NaN makes the caller take a bisection step.
+__device__ __forceinline__ double model_delta(double m, double g, double Spz, double Sppz, double xm, double sw,
+                                              double L, double U) {
+  const double e = rcp_1nr(m - xm);
+  const double a = sw * e;
+  const double a2 = a * a;
+  double r = Spz - a2;
+  const double rpp = Sppz - a2 * e;
+  double f = 0.0;
+  // (slopes below 2^-80 count for nothing beside the 1, and have no reciprocal
+  // where they are subnormal)
+  if (r > 0x1p-80 && rpp > 0.0)
+    f = fmin(rpp * rcp_1nr(r), e);
+  else
+    r = 0.0;
+  if (!(fabs(g) < INFINITY) || !(e < INFINITY) || !(a2 + r < INFINITY)) return NAN;
+  double lo = fmax(L, xm) - m, hi = U - m;
+  double D = 0.0, h = -g, u1 = 1.0, u2 = 1.0;
   for (int q = 0; q < 40; ++q) {
-    const double e1 = 1.0 / (t - xm), e2 = 1.0 / (t - p);
-    const double s1 = sw * e1, s2 = sa * e2;
-    const double h = ((bp - t) + B) + (sw * s1 + sa * s2);
-    if (!(h == h)) return NAN;
-    if (h == 0.0) break;  // t is a root of the model
-    const double hp = -1.0 - (s1 * s1 + s2 * s2);
-    if (h > 0.0) lo = t; else hi = t;
-    double tn = t - h / hp;
-    // a step below the resolution of t ends the iteration (t may sit on the
-    // bracket end it has just set, where tn == t would fail the test below)
-    if (fabs(tn - t) <= 0x1p-52 * t) {
-      t = tn;
+    const double A1 = a2 * (u1 * u1), R1 = r * (u2 * u2);
+    const double sl = A1 + R1;
+    double x;
+    if (sl > 0x1p-80) {
+      // be x^2 + B x + h = 0, the root that goes to 0 with h
+      const double be = __builtin_fma(A1 * u1, e, R1 * u2 * f) * rcp_1nr(sl);
+      const double B = __builtin_fma(h, be, 1.0 + sl);
+      const double iB = rcp_1nr(B);
+      const double t = -h * iB;
+      const double w = __builtin_fma(4.0 * be * t, iB, 1.0);
+      const double y = __builtin_amdgcn_rsq(w);
+      double S = w * y;
+      S = __builtin_fma(__builtin_fma(-S, S, w), 0.5 * y, S);
+      x = B > 0.0 ? 2.0 * t * rcp_1nr(1.0 + S) : -0.5 * B * (1.0 + S) * rcp_1nr(be);
+    } else {
+      x = -h;  // no slope beside t's own
+    }
+    double n = D + x;
+    // (tested before the bracket: D may sit on the end that it has just set)
+    if (fabs(x) <= 0x1p-20 * fabs(n)) {
+      D = n;
       break;
     }
-    if (!(tn > lo && tn < hi)) tn = (hi < INFINITY) ? 0.5 * (lo + hi) : 2.0 * t;
-    t = tn;
+    // outside the bracket: a point just inside the end passed; where the
+    // model's root lies beyond that too, it is the answer if the end is within
+    // 2^20 of m (else the caller halves the bracket in the exponent)
+    const int out = n <= lo ? -1 : n >= hi ? 1 : 0;
+    if (out) n = out < 0 ? __builtin_fma(0x1p-45, D - lo, lo) : __builtin_fma(0x1p-45, D - hi, hi);
+    if (!(n != D)) return NAN;
+    D = n;
+    u1 = rcp_1nr(__builtin_fma(D, e, 1.0));
+    u2 = rcp_1nr(__builtin_fma(D, f, 1.0));
+    h = __builtin_fma(D, 1.0 + __builtin_fma(a2, u1, r * u2), -g);
+    if (!(h == h)) return NAN;
+    if ((out < 0 && h > 0.0) || (out > 0 && h < 0.0)) {
+      const double t = m + D;
+      return t > 0x1p-19 * m && t < 0x1p20 * m ? D : NAN;
+    }
+    if (h == 0.0) break;
+    if (h < 0.0) lo = D; else hi = D;
   }
-  return t;
+  return D;
+}
+
+// g(m) = b' - m + S/zeta_i^2 of an accurate pass: b' = bh + bl, S = sh + sl,
+// every sum and the quotient carried with its rounding error, so that only the
+// errors of the terms of S are left (Sz: the quotient in working precision).
+__device__ __forceinline__ double g_value(double bh, double bl, double m, double sh, double sl, double zi,
+                                          double& Sz) {
+  const double z2 = zi * zi, z2l = __builtin_fma(zi, zi, -z2);
+  Sz = (sh + sl) / z2;
+  double e = __builtin_fma(-Sz, z2, sh);
+  e = __builtin_fma(-Sz, z2l, e + sl);
+  const dd a = two_sum(bh, -m);
+  const dd b = two_sum(a.hi, Sz);
+  const double g = b.hi + (((a.lo + b.lo) + bl) + e / z2);
+  return g == g ? g : (bh - m) + Sz;
 }
 
 // One step of the safeguarded iteration for the rightmost root of g from its
@@ -453,10 +495,9 @@ __device__ __forceinline__ double model_root(double m, double Sz, double Spz, do
 // is the next iterate of a two-cycle: g changed sign at the last two steps
 // while |g| fell by less than a factor 10 on the same side (g1, g2 keep the
 // two previous values of g).
-__device__ __forceinline__ void model_step(double m, double g, double Sz, double Spz, double Sppz, double bp,
-                                           double xm, double sw, int iters, double L, double U, double& nu,
-                                           double& nu0, double& prevstep, double& g1, double& g2, bool& done,
-                                           double tol = 0x1p-20) {
+__device__ __forceinline__ void model_step(double m, double g, double Spz, double Sppz, double xm, double sw,
+                                           int iters, double L, double U, double& nu, double& nu0, double& prevstep,
+                                           double& g1, double& g2, bool& done, double tol = 0x1p-20) {
   if (g == 0.0) {
     done = true;
     nu0 = m;
@@ -465,9 +506,9 @@ __device__ __forceinline__ void model_step(double m, double g, double Sz, double
   const bool cycle = (g * g1 < 0.0) && (g1 * g2 < 0.0) && (fabs(g) > 0.1 * fabs(g2));
   g2 = g1;
   g1 = g;
-  const double nn0 = model_root(m, Sz, Spz, Sppz, bp, xm, sw, L, U);
-  double nn = nn0;
-  const double step = fabs(nn - m);
+  const double dm = model_delta(m, g, Spz, Sppz, xm, sw, L, U);
+  double nn = m + dm;
+  const double step = fabs(dm);
   // Cubic convergence: a step e leaves a model error of about 8 e^3 (the
   // shift keeps every pole at least nu/2 from the root), so after a step
   // below 2^-20 the new iterate is exact to rounding.  The same tolerance
@@ -822,25 +863,56 @@ __global__ void __launch_bounds__(FAR_BLK, 2) k_far(FarArgs F) {
 
 // Values of an expansion held in LDS (the layout of a record) by Clenshaw's
 // recurrence, differentiated for the slopes.
-// f, f' and f''/2 at x
-__device__ __forceinline__ void far_eval(const double* cf, double x, double& f, double& f1, double& f2) {
+// The orders FAR_ND-1 .. 1 (26 - 1 = 5 x 5) run in fives, whose coefficients
+// are loaded together: one LDS latency per five steps.
+template <class F>
+__device__ __forceinline__ void far_orders(const double* cf, F&& step) {
+  static_assert((FAR_ND - 1) % 5 == 0, "orders in fives");
+#pragma unroll 1
+  for (int c = FAR_ND - 5; c >= 1; c -= 5) {
+    double k[5];
+#pragma unroll
+    for (int u = 0; u < 5; ++u) k[u] = cf[c + u];
+#pragma unroll
+    for (int u = 4; u >= 0; --u) step(k[u]);
+  }
+}
+template <class F>
+__device__ __forceinline__ void far_orders2(const double* cf, const double* cg, F&& step) {
+#pragma unroll 1
+  for (int c = FAR_ND - 5; c >= 1; c -= 5) {
+    double k[5], l[5];
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+      k[u] = cf[c + u];
+      l[u] = cg[c + u];
+    }
+#pragma unroll
+    for (int u = 4; u >= 0; --u) step(k[u], l[u]);
+  }
+}
+// f, f' and f''/2 at x, and the sum of magnitudes fa
+__device__ __forceinline__ void far_eval(const double* cf, double x, double& f, double& f1, double& f2, double& fa) {
   const double x2 = 2.0 * x;
-  double b1 = 0.0, b2 = 0.0, p1 = 0.0, p2 = 0.0, h1 = 0.0, h2 = 0.0;
-#pragma unroll 5
-  for (int q = FAR_ND - 1; q >= 1; --q) {
+  double b1 = 0.0, b2 = 0.0, p1 = 0.0, p2 = 0.0, h1 = 0.0, h2 = 0.0, m1 = 0.0, m2 = 0.0;
+  far_orders2(cf, cf + FR_ABS, [&](double a, double am) {
     const double h0 = __builtin_fma(x2, h1, __builtin_fma(2.0, p1, -h2));
     const double p0 = __builtin_fma(x2, p1, __builtin_fma(2.0, b1, -p2));
-    const double b0 = __builtin_fma(x2, b1, cf[q] - b2);
+    const double b0 = __builtin_fma(x2, b1, a - b2);
+    const double m0 = __builtin_fma(x2, m1, am - m2);
     b2 = b1;
     b1 = b0;
     p2 = p1;
     p1 = p0;
     h2 = h1;
     h1 = h0;
-  }
+    m2 = m1;
+    m1 = m0;
+  });
   f = __builtin_fma(x, b1, cf[0] - b2);
   f1 = __builtin_fma(x, p1, b1 - p2);
   f2 = __builtin_fma(x, h1, p1 - h2);
+  fa = __builtin_fma(x, m1, cf[FR_ABS] - m2);
 }
 // the divided difference f[x, y], and f', f''/2 and the third derivative / 6 at y
 __device__ __forceinline__ void far_diff(const double* cf, double x, double y, double& fxy, double& f1, double& f2,
@@ -848,14 +920,13 @@ __device__ __forceinline__ void far_diff(const double* cf, double x, double y, d
   const double x2 = 2.0 * x, y2 = 2.0 * y;
   double a1 = 0.0, a2 = 0.0, c1 = 0.0, c2 = 0.0;
   double b1 = 0.0, b2 = 0.0, p1 = 0.0, p2 = 0.0, h1 = 0.0, h2 = 0.0, g1 = 0.0, g2 = 0.0;
-#pragma unroll 5
-  for (int q = FAR_ND - 1; q >= 1; --q) {
+  far_orders(cf, [&](double k) {
     const double c0 = __builtin_fma(y2, c1, __builtin_fma(2.0, a1, -c2));
-    const double a0 = __builtin_fma(x2, a1, cf[q] - a2);
+    const double a0 = __builtin_fma(x2, a1, k - a2);
     const double g0 = __builtin_fma(y2, g1, __builtin_fma(2.0, h1, -g2));
     const double h0 = __builtin_fma(y2, h1, __builtin_fma(2.0, p1, -h2));
     const double p0 = __builtin_fma(y2, p1, __builtin_fma(2.0, b1, -p2));
-    const double b0 = __builtin_fma(y2, b1, cf[q] - b2);
+    const double b0 = __builtin_fma(y2, b1, k - b2);
     a2 = a1;
     a1 = a0;
     c2 = c1;
@@ -868,42 +939,49 @@ __device__ __forceinline__ void far_diff(const double* cf, double x, double y, d
     h1 = h0;
     g2 = g1;
     g1 = g0;
-  }
+  });
   fxy = __builtin_fma(y, c1, a1 - c2);
   f1 = __builtin_fma(y, p1, b1 - p2);
   f2 = __builtin_fma(y, h1, p1 - h2);
   f3 = __builtin_fma(y, g1, h1 - g2);
 }
-// the sum of magnitudes at x
-__device__ __forceinline__ double far_mag(const double* cf, double x) {
-  const double x2 = 2.0 * x;
-  double m1 = 0.0, m2 = 0.0;
-#pragma unroll 5
-  for (int q = FAR_ND - 1; q >= 1; --q) {
-    const double m0 = __builtin_fma(x2, m1, cf[FR_ABS + q] - m2);
-    m2 = m1;
-    m1 = m0;
-  }
-  return __builtin_fma(x, m1, cf[FR_ABS] - m2);
-}
-// f in double-double at a double-double x
-__device__ __forceinline__ dd far_value(const double* cf, dd x) {
+// f in double-double at a double-double x, and the sum of magnitudes fa
+__device__ __forceinline__ dd far_value(const double* cf, dd x, double& fa) {
   const double x2 = 2.0 * x.hi;
   double b1 = 0.0, b2 = 0.0;
-#pragma unroll 6
-  for (int q = FAR_P - 1; q >= FAR_Q; --q) {
-    const double b0 = __builtin_fma(x2, b1, cf[q] - b2);
-    b2 = b1;
-    b1 = b0;
+  static_assert((FAR_P - FAR_Q) % 6 == 0 && (FAR_Q - 1) == 23, "orders in groups");
+#pragma unroll 1
+  for (int c = FAR_P - 6; c >= FAR_Q; c -= 6) {
+    double k[6];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) k[u] = cf[c + u];
+#pragma unroll
+    for (int u = 5; u >= 0; --u) {
+      const double b0 = __builtin_fma(x2, b1, k[u] - b2);
+      b2 = b1;
+      b1 = b0;
+    }
   }
   const dd X2 = {x2, 2.0 * x.lo};
   dd B1 = {b1, 0.0}, B2 = {b2, 0.0};
+  double m1 = 0.0, m2 = 0.0;
+  double kh = cf[FAR_Q - 1], kl = cf[FR_LO + FAR_Q - 1], km = cf[FR_ABS + FAR_Q - 1];
+#pragma unroll 1
   for (int q = FAR_Q - 1; q >= 1; --q) {
-    const dd B0 = dd_add_same(dd_add_same(dd{cf[q], cf[FR_LO + q]}, dd_neg(B2)), dd_mul(X2, B1));
+    // the next order's coefficients while this one's are used (order 0 last)
+    const double nh = cf[q - 1], nl = cf[FR_LO + q - 1], nm = cf[FR_ABS + q - 1];
+    const dd B0 = dd_add_same(dd_add_same(dd{kh, kl}, dd_neg(B2)), dd_mul(X2, B1));
     B2 = B1;
     B1 = B0;
+    const double m0 = __builtin_fma(x2, m1, km - m2);
+    m2 = m1;
+    m1 = m0;
+    kh = nh;
+    kl = nl;
+    km = nm;
   }
-  return dd_add_same(dd_add_same(dd{cf[0], cf[FR_LO]}, dd_neg(B2)), dd_mul(x, B1));
+  fa = __builtin_fma(x.hi, m1, km - m2);
+  return dd_add_same(dd_add_same(dd{kh, kl}, dd_neg(B2)), dd_mul(x, B1));
 }
 
 // Expansions of one block: the levels that hold poles (their records in LDS,
@@ -984,6 +1062,7 @@ __device__ __forceinline__ void ext_eval(const double* P, int n, const Far& F, d
                                          int W, int wv, int lane, double* red) {
   for (int q = 0; q < 5; ++q) v[q] = 0.0;
   const int len = F.na + (n - F.nb);
+#pragma unroll 4
   for (int e = threadIdx.x; e < len; e += blockDim.x) {
     const int j = e < F.na ? e : e - F.na + F.nb;
     const double den = (P[2 * j] - sigma) - tau, z2 = P[2 * j + 1];
@@ -1003,6 +1082,7 @@ __device__ __forceinline__ void ext_sums(const double* P, int n, const Far& F, d
                                          int W, int wv, int lane, double* red) {
   for (int q = 0; q < 5; ++q) v[q] = 0.0;
   const int len = F.na + (n - F.nb);
+#pragma unroll 4
   for (int e = threadIdx.x; e < len; e += blockDim.x) {
     const int j = e < F.na ? e : e - F.na + F.nb;
     const double dl = P[2 * j] - sigma, z2 = P[2 * j + 1];
@@ -1113,20 +1193,17 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
     Fs[3] = __builtin_fma(tr, r, Fs[3]);
   });
   double Ff = 0.0;  // the far poles' part of the sum
-  if (wv == 0) {
-    for (int l = 0; l < FF.lev; ++l) {
-      const double* q = FF.cf + l * FAR_REC;
-      const double ir = q[FR_IR], x = kk > 0 ? ((dk - q[FR_C]) + tau) * ir : 0.0;
-      double f, f1, f2;
-      far_eval(q, x, f, f1, f2);
-      const double fa = far_mag(q, x);
-      if (kk > 0) {
-        Ff += f;
-        Fs[0] += 0.5 * (f + fa);
-        Fs[1] += 0.5 * (f - fa);
-        Fs[2] = __builtin_fma(f1, ir, Fs[2]);
-        Fs[3] = __builtin_fma(f2 * ir, ir, Fs[3]);
-      }
+  for (int l = wv; l < FF.lev; l += W) {  // (one wave per level where there are two)
+    const double* q = FF.cf + l * FAR_REC;
+    const double ir = q[FR_IR], x = kk > 0 ? ((dk - q[FR_C]) + tau) * ir : 0.0;
+    double f, f1, f2, fa;
+    far_eval(q, x, f, f1, f2, fa);
+    if (kk > 0) {
+      Ff += f;
+      Fs[0] += 0.5 * (f + fa);
+      Fs[1] += 0.5 * (f - fa);
+      Fs[2] = __builtin_fma(f1, ir, Fs[2]);
+      Fs[3] = __builtin_fma(f2 * ir, ir, Fs[3]);
     }
   }
   wg_sum<4>(Fs, W, wv, lane, red);
@@ -1162,7 +1239,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
       t = __builtin_fma(__builtin_fma(-t, den, z2), r, t);
       Fr[0] += t;
     });
-    if (wv == 0) Fr[0] += Ff;
+    Fr[0] += Ff;
     wg_sum<1>(Fr, W, wv, lane, red);
     if (open) F = 1.0 + rho * Fr[0];
   }
@@ -1200,29 +1277,32 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
       acc(ps, pc, q1, q2);
     } else if (seg == 2) {
       acc(ns, nc, -q1, -q2);
-    } else if (j != i) {
+    } else {
+      // selects, no branch: the shift pole's own term (not finite) adds 0
       const bool up = j < i;
+      if (j == i) q1 = q2 = 0.0;
       double a = up ? ps : ns, c = up ? pc : nc;
       acc(a, c, up ? q1 : -q1, up ? q2 : -q2);
-      if (up) { ps = a; pc = c; } else { ns = a; nc = c; }
+      ps = up ? a : ps;
+      pc = up ? c : pc;
+      ns = up ? ns : a;
+      nc = up ? nc : c;
     }
   });
   dd Pd = fast_two_sum(ps, pc);
   dd Nd = fast_two_sum(-ns, -nc);
-  if (wv == 0) {
-    // the far poles' f = P + N in double-double, cut with the sum of
-    // magnitudes P - N so that P and N keep their meaning in K_b (the split is
-    // exact: P rounded, N the rest)
-    for (int l = 0; l < FF.lev; ++l) {
-      const double* q = FF.cf + l * FAR_REC;
-      const dd x = dd_mul_d(two_sum(sigma, -q[FR_C]), q[FR_IR]);
-      const dd f = far_value(q, x);
-      const double pf = 0.5 * (f.hi + far_mag(q, x.hi));
-      dd nf = two_sum(f.hi, -pf);
-      nf.lo += f.lo;
-      Pd = dd_add_same(Pd, dd{pf, 0.0});
-      Nd = dd_add_same(Nd, nf);
-    }
+  // the far poles' f = P + N in double-double, cut with the sum of magnitudes
+  // P - N so that P and N keep their meaning in K_b (the split is exact: P
+  // rounded, N the rest)
+  for (int l = wv; l < FF.lev; l += W) {
+    const double* q = FF.cf + l * FAR_REC;
+    double fa;
+    const dd f = far_value(q, dd_mul_d(two_sum(sigma, -q[FR_C]), q[FR_IR]), fa);
+    const double pf = 0.5 * (f.hi + fa);
+    dd nf = two_sum(f.hi, -pf);
+    nf.lo += f.lo;
+    Pd = dd_add_same(Pd, dd{pf, 0.0});
+    Nd = dd_add_same(Nd, nf);
   }
   wg_sum_dd(Pd, W, wv, lane, red);
   wg_sum_dd(Nd, W, wv, lane, red);
@@ -1281,13 +1361,12 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   // leaves the sign of g open the pole is kept as the lower end.  For k = 1
   // the probe may lie on either side of the root.
   bool pre = valid;
-  double pre_Sz = 0.0, pre_Spz = 0.0, pre_Sppz = 0.0, pre_g = 0.0;
+  double pre_Spz = 0.0, pre_Sppz = 0.0, pre_g = 0.0;
   if (pre) {
     // error of f(lambda) from the estimated reciprocals: 2^-23 of |terms|,
     // taken with a margin of 8
     const double gerr = 0x1p-20 * (1.0 + rho * Fs[1]) / (rho * zi2);
     pre_g = s * (1.0 + rho * Fs[0]) / (rho * zi2);
-    pre_Sz = (pre_g - bp) + nu;
     // g' = -F2/(zeta_i^2 nu^2) and g'' = 2 (s F3/nu^4 + F2/nu^3)/zeta_i^2 with
     // F2, F3 the sums of zeta_j^2/(d_j - lambda)^2 and ^3 (lambda = sigma + s/nu)
     const double inu = 1.0 / nu;
@@ -1305,16 +1384,16 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   }
   const double L0 = L, U0 = U;
 
-  // The far poles' part of a pass at nu = m, in wave 0 (the other waves add
-  // 0): with mu = s/m, zeta^2/(delta' pp) = |mu| zeta^2/((d - sigma)(d - lambda)),
+  // The far poles' part of a pass at nu = m, one wave per level (the other
+  // waves add 0): with mu = s/m, zeta^2/(delta' pp) = |mu| zeta^2/((d - sigma)(d - lambda)),
   // a divided difference of f, and zeta^2/pp^2, zeta^2 delta'/pp^3, zeta^2
   // delta'^2/pp^4 are its derivatives at lambda times powers of |mu|.  The
   // exterior eigenvalue takes its direct sums instead.
   auto far_sums = [&](double m, double (&v)[4]) {
     v[0] = v[1] = v[2] = v[3] = 0.0;
-    if (wv == 0) {
+    if (wv < FF.lev) {
       const double muv = s / m, am = fabs(muv);
-      for (int l = 0; l < FF.lev; ++l) {
+      for (int l = wv; l < FF.lev; l += W) {
         const double* q = FF.cf + l * FAR_REC;
         const double ir = q[FR_IR], x = (sigma - q[FR_C]) * ir;
         const double y = interior ? __builtin_fma(muv, ir, x) : x;
@@ -1419,7 +1498,6 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
         double Sppz = S[2] * rz2;
         double g = (bp - m) + Sz;
         if (pre) {
-          Sz = pre_Sz;
           Spz = pre_Spz;
           Sppz = pre_Sppz;
           g = pre_g;
@@ -1431,7 +1509,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
           const double gtol = 0x1p-20 * Sz + 0x1p-50 * fabs(bp);
           if (g > gtol) L = m; else if (g < -gtol) U = m;
         }
-        model_step(m, g, Sz, Spz, Sppz, bp, xm, sw, iters, L, U, nu, nu0, prevstep, g1, g2, done);
+        model_step(m, g, Spz, Sppz, xm, sw, iters, L, U, nu, nu0, prevstep, g1, g2, done);
       }
     }
   }
@@ -1500,8 +1578,8 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   }
   wg_sum_comp(cs, cc, W, wv, lane, red);
   wg_sum<3>(Sp, W, wv, lane, red);
-  const double Sz = (cs + cc) / zi2;
-  const double g = (bp - m) + Sz;
+  double Sz;
+  const double g = g_value(bp, s * bl, m, cs, cc, zi, Sz);
   const double gp = -1.0 - Sp[0] / zi2;
   // divided in two steps: m |g'| overflows when nu nears 1e304
   const double kap = ((fabs(bp) + m + Sz) / m) / fabs(gp);
@@ -1513,7 +1591,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
     fin = false;
     if (g > 0) L = m; else if (g < 0) U = m;
     double nn = m;
-    model_step(m, g, Sz, Sp[0] / zi2, Sp[1] / zi2, bp, xm, sw, iters, L, U, nu, nn, prevstep, g1, g2, fin);
+    model_step(m, g, Sp[0] / zi2, Sp[1] / zi2, xm, sw, iters, L, U, nu, nn, prevstep, g1, g2, fin);
     if (fin) nu1 = nn;
   }
   const bool cont = valid && !fin;  // unfinished: continued in k_fix
@@ -1730,10 +1808,10 @@ __device__ __forceinline__ double block_sum_comp(double s, double c, double* sm)
 // One block of FIXT threads per flagged eigenpair at a time; the inner index
 // is strided over the block and every pass ends in a block-wide sum.
 // The four sums of a continued pass in one exchange: the Neumaier partials
-// (s, c) combined as in block_sum_comp and three plain sums a, b, e as in
-// block_sum (same orders, so the same results), with one pair of barriers
-// instead of four.  sm holds 20 values.
-__device__ __forceinline__ double block_sum_comp3(double s, double c, double& a, double& b, double& e,
+// (s, c) combined as in block_sum_comp (returned, its compensation in c) and
+// three plain sums a, b, e as in block_sum, with one pair of barriers instead
+// of four.  sm holds 20 values.
+__device__ __forceinline__ double block_sum_comp3(double s, double& c, double& a, double& b, double& e,
                                                   double* sm) {
   for (int o = 32; o > 0; o >>= 1) {
     const double s2 = __shfl_xor(s, o), c2 = __shfl_xor(c, o);
@@ -1763,7 +1841,8 @@ __device__ __forceinline__ double block_sum_comp3(double s, double c, double& a,
   a = (sm[8] + sm[9]) + (sm[10] + sm[11]);
   b = (sm[12] + sm[13]) + (sm[14] + sm[15]);
   e = (sm[16] + sm[17]) + (sm[18] + sm[19]);
-  return S + C;
+  c = C;
+  return S;
 }
 
 // Safeguarded iteration for the extreme root of g (eq. secAi) at the shift
@@ -1933,11 +2012,11 @@ __device__ void fix_items(const KArgs& A) {
           sp3 += tp3;
           sp4 = __builtin_fma(tp3, u, sp4);
         }
-        Sz = block_sum_comp3(cs, cc, sp, sp3, sp4, sm) / zi2;
+        cs = block_sum_comp3(cs, cc, sp, sp3, sp4, sm);
         ++iters;
-        const double g = (bp - m) + Sz;
+        const double g = g_value(bp, it.blo, m, cs, cc, zi, Sz);
         if (g > 0) L = m; else if (g < 0) U = m;
-        model_step(m, g, Sz, sp / zi2, sp3 / zi2, bp, xm, sw, iters, L, U, nu, nu0, prevstep, g1, g2, done);
+        model_step(m, g, sp / zi2, sp3 / zi2, xm, sw, iters, L, U, nu, nu0, prevstep, g1, g2, done);
       }
       nu1 = nu0;
       const double gp = -1.0 - sp / zi2;
@@ -2785,28 +2864,20 @@ static void fill_opts(const dpr1_opts* in, dpr1_opts* o) {
   }
 }
 
-// The split when the options leave it open: the W that ends the launch
-// soonest, with a block of W waves taking time in proportion to its slice
-// n/W and each of the 256 CUs holding floor(4 occ / W) blocks at a time (a
-// block's waves stay on one CU, 4 occ wave slots per CU): minimise
-// ceil(nblocks / (256 floor(4 occ / W))) / W, the smaller W on a tie (fewer
-// partial sums), keeping slices of at least 256 terms.  (Filling the wave
-// slots alone is not enough: 423 blocks at W = 10 fit one block per CU and
-// take two rounds, 1.6 times longer than W = 8 in one.)
-static int pick_split(int64_t nblocks, int64_t nmax, int occ) {
-  int best = 1;
-  double bc = 1e300;
-  for (int w = 1; w <= MAXW; ++w) {
-    if (w > 1 && nmax / w < 256) break;
-    const int64_t per_cu = (4 * (int64_t)occ) / w;
-    if (per_cu < 1) break;
-    const double c = std::ceil((double)std::max<int64_t>(nblocks, 1) / (256.0 * (double)per_cu)) / w;
-    if (c < bc * (1.0 - 1e-9)) {
-      bc = c;
-      best = w;
-    }
-  }
-  return best;
+// The split when the options leave it open.  What a block does between its
+// sums (the tip's quotients, the model steps, the expansions) does not shrink
+// with W, so W only pays while the GPU has idle issue slots: few blocks.
+// Measured, k_eig with W = 1 / 2 / 4 / 8 in us: n = 256 (4 blocks) 72 / 51 / 39
+// / 40, n = 1501 (24) 64 / 51 / 44 / 50, n = 4096 (64) 107 / 74 / 58 / 59, 512
+// problems of n = 100 (1024) 89 / 67 / 72 / -, 256 of n = 512 (2048) 168 / 142
+// / 162 / -, the 2048-problem mix (14 700) 641 / 694 / 820 / -.  From n = 2048
+// on few blocks take 8, which costs nothing there and halves the time of a
+// block whose poles are all near (steeply graded poles).  A slice has at least
+// 16 poles.
+static int pick_split(int64_t nblocks, int64_t nmax) {
+  int w = nblocks <= 640 ? (nmax >= 2048 ? 8 : 4) : nblocks <= 6144 ? 2 : 1;
+  while (w > 1 && nmax / w < 16) w /= 2;
+  return w;
 }
 
 // k_eig occupancy variant of the options: 4 (default), 6 or 8 waves per SIMD.
@@ -2990,11 +3061,11 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   A.polish = o.polish;
   A.kappa_polish = o.kappa_polish;
   A.nearzero = o.nearzero;
-  // Default budget: 2 passes (one plain, one accurate) for a single problem,
-  // whose stragglers (under a tenth of the roots) are finished beside the V
-  // write; a batch runs one more, since its many small problems would queue
-  // their stragglers in k_fix.
-  A.main_passes = o.main_passes > 0 ? o.main_passes : far ? 4 : (persistent_grid ? 3 : 2);
+  // Default budget: two plain passes and the accurate one, which leave 0.2 to
+  // 0.4 % of the roots to k_fix (one plain pass leaves 8 %: eigenvalues only
+  // 99 against 101 us at n = 1501 but 2050 against 1230 us on the 2048-problem
+  // mix; three cost 5 us at small orders and win nothing elsewhere).
+  A.main_passes = o.main_passes > 0 ? o.main_passes : 3;
   A.remedy = o.remedy;
   A.knu_thr = o.knu_thr;
   A.knu = o.knu;
@@ -3203,7 +3274,7 @@ int dpr1_eig(const double* d, const double* z, double rho, int64_t n, double* la
   if (!occ_valid(o.waves_per_simd) || o.vwrite < 0 || o.vwrite > VEC_CHUNKS_MAX || o.mode_b < 0 || o.mode_b > 3)
     return -13;
   int64_t nblocks = (n + WAVE - 1) / WAVE;
-  int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nblocks, n, occ_of(o));
+  int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nblocks, n);
   return launch_solve(L, (char*)work, 1, n, n, nullptr, n, d, z, nullptr, rho, lambda, V, nullptr, ldv, shift_idx,
                       mu, xnorm, info, stats, o, W, nblocks, 0, 0, (hipStream_t)stream);
 }
@@ -3231,7 +3302,7 @@ int dpr1_eig_noalloc(const double* d, const double* z, double rho, int64_t n, do
   if (!work) return DPR1_EHIP;
   const Layout L = layout_single(n);
   int64_t nblocks = (n + WAVE - 1) / WAVE;
-  int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nblocks, n, occ_of(o));
+  int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nblocks, n);
   return launch_solve(L, (char*)work, 1, n, n, nullptr, n, d, z, nullptr, rho, lambda, V, nullptr, ldv, shift_idx,
                       mu, xnorm, info, stats, o, W, nblocks, 0, 0, (hipStream_t)stream,
                       /*aux_ok=*/false);
@@ -3291,7 +3362,7 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
     if (np >= FAR_MIN) hdr.nown = (int64_t)items.size();
   }
   int64_t nitems = (int64_t)items.size();
-  int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax, occ_of(o));
+  int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax);
   // blocks of the eigenvector kernel: (problem, first column, columns,
   // first row), largest problems first
   std::vector<int4> groups;
