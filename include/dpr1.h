@@ -83,8 +83,7 @@ extern "C" {
 #define DPR1_STAT_CONTINUED 6 /* root searches finished by the cooperative
                                  kernel after the pass budget               */
 #define DPR1_STAT_POLISH_STEPS_MAX 7 /* most double-double steps one polish
-                                 took (including the one that confirmed the
-                                 root)                                      */
+                                 took                                       */
 #define DPR1_STAT_KNU_GT 8    /* eigenpairs with K_nu > knu_thr (eq. K0)     */
 #define DPR1_STAT_REMEDY_R1 9 /* eigenpairs recomputed by remedy (R1)        */
 #define DPR1_STAT_REMEDY_R2 10 /* eigenpairs recomputed by remedy (R2)       */

@@ -1845,19 +1845,62 @@ __device__ __forceinline__ double block_sum_comp3(double s, double& c, double& a
   return S;
 }
 
+// The block's threads along the n poles of a problem, in rounds of U per
+// thread whose loads (pairs and, with LO, the low parts of zeta_j^2) are all
+// issued before the first is used: a block has its CU nearly to itself, so
+// one load latency per pole and pass was most of its time.  f(j, d_j,
+// zeta_j^2, low part, j < n) for consecutive rounds of FIXT poles; past the end
+// it gets the last pole again.
+template <int U, bool LO, class F>
+__device__ __forceinline__ void fix_poles(const double2* Z2v, const double* Zl, int n, F&& f) {
+  for (int b = threadIdx.x; b < n; b += U * FIXT) {
+    double2 p[U];
+    double l[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = min(b + u * FIXT, n - 1);
+      p[u] = Z2v[j];
+      l[u] = LO ? Zl[j] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) f(b + u * FIXT, p[u].x, p[u].y, l[u], b + u * FIXT < n);
+  }
+}
+
+// The sums of a polish step in one exchange: the same-signed double-doubles a
+// and the plain sums b, in the orders of block_sum_same and block_sum.
+__device__ __forceinline__ dd block_sum_polish(dd a, double& b, double* sm) {
+  a = wave_sum_same(a);
+  b = wave_sum(b);
+  const int wv = threadIdx.x / WAVE;
+  __syncthreads();
+  if (threadIdx.x % WAVE == 0) {
+    sm[wv] = a.hi;
+    sm[4 + wv] = a.lo;
+    sm[8 + wv] = b;
+  }
+  __syncthreads();
+  b = (sm[8] + sm[9]) + (sm[10] + sm[11]);
+  dd r = dd_add_same(dd{sm[0], sm[4]}, dd{sm[1], sm[5]});
+  r = dd_add_same(r, dd{sm[2], sm[6]});
+  return dd_add_same(r, dd{sm[3], sm[7]});
+}
+
 // Safeguarded iteration for the extreme root of g (eq. secAi) at the shift
 // pole d_i (side s), g evaluated in double-double: far from the root the
 // rational model step of the main solver, close to it Newton (g exact to
 // ~2^-100, so the last step lands on the rounded root).  b' = s b in
 // double-double, xm the nearest pole of g (in nu), (lo0, hi0) a rigorous
-// bracket, cur the start.  Returns the last iterate; *last receives the
-// Newton correction at it (nu = cur + *last to about 2^-100), *steps the
-// number of double-double evaluations.  All threads of the block call it and
+// bracket, cur the start.  Returns the last iterate.  With `confirm` the
+// iteration goes on until a step no longer changes it, *last then receives the
+// Newton correction at it (nu = cur + *last to about 2^-100); without, a Newton
+// step below 2^-36 relative is the last (its own error is below 2^-70) and is
+// not followed by an evaluation that only confirms it.  *steps: the number of
+// double-double evaluations less one.  All threads of the block call it and
 // return the same values.
 __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, double s, double sigma, double zi,
-                           dd bdd, double xm, double lo0, double hi0, double cur, double* last, int* steps,
-                           double* sm) {
-  const int tid = threadIdx.x;
+                           dd bdd, double xm, double lo0, double hi0, double cur, bool confirm, double* last,
+                           int* steps, double* sm) {
   const double zi2 = zi * zi;
   double lo = lo0, hi = hi0;
   if (!(cur > lo && cur < hi)) cur = fmid(lo, hi);
@@ -1869,13 +1912,9 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
   for (pit = 0; pit < 100; ++pit) {
     dd acc = {0.0, 0.0};
     double sp = 0.0;
-#pragma unroll 4
-    for (int j = tid; j < n; j += FIXT) {
-      if (j == i) continue;
-      const double2 pj = Z2v[j];
-      double dj = pj.x, z2 = pj.y;
-      dd dl = two_sum(s * dj, -s * sigma);               // delta'_j exactly
-      dd pp = dd_add(dd_mul_d(dl, cur), dd{-1.0, 0.0});   // nu delta' - 1
+    fix_poles<4, true>(Z2v, Zl, n, [&](int j, double dj, double z2, double z2l, bool in) {
+      const dd dl = two_sum(s * dj, -s * sigma);               // delta'_j exactly
+      const dd pp = dd_add(dd_mul_d(dl, cur), dd{-1.0, 0.0});  // nu delta' - 1
       dd q = dd_mul(dl, pp);
       if (!(q.hi < DBL_MAX)) q = {DBL_MAX, 0.0};  // beyond binary64: the term is 0
       // (zeta_j^2 hi + lo)/q: leading quotient from the refined reciprocal
@@ -1883,13 +1922,17 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
       const double r = rcp_1nr(q.hi);
       const double q1 = z2 * r;
       double e = __builtin_fma(-q1, q.hi, z2);
-      e = __builtin_fma(-q1, q.lo, e + Zl[j]);
+      e = __builtin_fma(-q1, q.lo, e + z2l);
       dd t = fast_two_sum(q1, e * r);
+      double u = z2 * rcp_1nr(pp.hi * pp.hi);  // g' only steers the step
+      if (j == i || !in) {
+        t = {0.0, 0.0};
+        u = 0.0;
+      }
       acc = dd_add_same(acc, t);
-      sp += z2 * rcp_1nr(pp.hi * pp.hi);  // g' only steers the step
-    }
-    acc = block_sum_same(acc, sm);
-    sp = block_sum(sp, sm);
+      sp += u;
+    });
+    acc = block_sum_polish(acc, sp, sm);
     dd Sdd = dd_div_sq(acc, zi);
     dd gd = dd_add(dd_add(bdd, dd{-cur, 0.0}), Sdd);
     double Spz = sp / zi2;
@@ -1902,6 +1945,7 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
     gprev = ag;
     newton = -(gd.hi + gd.lo) / gpv;
     double t;
+    bool last_one = !confirm && fabs(newton) <= 0x1p-36 * cur;
     if (fabs(newton) <= 0x1p-30 * cur) {
       t = cur + newton;
     } else {
@@ -1916,9 +1960,11 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
     if (!(t >= lo && t <= hi) || !(t > lo0) || !(t < INFINITY) || (slow >= 2 && fabs(newton) > 0x1p-30 * cur)) {
       t = fmid(lo, hi);
       slow = 0;
+      last_one = false;
     }
     if (t == cur) break;
     cur = t;
+    if (last_one) break;
   }
   *last = fabs(newton) <= 0x1p-30 * cur ? newton : 0.0;
   *steps = pit;
@@ -1991,27 +2037,25 @@ __device__ void fix_items(const KArgs& A) {
         sp = 0.0;
         sp3 = 0.0;
         sp4 = 0.0;
-#pragma unroll 4
-        for (int j = tid; j < n; j += FIXT) {
-          if (j == i) continue;
-          const double2 pj = Z2v[j];
-          const double dl = __builtin_fma(s, pj.x, -s * sigma);
+        fix_poles<8, false>(Z2v, nullptr, n, [&](int j, double dj, double z2, double, bool in) {
+          const double dl = __builtin_fma(s, dj, -s * sigma);
           const double pp = __builtin_fma(m, dl, -1.0);
           const double q = fmin(dl * pp, DBL_MAX);  // as in k_eig's accurate pass
           const double r = rcp_1nr(q);
-          double t = pj.y * r;
-          t = __builtin_fma(__builtin_fma(-t, q, pj.y), r, t);  // corrected quotient
-          const double u = (dl * r) * dl;                       // 1/(m - xi_j)
+          double t = z2 * r;
+          t = __builtin_fma(__builtin_fma(-t, q, z2), r, t);  // corrected quotient
+          double u = (dl * r) * dl;                           // 1/(m - xi_j)
+          if (j == i || !in) t = u = 0.0;
           const double tp = t * u;
           const double tp3 = tp * u;
-          const double hi = fmax(cs, t), lo = fmin(cs, t);     // positive terms
+          const double hi = fmax(cs, t), lo = fmin(cs, t);    // positive terms
           const double y = hi + lo;
           cc += (hi - y) + lo;
           cs = y;
           sp += tp;
           sp3 += tp3;
           sp4 = __builtin_fma(tp3, u, sp4);
-        }
+        });
         cs = block_sum_comp3(cs, cc, sp, sp3, sp4, sm);
         ++iters;
         const double g = g_value(bp, it.blo, m, cs, cc, zi, Sz);
@@ -2044,7 +2088,7 @@ __device__ void fix_items(const KArgs& A) {
       double cur = nu1;
       if (!(cur > it.lo && cur < it.hi)) cur = nu0;
       double last;
-      cur = dd_polish(Z2v, Zl, n, i, s, sigma, zi, bdd, xm, it.lo, it.hi, cur, &last, &pit, sm);
+      cur = dd_polish(Z2v, Zl, n, i, s, sigma, zi, bdd, xm, it.lo, it.hi, cur, false, &last, &pit, sm);
       muv = s / cur;
       lam = sigma + muv;
       polished = true;
@@ -2059,16 +2103,14 @@ __device__ void fix_items(const KArgs& A) {
       // eq. (gamma): f(0) = 1 + rho z^T D^{-1} z in double-double
       dd f0 = {0.0, 0.0};
       double uu = 0.0, dmin = INFINITY;
-      #pragma unroll 4
-        for (int j = tid; j < n; j += FIXT) {
-        const double2 pj = Z2v[j];
-          double dj = pj.x, z2 = pj.y;
-        dd t = dd_div(dd{z2, Zl[j]}, dd{dj, 0.0});
-        f0 = dd_add(f0, t);
-        double u = Zv[j] / dj;
-        uu += u * u;
-        dmin = fmin(dmin, fabs(dj));
-      }
+      fix_poles<4, true>(Z2v, Zl, n, [&](int, double dj, double z2, double z2l, bool in) {
+        const dd t = dd_div(dd{z2, z2l}, dd{dj, 0.0});
+        if (in) {
+          f0 = dd_add(f0, t);
+          uu += (z2 / dj) / dj;
+          dmin = fmin(dmin, fabs(dj));
+        }
+      });
       f0 = block_sum_dd(f0, sm);
       uu = block_sum(uu, sm);
       dmin = block_min(dmin, sm);
@@ -2089,32 +2131,49 @@ __device__ void fix_items(const KArgs& A) {
         double hi = (1.0 / dmin + fabs(gam) * uu) * GROW;
         if (!(lo > 0)) lo = 4.9406564584124654e-324;
         if (!(hi > lo)) hi = lo * 2.0;
-        for (int hit = 0; hit < 200 && !adjacent(lo, hi); ++hit) {
-          double m = fmid(lo, hi);
-          double acc = 0.0;
-          #pragma unroll 4
-        for (int j = tid; j < n; j += FIXT) {
-            const double2 pj = Z2v[j];
-            double dt = sh * pj.x, z2 = pj.y;
-            acc += z2 / (dt * __builtin_fma(-m, dt, 1.0));
-          }
+        // h rises and is concave right of its poles: Newton steps from the
+        // eigenvalue found so far, inside the bracket that the signs of h
+        // narrow (bisection alone took 60 passes over the poles, 1.1 ms for one
+        // eigenpair at n = 32768).  The compensated step below follows.
+        double e0 = sh / lam;
+        if (!(e0 > lo && e0 < hi)) e0 = fmid(lo, hi);
+        for (int hit = 0; hit < 200; ++hit) {
+          double acc = 0.0, der = 0.0;
+          fix_poles<8, false>(Z2v, nullptr, n, [&](int, double dj, double z2, double, bool in) {
+            const double dt = sh * dj;
+            const double om = __builtin_fma(-e0, dt, 1.0);
+            const double t = z2 / (dt * om);
+            acc += in ? t : 0.0;
+            der += in ? t * dt / om : 0.0;
+          });
           acc = block_sum(acc, sm);
-          double hv = 1.0 + gt * acc;
-          if (hv < 0) lo = m; else hi = m;
+          der = block_sum(der, sm);
+          const double hv = 1.0 + gt * acc;
+          if (hv < 0) lo = e0; else hi = e0;
+          const double step = -hv / (gt * der);
+          double t = e0 + step;
+          const bool near = fabs(step) <= 0x1p-30 * e0;
+          if (adjacent(lo, hi)) {
+            e0 = hi;
+            break;
+          }
+          if (!(t > lo && t < hi)) {
+            if (near) break;
+            t = fmid(lo, hi);
+          }
+          e0 = t;
+          if (near) break;
         }
-        const double e0 = hi;
         double cs = 0.0, cc = 0.0, sp = 0.0;
-        #pragma unroll 4
-        for (int j = tid; j < n; j += FIXT) {
-          const double2 pj = Z2v[j];
-            double dt = sh * pj.x, z2 = pj.y;
-          double om = __builtin_fma(-e0, dt, 1.0);
-          double t = z2 / (dt * om);
-          double y = cs + t;
+        fix_poles<4, false>(Z2v, nullptr, n, [&](int, double dj, double z2, double, bool in) {
+          const double dt = sh * dj;
+          const double om = __builtin_fma(-e0, dt, 1.0);
+          const double t = in ? z2 / (dt * om) : 0.0;
+          const double y = cs + t;
           cc += (fabs(cs) >= fabs(t)) ? ((cs - y) + t) : ((t - y) + cs);
           cs = y;
-          sp += z2 / (om * om);
-        }
+          sp += in ? z2 / (om * om) : 0.0;
+        });
         double S = block_sum_comp(cs, cc, sm);
         sp = block_sum(sp, sm);
         double hv = 1.0 + gt * S;
@@ -2126,12 +2185,13 @@ __device__ void fix_items(const KArgs& A) {
 
     if (polished) {
       double acc = 0.0;
-      #pragma unroll 4
-        for (int j = tid; j < n; j += FIXT) {
-        double r = muv / ((Dv[j] - sigma) - muv);
-        double z2 = Z2[2 * j + 1];
-        acc = __builtin_fma(z2 * r, r, acc);
-      }
+      fix_poles<8, false>(Z2v, nullptr, n, [&](int, double dj, double z2, double, bool in) {
+        const double den = (dj - sigma) - muv;
+        const double rc = rcp_1nr(den);
+        double r = muv * rc;
+        r = __builtin_fma(__builtin_fma(-r, den, muv), rc, r);  // corrected quotient
+        acc = __builtin_fma(in ? z2 * r : 0.0, r, acc);
+      });
       xsv = sqrt(block_sum(acc, sm));
     }
     if (tid == 0) {
@@ -2155,7 +2215,7 @@ __device__ void fix_items(const KArgs& A) {
   }
 }
 
-__global__ void __launch_bounds__(FIXT) k_fix(KArgs A) { fix_items(A); }
+__global__ void __launch_bounds__(FIXT, 4) k_fix(KArgs A) { fix_items(A); }
 
 // ------------------------------------------------------------------- out
 // The shifted representation of an eigenpair is usable when lambda is finite,
@@ -2490,7 +2550,7 @@ __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
 // flagged eigenpairs from the queue (latency-bound work), the others write V
 // (HBM-bound), so the two overlap.
 template <int CB>
-__global__ void __launch_bounds__(VEC_T) k_fixvec(KArgs A, VArgs v, int nfix) {
+__global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix) {
   if (blockIdx.x < (unsigned)nfix)
     fix_items(A);
   else if (v.sweep)
@@ -2679,7 +2739,7 @@ __global__ void __launch_bounds__(FIXT) k_remedy(KArgs A, OArgs O) {
       double cur = 1.0 / (s * (lp.hi + lp.lo));
       double last;
       int steps;
-      cur = dd_polish(Z2v, Zl, n, po, s, sigma, zp, bdd, xm, xm, INFINITY, cur, &last, &steps, sm);
+      cur = dd_polish(Z2v, Zl, n, po, s, sigma, zp, bdd, xm, xm, INFINITY, cur, true, &last, &steps, sm);
       const dd nu = fast_two_sum(cur, last);
       const dd mup = dd_div(dd{s, 0.0}, nu);
       const dd mi = dd_add(two_sum(sigma, -Dv[i]), mup);
