@@ -2295,6 +2295,10 @@ constexpr int VEC_ROWS = 2048;
 // columns per block: 32 for a batch as for one problem (64 measured 4-7 %
 // slower on the 2048-problem mix and on 4 problems of n = 16384, 16 no faster)
 constexpr int VEC_C_SINGLE = 32, VEC_C_BATCH = 32;
+// Where blocks of that many columns leave the GPU idle their width is halved,
+// to 4 at least, until VEC_BLOCKS run (n = 1501: 47 blocks of 32 columns took
+// 54 us for 18 MB).
+constexpr int64_t VEC_BLOCKS = 1024;
 // most chunks of the overlapped single-problem solve (opts.vwrite)
 constexpr int VEC_CHUNKS_MAX = 8;
 
@@ -2305,6 +2309,7 @@ struct VArgs {
   const Meta* meta;
   const int4* groups;  // batched: (problem, first column, columns, first row) per block
   int64_t ncolgroups;  // single problem: column groups per row tile
+  int32_t cb;          // single problem: columns per group (at most VEC_C_SINGLE)
   const double* sd;
   const double* sz;
   const double* mu;
@@ -2342,14 +2347,14 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
     r0 = g.w;
   } else {
     p = 0;
-    c0 = v.cbase + (int)(bid % ncolgroups) * CB;
+    c0 = v.cbase + (int)(bid % ncolgroups) * v.cb;
     r0 = (int64_t)(bid / ncolgroups) * VEC_ROWS;
     nc = 0;
   }
   const Meta M = meta[p];
   if (M.info != 0) return;
   const int n = M.n;
-  if (!groups) nc = min(CB, min(n, v.cend) - c0);
+  if (!groups) nc = min(v.cb, min(n, v.cend) - c0);
   const int nr = (int)min((int64_t)VEC_ROWS, (int64_t)n - r0);
   if (nc <= 0 || nr <= 0) return;
   const double sg = M.neg ? -1.0 : 1.0;
@@ -2901,7 +2906,11 @@ static constexpr Layout layout_single(int64_t n) {
   return layout(1, n, 0, 0, n < FAR_MIN ? 0 : (n + WAVE - 1) / WAVE + far_wide_records(n));
 }
 // A batch: records for the whole queue; its wide level lies behind.
+// Halving the columns of the writer's blocks at most doubles a count below
+// VEC_BLOCKS, so 2 VEC_BLOCKS entries hold the table wherever it is not the one
+// of full blocks: the size grows with the problems and their number.
 static Layout layout_batch(int64_t nprob, int64_t N, int64_t ngroups) {
+  ngroups = std::max(ngroups, 2 * VEC_BLOCKS);
   const int64_t nitems = N / WAVE + nprob;  // upper bound of sum ceil(n_p/64)
   return layout(nprob, N, nitems, ngroups, nitems);
 }
@@ -2995,14 +3004,19 @@ static const int OCC_CAND[3] = {4, 6, 8};
 static double occ_margin(int oc) { return oc > 4 ? 0.96 : 1.0; }
 
 // Number of (problem, column group, row tile) blocks of the batched
-// eigenvector launch.
-static int64_t count_groups(int64_t nprob, const int64_t* offs) {
+// eigenvector launch with cb columns each, and its columns per block.
+static int64_t count_groups(int64_t nprob, const int64_t* offs, int cb) {
   int64_t c = 0;
   for (int64_t p = 0; p < nprob; ++p) {
     const int64_t np = offs[p + 1] - offs[p];
-    c += ((np + VEC_C_BATCH - 1) / VEC_C_BATCH) * ((np + VEC_ROWS - 1) / VEC_ROWS);
+    c += ((np + cb - 1) / cb) * ((np + VEC_ROWS - 1) / VEC_ROWS);
   }
   return c;
+}
+static int batch_columns(int64_t nprob, const int64_t* offs) {
+  int cb = VEC_C_BATCH;
+  while (cb > 4 && count_groups(nprob, offs, cb) < VEC_BLOCKS) cb /= 2;
+  return cb;
 }
 
 // LDS of k_eig's cross-wave reductions: the widest, wg_sum<RED_NV>, stores
@@ -3167,6 +3181,9 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   va.V = V;
   va.voffs = voffs;
   va.ldv = ldv;
+  const int64_t rtiles = (N + VEC_ROWS - 1) / VEC_ROWS;
+  va.cb = VEC_C_SINGLE;
+  while (va.cb > 4 && (N + va.cb - 1) / va.cb * rtiles < VEC_BLOCKS) va.cb /= 2;
   va.cbase = 0;
   va.cend = (int32_t)N;
   va.prio = 0;
@@ -3211,7 +3228,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     }
   };
   auto launch_vec = [&](int64_t cb, int64_t ce, hipStream_t s2, bool prio) {
-    const int64_t cg = (ce - cb + VEC_C_SINGLE - 1) / VEC_C_SINGLE;
+    const int64_t cg = (ce - cb + va.cb - 1) / va.cb;
     const int64_t rt = (N + VEC_ROWS - 1) / VEC_ROWS;
     VArgs vb = va;
     vb.groups = nullptr;
@@ -3294,7 +3311,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
       va.ncolgroups = ngroups;
       hipLaunchKernelGGL((k_fixvec<VEC_C_BATCH>), dim3((unsigned)(nfix + ngroups)), dim3(VEC_T), 0, st, A, va, nfix);
     } else {
-      const int64_t cg = (N + VEC_C_SINGLE - 1) / VEC_C_SINGLE;
+      const int64_t cg = (N + va.cb - 1) / va.cb;
       const int64_t rt = (N + VEC_ROWS - 1) / VEC_ROWS;
       va.groups = nullptr;
       va.ncolgroups = cg;
@@ -3374,7 +3391,8 @@ size_t dpr1_batched_workspace_size(int64_t nprob, const int64_t* offs_host) {
   for (int64_t p = 0; p < nprob; ++p)
     if (offs_host[p + 1] - offs_host[p] < 1) return 0;
   int64_t ntotal = offs_host[nprob];
-  return batch_bytes(layout_batch(nprob, ntotal, count_groups(nprob, offs_host)), count_wide(nprob, offs_host));
+  return batch_bytes(layout_batch(nprob, ntotal, count_groups(nprob, offs_host, VEC_C_BATCH)),
+                     count_wide(nprob, offs_host));
 }
 
 int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* opts, dpr1_plan* plan,
@@ -3392,7 +3410,7 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   }
   int64_t N = offs_host[nprob];
   if (N > (int64_t)INT32_MAX) return -2;
-  const Layout L0 = layout_batch(nprob, N, count_groups(nprob, offs_host));
+  const Layout L0 = layout_batch(nprob, N, count_groups(nprob, offs_host, VEC_C_BATCH));
   const int64_t nwide = count_wide(nprob, offs_host);
   if (work_bytes < batch_bytes(L0, nwide)) return -6;
   dpr1_opts o;
@@ -3426,11 +3444,12 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   // blocks of the eigenvector kernel: (problem, first column, columns,
   // first row), largest problems first
   std::vector<int4> groups;
+  const int cb = batch_columns(nprob, offs_host);
   for (int32_t p : order) {
     const int64_t np = offs_host[p + 1] - offs_host[p];
-    for (int64_t c0 = 0; c0 < np; c0 += VEC_C_BATCH)
+    for (int64_t c0 = 0; c0 < np; c0 += cb)
       for (int64_t r0 = 0; r0 < np; r0 += VEC_ROWS)
-        groups.push_back(make_int4(p, (int)c0, (int)std::min<int64_t>(VEC_C_BATCH, np - c0), (int)r0));
+        groups.push_back(make_int4(p, (int)c0, (int)std::min<int64_t>(cb, np - c0), (int)r0));
   }
   hipStream_t st = (hipStream_t)stream;
   HIPCHECK(hipMemcpyAsync((char*)work + L0.items, items.data(), sizeof(int4) * nitems, hipMemcpyHostToDevice, st));
