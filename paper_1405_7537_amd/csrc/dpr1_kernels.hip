@@ -22,16 +22,14 @@
 //              Instances for 4, 6 and 8 waves per SIMD (register budgets);
 //              the split W, the budget and the pass count are options that
 //              dpr1_autotune / dpr1_batched_autotune choose by timing.
-//   k_out   -- user outputs in the caller's index order.
 //   k_fix   -- one 256-thread block at a time per flagged eigenpair: root
 //              search continued past k_eig's pass budget, double-double
 //              Newton polish, and the near-zero recomputation of eq. (gamma).
 //   k_fixvec -- k_fix's work and the eigenvector writer in one launch: a few
 //              blocks finish the flagged eigenpairs while the others write V,
 //              one block per column group and row range, non-temporal stores
-//              in windows aligned to whole cache lines; flagged columns are
-//              left to k_fixout.
-//   k_fixout -- outputs and V columns of the flagged eigenpairs.
+//              in windows aligned to whole cache lines; a flagged column is
+//              written by the block that finishes its eigenpair.
 #include <float.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -109,6 +107,18 @@ struct KArgs {
   int32_t remedy;       // apply (R1)/(R2) where K_nu > knu_thr
   double knu_thr;
   double* knu;          // optional output: K_nu per eigenpair (caller's order)
+  // the caller's outputs (all but lam_out and info_out may be null) and the
+  // eigenvector writer's per-column constants
+  double* lam_out;
+  int32_t* idx_out;
+  double* mu_out;
+  double* xn_out;
+  int32_t* info_out;
+  double* V;
+  const int64_t* voffs;
+  int64_t ldv;
+  double* csig;         // [N]  sigma_k
+  double* cinv;         // [N]  1/||x_k||
 };
 
 // ------------------------------------------------------------ bit helpers
@@ -274,20 +284,45 @@ __device__ __forceinline__ void sweep_lo(const double* P, const double* Zl, int 
 
 // ------------------------------------------------------------------ prep
 // nsplit == 1: block p stages problem p and writes its meta.  nsplit > 1 (a
-// single problem): block b stages one slice and leaves its partial sum and
-// flags in `part`; the last block to finish adds the partials in slice order
-// (so the result does not depend on the order the blocks ran in) and writes
-// the meta.
+// single problem): block b stages one slice and leaves its partial sums and
+// flags in `part`, which k_meta adds in slice order (the last block of k_prep
+// doing it behind a fence cost 20 us at n = 32768: the fence writes back the
+// XCD's L2).  Block 0 also clears the counters and the stats.
 constexpr int PREP_MAX_SPLIT = 64;
+__device__ __forceinline__ void put_meta(int p, int64_t off, int64_t n, double rho, double zz, double za, int fl,
+                                         Meta* meta, int32_t* info) {
+  int code = 0;
+  if (!isfinite(rho) || rho == 0.0) code = DPR1_INFO_BAD_RHO;
+  else if (fl & 4) code = DPR1_INFO_NONFINITE;
+  else if (fl & 1) code = DPR1_INFO_UNSORTED;
+  else if (fl & 2) code = DPR1_INFO_ZERO_Z;
+  else if (fl & 8) code = DPR1_INFO_RANGE;
+  Meta m;
+  m.off = off;
+  m.n = (int32_t)n;
+  m.neg = rho < 0;
+  m.info = code;
+  m.pad = 0;
+  m.rho = fabs(rho);
+  m.zz = zz;
+  m.zabs = za;
+  meta[p] = m;
+  if (info) info[p] = code;
+}
 __global__ void __launch_bounds__(256) k_prep(int nprob, int nsplit, const int64_t* __restrict__ offs,
                                               int64_t n_single, const double* __restrict__ d,
                                               const double* __restrict__ z, const double* __restrict__ rho_dev,
                                               double rho_host, Meta* __restrict__ meta, double* __restrict__ sd,
                                               double* __restrict__ sz, double* __restrict__ pairs,
                                               double* __restrict__ z2lo, int32_t* __restrict__ info,
-                                              double* __restrict__ part, int32_t* __restrict__ done_ctr) {
+                                              double* __restrict__ part, int32_t* __restrict__ ctr,
+                                              int32_t* __restrict__ stats) {
   const int p = nsplit == 1 ? (int)blockIdx.x : 0;
   const int bs = nsplit == 1 ? 0 : (int)blockIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < 16) {
+    ctr[threadIdx.x] = 0;
+    if (stats && threadIdx.x < DPR1_NSTATS) stats[threadIdx.x] = 0;
+  }
   if (p >= nprob) return;
   const int64_t off = offs ? offs[p] : 0;
   const int64_t n = offs ? offs[p + 1] - offs[p] : n_single;
@@ -296,7 +331,7 @@ __global__ void __launch_bounds__(256) k_prep(int nprob, int nsplit, const int64
   const int64_t chunk = (n + nsplit - 1) / nsplit;
   const int64_t ja = min(n, (int64_t)bs * chunk), jb = min(n, ja + chunk);
   __shared__ double red[256], red2[256];
-  __shared__ int flags, last;
+  __shared__ int flags;
   if (threadIdx.x == 0) flags = 0;
   __syncthreads();
   int f = 0;
@@ -337,56 +372,56 @@ __global__ void __launch_bounds__(256) k_prep(int nprob, int nsplit, const int64
     }
     __syncthreads();
   }
-  double zz = red[0], za = red2[0];
-  int fl = flags;
+  if (threadIdx.x != 0) return;
   if (nsplit > 1) {
     // part: (sum zeta^2, sum |zeta|, flags) per slice
-    if (threadIdx.x == 0) {
-      part[3 * bs] = zz;
-      part[3 * bs + 1] = za;
-      part[3 * bs + 2] = (double)fl;
-      __threadfence();
-      last = atomicAdd(done_ctr, 1) == nsplit - 1;
-    }
-    __syncthreads();
-    if (!last) return;
-    __threadfence();
-    if (threadIdx.x == 0) {
-      const volatile double* vp = part;
-      zz = 0.0;
-      za = 0.0;
-      fl = 0;
-      for (int q = 0; q < nsplit; ++q) {
-        zz += vp[3 * q];
-        za += vp[3 * q + 1];
-        fl |= (int)vp[3 * q + 2];
-      }
-    }
-  }
-  if (threadIdx.x == 0) {
-    int code = 0;
-    if (!isfinite(rho) || rho == 0.0) code = DPR1_INFO_BAD_RHO;
-    else if (fl & 4) code = DPR1_INFO_NONFINITE;
-    else if (fl & 1) code = DPR1_INFO_UNSORTED;
-    else if (fl & 2) code = DPR1_INFO_ZERO_Z;
-    else if (fl & 8) code = DPR1_INFO_RANGE;
-    Meta m;
-    m.off = off;
-    m.n = (int32_t)n;
-    m.neg = neg;
-    m.info = code;
-    m.pad = 0;
-    m.rho = fabs(rho);
-    m.zz = zz;
-    m.zabs = za;
-    meta[p] = m;
-    if (info) info[p] = code;
+    part[3 * bs] = red[0];
+    part[3 * bs + 1] = red2[0];
+    part[3 * bs + 2] = (double)flags;
+  } else {
+    put_meta(p, off, n, rho, red[0], red2[0], flags, meta, info);
   }
 }
+__global__ void __launch_bounds__(64) k_meta(int nsplit, const int64_t* __restrict__ offs, int64_t n_single,
+                                             const double* __restrict__ rho_dev, double rho_host,
+                                             const double* __restrict__ part, Meta* __restrict__ meta,
+                                             int32_t* __restrict__ info) {
+  __shared__ double lp[3 * PREP_MAX_SPLIT];
+  for (int t = threadIdx.x; t < 3 * nsplit; t += 64) lp[t] = part[t];
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  double zz = 0.0, za = 0.0;
+  int fl = 0;
+  for (int q = 0; q < nsplit; ++q) {
+    zz += lp[3 * q];
+    za += lp[3 * q + 1];
+    fl |= (int)lp[3 * q + 2];
+  }
+  put_meta(0, offs ? offs[0] : 0, offs ? offs[1] - offs[0] : n_single, rho_dev ? rho_dev[0] : rho_host, zz, za, fl,
+           meta, info);
+}
 
-__global__ void k_zero(int32_t* __restrict__ a, int n) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) a[t] = 0;
+// ------------------------------------------------------------------- out
+// The shifted representation of an eigenpair is usable when lambda is finite,
+// mu is a normal number and |mu| ||x|| is finite and positive.  It leaves the
+// binary64 range when |delta_j / mu| exceeds it (mu beside a pole with zeta
+// near 1e-150 while the poles spread over many decades): the problem's info
+// then reports DPR1_INFO_RANGE instead of returning NaN silently.
+__device__ __forceinline__ bool range_ok(double lam, double mu, double xs) {
+  return fabs(lam) < INFINITY && fabs(mu) >= 2.2250738585072014e-308 && fabs(mu) < INFINITY && xs > 0.0 &&
+         xs < INFINITY;
+}
+// An eigenpair's values in the caller's order (rho < 0 maps k -> n-1-k,
+// lambda -> -lambda); final: checked for range too.
+__device__ __forceinline__ void put_outputs(const KArgs& A, const Meta& M, int p, int k, int i, double lam, double mu,
+                                            double xs, bool final) {
+  const int64_t b = M.off + (M.neg ? M.n - 1 - k : k);
+  const double sg = M.neg ? -1.0 : 1.0;
+  A.lam_out[b] = sg * lam;
+  if (A.idx_out) A.idx_out[b] = M.neg ? M.n - 1 - i : i;
+  if (A.mu_out) A.mu_out[b] = sg * mu;
+  if (A.xn_out) A.xn_out[b] = xs / fabs(mu);
+  if (final && !range_ok(lam, mu, xs)) A.info_out[p] = DPR1_INFO_RANGE;
 }
 
 // ------------------------------------------------------------------- eig
@@ -1113,7 +1148,17 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   const int wv = wave_id();
   const int lane = lane_id();
   const Meta M = A.meta[p];
-  if (M.info != 0) return;
+  if (M.info != 0) {
+    // rejected problem: defined outputs (NaN values, in-range shift indices)
+    if (wv == 0 && k0 + lane < M.n) {
+      const int64_t b = M.off + k0 + lane;
+      A.lam_out[b] = NAN;
+      if (A.idx_out) A.idx_out[b] = k0 + lane;
+      if (A.mu_out) A.mu_out[b] = NAN;
+      if (A.xn_out) A.xn_out[b] = NAN;
+    }
+    return;
+  }
   const int n = M.n;
   const int64_t off = M.off;
   const double* P = A.pairs + 2 * off;
@@ -1135,6 +1180,9 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
       A.mu[off] = m;
       A.xs[off] = fabs(z0);
       A.lam[off] = Dv[0] + m;
+      A.csig[off] = Dv[0];
+      A.cinv[off] = fabs(m) / fabs(z0);
+      put_outputs(A, M, p, 0, 0, Dv[0] + m, m, fabs(z0), true);
     }
     return;
   }
@@ -1625,8 +1673,19 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
     // a tip b' beyond binary64 (zeta_i near 1e-150 beside a pole 1e-13 away
     // with an O(1) zeta) leaves g undefined: the NaN norm makes the output
     // check report DPR1_INFO_RANGE instead of a wrong vector
-    A.xs[off + k] = fabs(bp) < INFINITY ? sqrt(Nx[0]) : NAN;
+    const double xs = fabs(bp) < INFINITY ? sqrt(Nx[0]) : NAN;
+    A.xs[off + k] = xs;
     A.lam[off + k] = lam;
+    // per-column constants of the eigenvector writer: sigma_k and
+    // w_k = 1/||x_k|| = |mu|/(|mu| ||x||), so that v_j = zeta_j (w_k/(delta_j -
+    // mu)).  The quotient w/(delta_j - mu) = v_j/zeta_j is at most 1/|zeta_j|
+    // and underflows only where v_j/zeta_j does; mu/(delta_j - mu) alone would
+    // be subnormal beside a distant pole when mu is tiny (1e-304 against
+    // delta_j = 1e10) and lose bits although v_j is a normal number
+    A.csig[off + k] = sigma;
+    A.cinv[off + k] = fabs(muv) / xs;
+    // flagged pairs are finished, checked and written by k_fix
+    if (!(pol || nz || cont)) put_outputs(A, M, p, k, i, lam, muv, xs, true);
     if (pol || nz || cont) {
       // the long items (polish, near-zero recomputation) fill the list from
       // the front, roots only continued fill it from the back, so that the
@@ -2194,13 +2253,29 @@ __device__ void fix_items(const KArgs& A) {
       });
       xsv = sqrt(block_sum(acc, sm));
     }
+    const double xs = polished || have_xs ? (fabs(it.bhi) < INFINITY ? xsv : NAN) : A.xs[off + k];
+    if (A.V) {
+      // the pair's column, in the writer's arithmetic
+      const int64_t ko = M.neg ? n - 1 - k : k;
+      const double sg = M.neg ? -1.0 : 1.0;
+      const double iv = fabs(muv) / xs;  // 1/||x||
+      double* col = A.V + (A.voffs ? A.voffs[it.p] : 0) + ko * (A.voffs ? (int64_t)n : A.ldv);
+#pragma unroll 8
+      for (int pos = tid; pos < n; pos += FIXT) {
+        const int j = M.neg ? n - 1 - pos : pos;
+        const double den = (Dv[j] - sigma) - muv;
+        const double rc = rcp_1nr(den);
+        double q = iv * rc;
+        q = __builtin_fma(__builtin_fma(-q, den, iv), rc, q);  // corrected quotient
+        __builtin_nontemporal_store((sg * Zv[j]) * q, &col[pos]);
+      }
+    }
     if (tid == 0) {
+      put_outputs(A, M, it.p, k, i, lam, muv, xs, true);
       A.lam[off + k] = lam;
       if (nz) A.vflag[off + k] = 2;  // lambda from eq. (gamma): no remedy of K_nu
-      if (polished || have_xs) {
-        A.mu[off + k] = muv;
-        A.xs[off + k] = fabs(it.bhi) < INFINITY ? xsv : NAN;
-      }
+      A.mu[off + k] = muv;
+      A.xs[off + k] = xs;
       if (A.stats) {
         if (polished) {
           atomicAdd(&A.stats[DPR1_STAT_POLISHED], 1);
@@ -2216,67 +2291,6 @@ __device__ void fix_items(const KArgs& A) {
 }
 
 __global__ void __launch_bounds__(FIXT, 4) k_fix(KArgs A) { fix_items(A); }
-
-// ------------------------------------------------------------------- out
-// The shifted representation of an eigenpair is usable when lambda is finite,
-// mu is a normal number and |mu| ||x|| is finite and positive.  It leaves the
-// binary64 range when |delta_j / mu| exceeds it (mu beside a pole with zeta
-// near 1e-150 while the poles spread over many decades): the problem's info
-// then reports DPR1_INFO_RANGE instead of returning NaN silently.
-__device__ __forceinline__ bool range_ok(double lam, double mu, double xs) {
-  return fabs(lam) < INFINITY && fabs(mu) >= 2.2250738585072014e-308 && fabs(mu) < INFINITY && xs > 0.0 &&
-         xs < INFINITY;
-}
-
-// user outputs in the caller's order (rho < 0 maps k -> n-1-k, lambda -> -lambda)
-__global__ void __launch_bounds__(256) k_out(const Meta* __restrict__ meta, int nprob,
-                                             const int32_t* __restrict__ ii, const double* __restrict__ mu,
-                                             const double* __restrict__ xs, const double* __restrict__ lam,
-                                             const double* __restrict__ sd, double* __restrict__ csig,
-                                             double* __restrict__ cinv, double* __restrict__ lam_out,
-                                             int32_t* __restrict__ idx_out, double* __restrict__ mu_out,
-                                             double* __restrict__ xn_out, const uint8_t* __restrict__ vflag,
-                                             int32_t* __restrict__ info_out, int kb, int ke) {
-  // a batch: block p handles problem p; one problem: the grid strides over
-  // its eigenvalues kb .. ke-1
-  const int p = nprob > 1 ? (int)blockIdx.x : 0;
-  const int k0 = nprob > 1 ? (int)threadIdx.x : (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  const int kstep = nprob > 1 ? (int)blockDim.x : (int)(gridDim.x * blockDim.x);
-  if (p >= nprob) return;
-  const Meta M = meta[p];
-  const int n = M.n;
-  if (M.info != 0) {
-    // rejected problem: the solver wrote nothing; leave defined outputs
-    // (NaN values, in-range shift indices) and no eigenvector constants
-    for (int k = k0; k < n; k += kstep) {
-      int64_t b = M.off + k;
-      lam_out[b] = NAN;
-      if (idx_out) idx_out[b] = k;
-      if (mu_out) mu_out[b] = NAN;
-      if (xn_out) xn_out[b] = NAN;
-    }
-    return;
-  }
-  for (int k = kb + k0; k < min(n, ke); k += kstep) {
-    int ko = M.neg ? n - 1 - k : k;
-    int64_t a = M.off + k, b = M.off + ko;
-    double sg = M.neg ? -1.0 : 1.0;
-    lam_out[b] = sg * lam[a];
-    // per-column constants of the eigenvector kernel: sigma_k and
-    // w_k = 1/||x_k|| = |mu|/(|mu| ||x||), so that v_j = zeta_j (w_k/(delta_j -
-    // mu)).  The quotient w/(delta_j - mu) = v_j/zeta_j is at most 1/|zeta_j|
-    // and underflows only where v_j/zeta_j does; mu/(delta_j - mu) alone would
-    // be subnormal beside a distant pole when mu is tiny (1e-304 against
-    // delta_j = 1e10) and lose bits although v_j is a normal number
-    csig[a] = sd[M.off + ii[a]];
-    cinv[a] = fabs(mu[a]) / xs[a];
-    if (idx_out) idx_out[b] = M.neg ? n - 1 - ii[a] : ii[a];
-    if (mu_out) mu_out[b] = sg * mu[a];
-    if (xn_out) xn_out[b] = xs[a] / fabs(mu[a]);
-    // flagged pairs are finished (and checked) by k_fix / k_fixout
-    if (!vflag[a] && !range_ok(lam[a], mu[a], xs[a])) info_out[p] = DPR1_INFO_RANGE;
-  }
-}
 
 // ------------------------------------------------------------------- vec
 // v_j = zeta_j w/(delta_j - mu), w = 1/||x|| (eq. eigenvecAi).  A block owns up
@@ -2303,8 +2317,8 @@ constexpr int64_t VEC_BLOCKS = 1024;
 constexpr int VEC_CHUNKS_MAX = 8;
 
 // Arguments of the eigenvector writer.  Columns flagged in vflag belong to
-// eigenpairs that k_fix finishes; they are skipped here and written by
-// k_fixout once their values are final.
+// eigenpairs that k_fix finishes; they are skipped here and written there once
+// their values are final.
 struct VArgs {
   const Meta* meta;
   const int4* groups;  // batched: (problem, first column, columns, first row) per block
@@ -2488,7 +2502,7 @@ __device__ void vec_sweep(const VArgs& v, int g, int nw) {
   const int ngrp = (ce - cb + SWEEP_U - 1) / SWEEP_U;
   // the constants of group q in one load across the wave: lane u + 8 t
   // holds, for column cb + q SWEEP_U + u, sigma (t = 0), mu (1), 1/||x||
-  // (2) or 1 for a column to skip (3: past the range, or one k_fixout
+  // (2) or 1 for a column to skip (3: past the range, or one k_fix
   // writes)
   auto load = [&](int q) {
     const int u = lane & (SWEEP_U - 1), t = lane / SWEEP_U;
@@ -2565,50 +2579,6 @@ __global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix)
     vec_block<CB>(blockIdx.x - nfix, v);
 }
 
-// Outputs and V columns of the eigenpairs finished in k_fix, in the same
-// arithmetic as k_out and the eigenvector writer.
-__global__ void __launch_bounds__(256) k_fixout(KArgs A, double* __restrict__ lam_out,
-                                                int32_t* __restrict__ idx_out, double* __restrict__ mu_out,
-                                                double* __restrict__ xn_out, double* __restrict__ V,
-                                                const int64_t* __restrict__ voffs, int64_t ldv,
-                                                int32_t* __restrict__ info_out) {
-  const int n0 = A.ctr[0];
-  const int cnt = n0 + A.ctr[3];
-  for (int e = blockIdx.x; e < cnt; e += gridDim.x) {
-    const FixItem it = A.fix[fix_slot(A, n0, e)];
-    const Meta M = A.meta[it.p];
-    const int n = M.n, k = it.k;
-    const int64_t a = M.off + k;
-    const int ii = A.ii[a];
-    const double m = A.mu[a], xs = A.xs[a];
-    const int ko = M.neg ? n - 1 - k : k;
-    const double sg = M.neg ? -1.0 : 1.0;
-    if (threadIdx.x == 0) {
-      const int64_t b = M.off + ko;
-      lam_out[b] = sg * A.lam[a];
-      if (idx_out) idx_out[b] = M.neg ? n - 1 - ii : ii;
-      if (mu_out) mu_out[b] = sg * m;
-      if (!range_ok(A.lam[a], m, xs)) info_out[it.p] = DPR1_INFO_RANGE;
-      if (xn_out) xn_out[b] = xs / fabs(m);
-    }
-    if (V) {
-      const double sc = A.sd[M.off + ii];
-      const double iv = fabs(m) / xs;  // 1/||x||, as in k_out
-      const int64_t ld = voffs ? (int64_t)n : ldv;
-      double* col = V + (voffs ? voffs[it.p] : 0) + (int64_t)ko * ld;
-#pragma unroll 8
-      for (int pos = threadIdx.x; pos < n; pos += 256) {
-        const int j = M.neg ? n - 1 - pos : pos;
-        const double den = (A.sd[M.off + j] - sc) - m;
-        const double rc = rcp_1nr(den);
-        double q = iv * rc;
-        q = __builtin_fma(__builtin_fma(-q, den, iv), rc, q);  // corrected quotient
-        __builtin_nontemporal_store((sg * A.sz[M.off + j]) * q, &col[pos]);
-      }
-    }
-  }
-}
-
 // ------------------------------------------------------- K_nu, remedies
 // K_nu of eq. (K0) for eigenpair k shifted to d_i: ||A_i^{-1}||_2 =
 // 1/min_j |lambda_j - d_i|, and by the interlacing (eq. interlace) the
@@ -2670,18 +2640,6 @@ __global__ void __launch_bounds__(256) k_knu(KArgs A, int nprob) {
   }
 }
 
-// Outputs written by the remedy kernel.
-struct OArgs {
-  double* lam_out;
-  int32_t* idx_out;
-  double* mu_out;
-  double* xn_out;
-  double* V;
-  const int64_t* voffs;
-  int64_t ldv;
-  int32_t* info_out;
-};
-
 // Remedies of Sec. 2 (Algorithm 1, last branch), one block of FIXT threads
 // per listed eigenpair:
 //  (R1) the other neighbouring pole d_po: its tip b (eq. b_ob) in
@@ -2699,7 +2657,7 @@ struct OArgs {
 //       from the current estimate; mu_i = (sigma - d_i) + 1/eta.
 // The eigenpair keeps its nearest pole; ||x||, the outputs and its column of
 // V are recomputed from the new mu.
-__global__ void __launch_bounds__(FIXT) k_remedy(KArgs A, OArgs O) {
+__global__ void __launch_bounds__(FIXT) k_remedy(KArgs A) {
   __shared__ double sm[20];
   const int tid = threadIdx.x;
   const int cnt = A.ctr[4];
@@ -2840,19 +2798,14 @@ __global__ void __launch_bounds__(FIXT) k_remedy(KArgs A, OArgs O) {
       A.mu[off + k] = newmu;
       A.xs[off + k] = xsv;
       A.lam[off + k] = lam;
-      const int64_t b = off + ko;
-      O.lam_out[b] = sg * lam;
-      if (O.idx_out) O.idx_out[b] = M.neg ? n - 1 - i : i;
-      if (O.mu_out) O.mu_out[b] = sg * newmu;
-      if (O.xn_out) O.xn_out[b] = xsv / fabs(newmu);
-      if (!range_ok(lam, newmu, xsv)) O.info_out[it.p] = DPR1_INFO_RANGE;
+      put_outputs(A, M, it.p, k, i, lam, newmu, xsv, true);
       if (A.stats) atomicAdd(&A.stats[how == 1 ? DPR1_STAT_REMEDY_R1 : DPR1_STAT_REMEDY_R2], 1);
     }
-    if (O.V) {
+    if (A.V) {
       const double sc = Dv[i];
       const double iv = fabs(newmu) / xsv;
-      const int64_t ld = O.voffs ? (int64_t)n : O.ldv;
-      double* col = O.V + (O.voffs ? O.voffs[it.p] : 0) + (int64_t)ko * ld;
+      const int64_t ld = A.voffs ? (int64_t)n : A.ldv;
+      double* col = A.V + (A.voffs ? A.voffs[it.p] : 0) + (int64_t)ko * ld;
       for (int pos = tid; pos < n; pos += FIXT) {
         const int j = M.neg ? n - 1 - pos : pos;
         const double den = (Dv[j] - sc) - newmu;
@@ -3144,12 +3097,25 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   A.knu_thr = o.knu_thr;
   A.knu = o.knu;
 
-  hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, A.ctr, 16);
-  if (stats) hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, stats, DPR1_NSTATS);
+  A.lam_out = lambda;
+  A.idx_out = shift_idx;
+  A.mu_out = mu;
+  A.xn_out = xnorm;
+  A.info_out = info;
+  A.V = V;
+  A.voffs = voffs;
+  A.ldv = ldv;
+  A.csig = (double*)(w + L.csig);
+  A.cinv = (double*)(w + L.cinv);
+
   const int nsplit = nprob == 1 ? (int)std::min<int64_t>(PREP_MAX_SPLIT, std::max<int64_t>(1, N / 512)) : 1;
   hipLaunchKernelGGL(k_prep, dim3((unsigned)(nsplit > 1 ? nsplit : nprob)), dim3(256), 0, st, (int)nprob, nsplit,
                      offs, n_single, d, z, rho_dev, rho_host, meta, (double*)A.sd, (double*)A.sz,
-                     (double*)A.pairs, (double*)A.z2lo, info, (double*)(w + L.part), A.ctr + 8);
+                     (double*)A.pairs, (double*)A.z2lo, info, (double*)(w + L.part), A.ctr,
+                     stats);
+  if (nsplit > 1)
+    hipLaunchKernelGGL(k_meta, dim3(1), dim3(64), 0, st, nsplit, offs, n_single, rho_dev, rho_host,
+                       (const double*)(w + L.part), meta, info);
   if (far) {
     FarArgs F;
     F.meta = meta;
@@ -3168,15 +3134,13 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   }
   HIPCHECK(hipGetLastError());
   hipEvent_t* ev = (hipEvent_t*)o.events;
-  double* csig = (double*)(w + L.csig);
-  double* cinv = (double*)(w + L.cinv);
   VArgs va;
   va.meta = meta;
   va.sd = A.sd;
   va.sz = A.sz;
   va.mu = A.mu;
-  va.csig = csig;
-  va.cinv = cinv;
+  va.csig = A.csig;
+  va.cinv = A.cinv;
   va.vflag = A.vflag;
   va.V = V;
   va.voffs = voffs;
@@ -3198,34 +3162,15 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
       default: hipLaunchKernelGGL(k_eig<4>, dim3(grid), dim3(64 * W), red_bytes(W), st, A); break;
     }
   };
-  // user outputs of eigenvalues kb .. ke-1 (those of flagged ones are
-  // rewritten by k_fixout once k_fix has finished them) and the per-column
-  // constants of the eigenvector writer
-  auto launch_out = [&](int64_t kb, int64_t ke) {
-    const int64_t cnt = nprob > 1 ? N : ke - kb;
-    hipLaunchKernelGGL(k_out,
-                       dim3(nprob > 1 ? (unsigned)nprob : (unsigned)std::min<int64_t>((cnt + 255) / 256, 1024)),
-                       dim3(256), 0, st, meta, (int)nprob, A.ii, A.mu, A.xs, A.lam, A.sd, csig, cinv, lambda,
-                       shift_idx, mu, xnorm, A.vflag, info, (int)kb, (int)ke);
-  };
   // K_nu of every eigenpair and, with opts.remedy, the remedies (after every
   // eigenpair and column is final, on `stream`)
   auto launch_knu = [&]() {
+    if (!o.knu && !o.remedy && !stats) return;  // nobody reads it
     hipLaunchKernelGGL(k_knu, dim3(nprob > 1 ? (unsigned)nprob : (unsigned)std::min<int64_t>((N + 255) / 256, 1024)),
                        dim3(256), 0, st, A, (int)nprob);
-    if (o.remedy) {
-      OArgs oa;
-      oa.lam_out = lambda;
-      oa.idx_out = shift_idx;
-      oa.mu_out = mu;
-      oa.xn_out = xnorm;
-      oa.V = V;
-      oa.voffs = voffs;
-      oa.ldv = ldv;
-      oa.info_out = info;
+    if (o.remedy)
       hipLaunchKernelGGL(k_remedy, dim3((unsigned)std::min<int64_t>(std::max<int64_t>(N / 16, 1), 2048)),
-                         dim3(FIXT), 0, st, A, oa);
-    }
+                         dim3(FIXT), 0, st, A);
   };
   auto launch_vec = [&](int64_t cb, int64_t ce, hipStream_t s2, bool prio) {
     const int64_t cg = (ce - cb + va.cb - 1) / va.cb;
@@ -3245,7 +3190,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   // groups of 64 eigenvalues, and the columns of chunk c are written on a
   // second stream while chunk c + 1 is solved, so that the HBM-bound stores
   // overlap the ALU-bound sweeps; the last chunk's columns are written beside
-  // k_fix.  Flagged columns are left to k_fixout, as in the sequential path.
+  // k_fix.  Flagged columns are left to k_fix, as in the sequential path.
   // The default (0 or 1) writes V after the eigenvalue kernel, which measured
   // faster at every order tried (n = 8192 .. 65536) since the address-ordered
   // writer; below 8192 eigenpairs the write is short and the fork costs more
@@ -3270,7 +3215,6 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
       // budget, so that writer waves fit next to a 16-wave block
       launch_eig((unsigned)(gb - ga), (int)ga, c == 0 ? occ_of(o) : std::max(occ_of(o), 6));
       if (c == nchunks - 1 && ev && hipEventRecord(ev[1], st) != hipSuccess) rc = DPR1_EHIP;
-      launch_out(ka, kb);
       if (hipGetLastError() != hipSuccess || hipEventRecord(evs[c], st) != hipSuccess ||
           hipStreamWaitEvent(st2, evs[c], 0) != hipSuccess)
         rc = DPR1_EHIP;
@@ -3280,8 +3224,6 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     if (rc == DPR1_OK) {
       unsigned fgrid = (unsigned)std::min<int64_t>(std::max<int64_t>(N, 1), 2048);
       hipLaunchKernelGGL(k_fix, dim3(fgrid), dim3(FIXT), 0, st, A);
-      hipLaunchKernelGGL(k_fixout, dim3((unsigned)std::min<int64_t>(std::max<int64_t>(N, 1), 2048)), dim3(256), 0,
-                         st, A, lambda, shift_idx, mu, xnorm, V, voffs, ldv, info);
       if (hipGetLastError() != hipSuccess || hipEventRecord(evs[nchunks], st2) != hipSuccess ||
           hipStreamWaitEvent(st, evs[nchunks], 0) != hipSuccess || (ev && hipEventRecord(ev[3], st) != hipSuccess))
         rc = DPR1_EHIP;
@@ -3299,8 +3241,6 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   launch_eig(grid, 0, occ_of(o));
   HIPCHECK(hipGetLastError());
   if (ev) HIPCHECK(hipEventRecord(ev[1], st));
-  launch_out(0, N);
-  HIPCHECK(hipGetLastError());
   if (ev) HIPCHECK(hipEventRecord(ev[2], st));
   if (V) {
     // k_fix overlapped with the eigenvector writer: a few blocks take the
@@ -3323,9 +3263,6 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     unsigned fgrid = (unsigned)std::min<int64_t>(std::max<int64_t>(N, 1), 2048);
     hipLaunchKernelGGL(k_fix, dim3(fgrid), dim3(FIXT), 0, st, A);
   }
-  HIPCHECK(hipGetLastError());
-  hipLaunchKernelGGL(k_fixout, dim3((unsigned)std::min<int64_t>(std::max<int64_t>(N, 1), 2048)), dim3(256), 0, st,
-                     A, lambda, shift_idx, mu, xnorm, V, voffs, ldv, info);
   HIPCHECK(hipGetLastError());
   if (ev) HIPCHECK(hipEventRecord(ev[3], st));
   launch_knu();
