@@ -1927,19 +1927,22 @@ __device__ __forceinline__ void fix_poles(const double2* Z2v, const double* Zl, 
 }
 
 // The sums of a polish step in one exchange: the same-signed double-doubles a
-// and the plain sums b, in the orders of block_sum_same and block_sum.
-__device__ __forceinline__ dd block_sum_polish(dd a, double& b, double* sm) {
+// and the plain sums b, c, in the orders of block_sum_same and block_sum.
+__device__ __forceinline__ dd block_sum_polish(dd a, double& b, double& c, double* sm) {
   a = wave_sum_same(a);
   b = wave_sum(b);
+  c = wave_sum(c);
   const int wv = threadIdx.x / WAVE;
   __syncthreads();
   if (threadIdx.x % WAVE == 0) {
     sm[wv] = a.hi;
     sm[4 + wv] = a.lo;
     sm[8 + wv] = b;
+    sm[12 + wv] = c;
   }
   __syncthreads();
   b = (sm[8] + sm[9]) + (sm[10] + sm[11]);
+  c = (sm[12] + sm[13]) + (sm[14] + sm[15]);
   dd r = dd_add_same(dd{sm[0], sm[4]}, dd{sm[1], sm[5]});
   r = dd_add_same(r, dd{sm[2], sm[6]});
   return dd_add_same(r, dd{sm[3], sm[7]});
@@ -1947,9 +1950,11 @@ __device__ __forceinline__ dd block_sum_polish(dd a, double& b, double* sm) {
 
 // Safeguarded iteration for the extreme root of g (eq. secAi) at the shift
 // pole d_i (side s), g evaluated in double-double: far from the root the
-// rational model step of the main solver, close to it Newton (g exact to
+// model step of the main solver, close to it Newton (g exact to
 // ~2^-100, so the last step lands on the rounded root).  b' = s b in
-// double-double, xm the nearest pole of g (in nu), (lo0, hi0) a rigorous
+// double-double, xm the nearest pole of g (in nu) and sw the square root of its
+// weight (one pole and a constant, the model used before, took up to 34 steps
+// beside poles 1e-10 apart: 180 us for one root), (lo0, hi0) a rigorous
 // bracket, cur the start.  Returns the last iterate.  With `confirm` the
 // iteration goes on until a step no longer changes it, *last then receives the
 // Newton correction at it (nu = cur + *last to about 2^-100); without, a Newton
@@ -1958,7 +1963,7 @@ __device__ __forceinline__ dd block_sum_polish(dd a, double& b, double* sm) {
 // double-double evaluations less one.  All threads of the block call it and
 // return the same values.
 __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, double s, double sigma, double zi,
-                           dd bdd, double xm, double lo0, double hi0, double cur, bool confirm, double* last,
+                           dd bdd, double xm, double sw, double lo0, double hi0, double cur, bool confirm, double* last,
                            int* steps, double* sm) {
   const double zi2 = zi * zi;
   double lo = lo0, hi = hi0;
@@ -1970,7 +1975,7 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
   int slow = 0, pit;
   for (pit = 0; pit < 100; ++pit) {
     dd acc = {0.0, 0.0};
-    double sp = 0.0;
+    double sp = 0.0, sp3 = 0.0;
     fix_poles<4, true>(Z2v, Zl, n, [&](int j, double dj, double z2, double z2l, bool in) {
       const dd dl = two_sum(s * dj, -s * sigma);               // delta'_j exactly
       const dd pp = dd_add(dd_mul_d(dl, cur), dd{-1.0, 0.0});  // nu delta' - 1
@@ -1983,15 +1988,17 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
       double e = __builtin_fma(-q1, q.hi, z2);
       e = __builtin_fma(-q1, q.lo, e + z2l);
       dd t = fast_two_sum(q1, e * r);
-      double u = z2 * rcp_1nr(pp.hi * pp.hi);  // g' only steers the step
+      const double rp = rcp_1nr(pp.hi);
+      double u = (z2 * rp) * rp, u3 = u * (dl.hi * rp);  // the derivatives only steer the step
       if (j == i || !in) {
         t = {0.0, 0.0};
-        u = 0.0;
+        u = u3 = 0.0;
       }
       acc = dd_add_same(acc, t);
       sp += u;
+      sp3 += u3;
     });
-    acc = block_sum_polish(acc, sp, sm);
+    acc = block_sum_polish(acc, sp, sp3, sm);
     dd Sdd = dd_div_sq(acc, zi);
     dd gd = dd_add(dd_add(bdd, dd{-cur, 0.0}), Sdd);
     double Spz = sp / zi2;
@@ -2008,12 +2015,7 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
     if (fabs(newton) <= 0x1p-30 * cur) {
       t = cur + newton;
     } else {
-      double x = cur - xm;
-      double Am = Spz * x * x;
-      double C = (bdd.hi + (Sdd.hi - Spz * x)) - xm;
-      double disc = sqrt(C * C + 4.0 * Am);
-      double u = C >= 0 ? (C + disc) * 0.5 : (2.0 * Am) / (disc - C);
-      t = xm + u;
+      t = cur + model_delta(cur, gd.hi, Spz, sp3 / zi2, xm, sw, lo, hi);
     }
     // stay inside the sign bracket and off the pole / rigorous lower end
     if (!(t >= lo && t <= hi) || !(t > lo0) || !(t < INFINITY) || (slow >= 2 && fabs(newton) > 0x1p-30 * cur)) {
@@ -2147,7 +2149,9 @@ __device__ void fix_items(const KArgs& A) {
       double cur = nu1;
       if (!(cur > it.lo && cur < it.hi)) cur = nu0;
       double last;
-      cur = dd_polish(Z2v, Zl, n, i, s, sigma, zi, bdd, xm, it.lo, it.hi, cur, false, &last, &pit, sm);
+      const double zjm = (k > 0) ? Zv[i == k ? k - 1 : k] : 0.0;
+      const double sw = (k > 0) ? fabs(zjm * xm) / fabs(zi) : 0.0;
+      cur = dd_polish(Z2v, Zl, n, i, s, sigma, zi, bdd, xm, sw, it.lo, it.hi, cur, false, &last, &pit, sm);
       muv = s / cur;
       lam = sigma + muv;
       polished = true;
@@ -2702,7 +2706,8 @@ __global__ void __launch_bounds__(FIXT) k_remedy(KArgs A) {
       double cur = 1.0 / (s * (lp.hi + lp.lo));
       double last;
       int steps;
-      cur = dd_polish(Z2v, Zl, n, po, s, sigma, zp, bdd, xm, xm, INFINITY, cur, true, &last, &steps, sm);
+      const double sw = fabs(Zv[po == k ? k - 1 : k] * xm) / fabs(zp);
+      cur = dd_polish(Z2v, Zl, n, po, s, sigma, zp, bdd, xm, sw, xm, INFINITY, cur, true, &last, &steps, sm);
       const dd nu = fast_two_sum(cur, last);
       const dd mup = dd_div(dd{s, 0.0}, nu);
       const dd mi = dd_add(two_sum(sigma, -Dv[i]), mup);
