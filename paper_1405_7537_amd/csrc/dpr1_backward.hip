@@ -258,7 +258,9 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
     }
   }
 
-  // Epilogue.  Accumulator element q of a lane holds row lane/16 + 4q,
+  // Epilogue (256 x 512: 20 % of the kernel's instructions beside the matrix
+  // cores; one V load per element in turn and IEEE quotients cost 90 us a
+  // product).  Accumulator element q of a lane holds row lane/16 + 4q,
   // column lane%16 of its 16x16 block (checked on gfx950 with a probe that
   // multiplies A(:,0) = 2^i by B(0,:) = 3^j).  The per-row and per-column
   // quantities of this tile are staged in LDS first; per-row / per-column
@@ -307,16 +309,30 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     double rs1[4] = {0.0, 0.0, 0.0, 0.0}, rs2[4] = {0.0, 0.0, 0.0, 0.0};
+    // V(row, col) of the 4 NBT elements, all loads in flight together (indices
+    // past the matrix are clamped; their products are dropped)
+    double vj[NBT][4];
+    if (EPI == EPI_D) {
+#pragma unroll
+      for (int b = 0; b < NBT; ++b) {
+        const int col = min(n0 + wn + b * 16 + lane % 16, ni - 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int row = min(m0 + wm + a * 16 + (lane / 16) + 4 * q, ni - 1);
+          vj[b][q] = RV ? v_elem(g, vo, row, col) : A[row + col * lda];
+        }
+      }
+    }
 #pragma unroll
     for (int b = 0; b < NBT; ++b) {
       const int cl = wn + b * 16 + lane % 16;
-      const int64_t col = n0 + cl;
+      const int col = n0 + cl;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int rl = wm + a * 16 + (lane / 16) + 4 * q;
-        const int64_t row = m0 + rl;
-        if (row >= n || col >= n) continue;
-        double v = acc[a][b][q];
+        const int row = m0 + rl;
+        if (row >= ni || col >= ni) continue;
+        const double v = acc[a][b][q];
         if (EPI == EPI_X) {
           // X(row = l, col = k), stored row-major (consecutive lanes on
           // consecutive columns)
@@ -324,17 +340,23 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
           if (row == col) {
             x = clb[cl];
           } else {
-            dd gap = dd_add(two_sum(csig[cl], -rsig[rl]), two_sum(cmu[cl], -rmu[rl]));
-            x = v / (gap.hi + gap.lo);
+            // the gap from the shifted representation: both differences and
+            // their sum with their rounding errors; the quotient corrected
+            const dd ds = two_sum(csig[cl], -rsig[rl]), dm = two_sum(cmu[cl], -rmu[rl]);
+            const dd t = two_sum(ds.hi, dm.hi);
+            const double gap = t.hi + (t.lo + (ds.lo + dm.lo));
+            double r = __builtin_amdgcn_rcp(gap);
+            r = __builtin_fma(r, __builtin_fma(-gap, r, 1.0), r);
+            x = v * r;
+            if (fabs(x) < INFINITY) x = __builtin_fma(__builtin_fma(-x, gap, v), r, x);
           }
-          g.C[mo + row * n + col] = x;
+          g.C[mo + (int64_t)row * n + col] = x;
           rs1[q] += x * cy[cl];
           cs[b] += x * ry[rl];
         } else {
           // Q(row = j, col = k) V(j, k) for d_bar, V(j, k) u_k for z_bar
-          double vjk = RV ? v_elem(g, vo, row, col) : A[row + col * lda];
-          rs1[q] += v * vjk;
-          rs2[q] += vjk * cy[cl];
+          rs1[q] += v * vj[b][q];
+          rs2[q] += vj[b][q] * cy[cl];
         }
       }
     }
