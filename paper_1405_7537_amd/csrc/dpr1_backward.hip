@@ -17,10 +17,11 @@
 // Kernels:
 //   k_gemm<EPI_X>  P = V^T V_bar on FP64 matrix cores, epilogue X = F o P +
 //                  diag(lambda_bar), partial sums of X y (rows) and X^T y (cols)
-//   k_bwd_u        u = (X + X^T) y and rho_bar = y^T X y from those partials
+//   k_bwd_u        u = (X + X^T) y and parts of rho_bar = y^T X y from those
+//                  partials
 //   k_gemm<EPI_D>  Q = V X on FP64 matrix cores, epilogue partial row sums of
 //                  Q o V (for d_bar) and of V diag(u) (for z_bar)
-//   k_bwd_final    d_bar, z_bar = rho V u from the partials
+//   k_bwd_final    d_bar, z_bar = rho V u and rho_bar from the partials
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -427,41 +428,52 @@ __global__ void __launch_bounds__(256) k_bwd_y(int64_t n, int64_t nb, const doub
   }
 }
 
-// u = X y + X^T y and rho_bar = y^T X y from the partials of the first GEMM
+// u = X y + X^T y from the partials of the first GEMM, and the parts of
+// rho_bar = y^T X y that the block's 256 rows give (k_bwd_final adds them in
+// order; one block per problem took 42 us for one problem of n = 2000)
 __global__ void __launch_bounds__(256) k_bwd_u(int64_t n, int ntile, const double* __restrict__ part_r,
                                                const double* __restrict__ part_c, const double* __restrict__ y,
-                                               double* __restrict__ u, double* __restrict__ rho_bar) {
-  const int pb = blockIdx.x;
-  const int64_t vo = (int64_t)pb * n;
+                                               double* __restrict__ u, double* __restrict__ rho_part) {
+  const int64_t pb = blockIdx.y;
+  const int64_t vo = pb * n;
   __shared__ double red[256];
+  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   double acc = 0.0;
-  for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
+  if (j < n) {
     double r = 0.0, c = 0.0;
+#pragma unroll 4
     for (int t = 0; t < ntile; ++t) {
-      int64_t a = ((int64_t)pb * ntile + t) * n + j;
+      const int64_t a = (pb * ntile + t) * n + j;
       r += part_r[a];
       c += part_c[a];
     }
     u[vo + j] = r + c;
-    acc += y[vo + j] * r;
+    acc = y[vo + j] * r;
   }
   red[threadIdx.x] = acc;
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
+  for (int s = 128; s > 0; s >>= 1) {
     if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) rho_bar[pb] = red[0];
+  if (threadIdx.x == 0) rho_part[pb * gridDim.x + blockIdx.x] = red[0];
 }
 
 // d_bar_j = sum_k (V X)_jk V_jk and z_bar = rho V u from the second GEMM's partials
 __global__ void __launch_bounds__(256) k_bwd_final(int64_t n, int64_t nb, int ntile, const double* __restrict__ rho,
                                                    const double* __restrict__ part_d,
-                                                   const double* __restrict__ part_z, double* __restrict__ d_bar,
-                                                   double* __restrict__ z_bar) {
+                                                   const double* __restrict__ part_z,
+                                                   const double* __restrict__ rho_part, double* __restrict__ d_bar,
+                                                   double* __restrict__ z_bar, double* __restrict__ rho_bar) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n * nb) return;
   int64_t pb = t / n, j = t % n;
+  if (j == 0) {
+    const int nr = (int)((n + 255) / 256);
+    double r = 0.0;
+    for (int q = 0; q < nr; ++q) r += rho_part[pb * nr + q];
+    rho_bar[pb] = r;
+  }
   double sd = 0.0, sz = 0.0;
   for (int q = 0; q < ntile; ++q) {
     int64_t a = (pb * ntile + q) * n + j;
@@ -583,7 +595,7 @@ __global__ void __launch_bounds__(256) k_bwd_eigsum(int64_t n, int64_t nb, int p
 __global__ void k_set_rho(double* __restrict__ dst, double v) { *dst = v; }
 
 struct BLayout {
-  size_t X, y, u, pr, pc, pd, pz, sig, ixn, rho, total;
+  size_t X, y, u, pr, pc, pd, pz, sig, ixn, rho, rp, total;
 };
 static size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 static BLayout blayout(int64_t n, int64_t nb) {
@@ -600,6 +612,7 @@ static BLayout blayout(int64_t n, int64_t nb) {
   L.sig = o; o = al(o + sizeof(double) * n * nb);
   L.ixn = o; o = al(o + sizeof(double) * n * nb);
   L.rho = o; o = al(o + sizeof(double));
+  L.rp = o; o = al(o + sizeof(double) * ((n + 255) / 256) * nb);
   L.total = o;
   return L;
 }
@@ -618,6 +631,7 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
   double* pc = (double*)(w + L.pc);
   double* pd = (double*)(w + L.pd);
   double* pz = (double*)(w + L.pz);
+  double* rp = (double*)(w + L.rp);
   const int tiles = (int)((n + BM - 1) / BM);
   const unsigned ggrid = (unsigned)((nbatch * tiles * tiles + NXCD - 1) / NXCD * NXCD);
 
@@ -668,7 +682,8 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
   else
     hipLaunchKernelGGL((k_gemm<EPI_X, true, false>), dim3(ggrid), dim3(NT), 0, st, g);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
-  hipLaunchKernelGGL(k_bwd_u, dim3((unsigned)nbatch), dim3(256), 0, st, n, tiles, pr, pc, y, u, rho_bar);
+  hipLaunchKernelGGL(k_bwd_u, dim3((unsigned)((n + 255) / 256), (unsigned)nbatch), dim3(256), 0, st, n, tiles, pr, pc,
+                     y, u, rp);
   g.B = X;
   if (V)
     hipLaunchKernelGGL((k_gemm<EPI_D, false>), dim3(ggrid), dim3(NT), 0, st, g);
@@ -676,7 +691,7 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
     hipLaunchKernelGGL((k_gemm<EPI_D, true>), dim3(ggrid), dim3(NT), 0, st, g);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
   hipLaunchKernelGGL(k_bwd_final, dim3((unsigned)((n * nbatch + 255) / 256)), dim3(256), 0, st, n, nbatch, tiles,
-                     rho, pd, pz, d_bar, z_bar);
+                     rho, pd, pz, rp, d_bar, z_bar, rho_bar);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
   return DPR1_OK;
 }
