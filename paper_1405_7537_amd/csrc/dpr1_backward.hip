@@ -33,14 +33,10 @@
 namespace dpr1 {
 namespace bwd {
 
-// Block tile 128 x 128 (2 x WNW waves of 64 x TN, each 4 x TN/16 blocks of
-// the 16x16x4 FP64 MFMA), K staged through LDS in slices of 16,
-// double-buffered.
-constexpr int BM = 128, BN = 128, BK = 16;
-constexpr int WNW = 4;               // waves along n
-constexpr int TN = BN / WNW;         // columns per wave
-constexpr int NBT = TN / 16;         // MFMA blocks per wave along n
-constexpr int NT = 128 * WNW;
+// Block tile TB x TB: 128 (2 x 4 waves of 64 x 32) or 64 (2 x 2 waves of 32 x
+// 32), in blocks of the 16x16x4 FP64 MFMA, K staged through LDS in slices of
+// 16, double-buffered; tile_of chooses.
+constexpr int BK = 16;
 constexpr int PAD = 2;   // LDS row padding (doubles)
 constexpr int NXCD = 8;  // workgroups are dealt round-robin to the 8 XCDs
 
@@ -104,8 +100,15 @@ __device__ __forceinline__ double v_elem(const GArgs& g, int64_t vo, int64_t j, 
 // Two blocks per CU (66.5 KB of LDS each, 68 KB where V^T is rebuilt) are 4
 // waves per SIMD, which leaves 128 VGPRs a lane: the bound asks for that
 // budget.
-template <int EPI, bool RV, bool BR = EPI == EPI_D>
-__global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
+template <int TB, int EPI, bool RV, bool BR = EPI == EPI_D>
+__global__ void __launch_bounds__(4 * TB, 4) k_gemm(GArgs g) {
+  constexpr int BM = TB, BN = TB;
+  constexpr int WNW = TB / 32;          // waves along n (2 along m)
+  constexpr int TN = BN / WNW;          // columns per wave
+  constexpr int NBT = TN / 16;          // MFMA blocks per wave along n
+  constexpr int MAT = BM / 32;          // and along m
+  constexpr int NT = 128 * WNW;
+  static_assert(NT == 4 * TB, "launch bounds");
   const int64_t n = g.n;
   const int tiles = (int)((n + BM - 1) / BM);
   const int T = tiles * tiles;
@@ -127,7 +130,7 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x;
   const int wv = tid / 64, lane = tid % 64;
-  const int wm = (wv & 1) * 64, wn = (wv >> 1) * TN;
+  const int wm = (wv & 1) * (BM / 2), wn = (wv >> 1) * TN;
 
   // one LDS buffer: the double-buffered operand tiles during the K loop,
   // the epilogue's per-row / per-column arrays after it
@@ -138,9 +141,9 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
   double(*As)[BK][BM + PAD] = reinterpret_cast<double(*)[BK][BM + PAD]>(smem);
   double(*Bs)[BK][BN + PAD] = reinterpret_cast<double(*)[BK][BN + PAD]>(smem + TILE_D);
 
-  double4_t acc[4][NBT];
+  double4_t acc[MAT][NBT];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < MAT; ++a)
 #pragma unroll
     for (int b = 0; b < NBT; ++b) acc[a][b] = (double4_t){0.0, 0.0, 0.0, 0.0};
 
@@ -240,13 +243,13 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
         // 16x16x4 FP64 MFMA: lane holds A(row = lane%16, k = lane/16) and
         // B(k = lane/16, col = lane%16)
         const int r = lane % 16, q = lane / 16;
-        double af[4], bf[NBT];
+        double af[MAT], bf[NBT];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) af[x] = As[buf][ks + q][wm + 16 * x + r];
+        for (int x = 0; x < MAT; ++x) af[x] = As[buf][ks + q][wm + 16 * x + r];
 #pragma unroll
         for (int x = 0; x < NBT; ++x) bf[x] = Bs[buf][ks + q][wn + 16 * x + r];
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int a = 0; a < MAT; ++a)
 #pragma unroll
           for (int b = 0; b < NBT; ++b)
             acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
@@ -308,7 +311,7 @@ __global__ void __launch_bounds__(NT, 4) k_gemm(GArgs g) {
 #pragma unroll
   for (int b = 0; b < NBT; ++b) cs[b] = 0.0;
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
+  for (int a = 0; a < MAT; ++a) {
     double rs1[4] = {0.0, 0.0, 0.0, 0.0}, rs2[4] = {0.0, 0.0, 0.0, 0.0};
     // V(row, col) of the 4 NBT elements, all loads in flight together (indices
     // past the matrix are clamped; their products are dropped)
@@ -598,9 +601,21 @@ struct BLayout {
   size_t X, y, u, pr, pc, pd, pz, sig, ixn, rho, rp, total;
 };
 static size_t al(size_t x) { return (x + 255) & ~size_t(255); }
+// Tile size of the two products for nb problems of order n: the size whose
+// tiles the fullest of the 256 CUs finishes first.  A tile of 128 alone on its
+// CU takes 1 (two waves per SIMD), two together 1.72, a tile of 64 0.26.
+// Measured, the whole backward with tiles of 64 / 128 in us: n = 400 73 / 156,
+// 1200 259 / 408, 1600 444 / 539, 2000 688 / 664, 2400 1244 / 1373, 2800 1819
+// / 1596; 16 problems of n = 128 40 / 72, 40 of n = 300 133 / 210.
+static int tile_of(int64_t n, int64_t nb) {
+  const int64_t t = (n + 127) / 128, h = (n + 63) / 64;
+  const int64_t u = (t * t * nb + 255) / 256, v = (h * h * nb + 255) / 256;
+  return 0.26 * (double)v < (u == 1 ? 1.0 : 0.86 * (double)u) ? 64 : 128;
+}
 static BLayout blayout(int64_t n, int64_t nb) {
   BLayout L;
-  int64_t nt = (n + BM - 1) / BM;
+  const int tb = tile_of(n, nb);
+  const int64_t nt = (n + tb - 1) / tb;
   size_t o = 0;
   L.X = o; o = al(o + sizeof(double) * n * n * nb);
   L.y = o; o = al(o + sizeof(double) * n * nb);
@@ -632,7 +647,8 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
   double* pd = (double*)(w + L.pd);
   double* pz = (double*)(w + L.pz);
   double* rp = (double*)(w + L.rp);
-  const int tiles = (int)((n + BM - 1) / BM);
+  const int tb = tile_of(n, nbatch);
+  const int tiles = (int)((n + tb - 1) / tb);
   const unsigned ggrid = (unsigned)((nbatch * tiles * tiles + NXCD - 1) / NXCD * NXCD);
 
   double* sig = V ? nullptr : (double*)(w + L.sig);
@@ -673,22 +689,28 @@ static int run_backward(int64_t nbatch, int64_t n, const double* d, const double
     if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
     return DPR1_OK;
   }
+  const auto product = [&](auto small, auto large) {
+    if (tb == 64)
+      hipLaunchKernelGGL(small, dim3(ggrid), dim3(256), 0, st, g);
+    else
+      hipLaunchKernelGGL(large, dim3(ggrid), dim3(512), 0, st, g);
+  };
   if (V && rows)
-    hipLaunchKernelGGL((k_gemm<EPI_X, false, true>), dim3(ggrid), dim3(NT), 0, st, g);
+    product(k_gemm<64, EPI_X, false, true>, k_gemm<128, EPI_X, false, true>);
   else if (V)
-    hipLaunchKernelGGL((k_gemm<EPI_X, false, false>), dim3(ggrid), dim3(NT), 0, st, g);
+    product(k_gemm<64, EPI_X, false, false>, k_gemm<128, EPI_X, false, false>);
   else if (rows)
-    hipLaunchKernelGGL((k_gemm<EPI_X, true, true>), dim3(ggrid), dim3(NT), 0, st, g);
+    product(k_gemm<64, EPI_X, true, true>, k_gemm<128, EPI_X, true, true>);
   else
-    hipLaunchKernelGGL((k_gemm<EPI_X, true, false>), dim3(ggrid), dim3(NT), 0, st, g);
+    product(k_gemm<64, EPI_X, true, false>, k_gemm<128, EPI_X, true, false>);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
   hipLaunchKernelGGL(k_bwd_u, dim3((unsigned)((n + 255) / 256), (unsigned)nbatch), dim3(256), 0, st, n, tiles, pr, pc,
                      y, u, rp);
   g.B = X;
   if (V)
-    hipLaunchKernelGGL((k_gemm<EPI_D, false>), dim3(ggrid), dim3(NT), 0, st, g);
+    product(k_gemm<64, EPI_D, false>, k_gemm<128, EPI_D, false>);
   else
-    hipLaunchKernelGGL((k_gemm<EPI_D, true>), dim3(ggrid), dim3(NT), 0, st, g);
+    product(k_gemm<64, EPI_D, true>, k_gemm<128, EPI_D, true>);
   if (hipGetLastError() != hipSuccess) return DPR1_EHIP;
   hipLaunchKernelGGL(k_bwd_final, dim3((unsigned)((n * nbatch + 255) / 256)), dim3(256), 0, st, n, nbatch, tiles,
                      rho, pd, pz, rp, d_bar, z_bar, rho_bar);
