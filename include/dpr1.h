@@ -380,7 +380,8 @@ int dpr1_eig_hermitian(const double* d, const double* z, double rho, int64_t n, 
  * off-diagonal b [n-1] (device).  A block is split at m = size/2 with
  * beta = b there: T = diag(T1 - beta e_m e_m^T, T2 - beta e_1 e_1^T)
  * + beta u u^T, u = e_m + e_{m+1}; the halves are solved recursively down to
- * 1 x 1, and each merge is the DPR1 problem D = diag(Lambda1, Lambda2),
+ * blocks of at most 32 rows, solved by Jacobi rotations (where an entry is
+ * neither 0 nor within 2^+-450: down to 1 x 1), and each merge is the DPR1 problem D = diag(Lambda1, Lambda2),
  * z = [last row of Q1, first row of Q2], rho = beta, reduced as by
  * dpr1_eig_general (beta = 0 decouples the halves), solved for all merges
  * of one depth in one batched launch, and followed by Q = diag(Q1, Q2) V.

@@ -9,9 +9,10 @@
 //   Q (diag(Lambda1, Lambda2) + beta z z^T) Q^T, Q = diag(Q1, Q2),
 //   z = Q^T u = [last row of Q1, first row of Q2],
 // and its eigenvectors are Q V for the DPR1 eigenvectors V.  The split tree
-// goes down to 1 x 1 leaves; all merges of one depth are done together:
-//   1. z of every merge: a 1 x 1 child gives 1; the row of a larger child's Q
-//      was formed by k_zrows when that child was merged, straight from its
+// goes down to leaves of at most 32 rows, which one kernel solves by Jacobi
+// rotations; all merges of one depth are done together:
+//   1. z of every merge: the row of a leaf's Q comes from that kernel; the row
+//      of a merged child's Q was formed by k_zrows when that child was merged, straight from its
 //      children's Q and its V, so it is on the host before that child's
 //      product (step 5) has finished;
 //   2. the host reduces each merge as in Sec. 1 (unsorted poles, equal poles,
@@ -26,8 +27,8 @@
 //      FP64 matrix cores).
 // The two Q buffers alternate between depths so that the root's product
 // lands in the caller's Q.  A block is written only by its own merge and read
-// only by its parent's, and a leaf's 1 x 1 block (= 1) is set in both buffers
-// at the start, so no buffer is ever cleared.
+// only by its parent's, and a leaf's block is set in both buffers at the
+// start, so no buffer is ever cleared.
 // Steps 2 and 3 of a depth overlap the product of the depth below: the
 // host work runs while that product occupies the caller's stream, and the
 // DPR1 solves go to a second stream of the library (nothing they read or
@@ -42,6 +43,7 @@
 #include <vector>
 
 #include "../../include/dpr1.h"
+#include "dd.h"
 #include "reduce.h"
 
 namespace dpr1 {
@@ -57,32 +59,237 @@ struct Node {
   int side;  // 0 the root, 1 the left child of its parent, 2 the right child
 };
 
-static void build_tree(int64_t start, int64_t size, int depth, std::vector<Node>& out, int& maxd, int side = 0) {
-  if (size < 2) return;
+// Blocks of at most LEAF rows are not split: k_leaf solves them (below), where
+// every entry of T is 0 or within 2^+-LEAF_EXP.  Beyond that the merges go down
+// to 1 x 1 blocks: their solver refuses what leaves its range (DPR1_INFO_RANGE
+// from about 2^-950 and 2^900 on), which rotations would answer.
+constexpr int64_t LEAF = 32;
+constexpr int LEAF_EXP = 450;
+struct Leaf {
+  int32_t start, size, side, pad;
+};
+
+static void build_tree(int64_t start, int64_t size, int depth, std::vector<Node>& out, int& maxd,
+                       int64_t leaf = 1, std::vector<Leaf>* leaves = nullptr, int side = 0) {
+  if (size <= leaf) {
+    if (leaves) leaves->push_back({(int32_t)start, (int32_t)size, side, 0});
+    return;
+  }
   const int64_t m = size / 2;
   out.push_back({start, size, m, depth, side});
   maxd = std::max(maxd, depth);
-  build_tree(start, m, depth + 1, out, maxd, 1);
-  build_tree(start + m, size - m, depth + 1, out, maxd, 2);
+  build_tree(start, m, depth + 1, out, maxd, leaf, leaves, 1);
+  build_tree(start + m, size - m, depth + 1, out, maxd, leaf, leaves, 2);
 }
 
 // The diagonal of every leaf after the splits above it: each split subtracts
 // beta from the two diagonal entries beside it, the split nearer the root
 // first (the order of the recursion).
-static void modify_diag(std::vector<double>& a, const std::vector<double>& b, int64_t start, int64_t size) {
-  if (size < 2) return;
+static void modify_diag(std::vector<double>& a, const std::vector<double>& b, int64_t start, int64_t size,
+                        int64_t leaf) {
+  if (size <= leaf) return;
   const int64_t m = size / 2;
   const double beta = b[start + m - 1];
   a[start + m - 1] -= beta;
   a[start + m] -= beta;
-  modify_diag(a, b, start, m);
-  modify_diag(a, b, start + m, size - m);
+  modify_diag(a, b, start, m, leaf);
+  modify_diag(a, b, start + m, size - m, leaf);
 }
 
 // --------------------------------------------------------------- kernels
-__global__ void k_diag_one(double* Q, int64_t ld, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) Q[i + i * ld] = 1.0;
+// A leaf: all eigenpairs of a symmetric tridiagonal block T of at most LEAF
+// rows by Jacobi rotations in LDS.  Round robin order: 31 steps a sweep of 16
+// disjoint pairs; thread (i, j) of 16 x 16 carries the 2 x 2 block of pairs i
+// and j and two rows of V from one buffer to the other, so a step has one
+// barrier; every wave computes the 16 rotations for itself.  A step is bound by
+// the latency of its rotation (tangent from the hardware's reciprocals, cosine
+// refined to full precision).  An element within 2^-56 ||T|| or 2^-32 of the
+// difference of its diagonal entries stays; a sweep without a rotation is the
+// last (5 to 7 sweeps, 20 at most).
+// What stays, and the rotations' rounding, is taken out by one step of
+// first-order correction with the residuals r_j = T v_j - l_j v_j, summed in
+// double-double: lambda_j = l_j + v_j.r_j / v_j.v_j, V += V E, E_ij = v_i.r_j /
+// (lambda_j - lambda_i), and (I - V^T V)_ij / 2 on the diagonal and between
+// eigenvalues closer than 2^-20 of the largest.  A column's sign is that of
+// merges down to 1 x 1 blocks, which make beta (q_m + q_m+1) negative at the
+// split of the smallest half that the column does not vanish beside.  Measured
+// at n = 4096 (128 blocks): 141 us (437 with separate row and column phases
+// behind barriers and exact divisions), in place of the five deepest levels of
+// merges, each a host round trip of about 0.4 ms: the solve 6.1 -> 3.75 ms.
+// Writes the eigenvalues (decreasing) to lam (which may be diag: a block reads
+// its entries first), the block of Q to both Q buffers (a leaf may lie at
+// either parity of the depth) and the row that the parent's z takes to zl.
+__device__ __forceinline__ void leaf_add(dd& a, dd t) {
+  const dd y = two_sum(a.hi, t.hi);
+  a = fast_two_sum(y.hi, y.lo + (a.lo + t.lo));
+}
+// (V^T V)_ij - [i = j]
+__device__ __forceinline__ double leaf_gram(const double* V, int ld, int i, int j) {
+  dd g = {i == j ? -1.0 : 0.0, 0.0};
+  for (int k = 0; k < LEAF; ++k) leaf_add(g, two_prod(V[k * ld + i], V[k * ld + j]));
+  return g.hi + g.lo;
+}
+
+__global__ void __launch_bounds__(256) k_leaf(const Leaf* leaves, const double* diag, const double* off, double* lam,
+                                              double* Q, int64_t ldq, double* Qw, int64_t ldw, double* zl) {
+  constexpr int LD = LEAF + 1, NP = LEAF / 2, NR = LEAF - 1;
+  __shared__ double As[2][LEAF * LD], Vs[2][LEAF * LD];
+  __shared__ double ta[LEAF], tb[LEAF], ev[LEAF], sg[LEAF];
+  __shared__ int rank[LEAF];
+  static_assert(LEAF == 32, "256 threads are the 2 x 2 blocks of a block of 32 rows");
+  const Leaf L = leaves[blockIdx.x];
+  const int s = L.size, t = threadIdx.x;
+  const int64_t o = L.start;
+  if (t < LEAF) {
+    ta[t] = t < s ? diag[o + t] : 0.0;
+    tb[t] = t + 1 < s ? off[o + t] : 0.0;
+  }
+  __syncthreads();
+  double norm = 0.0;
+  for (int k = 0; k < LEAF; ++k) norm = fmax(norm, fmax(fabs(ta[k]), fabs(tb[k])));
+  const double tiny = 0x1p-56 * norm;
+  for (int e = t; e < LEAF * LEAF; e += 256) {
+    const int i = e / LEAF, j = e % LEAF;  // rows s .. 31: zero, never rotated
+    As[0][i * LD + j] = i == j ? ta[i] : (i == j + 1 ? tb[j] : (j == i + 1 ? tb[i] : 0.0));
+    Vs[0][i * LD + j] = i == j ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  const int bi = t / NP, bj = t % NP, lane0 = t & 48;
+  int cur = 0;
+  for (int sweep = 0; sweep < 20; ++sweep) {
+    bool rotated = false;
+    for (int r = 0; r < NR; ++r) {
+      // pair u of step r: 0 and 31 - r, or u + r and 31 - u + r (1 .. 31 in a ring)
+      auto ring = [](int x) { return x >= NR ? x - NR + 1 : x + 1; };
+      auto pair = [&](int u, int& p, int& q) {
+        p = u == 0 ? 0 : ring(u - 1 + r);
+        q = ring(NR - 1 - u + r);
+      };
+      int pi, qi, pj, qj;
+      pair(bi, pi, qi);
+      pair(bj, pj, qj);
+      const double* A = As[cur];
+      const double* V = Vs[cur];
+      const double app = A[pj * LD + pj], aqq = A[qj * LD + qj], apq = A[pj * LD + qj];
+      const double x00 = A[pi * LD + pj], x01 = A[pi * LD + qj], x10 = A[qi * LD + pj], x11 = A[qi * LD + qj];
+      const double v0 = V[bi * LD + pj], w0 = V[bi * LD + qj];
+      const double v1 = V[(bi + NP) * LD + pj], w1 = V[(bi + NP) * LD + qj];
+      double cj = 1.0, sj = 0.0;
+      const double df = aqq - app;
+      if (fabs(apq) > fmax(tiny, 0x1p-32 * fabs(df))) {
+        const double th = df * __builtin_amdgcn_rcp(2.0 * apq), x = __builtin_fma(th, th, 1.0);
+        const double tn = copysign(__builtin_amdgcn_rcp(__builtin_fma(x, __builtin_amdgcn_rsq(x), fabs(th))), th);
+        const double y = __builtin_fma(tn, tn, 1.0), c0 = __builtin_amdgcn_rsq(y);
+        const double d = __builtin_fma(-y * c0, c0, 1.0);
+        cj = __builtin_fma(c0 * d, __builtin_fma(0.375, d, 0.5), c0);
+        sj = tn * cj;
+        rotated = true;
+      }
+      const double ci = __shfl(cj, lane0 + bi % NP, 64), si = __shfl(sj, lane0 + bi % NP, 64);
+      const double y00 = ci * x00 - si * x10, y01 = ci * x01 - si * x11;
+      const double y10 = si * x00 + ci * x10, y11 = si * x01 + ci * x11;
+      double* B = As[cur ^ 1];
+      double* W = Vs[cur ^ 1];
+      B[pi * LD + pj] = cj * y00 - sj * y01;
+      B[pi * LD + qj] = sj * y00 + cj * y01;
+      B[qi * LD + pj] = cj * y10 - sj * y11;
+      B[qi * LD + qj] = sj * y10 + cj * y11;
+      W[bi * LD + pj] = cj * v0 - sj * w0;
+      W[bi * LD + qj] = sj * v0 + cj * w0;
+      W[(bi + NP) * LD + pj] = cj * v1 - sj * w1;
+      W[(bi + NP) * LD + qj] = sj * v1 + cj * w1;
+      cur ^= 1;
+      __syncthreads();
+    }
+    if (!__any(rotated)) break;  // the same in every wave: each holds all pairs
+  }
+  // correction: residuals into A, E into the other buffer
+  double* A = As[cur];
+  double* E = As[cur ^ 1];
+  double* V = Vs[cur];
+  if (t < LEAF) ev[t] = A[t * LD + t];
+  __syncthreads();
+  for (int e = t; e < LEAF * LEAF; e += 256) {
+    const int k = e / LEAF, j = e % LEAF;
+    dd w = two_prod(ta[k], V[k * LD + j]);
+    if (k > 0) leaf_add(w, two_prod(tb[k - 1], V[(k - 1) * LD + j]));
+    if (k + 1 < LEAF) leaf_add(w, two_prod(tb[k], V[(k + 1) * LD + j]));
+    leaf_add(w, two_prod(-ev[j], V[k * LD + j]));
+    A[k * LD + j] = w.hi + w.lo;
+  }
+  __syncthreads();
+  if (t < LEAF) {
+    double c = 0.0;
+    for (int k = 0; k < LEAF; ++k) c = __builtin_fma(V[k * LD + t], A[k * LD + t], c);
+    ev[t] += c;  // v.v = 1 to some eps, and c is some eps ||T||
+  }
+  __syncthreads();
+  double vmax = 0.0;
+  for (int j = 0; j < LEAF; ++j) vmax = fmax(vmax, fabs(ev[j]));
+  for (int e = t; e < LEAF * LEAF; e += 256) {
+    const int i = e / LEAF, j = e % LEAF;
+    const double gap = ev[j] - ev[i];
+    double x = 0.0;
+    if (i != j && fabs(gap) > 0x1p-20 * vmax) {
+      for (int k = 0; k < LEAF; ++k) x = __builtin_fma(V[k * LD + i], A[k * LD + j], x);
+      x /= gap;
+    } else {
+      x = -0.5 * leaf_gram(V, LD, i, j);
+    }
+    E[i * LD + j] = x;
+  }
+  __syncthreads();
+  double* U = Vs[cur ^ 1];
+  for (int e = t; e < LEAF * LEAF; e += 256) {
+    const int i = e / LEAF, j = e % LEAF;
+    double c = 0.0;
+    for (int k = 0; k < LEAF; ++k) c = __builtin_fma(V[i * LD + k], E[k * LD + j], c);
+    U[i * LD + j] = V[i * LD + j] + c;
+  }
+  V = U;
+  __syncthreads();
+  if (t < s) {
+    const double x = ev[t];
+    int k = 0;
+    for (int j = 0; j < s; ++j) {
+      const double y = ev[j];
+      k += y > x || (y == x && j < t);
+    }
+    rank[t] = k;
+    lam[o + k] = x;
+    // the column's sign
+    int lo = 0, len = s;
+    bool flip = false, found = false;
+    while (len > 1) {
+      const int m = len / 2;
+      const double beta = tb[lo + m - 1], w = V[(lo + m - 1) * LD + t] + V[(lo + m) * LD + t];
+      if (fabs(beta * w) > 0x1p-51 * vmax) {
+        flip = (beta > 0.0) == (w > 0.0);
+        found = true;
+        break;
+      }
+      double n1 = 0.0, n2 = 0.0;
+      for (int i = 0; i < m; ++i) n1 += V[(lo + i) * LD + t] * V[(lo + i) * LD + t];
+      for (int i = m; i < len; ++i) n2 += V[(lo + i) * LD + t] * V[(lo + i) * LD + t];
+      if (n1 >= n2) {
+        len = m;
+      } else {
+        lo += m;
+        len -= m;
+      }
+    }
+    if (!found) flip = V[lo * LD + t] < 0.0;
+    sg[t] = flip ? -1.0 : 1.0;
+  }
+  __syncthreads();
+  for (int e = t; e < s * s; e += 256) {
+    const int i = e % s, j = e / s;
+    const double v = sg[j] * V[i * LD + j];
+    const int64_t k = o + rank[j];
+    Q[(o + i) + k * ldq] = v;
+    Qw[(o + i) + k * ldw] = v;
+    if (L.side == 1 ? i == s - 1 : i == 0) zl[k] = v;
+  }
 }
 
 // The row of a merged block's Q that its parent's z takes (the last row for a
@@ -353,27 +560,29 @@ static TLayout tlayout(int64_t n, const std::vector<Node>& nodes, int maxd) {
   L.maxNodes = 0;
   L.maxZ = 0;
   L.solver_bytes = 0;
-  std::vector<int64_t> offs;
-  for (int D = maxd; D >= 0; --D) {
+  struct Depth {
     int64_t v = 0, as = 0, ti = 0, cnt = 0, zi = 0;
-    offs.assign(1, 0);
-    for (const Node& nd : nodes) {
-      if (nd.depth != D) continue;
-      ++cnt;
-      v += nd.size * nd.size;
-      as += cdiv(nd.size, TA_CB) * cdiv(nd.size, TA_T * TA_R);
-      ti += (cdiv(nd.m, GT) + cdiv(nd.size - nd.m, GT)) * cdiv(nd.size, GT);
-      if (nd.side) zi += cdiv(nd.size, ZC);
-      offs.push_back(offs.back() + nd.size);
-    }
-    if (!cnt) continue;
-    L.maxV = std::max(L.maxV, v);
-    L.maxAsm = std::max(L.maxAsm, as);
-    L.maxTiles = std::max(L.maxTiles, ti);
-    L.maxNodes = std::max(L.maxNodes, cnt);
-    L.maxZ = std::max(L.maxZ, zi);
+    std::vector<int64_t> offs{0};
+  };
+  std::vector<Depth> depths(maxd + 1);
+  for (const Node& nd : nodes) {
+    Depth& d = depths[nd.depth];
+    ++d.cnt;
+    d.v += nd.size * nd.size;
+    d.as += cdiv(nd.size, TA_CB) * cdiv(nd.size, TA_T * TA_R);
+    d.ti += (cdiv(nd.m, GT) + cdiv(nd.size - nd.m, GT)) * cdiv(nd.size, GT);
+    if (nd.side) d.zi += cdiv(nd.size, ZC);
+    d.offs.push_back(d.offs.back() + nd.size);
+  }
+  for (const Depth& d : depths) {
+    if (!d.cnt) continue;
+    L.maxV = std::max(L.maxV, d.v);
+    L.maxAsm = std::max(L.maxAsm, d.as);
+    L.maxTiles = std::max(L.maxTiles, d.ti);
+    L.maxNodes = std::max(L.maxNodes, d.cnt);
+    L.maxZ = std::max(L.maxZ, d.zi);
     // the reduced problems of a depth are no more and no larger than its merges
-    L.solver_bytes = std::max(L.solver_bytes, dpr1_batched_workspace_size(cnt, offs.data()));
+    L.solver_bytes = std::max(L.solver_bytes, dpr1_batched_workspace_size(d.cnt, d.offs.data()));
   }
   const int64_t P = std::max<int64_t>(L.maxNodes, 1);
   size_t o = 0;
@@ -497,17 +706,35 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
   for (double x : hb)
     if (!std::isfinite(x)) return tri_set_info(info, DPR1_INFO_NONFINITE, st);
 
-  // leaves: the diagonal after every split's modification, Q = 1 in both buffers
+  // leaves: the diagonal after every split's modification (staged in lambda)
+  bool ranged = true;
+  auto in_range = [](double x) {
+    return x == 0.0 || (std::fabs(x) >= std::ldexp(1.0, -LEAF_EXP) && std::fabs(x) <= std::ldexp(1.0, LEAF_EXP));
+  };
+  for (double x : ha) ranged = ranged && in_range(x);
+  for (double x : hb) ranged = ranged && in_range(x);
+  const int64_t leaf = ranged ? LEAF : 1;
+  std::vector<Leaf> leaves;
+  nodes.clear();
+  maxd = 0;
+  build_tree(0, n, 0, nodes, maxd, leaf, &leaves);
   std::vector<double> hlam = ha;
-  modify_diag(hlam, hb, 0, n);
+  modify_diag(hlam, hb, 0, n, leaf);
   TCHECK(hipMemcpyAsync(lambda, hlam.data(), 8 * n, hipMemcpyHostToDevice, st));
   double* Qw = (double*)(w + L.Qw);
-  const unsigned g1 = (unsigned)cdiv(n, 256);
-  hipLaunchKernelGGL(k_diag_one, dim3(g1), dim3(256), 0, st, Q, ldq, n);
-  hipLaunchKernelGGL(k_diag_one, dim3(g1), dim3(256), 0, st, Qw, n, n);
-  TCHECK(hipGetLastError());
-
   double* zl = (double*)(w + L.zl);
+  // the list of leaves (at most 16 bytes a row) in the room of the first
+  // merges' poles and z
+  Leaf* dleaves = (Leaf*)(w + L.rd);
+  TCHECK(hipMemcpyAsync(dleaves, leaves.data(), sizeof(Leaf) * leaves.size(), hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(k_leaf, dim3((unsigned)leaves.size()), dim3(256), 0, st, (const Leaf*)dleaves, (const double*)lambda,
+                     b, lambda, Q, ldq, Qw, n, zl);
+  TCHECK(hipGetLastError());
+  std::vector<double> hzleaf(n);
+  TCHECK(hipMemcpyAsync(hlam.data(), lambda, 8 * n, hipMemcpyDeviceToHost, st));
+  TCHECK(hipMemcpyAsync(hzleaf.data(), zl, 8 * n, hipMemcpyDeviceToHost, st));
+  TCHECK(hipStreamSynchronize(st));
+
   double* dl = (double*)(w + L.dl);
   TArgs ta;
   ta.d = dl;
@@ -571,7 +798,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     const int64_t ldc = (D % 2 == 0) ? n : ldq;
 
     // 1. z of every merge: the rows k_zrows formed for its merged children
-    // (copied to hzr), 1 for a 1 x 1 child; 0 outside this depth's merges
+    // (copied to hzr), k_leaf's for a leaf; 0 outside this depth's merges
     if (zpending) {
       TCHECK(hipEventSynchronize(fin.ev));
       zpending = false;
@@ -579,8 +806,10 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     std::fill(hz.begin(), hz.end(), 0.0);
     for (const Node* nd : lv) {
       const int64_t o = nd->start, m = nd->m, s2 = nd->size - nd->m;
-      if (m == 1) hz[o] = 1.0; else std::copy(hzr.begin() + o, hzr.begin() + o + m, hz.begin() + o);
-      if (s2 == 1) hz[o + m] = 1.0; else std::copy(hzr.begin() + o + m, hzr.begin() + o + m + s2, hz.begin() + o + m);
+      const double* z1 = m <= leaf ? hzleaf.data() : hzr.data();
+      const double* z2 = s2 <= leaf ? hzleaf.data() : hzr.data();
+      std::copy(z1 + o, z1 + o + m, hz.begin() + o);
+      std::copy(z2 + o + m, z2 + o + m + s2, hz.begin() + o + m);
     }
 
     // 2. reduce each merge (hlam holds the current eigenvalues of every block)
