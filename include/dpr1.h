@@ -350,11 +350,10 @@ int dpr1_eig_backward_strided(int64_t nbatch, int64_t n, const double* d, const 
  *                waves_per_simd is argument -9)
  *   work, work_bytes  device workspace (>= dpr1_general_workspace_size(n),
  *                O(n) bytes)
- * Unlike every other entry point this one SYNCHRONISES the host with
- * `stream`: the reduction (a sort and a scan of n numbers) runs on the host
- * from a device-to-host copy of d and z, and the reduced eigenvalues are
- * merged with the deflated poles on the host.  It cannot be captured in a
- * hipGraph.  Returns 0, -p for an invalid argument p, or DPR1_EHIP.         */
+ * Unlike the entry points above this one SYNCHRONISES the host with `stream`:
+ * the reduction runs on the device, but the launches of the reduced solve
+ * depend on the reduced problem's order, which the host reads back; it returns
+ * when the work has finished.  It cannot be captured in a hipGraph.  Returns 0, -p for an invalid argument p, or DPR1_EHIP.         */
 size_t dpr1_general_workspace_size(int64_t n);   /* also for dpr1_eig_hermitian */
 int dpr1_eig_general(const double* d, const double* z, double rho, int64_t n, double* lambda,
                      double* V, int64_t ldv, int32_t* info, const dpr1_opts* opts, void* work,

@@ -4,14 +4,18 @@
 // turns into the real problem with |z| (the extension the paper's closing
 // remarks mention).
 //
-// The reduction is host work on n numbers: sort the poles decreasingly,
-// deflate a pole whose z_j is zero (eigenpair (d_j, e_j)), and merge a group of
-// equal poles by a Householder reflection of its block that maps its part w
-// of z onto a multiple of e_first: the pole enters the reduced problem once,
-// with z = ||w||, and the other columns of the reflection are eigenvectors for
-// the same eigenvalue.  The reduced problem (strictly decreasing, no zero z)
-// is solved on the GPU by dpr1_eig without eigenvectors; k_assemble then
-// writes every column of V in the caller's row order.
+// The reduction: sort the poles decreasingly, deflate a pole whose z_j is zero
+// (eigenpair (d_j, e_j)), and merge a group of equal poles by a Householder
+// reflection of its block that maps its part w of z onto a multiple of e_first:
+// the pole enters the reduced problem once, with z = ||w||, and the other
+// columns of the reflection are eigenvectors for the same eigenvalue.  The
+// reduced problem (strictly decreasing, no zero z) is solved by dpr1_eig
+// without eigenvectors; k_front_columns orders its eigenvalues among the
+// deflated poles and k_assemble writes every column of V in the caller's row
+// order.  All of it runs on the GPU; the host reads back the reduced problem's
+// order, on which the solver's launches depend.  (On the host, with the copies
+// there and back, the reduction and the ordering took 1.1 ms at n = 32768 and
+// 0.3 ms at n = 4099, complex z.)
 //
 // A column k of the reduced problem needs no gather: in the caller's rows its
 // components are those of eq. (eigenvecAi) evaluated on the original d and z,
@@ -26,8 +30,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <numeric>
-#include <vector>
 
 #include "../../include/dpr1.h"
 #include "reduce.h"
@@ -160,11 +162,370 @@ __global__ void __launch_bounds__(ASM_T) k_assemble(AsmArgs a) {
   }
 }
 
+// ------------------------------------------------------------- reduction
+// Sort: runs of FR rows by rank counting in LDS (all pairs of a run, 0.5 M
+// comparisons a block), then FW runs at a time by binary searches in lock step
+// (an element's place is its own index plus its rank in each of the other
+// runs: FW independent loads a step, so a pass costs about as many load
+// latencies as a merge of two runs would).  A block first takes FS samples of
+// each run to LDS: only the steps between two samples, next to each other in
+// memory, are loads (n = 32768: 36 us for
+// the two passes, 59 with every step a load).  Keys
+// are the poles as integers that increase as the poles decrease (-0 as +0, any
+// NaN in some place, so that the order is a permutation whatever the input);
+// equal poles keep their row order.
+constexpr int FR = 512, FW = 16, FS = 128;
+
+__device__ __forceinline__ uint64_t pole_key(double x) {
+  const uint64_t b = x == 0.0 ? 0 : (uint64_t)__double_as_longlong(x);
+  return ~((b >> 63) ? ~b : (b | ((uint64_t)1 << 63)));
+}
+
+// Block b also leaves in bad[b] whether one of its rows is not finite, and
+// writes the deflated z: |z_j| < 2^-511 counts as zero (its square is not a
+// normal number, and the eigenvalue beside d_j would lie within rho z_j^2 of
+// it).  CPLX: z is complex; with Phi = diag(z_j / |z_j|) unitary (1 where z_j =
+// 0) Phi D Phi^H = D, A = Phi (D + rho |z| |z|^T) Phi^H, so the eigenvalues are
+// those of the real problem with |z| and v = Phi v_real.
+template <bool CPLX>
+__global__ void __launch_bounds__(FR) k_front_sort(const double* d, const double* z, int64_t n, double* zd,
+                                                   double* ph, uint64_t* key, int32_t* idx, int32_t* bad) {
+  __shared__ uint64_t s[FR];
+  const int t = threadIdx.x;
+  const int64_t b0 = (int64_t)blockIdx.x * FR, i = b0 + t;
+  const bool in = i < n;
+  uint64_t k = ~(uint64_t)0;  // rows beyond the last: behind every row
+  bool ok = true;
+  if (in) {
+    const double x = d[i];
+    k = pole_key(x);
+    ok = isfinite(x);
+    double r;
+    if (CPLX) {
+      const double re = z[2 * i], im = z[2 * i + 1];
+      ok = ok && isfinite(re) && isfinite(im);
+      r = hypot(re, im);
+      ph[2 * i] = r > 0.0 ? re / r : 1.0;
+      ph[2 * i + 1] = r > 0.0 ? im / r : 0.0;
+    } else {
+      r = z[i];
+      ok = ok && isfinite(r);
+    }
+    zd[i] = fabs(r) < 0x1p-511 ? 0.0 : r;
+  }
+  s[t] = k;
+  const int any = __syncthreads_or(!ok);
+  if (t == 0) bad[blockIdx.x] = any;
+  const int w0 = t & ~63;
+  int rank = 0;
+  for (int j = 0; j < w0; ++j) rank += s[j] <= k;
+  for (int j = w0; j < w0 + 64; ++j) rank += s[j] < k || (s[j] == k && j < t);
+  for (int j = w0 + 64; j < FR; ++j) rank += s[j] < k;
+  if (in) {
+    key[b0 + rank] = k;
+    idx[b0 + rank] = (int32_t)i;
+  }
+}
+
+// One pass: every FW runs of `len` (FR FW^p) rows become one.
+__global__ void __launch_bounds__(256) k_front_merge(int64_t n, int64_t len, const uint64_t* key, const int32_t* idx,
+                                                     uint64_t* key2, int32_t* idx2) {
+  const int64_t b0 = (int64_t)blockIdx.x * 256;  // one run: len is a multiple of 256
+  const int64_t run = b0 / len, base = run / FW * FW * len;
+  const int r = (int)(run % FW);
+  const int64_t i = b0 + threadIdx.x;
+  const int stride = (int)(len / FS);
+  __shared__ uint64_t smp[FW][FS];
+  __shared__ int cnt[FW];  // rows of the run
+  if (threadIdx.x < FW)
+    cnt[threadIdx.x] = (int)min(max(n - (base + threadIdx.x * len), (int64_t)0), len);
+  for (int e = threadIdx.x; e < FW * FS; e += 256) {
+    const int64_t at = base + (e / FS) * len + (int64_t)(e % FS + 1) * stride - 1;
+    smp[e / FS][e % FS] = at < n ? key[at] : ~(uint64_t)0;
+  }
+  __syncthreads();
+  if (i >= n) return;
+  const uint64_t k = key[i];
+  int lo[FW];
+#pragma unroll
+  for (int q = 0; q < FW; ++q) lo[q] = 0;
+  // samples that lie before k, then the rows between two samples
+  for (int h = FS; h > 0; h >>= 1) {
+#pragma unroll
+    for (int q = 0; q < FW; ++q) {
+      const int at = lo[q] + h;
+      const uint64_t x = smp[q][min(at, FS) - 1];
+      if (at <= cnt[q] / stride && (x < k || (x == k && q < r))) lo[q] = at;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < FW; ++q) lo[q] *= stride;
+  for (int h = stride / 2; h > 0; h >>= 1) {
+#pragma unroll
+    for (int q = 0; q < FW; ++q) {
+      const int at = lo[q] + h;
+      const bool inside = at <= cnt[q];
+      if (!inside) continue;
+      const uint64_t x = key[base + q * len + at - 1];
+      if (x < k || (x == k && q < r)) lo[q] = at;
+    }
+  }
+  int64_t pos = i - (base + r * len);
+#pragma unroll
+  for (int q = 0; q < FW; ++q)
+    if (q != r) pos += lo[q];
+  key2[base + pos] = k;
+  idx2[base + pos] = idx[i];
+}
+
+// What the reduction leaves for the host and for k_front_columns.
+struct FrontHdr {
+  int32_t m, bad;  // order of the reduced problem; an input is not finite
+};
+
+__device__ __forceinline__ double wave_sum(double x) {
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+
+// Groups of equal poles, in sorted positions.  A group of at most FT is taken by
+// the thread of its first position, a larger one by that thread's wave, 256
+// members in flight at a time (n = 32768 with pairs among the poles: 39 us with
+// every group by a wave, 6 so): the largest |w_t|, ||w|| scaled by it (no square
+// overflows), then u = w/||w|| + sign(u_first) e_first and beta = 2/(u^T u).
+// Per row: rgrp (the group's first position), rpos, ru; per group, at its first
+// position: gnw = ||w|| (z itself for a pole alone), gbeta.  cnt[b] = poles of
+// block b's positions that enter the reduced problem.
+constexpr int FT = 8;
+constexpr int FG = 4;  // members a lane has in flight
+__global__ void __launch_bounds__(FR) k_front_groups(int64_t n, const uint64_t* key, const int32_t* idx,
+                                                     const double* zd, int32_t* rgrp, int32_t* rpos, double* ru,
+                                                     double* gnw, double* gbeta, int32_t* cnt) {
+  const int lane = threadIdx.x & 63;
+  const int64_t s = (int64_t)blockIdx.x * FR + threadIdx.x;
+  const bool in = s < n;
+  const uint64_t k = in ? key[s] : 0;
+  const bool head = in && (s == 0 || key[s - 1] != k);
+  int size = 0;  // members, FT + 1 for more than FT
+  if (head)
+    for (size = 1; size <= FT && s + size < n && key[s + size] == k; ++size) {
+    }
+  const bool small = head && size <= FT;
+  double nw = 0.0;
+  if (small) {
+    int32_t row[FT];
+    double wt[FT];
+    double big = 0.0, uu = 0.0;
+#pragma unroll
+    for (int t = 0; t < FT; ++t) row[t] = t < size ? idx[s + t] : 0;
+#pragma unroll
+    for (int t = 0; t < FT; ++t) {
+      wt[t] = t < size ? zd[row[t]] : 0.0;
+      big = fmax(big, fabs(wt[t]));
+    }
+    if (size == 1) {
+      nw = wt[0];
+    } else if (big > 0.0) {
+      double acc = 0.0;
+#pragma unroll
+      for (int t = 0; t < FT; ++t) {
+        const double q = wt[t] / big;
+        acc += q * q;
+      }
+      nw = big * sqrt(acc);
+    }
+#pragma unroll
+    for (int t = 0; t < FT; ++t) {
+      if (t >= size) continue;
+      double u = 0.0;
+      if (size > 1 && nw != 0.0) {
+        u = wt[t] / nw;
+        if (t == 0) u += u >= 0.0 ? 1.0 : -1.0;
+      }
+      uu += u * u;
+      rgrp[row[t]] = (int32_t)s;
+      rpos[row[t]] = t;
+      ru[row[t]] = u;
+    }
+    gnw[s] = nw;
+    gbeta[s] = uu != 0.0 ? 2.0 / uu : 0.0;
+  }
+  for (uint64_t todo = __ballot(head && !small); todo; todo &= todo - 1) {
+    const int l = __ffsll((unsigned long long)todo) - 1;
+    const int64_t h = s - lane + l;
+    const uint64_t kk = key[h];
+    double big = 0.0;
+    int64_t e = h;  // one behind the group's last
+    for (int64_t j = h;; j += 64 * FG) {
+      int same = 0;
+#pragma unroll
+      for (int g = 0; g < FG; ++g) {
+        const int64_t p = j + 64 * g + lane;
+        const bool mine = p < n && key[p] == kk;
+        if (mine) big = fmax(big, fabs(zd[idx[p]]));
+        same += __popcll(__ballot(mine));
+      }
+      e += same;
+      if (same < 64 * FG) break;
+    }
+    for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+    double norm = 0.0;
+    if (big > 0.0) {
+      double acc = 0.0;
+      for (int64_t j = h + lane; j < e; j += 64 * FG)
+#pragma unroll
+        for (int g = 0; g < FG; ++g) {
+          const int64_t p = j + 64 * g;
+          const double q = p < e ? zd[idx[p]] / big : 0.0;
+          acc += q * q;
+        }
+      norm = big * sqrt(wave_sum(acc));
+    }
+    double uu = 0.0;
+    for (int64_t j = h + lane; j < e; j += 64 * FG)
+#pragma unroll
+      for (int g = 0; g < FG; ++g) {
+        const int64_t p = j + 64 * g;
+        if (p >= e) continue;
+        const int32_t row = idx[p];
+        double u = 0.0;
+        if (norm != 0.0) {
+          u = zd[row] / norm;
+          if (p == h) u += u >= 0.0 ? 1.0 : -1.0;
+        }
+        uu += u * u;
+        rgrp[row] = (int32_t)h;
+        rpos[row] = (int32_t)(p - h);
+        ru[row] = u;
+      }
+    uu = wave_sum(uu);
+    if (lane == l) {
+      nw = norm;
+      gnw[h] = norm;
+      gbeta[h] = norm != 0.0 ? 2.0 / uu : 0.0;
+    }
+  }
+  __shared__ int part[FR / 64];
+  const int c = __popcll(__ballot(head && !(nw == 0.0)));
+  if (lane == 0) part[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int sum = 0;
+    for (int w = 0; w < FR / 64; ++w) sum += part[w];
+    cnt[blockIdx.x] = sum;
+  }
+}
+
+// The reduced problem and the columns that do not come from it, both in
+// decreasing pole order: a sorted position either enters the reduced problem
+// (the first of a group whose ||w|| is not 0) or gives a column, a unit vector
+// of its row (ct0 = -1) or column ct0 of its group's reflection.
+struct FrontCols {
+  double* val;   // the eigenvalue
+  double* ub;    // beta u_t
+  int32_t* idx;  // the row, or the group
+  int32_t* t;
+};
+__global__ void __launch_bounds__(FR) k_front_reduce(int64_t n, const double* d, const int32_t* idx,
+                                                     const int32_t* rgrp, const double* ru, const double* gnw,
+                                                     const double* gbeta, const int32_t* cnt, const int32_t* bad,
+                                                     double* rd, double* rz, FrontCols fc, FrontHdr* hdr) {
+  __shared__ int part[FR / 64], sums[FR / 64];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t s = (int64_t)blockIdx.x * FR + t;
+  const bool last = blockIdx.x == gridDim.x - 1;
+  int before = 0, nf = 0;
+  for (int64_t b = t; b < (int64_t)blockIdx.x; b += FR) before += cnt[b];
+  if (last)
+    for (int64_t b = t; b < (int64_t)gridDim.x; b += FR) nf |= bad[b];
+  const bool in = s < n;
+  const int32_t row = in ? idx[s] : 0;
+  const int32_t h = in ? rgrp[row] : 0;
+  const double nw = in ? gnw[h] : 0.0;
+  const bool red = in && h == s && !(nw == 0.0);
+  const uint64_t mask = __ballot(red);
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  if (lane == 0) {
+    part[w] = before;
+    sums[w] = __popcll(mask);
+  }
+  const int anybad = __syncthreads_or(nf);
+  int64_t r = __popcll(mask & (((uint64_t)1 << lane) - 1));
+  int64_t m = 0;
+  for (int q = 0; q < FR / 64; ++q) {
+    r += part[q] + (q < w ? sums[q] : 0);
+    m += part[q] + sums[q];
+  }
+  if (last && t == 0) {
+    hdr->m = (int32_t)m;
+    hdr->bad = anybad;
+  }
+  if (!in) return;
+  if (red) {
+    rd[r] = d[row];
+    rz[r] = nw;
+  } else {
+    const int64_t c = s - r;
+    fc.val[c] = d[idx[h]];
+    const bool unit = nw == 0.0;
+    fc.idx[c] = unit ? row : h;
+    fc.t[c] = unit ? -1 : (int32_t)(s - h);
+    fc.ub[c] = unit ? 0.0 : gbeta[h] * ru[row];
+  }
+}
+
+// The columns in decreasing order of their eigenvalues, those of the reduction
+// first among equal ones: both lists are decreasing, so a column's place is its
+// own index plus its rank in the other list.
+__global__ void __launch_bounds__(256) k_front_columns(int64_t n, int64_t m, FrontCols fc, const double* rd,
+                                                       const double* lamr, const int32_t* sidx, const double* mu,
+                                                       const double* xn, const int32_t* inf, double* lambda,
+                                                       int32_t* info, bool vectors, int32_t* ckind, int32_t* cidx,
+                                                       int32_t* ct, double* csig, double* cmu, double* cic,
+                                                       double* cub) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int32_t code = m > 0 ? inf[0] : 0;
+  if (t == 0) info[0] = code;
+  if (t >= n || code != 0) return;  // the solve left its outputs unspecified
+  const bool red = t < m;
+  const int64_t own = red ? t : t - m, cnt = red ? n - m : m;
+  const double v = red ? lamr[own] : fc.val[own];
+  const double* other = red ? fc.val : lamr;
+  int64_t lo = 0, hi = cnt;  // entries of the other list that come first
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) / 2;
+    const double x = other[mid];
+    if (red ? x >= v : x > v)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  const int64_t c = own + lo;
+  lambda[c] = v;
+  if (!vectors) return;
+  if (red) {
+    ckind[c] = COL_REDUCED;
+    cidx[c] = (int32_t)own;
+    ct[c] = 0;
+    csig[c] = rd[sidx[own]];
+    cmu[c] = mu[own];
+    cic[c] = 1.0 / xn[own];
+    cub[c] = 0.0;
+  } else {
+    const int32_t tt = fc.t[own];
+    ckind[c] = tt < 0 ? COL_UNIT : COL_REFLECT;
+    cidx[c] = fc.idx[own];
+    ct[c] = max(tt, 0);
+    csig[c] = cmu[c] = cic[c] = 0.0;
+    cub[c] = fc.ub[own];
+  }
+}
+
 static size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct GLayout {
-  size_t dr, zr, lamr, sidx, mu, xn, inf, rgrp, rpos, ru, ckind, cidx, ct, csig, cmu, cic, cub, zabs, ph, solver,
-      total;
+  size_t dr, zr, lamr, sidx, mu, xn, inf, rgrp, rpos, ru, ckind, cidx, ct, csig, cmu, cic, cub, zabs, ph, val0, ub0,
+      idx0, t0, cnt, bad, hdr, solver, total;
 };
 static GLayout glayout(int64_t n) {
   GLayout L;
@@ -188,6 +549,13 @@ static GLayout glayout(int64_t n) {
   L.cub = o; o = al(o + 8 * n);
   L.zabs = o; o = al(o + 8 * n);
   L.ph = o; o = al(o + 16 * n);
+  L.val0 = o; o = al(o + 8 * n);
+  L.ub0 = o; o = al(o + 8 * n);
+  L.idx0 = o; o = al(o + 4 * n);
+  L.t0 = o; o = al(o + 4 * n);
+  L.cnt = o; o = al(o + 4 * ((n + FR - 1) / FR));
+  L.bad = o; o = al(o + 4 * ((n + FR - 1) / FR));
+  L.hdr = o; o = al(o + sizeof(FrontHdr));
   L.solver = o; o = al(o + dpr1_workspace_size(n));
   L.total = o;
   return L;
@@ -197,7 +565,6 @@ static GLayout glayout(int64_t n) {
 }  // namespace dpr1
 
 using namespace dpr1::gen;
-namespace fe = dpr1::fe;
 
 #define GCHECK(x)                            \
   do {                                       \
@@ -238,134 +605,84 @@ static int set_info(int32_t* info, int32_t code, hipStream_t st) {
   return DPR1_OK;
 }
 
-// The reduction, the reduced solve and the assembly.  hd, hz: host copies of
-// the poles and of the (real, here nonnegative in the Hermitian case) z; zdev
-// the same z on the device; ph the device phases for a complex V, else null.
-static int front_end(const double* d, const double* zdev, const std::vector<double>& hd,
-                     const std::vector<double>& hz, const double* ph, double rho, int64_t n, double* lambda,
-                     double* V, int64_t ldv, int32_t* info, const dpr1_opts* opts, char* w, const GLayout& L,
-                     hipStream_t st, void* stream) {
-  // |z_j| < 2^-511 counts as zero: its square is not a normal number, and
-  // the eigenvalue beside d_j would lie within rho z_j^2 of it; the assembly
-  // then reads this deflated z from the workspace
-  std::vector<double> hz0(hz);
-  for (double& x : hz0)
-    if (std::fabs(x) < 0x1p-511) x = 0.0;
-  double* zdef = (double*)(w + L.zabs);
-  GCHECK(hipMemcpyAsync(zdef, hz0.data(), 8 * n, hipMemcpyHostToDevice, st));
-  zdev = zdef;
-  std::vector<double> rd, rz;
-  std::vector<int32_t> rgrp(n), rpos(n);
-  std::vector<double> ru(n);
-  std::vector<fe::Col> cols;
-  cols.reserve(n);
-  fe::reduce(hd.data(), hz0.data(), n, false, rd, rz, rgrp.data(), rpos.data(), ru.data(), cols);
-  const int64_t m = (int64_t)rd.size();
+// The reduction, the reduced solve and the assembly.
+template <bool CPLX>
+static int front_end(const double* d, const double* z, double rho, int64_t n, double* lambda, double* V, int64_t ldv,
+                     int32_t* info, const dpr1_opts* opts, char* w, hipStream_t st) {
+  const GLayout L = glayout(n);
+  auto f64 = [&](size_t off) { return (double*)(w + off); };
+  auto i32 = [&](size_t off) { return (int32_t*)(w + off); };
+  double *zd = f64(L.zabs), *ph = f64(L.ph), *rd = f64(L.dr), *rz = f64(L.zr);
+  // the sort and the groups work in the room of arrays that are written later
+  uint64_t *key = (uint64_t*)(w + L.lamr), *key2 = (uint64_t*)(w + L.csig);
+  int32_t *idx = i32(L.sidx), *idx2 = i32(L.cidx);
+  double *gnw = f64(L.cmu), *gbeta = f64(L.cic);
+  const FrontCols fc = {f64(L.val0), f64(L.ub0), i32(L.idx0), i32(L.t0)};
+  FrontHdr* dhdr = (FrontHdr*)(w + L.hdr);
+  const dim3 runs((unsigned)((n + FR - 1) / FR)), rows((unsigned)((n + 255) / 256));
+  hipLaunchKernelGGL(k_front_sort<CPLX>, runs, dim3(FR), 0, st, d, z, n, zd, ph, key, idx, i32(L.bad));
+  for (int64_t len = FR; len < n; len *= FW) {
+    hipLaunchKernelGGL(k_front_merge, rows, dim3(256), 0, st, n, len, (const uint64_t*)key, (const int32_t*)idx, key2,
+                       idx2);
+    std::swap(key, key2);
+    std::swap(idx, idx2);
+  }
+  hipLaunchKernelGGL(k_front_groups, runs, dim3(FR), 0, st, n, (const uint64_t*)key, (const int32_t*)idx,
+                     (const double*)zd, i32(L.rgrp), i32(L.rpos), f64(L.ru), gnw, gbeta, i32(L.cnt));
+  hipLaunchKernelGGL(k_front_reduce, runs, dim3(FR), 0, st, n, d, (const int32_t*)idx, (const int32_t*)i32(L.rgrp),
+                     (const double*)f64(L.ru), (const double*)gnw, (const double*)gbeta, (const int32_t*)i32(L.cnt),
+                     (const int32_t*)i32(L.bad), rd, rz, fc, dhdr);
+  GCHECK(hipGetLastError());
+  FrontHdr h;
+  GCHECK(hipMemcpyAsync(&h, dhdr, sizeof(h), hipMemcpyDeviceToHost, st));
+  GCHECK(hipStreamSynchronize(st));
+  if (h.bad) return set_info(info, DPR1_INFO_NONFINITE, st);
+  const int64_t m = h.m;
 
-  // the reduced problem on the GPU: eigenvalues and the shifted representation
-  // (sigma_k, mu_k, ||x_k||) from which k_assemble evaluates the vectors
-  std::vector<double> lamr(m), mur(m), xnr(m);
-  std::vector<int32_t> sir(m);
-  std::vector<char> mir;
+  // the reduced problem: eigenvalues and the shifted representation (sigma_k,
+  // mu_k, ||x_k||) from which k_assemble evaluates the vectors
   if (m > 0) {
-    double* ddr = (double*)(w + L.dr);
-    double* dzr = (double*)(w + L.zr);
-    double* dlr = (double*)(w + L.lamr);
-    int32_t* dsi = (int32_t*)(w + L.sidx);
-    double* dmu = (double*)(w + L.mu);
-    double* dxn = (double*)(w + L.xn);
-    int32_t* dinf = (int32_t*)(w + L.inf);
-    // the inputs [dr, zr] and the outputs [lamr, inf] are contiguous in the
-    // workspace: one copy each way through a host mirror
-    mir.resize(std::max(L.zr + 8 * m - L.dr, L.inf + 4 - L.lamr));
-    memcpy(mir.data(), rd.data(), 8 * m);
-    memcpy(mir.data() + (L.zr - L.dr), rz.data(), 8 * m);
-    GCHECK(hipMemcpyAsync(ddr, mir.data(), L.zr + 8 * m - L.dr, hipMemcpyHostToDevice, st));
-    const int rc = dpr1_eig(ddr, dzr, rho, m, dlr, nullptr, m, V ? dsi : nullptr, V ? dmu : nullptr,
-                            V ? dxn : nullptr, dinf, nullptr, opts, w + L.solver, dpr1_workspace_size(m), stream);
+    const int rc = dpr1_eig(rd, rz, rho, m, f64(L.lamr), nullptr, m, V ? i32(L.sidx) : nullptr,
+                            V ? f64(L.mu) : nullptr, V ? f64(L.xn) : nullptr, i32(L.inf), nullptr, opts,
+                            w + L.solver, dpr1_workspace_size(m), (void*)st);
     if (rc != DPR1_OK) return rc;
-    int32_t hinf = 0;
-    GCHECK(hipMemcpyAsync(mir.data(), dlr, L.inf + 4 - L.lamr, hipMemcpyDeviceToHost, st));
-    GCHECK(hipStreamSynchronize(st));
-    memcpy(lamr.data(), mir.data(), 8 * m);
-    if (V) {
-      memcpy(sir.data(), mir.data() + (L.sidx - L.lamr), 4 * m);
-      memcpy(mur.data(), mir.data() + (L.mu - L.lamr), 8 * m);
-      memcpy(xnr.data(), mir.data() + (L.xn - L.lamr), 8 * m);
-    }
-    memcpy(&hinf, mir.data() + (L.inf - L.lamr), 4);
-    if (hinf != DPR1_INFO_OK) return set_info(info, hinf, st);
   }
-  {
-    std::vector<fe::Col> all;
-    fe::merge_cols(cols, lamr.data(), m, all);
-    cols.swap(all);
-  }
-  std::vector<double> lam(n), csig(n, 0.0), cmu(n, 0.0), cic(n, 0.0), cub(n, 0.0);
-  std::vector<int32_t> ckind(n), cidx(n), ct(n);
-  for (int64_t c = 0; c < n; ++c) {
-    const fe::Col& q = cols[c];
-    lam[c] = q.val;
-    ckind[c] = q.kind;
-    cidx[c] = q.idx;
-    ct[c] = q.t;
-    cub[c] = q.ub;
-    if (V && q.kind == COL_REDUCED) {
-      csig[c] = rd[sir[q.idx]];
-      cmu[c] = mur[q.idx];
-      cic[c] = 1.0 / xnr[q.idx];
-    }
-  }
-  GCHECK(hipMemcpyAsync(lambda, lam.data(), 8 * n, hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(k_front_columns, rows, dim3(256), 0, st, n, m, fc, (const double*)rd, (const double*)f64(L.lamr),
+                     (const int32_t*)i32(L.sidx), (const double*)f64(L.mu), (const double*)f64(L.xn),
+                     (const int32_t*)i32(L.inf), lambda, info, V != nullptr, i32(L.ckind), i32(L.cidx), i32(L.ct),
+                     f64(L.csig), f64(L.cmu), f64(L.cic), f64(L.cub));
+  GCHECK(hipGetLastError());
   if (V) {
     AsmArgs a;
     a.n = n;
     a.ldv = ldv;
     a.d = d;
-    a.z = zdev;
-    a.ph = ph;
-    a.rgrp = (int32_t*)(w + L.rgrp);
-    a.rpos = (int32_t*)(w + L.rpos);
-    a.ru = (double*)(w + L.ru);
-    a.ckind = (int32_t*)(w + L.ckind);
-    a.cidx = (int32_t*)(w + L.cidx);
-    a.ct = (int32_t*)(w + L.ct);
-    a.csig = (double*)(w + L.csig);
-    a.cmu = (double*)(w + L.cmu);
-    a.cic = (double*)(w + L.cic);
-    a.cub = (double*)(w + L.cub);
+    a.z = zd;
+    a.ph = CPLX ? ph : nullptr;
+    a.rgrp = i32(L.rgrp);
+    a.rpos = i32(L.rpos);
+    a.ru = f64(L.ru);
+    a.ckind = i32(L.ckind);
+    a.cidx = i32(L.cidx);
+    a.ct = i32(L.ct);
+    a.csig = f64(L.csig);
+    a.cmu = f64(L.cmu);
+    a.cic = f64(L.cic);
+    a.cub = f64(L.cub);
     a.V = V;
-    // the ten column tables [rgrp, cub] are contiguous: one copy
-    mir.resize(L.cub + 8 * n - L.rgrp);
-    auto put = [&](size_t off, const void* src, size_t bytes) { memcpy(mir.data() + (off - L.rgrp), src, bytes); };
-    put(L.rgrp, rgrp.data(), 4 * n);
-    put(L.rpos, rpos.data(), 4 * n);
-    put(L.ru, ru.data(), 8 * n);
-    put(L.ckind, ckind.data(), 4 * n);
-    put(L.cidx, cidx.data(), 4 * n);
-    put(L.ct, ct.data(), 4 * n);
-    put(L.csig, csig.data(), 8 * n);
-    put(L.cmu, cmu.data(), 8 * n);
-    put(L.cic, cic.data(), 8 * n);
-    put(L.cub, cub.data(), 8 * n);
-    GCHECK(hipMemcpyAsync(w + L.rgrp, mir.data(), mir.size(), hipMemcpyHostToDevice, st));
-    const int64_t rows = ASM_T * ASM_R;
-    const int64_t rtiles = (n + rows - 1) / rows;
+    const int64_t arows = ASM_T * ASM_R;
+    const int64_t rtiles = (n + arows - 1) / arows;
     // about 512 blocks, each looping over every gy-th column group: the grid's
     // write front then moves through V in order, which HBM takes faster than
     // one block per column group (n = 32768: 5.42 against 5.6 ms per call)
     const int64_t gy = std::min<int64_t>(std::max<int64_t>(16, (512 + rtiles - 1) / rtiles),
                                          std::min<int64_t>((n + ASM_CB - 1) / ASM_CB, 65535));
     const dim3 grid((unsigned)rtiles, (unsigned)gy);
-    if (ph)
-      hipLaunchKernelGGL(k_assemble<true>, grid, dim3(ASM_T), 0, st, a);
-    else
-      hipLaunchKernelGGL(k_assemble<false>, grid, dim3(ASM_T), 0, st, a);
+    hipLaunchKernelGGL(k_assemble<CPLX>, grid, dim3(ASM_T), 0, st, a);
     GCHECK(hipGetLastError());
   }
-  // set_info waits for the stream: the host vectors above are sources of the
-  // copies and must outlive them
-  return set_info(info, DPR1_INFO_OK, st);
+  GCHECK(hipStreamSynchronize(st));
+  return DPR1_OK;
 }
 
 extern "C" {
@@ -375,14 +692,7 @@ int dpr1_eig_general(const double* d, const double* z, double rho, int64_t n, do
                      void* stream) {
   const int bad = check_args(d, z, rho, n, lambda, V, ldv, info, opts, work, work_bytes);
   if (bad) return bad;
-  hipStream_t st = (hipStream_t)stream;
-  std::vector<double> hd(n), hz(n);
-  GCHECK(hipMemcpyAsync(hd.data(), d, 8 * n, hipMemcpyDeviceToHost, st));
-  GCHECK(hipMemcpyAsync(hz.data(), z, 8 * n, hipMemcpyDeviceToHost, st));
-  GCHECK(hipStreamSynchronize(st));
-  for (int64_t j = 0; j < n; ++j)
-    if (!std::isfinite(hd[j]) || !std::isfinite(hz[j])) return set_info(info, DPR1_INFO_NONFINITE, st);
-  return front_end(d, z, hd, hz, nullptr, rho, n, lambda, V, ldv, info, opts, (char*)work, glayout(n), st, stream);
+  return front_end<false>(d, z, rho, n, lambda, V, ldv, info, opts, (char*)work, (hipStream_t)stream);
 }
 
 int dpr1_eig_hermitian(const double* d, const double* z, double rho, int64_t n, double* lambda, double* V,
@@ -390,33 +700,7 @@ int dpr1_eig_hermitian(const double* d, const double* z, double rho, int64_t n, 
                        void* stream) {
   const int bad = check_args(d, z, rho, n, lambda, V, ldv, info, opts, work, work_bytes);
   if (bad) return bad;
-  hipStream_t st = (hipStream_t)stream;
-  const GLayout L = glayout(n);
-  char* w = (char*)work;
-  std::vector<double> hd(n), hzc(2 * n);
-  GCHECK(hipMemcpyAsync(hd.data(), d, 8 * n, hipMemcpyDeviceToHost, st));
-  GCHECK(hipMemcpyAsync(hzc.data(), z, 16 * n, hipMemcpyDeviceToHost, st));
-  GCHECK(hipStreamSynchronize(st));
-  for (int64_t j = 0; j < n; ++j)
-    if (!std::isfinite(hd[j]) || !std::isfinite(hzc[2 * j]) || !std::isfinite(hzc[2 * j + 1]))
-      return set_info(info, DPR1_INFO_NONFINITE, st);
-  // z = Phi |z| with Phi = diag(z_j / |z_j|) unitary (1 where z_j = 0), and
-  // Phi D Phi^H = D: A = Phi (D + rho |z| |z|^T) Phi^H, so the eigenvalues are
-  // those of the real problem with |z| and v = Phi v_real
-  std::vector<double> ha(n), hph(2 * n);
-  for (int64_t j = 0; j < n; ++j) {
-    const double re = hzc[2 * j], im = hzc[2 * j + 1];
-    const double r = std::hypot(re, im);
-    ha[j] = r;
-    hph[2 * j] = r > 0.0 ? re / r : 1.0;
-    hph[2 * j + 1] = r > 0.0 ? im / r : 0.0;
-  }
-  double* za = (double*)(w + L.zabs);
-  double* ph = (double*)(w + L.ph);
-  GCHECK(hipMemcpyAsync(za, ha.data(), 8 * n, hipMemcpyHostToDevice, st));
-  GCHECK(hipMemcpyAsync(ph, hph.data(), 16 * n, hipMemcpyHostToDevice, st));
-  // front_end synchronises before it returns, so ha and hph outlive the copies
-  return front_end(d, za, hd, ha, ph, rho, n, lambda, V, ldv, info, opts, w, L, st, stream);
+  return front_end<true>(d, z, rho, n, lambda, V, ldv, info, opts, (char*)work, (hipStream_t)stream);
 }
 
 }  // extern "C"
