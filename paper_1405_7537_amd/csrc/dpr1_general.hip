@@ -32,23 +32,16 @@
 #include <cstring>
 
 #include "../../include/dpr1.h"
-#include "reduce.h"
 
 namespace dpr1 {
 namespace gen {
 
-using fe::COL_REDUCED;
-using fe::COL_REFLECT;
-using fe::COL_UNIT;
-
 // Per original row i: rgrp its group id, rpos its position in the group, ru
 // the reflection vector's component there (0 for groups without reflection).
-// Per final column c:
-//   COL_REDUCED  csig = sigma_k (the shift pole), cmu = mu_k,
-//                cic = 1 / ||x_k||
-//   COL_UNIT     cidx = original row of the unit vector
-//   COL_REFLECT  cidx = group id, ct = column t of the reflection,
-//                cub = beta u_t
+// Per final column c, an eigenvector of the reduced problem (cgrp = -1):
+//   csig = sigma_k (the shift pole), cmu = mu_k, cic = 1 / ||x_k||
+// or a column of the reduction, column ct of the reflection of group cgrp:
+//   cub = beta u_t (0 for a deflated pole: a unit vector)
 struct AsmArgs {
   int64_t n, ldv;
   const double* d;
@@ -56,8 +49,7 @@ struct AsmArgs {
   const int32_t* rgrp;
   const int32_t* rpos;
   const double* ru;
-  const int32_t* ckind;
-  const int32_t* cidx;
+  const int32_t* cgrp;
   const int32_t* ct;
   const double* csig;
   const double* cmu;
@@ -72,27 +64,43 @@ __device__ __forceinline__ double rcp_nr(double x) {
   return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
 }
 
-// Tile: ASM_CB columns x ASM_T * ASM_R rows.  The block stages the column
-// parameters in LDS once; each thread keeps ASM_R rows in registers and, per
-// column, issues ASM_R streaming stores, each a contiguous, aligned 512-byte
-// window per wave when ldv is a multiple of 64.
-constexpr int ASM_T = 256, ASM_R = 4, ASM_CB = 16;
+__device__ __forceinline__ double lane_value(double x, int lane) {
+  const int64_t b = __double_as_longlong(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
+}
+
+// V in address order: wave g keeps rows 64 E (g % wpc) .. + 64 E - 1 in
+// registers, E consecutive ones a lane, and writes the groups of ASM_U
+// consecutive columns g / wpc, g / wpc + m, ... (m waves per row range), the
+// next group's column constants loaded while the current one is written.  The
+// whole GPU's write front then moves through V as a fill's does, in 16-byte
+// streaming stores.  Bound by HBM writes; n = 32768: 1533 us in tiles of 1024
+// rows with 8-byte stores, 1365 so (1597 with a branch per column).
+// An odd ldv puts every other column's stores across 16-byte boundaries, which
+// the hardware takes and which beats one row a lane (n = 4099: 288 us a call
+// against 299).  CPLX: V is complex (interleaved re, im; element (i, c) at 2 (i
+// + c ldv)), an element fills 16 bytes and row i is multiplied by the phase of
+// z_i.
+constexpr int ASM_T = 256, ASM_U = 8, ASM_WAVES = 2048;
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
+typedef dbl2 dbl2u __attribute__((aligned(8)));
 
-// CPLX: V is complex (interleaved re, im; element (i, c) at 2 (i + c ldv)) and
-// row i is multiplied by the phase of z_i.
 template <bool CPLX>
-__global__ void __launch_bounds__(ASM_T) k_assemble(AsmArgs a) {
-  __shared__ int s_kind[ASM_CB], s_idx[ASM_CB], s_t[ASM_CB];
-  __shared__ double s_sig[ASM_CB], s_mu[ASM_CB], s_ic[ASM_CB], s_ub[ASM_CB];
-  const int64_t n = a.n;
-  const int64_t r0 = (int64_t)blockIdx.x * (ASM_T * ASM_R);
-  double di[ASM_R], zi[ASM_R], ui[ASM_R], pr[ASM_R], pm[ASM_R];
-  int gi[ASM_R], pi[ASM_R];
+__global__ void __launch_bounds__(ASM_T) k_assemble(AsmArgs a, int64_t wpc, int64_t m) {
+  constexpr int E = CPLX ? 1 : 2;
+  const int lane = threadIdx.x & 63;
+  const int64_t g = (int64_t)blockIdx.x * (ASM_T / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t n = a.n, r = g % wpc, i0 = 64 * E * r + E * lane;
+  const int64_t ngrp = (n + ASM_U - 1) / ASM_U;
+  if (g >= wpc * m) return;
+  double di[E], zi[E], ui[E], pr[E], pm[E];
+  int gi[E], pi[E];
 #pragma unroll
-  for (int j = 0; j < ASM_R; ++j) {
-    const int64_t i = r0 + threadIdx.x + j * ASM_T;
+  for (int j = 0; j < E; ++j) {
+    const int64_t i = i0 + j;
     const bool ok = i < n;
     if (CPLX) {
       pr[j] = ok ? a.ph[2 * i] : 0.0;
@@ -104,61 +112,68 @@ __global__ void __launch_bounds__(ASM_T) k_assemble(AsmArgs a) {
     gi[j] = ok ? a.rgrp[i] : -1;
     pi[j] = ok ? a.rpos[i] : -1;
   }
-  const int64_t ncg = (n + ASM_CB - 1) / ASM_CB;
-  for (int64_t cg = blockIdx.y; cg < ncg; cg += gridDim.y) {
-    const int64_t c0 = cg * ASM_CB;
-    const int nc = (int)min((int64_t)ASM_CB, n - c0);
-    __syncthreads();  // the previous group's parameters are no longer read
-    if (threadIdx.x < nc) {
-      const int64_t c = c0 + threadIdx.x;
-      s_kind[threadIdx.x] = a.ckind[c];
-      s_idx[threadIdx.x] = a.cidx[c];
-      s_t[threadIdx.x] = a.ct[c];
-      s_sig[threadIdx.x] = a.csig[c];
-      s_mu[threadIdx.x] = a.cmu[c];
-      s_ic[threadIdx.x] = a.cic[c];
-      s_ub[threadIdx.x] = a.cub[c];
-    }
-    __syncthreads();
-    for (int cc = 0; cc < nc; ++cc) {
-      const int kind = s_kind[cc];
-      const int64_t e0 = (c0 + cc) * a.ldv + r0 + threadIdx.x;
-      double v[ASM_R];
-      if (kind == COL_REDUCED) {
-        const double m = s_mu[cc], sg = s_sig[cc], ic = s_ic[cc];
-#pragma unroll
-        for (int j = 0; j < ASM_R; ++j) {
-          // mu / den with one residual correction, then the scaled norm; a
-          // row with z_i == 0 (deflated, or a zero member of a merged group)
-          // is exactly 0 whatever den is
-          const double den = (di[j] - sg) - m;
-          const double rc = rcp_nr(den);
-          double q = ic * rc;
-          q = __builtin_fma(__builtin_fma(-q, den, ic), rc, q);
-          v[j] = zi[j] != 0.0 ? zi[j] * q : 0.0;
-        }
-      } else if (kind == COL_UNIT) {
-        const int64_t at = s_idx[cc];
-#pragma unroll
-        for (int j = 0; j < ASM_R; ++j) v[j] = (r0 + threadIdx.x + j * ASM_T == at) ? 1.0 : 0.0;
-      } else {
-        // column t of H = I - beta u u^T restricted to the group
-        const int g = s_idx[cc], t = s_t[cc];
-        const double ub = s_ub[cc];
-#pragma unroll
-        for (int j = 0; j < ASM_R; ++j) v[j] = gi[j] == g ? (pi[j] == t ? 1.0 : 0.0) - ub * ui[j] : 0.0;
+  // a group's constants in one load across the wave: lane u + 8 f holds field f
+  // of column q ASM_U + u
+  auto load = [&](int64_t q) {
+    const int f = lane / ASM_U;
+    const int64_t c = min(q * ASM_U + (lane & (ASM_U - 1)), n - 1);
+    double x = 0.0;
+    if (f == 0) x = a.csig[c];
+    else if (f == 1) x = a.cmu[c];
+    else if (f == 2) x = a.cic[c];
+    else if (f == 3) x = a.cub[c];
+    else if (f == 4) x = a.cgrp[c];
+    else if (f == 5) x = a.ct[c];
+    return x;
+  };
+  auto store = [&](int64_t c, const double* v) {
+    if (CPLX) {
+      if (i0 < n) {
+        const dbl2 cv = {v[0] * pr[0], v[0] * pm[0]};
+        __builtin_nontemporal_store(cv, (dbl2*)(a.V + 2 * (c * a.ldv + i0)));
       }
+    } else if (E == 2 && i0 + 1 < n) {
+      const dbl2 cv = {v[0], v[E - 1]};
+      __builtin_nontemporal_store(cv, (dbl2u*)(a.V + c * a.ldv + i0));
+    } else if (i0 < n) {
+      __builtin_nontemporal_store(v[0], a.V + c * a.ldv + i0);
+    }
+  };
+  double cur = g / wpc < ngrp ? load(g / wpc) : 0.0;
+  for (int64_t q = g / wpc; q < ngrp; q += m) {
+    const double nxt = q + m < ngrp ? load(q + m) : 0.0;
+    // every column's quotient first, then the few columns that are none: a
+    // branch per column around the quotients would keep them from overlapping
+    double v[ASM_U][E];
 #pragma unroll
-      for (int j = 0; j < ASM_R; ++j) {
-        if (r0 + threadIdx.x + j * ASM_T >= n) continue;
-        if (CPLX) {
-          const dbl2 cv = {v[j] * pr[j], v[j] * pm[j]};
-          __builtin_nontemporal_store(cv, (dbl2*)(a.V + 2 * (e0 + j * ASM_T)));
-        } else {
-          __builtin_nontemporal_store(v[j], a.V + e0 + j * ASM_T);
-        }
+    for (int u = 0; u < ASM_U; ++u) {
+      const double sg = lane_value(cur, u), mu = lane_value(cur, ASM_U + u), ic = lane_value(cur, 2 * ASM_U + u);
+#pragma unroll
+      for (int j = 0; j < E; ++j) {
+        // mu / den with one residual correction, then the scaled norm; a row
+        // with z_i == 0 (deflated, or a zero member of a merged group) is
+        // exactly 0 whatever den is
+        const double den = (di[j] - sg) - mu;
+        const double rc = rcp_nr(den);
+        double w = ic * rc;
+        w = __builtin_fma(__builtin_fma(-w, den, ic), rc, w);
+        v[u][j] = zi[j] != 0.0 ? zi[j] * w : 0.0;
       }
     }
+#pragma unroll
+    for (int u = 0; u < ASM_U; ++u) {
+      const int h = (int)lane_value(cur, 4 * ASM_U + u);
+      if (h < 0) continue;
+      // column t of H = I - beta u u^T restricted to the group h
+      const int t = (int)lane_value(cur, 5 * ASM_U + u);
+      const double ub = lane_value(cur, 3 * ASM_U + u);
+#pragma unroll
+      for (int j = 0; j < E; ++j) v[u][j] = gi[j] == h ? (pi[j] == t ? 1.0 : 0.0) - ub * ui[j] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < ASM_U; ++u)
+      if (q * ASM_U + u < n) store(q * ASM_U + u, v[u]);
+    cur = nxt;
   }
 }
 
@@ -418,12 +433,12 @@ __global__ void __launch_bounds__(FR) k_front_groups(int64_t n, const uint64_t* 
 
 // The reduced problem and the columns that do not come from it, both in
 // decreasing pole order: a sorted position either enters the reduced problem
-// (the first of a group whose ||w|| is not 0) or gives a column, a unit vector
-// of its row (ct0 = -1) or column ct0 of its group's reflection.
+// (the first of a group whose ||w|| is not 0) or gives a column, that of its
+// place in its group's reflection (the identity where ||w|| = 0).
 struct FrontCols {
   double* val;   // the eigenvalue
   double* ub;    // beta u_t
-  int32_t* idx;  // the row, or the group
+  int32_t* grp;
   int32_t* t;
 };
 __global__ void __launch_bounds__(FR) k_front_reduce(int64_t n, const double* d, const int32_t* idx,
@@ -467,10 +482,9 @@ __global__ void __launch_bounds__(FR) k_front_reduce(int64_t n, const double* d,
   } else {
     const int64_t c = s - r;
     fc.val[c] = d[idx[h]];
-    const bool unit = nw == 0.0;
-    fc.idx[c] = unit ? row : h;
-    fc.t[c] = unit ? -1 : (int32_t)(s - h);
-    fc.ub[c] = unit ? 0.0 : gbeta[h] * ru[row];
+    fc.grp[c] = h;
+    fc.t[c] = (int32_t)(s - h);
+    fc.ub[c] = gbeta[h] * ru[row];  // 0 where ||w|| = 0
   }
 }
 
@@ -480,9 +494,8 @@ __global__ void __launch_bounds__(FR) k_front_reduce(int64_t n, const double* d,
 __global__ void __launch_bounds__(256) k_front_columns(int64_t n, int64_t m, FrontCols fc, const double* rd,
                                                        const double* lamr, const int32_t* sidx, const double* mu,
                                                        const double* xn, const int32_t* inf, double* lambda,
-                                                       int32_t* info, bool vectors, int32_t* ckind, int32_t* cidx,
-                                                       int32_t* ct, double* csig, double* cmu, double* cic,
-                                                       double* cub) {
+                                                       int32_t* info, bool vectors, int32_t* cgrp, int32_t* ct,
+                                                       double* csig, double* cmu, double* cic, double* cub) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int32_t code = m > 0 ? inf[0] : 0;
   if (t == 0) info[0] = code;
@@ -503,29 +516,19 @@ __global__ void __launch_bounds__(256) k_front_columns(int64_t n, int64_t m, Fro
   const int64_t c = own + lo;
   lambda[c] = v;
   if (!vectors) return;
-  if (red) {
-    ckind[c] = COL_REDUCED;
-    cidx[c] = (int32_t)own;
-    ct[c] = 0;
-    csig[c] = rd[sidx[own]];
-    cmu[c] = mu[own];
-    cic[c] = 1.0 / xn[own];
-    cub[c] = 0.0;
-  } else {
-    const int32_t tt = fc.t[own];
-    ckind[c] = tt < 0 ? COL_UNIT : COL_REFLECT;
-    cidx[c] = fc.idx[own];
-    ct[c] = max(tt, 0);
-    csig[c] = cmu[c] = cic[c] = 0.0;
-    cub[c] = fc.ub[own];
-  }
+  cgrp[c] = red ? -1 : fc.grp[own];
+  ct[c] = red ? 0 : fc.t[own];
+  csig[c] = red ? rd[sidx[own]] : 0.0;
+  cmu[c] = red ? mu[own] : 0.0;
+  cic[c] = red ? 1.0 / xn[own] : 0.0;
+  cub[c] = red ? 0.0 : fc.ub[own];
 }
 
 static size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct GLayout {
-  size_t dr, zr, lamr, sidx, mu, xn, inf, rgrp, rpos, ru, ckind, cidx, ct, csig, cmu, cic, cub, zabs, ph, val0, ub0,
-      idx0, t0, cnt, bad, hdr, solver, total;
+  size_t dr, zr, lamr, sidx, mu, xn, inf, rgrp, rpos, ru, cgrp, ct, csig, cmu, cic, cub, zabs, ph, val0, ub0,
+      grp0, t0, cnt, bad, hdr, solver, total;
 };
 static GLayout glayout(int64_t n) {
   GLayout L;
@@ -540,8 +543,7 @@ static GLayout glayout(int64_t n) {
   L.rgrp = o; o = al(o + 4 * n);
   L.rpos = o; o = al(o + 4 * n);
   L.ru = o; o = al(o + 8 * n);
-  L.ckind = o; o = al(o + 4 * n);
-  L.cidx = o; o = al(o + 4 * n);
+  L.cgrp = o; o = al(o + 4 * n);
   L.ct = o; o = al(o + 4 * n);
   L.csig = o; o = al(o + 8 * n);
   L.cmu = o; o = al(o + 8 * n);
@@ -551,7 +553,7 @@ static GLayout glayout(int64_t n) {
   L.ph = o; o = al(o + 16 * n);
   L.val0 = o; o = al(o + 8 * n);
   L.ub0 = o; o = al(o + 8 * n);
-  L.idx0 = o; o = al(o + 4 * n);
+  L.grp0 = o; o = al(o + 4 * n);
   L.t0 = o; o = al(o + 4 * n);
   L.cnt = o; o = al(o + 4 * ((n + FR - 1) / FR));
   L.bad = o; o = al(o + 4 * ((n + FR - 1) / FR));
@@ -615,9 +617,9 @@ static int front_end(const double* d, const double* z, double rho, int64_t n, do
   double *zd = f64(L.zabs), *ph = f64(L.ph), *rd = f64(L.dr), *rz = f64(L.zr);
   // the sort and the groups work in the room of arrays that are written later
   uint64_t *key = (uint64_t*)(w + L.lamr), *key2 = (uint64_t*)(w + L.csig);
-  int32_t *idx = i32(L.sidx), *idx2 = i32(L.cidx);
+  int32_t *idx = i32(L.sidx), *idx2 = i32(L.cgrp);
   double *gnw = f64(L.cmu), *gbeta = f64(L.cic);
-  const FrontCols fc = {f64(L.val0), f64(L.ub0), i32(L.idx0), i32(L.t0)};
+  const FrontCols fc = {f64(L.val0), f64(L.ub0), i32(L.grp0), i32(L.t0)};
   FrontHdr* dhdr = (FrontHdr*)(w + L.hdr);
   const dim3 runs((unsigned)((n + FR - 1) / FR)), rows((unsigned)((n + 255) / 256));
   hipLaunchKernelGGL(k_front_sort<CPLX>, runs, dim3(FR), 0, st, d, z, n, zd, ph, key, idx, i32(L.bad));
@@ -649,8 +651,8 @@ static int front_end(const double* d, const double* z, double rho, int64_t n, do
   }
   hipLaunchKernelGGL(k_front_columns, rows, dim3(256), 0, st, n, m, fc, (const double*)rd, (const double*)f64(L.lamr),
                      (const int32_t*)i32(L.sidx), (const double*)f64(L.mu), (const double*)f64(L.xn),
-                     (const int32_t*)i32(L.inf), lambda, info, V != nullptr, i32(L.ckind), i32(L.cidx), i32(L.ct),
-                     f64(L.csig), f64(L.cmu), f64(L.cic), f64(L.cub));
+                     (const int32_t*)i32(L.inf), lambda, info, V != nullptr, i32(L.cgrp), i32(L.ct), f64(L.csig),
+                     f64(L.cmu), f64(L.cic), f64(L.cub));
   GCHECK(hipGetLastError());
   if (V) {
     AsmArgs a;
@@ -662,23 +664,18 @@ static int front_end(const double* d, const double* z, double rho, int64_t n, do
     a.rgrp = i32(L.rgrp);
     a.rpos = i32(L.rpos);
     a.ru = f64(L.ru);
-    a.ckind = i32(L.ckind);
-    a.cidx = i32(L.cidx);
+    a.cgrp = i32(L.cgrp);
     a.ct = i32(L.ct);
     a.csig = f64(L.csig);
     a.cmu = f64(L.cmu);
     a.cic = f64(L.cic);
     a.cub = f64(L.cub);
     a.V = V;
-    const int64_t arows = ASM_T * ASM_R;
-    const int64_t rtiles = (n + arows - 1) / arows;
-    // about 512 blocks, each looping over every gy-th column group: the grid's
-    // write front then moves through V in order, which HBM takes faster than
-    // one block per column group (n = 32768: 5.42 against 5.6 ms per call)
-    const int64_t gy = std::min<int64_t>(std::max<int64_t>(16, (512 + rtiles - 1) / rtiles),
-                                         std::min<int64_t>((n + ASM_CB - 1) / ASM_CB, 65535));
-    const dim3 grid((unsigned)rtiles, (unsigned)gy);
-    hipLaunchKernelGGL(k_assemble<CPLX>, grid, dim3(ASM_T), 0, st, a);
+    const int64_t span = CPLX ? 64 : 128;  // rows of a wave
+    const int64_t wpc = (n + span - 1) / span;
+    const int64_t per = std::min<int64_t>(std::max<int64_t>(1, ASM_WAVES / wpc), (n + ASM_U - 1) / ASM_U);
+    const dim3 grid((unsigned)((wpc * per + ASM_T / 64 - 1) / (ASM_T / 64)));
+    hipLaunchKernelGGL(k_assemble<CPLX>, grid, dim3(ASM_T), 0, st, a, wpc, per);
     GCHECK(hipGetLastError());
   }
   GCHECK(hipStreamSynchronize(st));
