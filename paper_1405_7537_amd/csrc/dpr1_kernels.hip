@@ -27,7 +27,7 @@
 //              Newton polish, and the near-zero recomputation of eq. (gamma).
 //   k_fixvec -- k_fix's work and the eigenvector writer in one launch: a few
 //              blocks finish the flagged eigenpairs while the others write V,
-//              one block per column group and row range, non-temporal stores
+//              a block per tile of rows and columns, non-temporal stores
 //              in windows aligned to whole cache lines; a flagged column is
 //              written by the block that finishes its eigenpair.
 #include <float.h>
@@ -2044,11 +2044,16 @@ __device__ void fix_items(const KArgs& A) {
   const int tid = threadIdx.x;
   const int n0 = A.ctr[0];
   const int cnt = n0 + A.ctr[3];
-  for (;;) {
+  for (bool first = true;; first = false) {
     // items are taken from a queue, long ones first, so a block that drew
     // cheap items takes more of them (polish steps cost several times a
-    // continued root's)
-    if (tid == 0) next = atomicAdd(&A.ctr[2], 1);
+    // continued root's); a block that comes to an empty queue only reads it,
+    // since atomics on one address take their turns (512 blocks, 15 us).  One
+    // thread looks, for the whole block: others may see later values
+    if (tid == 0) {
+      const bool empty = first && __hip_atomic_load(&A.ctr[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= cnt;
+      next = empty ? cnt : atomicAdd(&A.ctr[2], 1);
+    }
     __syncthreads();
     const int e = next;
     __syncthreads();
@@ -2304,18 +2309,17 @@ __global__ void __launch_bounds__(FIXT, 4) k_fix(KArgs A) { fix_items(A); }
 // store instruction covers whole cache lines whatever the column's offset
 // (a packed ragged batch puts most columns at odd offsets; misaligned
 // non-temporal stores write partial lines and halve the write bandwidth).
-// Only the first and last window of a column segment are partial.  The
-// single-problem launch derives (column group, row tile) from the block
-// index; the batched launch reads (problem, first column, columns, first
-// row) from a table built by the plan.
+// Only the first and last window of a column segment are partial.  The block
+// reads (problem, first column, columns, first row) from a table built by the
+// plan.
 constexpr int VEC_T = 256;
 constexpr int VEC_ROWS = 2048;
-// columns per block: 32 for a batch as for one problem (64 measured 4-7 %
-// slower on the 2048-problem mix and on 4 problems of n = 16384, 16 no faster)
-constexpr int VEC_C_SINGLE = 32, VEC_C_BATCH = 32;
+// columns per block: 32 (64 measured 4-7 % slower on the 2048-problem mix and
+// on 4 problems of n = 16384, 16 no faster)
+constexpr int VEC_C = 32;
 // Where blocks of that many columns leave the GPU idle their width is halved,
-// to 4 at least, until VEC_BLOCKS run (n = 1501: 47 blocks of 32 columns took
-// 54 us for 18 MB).
+// to 4 at least, until VEC_BLOCKS run (a problem of n = 1501: 47 blocks of 32
+// columns took 54 us for 18 MB).
 constexpr int64_t VEC_BLOCKS = 1024;
 // most chunks of the overlapped single-problem solve (opts.vwrite)
 constexpr int VEC_CHUNKS_MAX = 8;
@@ -2326,8 +2330,6 @@ constexpr int VEC_CHUNKS_MAX = 8;
 struct VArgs {
   const Meta* meta;
   const int4* groups;  // batched: (problem, first column, columns, first row) per block
-  int64_t ncolgroups;  // single problem: column groups per row tile
-  int32_t cb;          // single problem: columns per group (at most VEC_C_SINGLE)
   const double* sd;
   const double* sz;
   const double* mu;
@@ -2339,40 +2341,23 @@ struct VArgs {
   int64_t ldv;
   int32_t cbase, cend;  // single problem: columns cbase .. cend-1
   int32_t prio;         // k_vec: raise the waves' issue priority
-  int32_t sweep;        // single problem: waves of vec_sweep (0: vec_block)
+  int32_t n, neg;       // single problem: its order, rho < 0 (-1: in meta)
 };
 
-template <int CB>
 __device__ void vec_block(unsigned bid, const VArgs& v) {
   __shared__ double ld_d[VEC_ROWS], ld_z[VEC_ROWS];
-  __shared__ double lsig[CB], lmu[CB], linv[CB];
-  __shared__ uint8_t lskip[CB];
+  __shared__ double lsig[VEC_C], lmu[VEC_C], linv[VEC_C];
+  __shared__ uint8_t lskip[VEC_C];
   const Meta* __restrict__ meta = v.meta;
-  const int4* __restrict__ groups = v.groups;
-  const int64_t ncolgroups = v.ncolgroups;
   const double* __restrict__ sd = v.sd;
   const double* __restrict__ sz = v.sz;
   double* __restrict__ V = v.V;
-  const int64_t* __restrict__ voffs = v.voffs;
-  const int64_t ldv = v.ldv;
-  int p, c0, nc;
-  int64_t r0;
-  if (groups) {
-    const int4 g = groups[bid];
-    p = g.x;
-    c0 = g.y;
-    nc = g.z;
-    r0 = g.w;
-  } else {
-    p = 0;
-    c0 = v.cbase + (int)(bid % ncolgroups) * v.cb;
-    r0 = (int64_t)(bid / ncolgroups) * VEC_ROWS;
-    nc = 0;
-  }
+  const int4 grp = v.groups[bid];
+  const int p = grp.x, c0 = grp.y, nc = grp.z;
+  const int64_t r0 = grp.w;
   const Meta M = meta[p];
   if (M.info != 0) return;
   const int n = M.n;
-  if (!groups) nc = min(v.cb, min(n, v.cend) - c0);
   const int nr = (int)min((int64_t)VEC_ROWS, (int64_t)n - r0);
   if (nc <= 0 || nr <= 0) return;
   const double sg = M.neg ? -1.0 : 1.0;
@@ -2392,11 +2377,10 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
     lskip[threadIdx.x] = v.vflag ? v.vflag[a] : 0;
   }
   __syncthreads();
-  const int64_t ld = voffs ? (int64_t)n : ldv;
-  const int64_t base = voffs ? voffs[p] : 0;
+  const int64_t ld = n, base = v.voffs[p];
   const int wv = wave_id(), lane = threadIdx.x % WAVE;
   constexpr int NW = VEC_T / WAVE;
-  if (r0 == 0 && nr == n && ld == n) {
+  if (nr == n) {
     // Whole columns of a packed block: the group's columns are one
     // contiguous range of nc n elements, written in aligned windows with
     // (column, position) recovered per element.  nc n <= CB VEC_ROWS < 2^24,
@@ -2475,112 +2459,153 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
 }
 
 
-// The eigenvector writer of one problem in address order, for a V whose
-// columns all start 16-byte aligned (the other case, and batches, take
-// vec_block).  HBM takes writes fastest when the whole GPU's write front
-// moves through memory in order, as a fill does (a standalone test: 6.3
-// TB/s against 5.4 for column groups written independently): wave g keeps
-// positions 128 (g % wpc) .. + 127 of every column it writes, their d and
-// zeta in registers, two per lane in one 16-byte non-temporal store, and writes the
-// groups of SWEEP_U consecutive columns g / wpc, g / wpc + m, ... (m waves
-// per position range, nw = m wpc waves in all), the next group's column
-// constants loaded while the current one is written.  The arithmetic is
-// vec_block's.
-constexpr int SWEEP_U = 8, SWEEP_WAVES = 2048;
-__device__ void vec_sweep(const VArgs& v, int g, int nw) {
-  const Meta M = v.meta[0];
-  if (M.info != 0) return;
-  const int n = M.n;
-  const int wpc = (n + 2 * WAVE - 1) / (2 * WAVE);
-  const int m = nw / wpc;
-  const int r = g % wpc, cg = g / wpc;
-  if (cg >= m) return;
-  const int lane = lane_id();
-  const int pos = 2 * WAVE * r + 2 * lane;
-  const bool a0 = pos < n, a1 = pos + 1 < n;
+// The eigenvector writer of one problem (batches take vec_block): a block
+// writes TILE_ROWS positions of TILE_C columns, two consecutive positions per
+// thread in one 16-byte non-temporal store, and ends; blocks go down the
+// columns first, in memory order.  HBM takes writes fastest when the whole
+// GPU's write front moves through memory in order, as a fill does, and blocks
+// that start in order and end soon hold it together better than resident waves
+// that loop over columns: n = 32768, the writer alone 1230 us (7.0 TB/s; a fill
+// 1270) against 1430 to 1780 for 1024 or 2048 looping waves, and 1440 with 8
+// blocks per CU in place of the 4 that k_fix's registers leave.  A call: n =
+// 32768 1497 us (1622 with looping waves), n = 24000 841 (930).  A tile's
+// columns pay for its start-up: 8 columns, 6 and 10 are 1 to 3 % slower, 4 10 %.
+// The arithmetic is vec_block's.
+// Where every column starts on a 128-byte line a thread's d and zeta stay in
+// registers.  Else (SH) a column's windows are shifted back to whole lines, by
+// up to LINE - 1 positions, and the block keeps the positions that it may meet
+// in LDS; the last range also writes the up to LINE - 1 positions behind its
+// window.  A call: n = 32767 1700 us (2020 with 2048 rows by 32 columns a block,
+// windows aligned but each block's columns far apart), n = 16001 474 (562).
+constexpr int TILE_ROWS = 2 * VEC_T;
+constexpr int TILE_C = 8;
+constexpr int LINE = 16;  // doubles of a line
+template <bool SH>
+__device__ void vec_tile(const VArgs& v, unsigned bid) {
+  constexpr int C = TILE_C;
+  // rho's sign on the host: the loads below need not wait for the meta record
+  Meta M;
+  const int info = v.meta[0].info;
+  if (v.neg >= 0) {
+    M.off = 0;
+    M.n = v.n;
+    M.neg = v.neg;
+  } else {
+    M = v.meta[0];
+  }
+  const int n = M.n, t = threadIdx.x;
+  const int rt = (n + TILE_ROWS - 1) / TILE_ROWS;
+  const int r = (int)(bid % rt), r0 = r * TILE_ROWS;
+  // columns in memory order: ko of the caller's, k = n - 1 - ko when reversed
+  const int ce = min(n, v.cend);
+  const int kb = M.neg ? n - ce : v.cbase, ke = M.neg ? n - v.cbase : ce;
+  const int64_t ko0 = kb + (int64_t)(bid / rt) * C;
+  if (ko0 >= ke) return;
   const double sg = M.neg ? -1.0 : 1.0;
-  const int64_t j0 = M.neg ? n - 1 - pos : pos, j1 = M.neg ? n - 2 - pos : pos + 1;
-  const double d0 = a0 ? v.sd[M.off + j0] : 0.0, z0 = a0 ? sg * v.sz[M.off + j0] : 0.0;
-  const double d1 = a1 ? v.sd[M.off + j1] : 0.0, z1 = a1 ? sg * v.sz[M.off + j1] : 0.0;
-  const int cb = v.cbase, ce = min(n, v.cend);
-  const int ngrp = (ce - cb + SWEEP_U - 1) / SWEEP_U;
-  // the constants of group q in one load across the wave: lane u + 8 t
-  // holds, for column cb + q SWEEP_U + u, sigma (t = 0), mu (1), 1/||x||
-  // (2) or 1 for a column to skip (3: past the range, or one k_fix
-  // writes)
-  auto load = [&](int q) {
-    const int u = lane & (SWEEP_U - 1), t = lane / SWEEP_U;
-    const int k = cb + q * SWEEP_U + u;
-    const int64_t a = M.off + min(k, ce - 1);
-    double x = 0.0;
-    if (t == 0) x = v.csig[a];
-    else if (t == 1) x = v.mu[a];
-    else if (t == 2) x = v.cinv[a];
-    else if (t == 3) x = (k >= ce || (v.vflag && v.vflag[a])) ? 1.0 : 0.0;
-    return x;
+  // (d, zeta) of a position, 0 outside the column
+  auto entry = [&](int at, double& d, double& z) {
+    const bool in = at >= 0 && at < n;
+    const int64_t j = M.off + (M.neg ? n - 1 - at : at);
+    d = in ? v.sd[j] : 0.0;
+    z = in ? sg * v.sz[j] : 0.0;
   };
-  double cur = cg < ngrp ? load(cg) : 0.0;
-  for (int q = cg; q < ngrp; q += m) {
-    const bool more = q + m < ngrp;
-    const double nxt = more ? load(q + m) : 0.0;
+  double sc[C], mm[C], iv[C];
+  bool skip[C];  // past the range, or a column k_fix writes
 #pragma unroll
-    for (int u = 0; u < SWEEP_U; ++u) {
-      if (lane_value(cur, 3 * SWEEP_U + u) != 0.0) continue;
-      const double sc = lane_value(cur, u), mm = lane_value(cur, SWEEP_U + u), iv = lane_value(cur, 2 * SWEEP_U + u);
-      const int k = cb + q * SWEEP_U + u;
-      const int64_t ko = M.neg ? n - 1 - k : k;
-      const double den0 = (d0 - sc) - mm, den1 = (d1 - sc) - mm;
-      const double rc0 = rcp_1nr(den0), rc1 = rcp_1nr(den1);
-      double q0 = iv * rc0, q1 = iv * rc1;
-      q0 = __builtin_fma(__builtin_fma(-q0, den0, iv), rc0, q0);  // corrected quotients
-      q1 = __builtin_fma(__builtin_fma(-q1, den1, iv), rc1, q1);
-      double* vp = v.V + ko * v.ldv + pos;
-      if (a1) {
-        typedef double vdbl2 __attribute__((ext_vector_type(2)));
-        const vdbl2 vv = {z0 * q0, z1 * q1};
-        __builtin_nontemporal_store(vv, reinterpret_cast<vdbl2*>(vp));
-      } else if (a0) {
-        __builtin_nontemporal_store(z0 * q0, vp);
-      }
+  for (int u = 0; u < C; ++u) {
+    const int ko = (int)min(ko0 + u, (int64_t)ke - 1);
+    const int64_t a = M.off + (M.neg ? n - 1 - ko : ko);
+    sc[u] = v.csig[a];
+    mm[u] = v.mu[a];
+    iv[u] = v.cinv[a];
+    skip[u] = ko0 + u >= ke || (v.vflag && v.vflag[a]);
+  }
+  constexpr int NB = TILE_ROWS + 2 * LINE;
+  __shared__ double ld_d[SH ? NB : 1], ld_z[SH ? NB : 1];
+  double d0, z0, d1, z1;
+  if (SH) {
+    for (int i = t; i < NB - 1; i += VEC_T) entry(r0 - (LINE - 1) + i, ld_d[i], ld_z[i]);
+    __syncthreads();
+  } else {
+    entry(r0 + 2 * t, d0, z0);
+    entry(r0 + 2 * t + 1, d1, z1);
+  }
+  if (info != 0) return;
+#pragma unroll
+  for (int u = 0; u < C; ++u) {
+    if (skip[u]) continue;
+    double* col = v.V + (ko0 + u) * v.ldv;
+    const int s = SH ? (int)(((uintptr_t)col >> 3) & (LINE - 1)) : 0;
+    if (SH) {
+      const int i = LINE - 1 - s + 2 * t;
+      d0 = ld_d[i];
+      d1 = ld_d[i + 1];
+      z0 = ld_z[i];
+      z1 = ld_z[i + 1];
     }
-    cur = nxt;
+    const double den0 = (d0 - sc[u]) - mm[u], den1 = (d1 - sc[u]) - mm[u];
+    const double rc0 = rcp_1nr(den0), rc1 = rcp_1nr(den1);
+    double q0 = iv[u] * rc0, q1 = iv[u] * rc1;
+    q0 = __builtin_fma(__builtin_fma(-q0, den0, iv[u]), rc0, q0);  // corrected quotients
+    q1 = __builtin_fma(__builtin_fma(-q1, den1, iv[u]), rc1, q1);
+    typedef double vdbl2 __attribute__((ext_vector_type(2)));
+    const vdbl2 vv = {z0 * q0, z1 * q1};
+    const int at = r0 - s + 2 * t;
+    const bool a0 = at >= 0 && at < n, a1 = at + 1 >= 0 && at + 1 < n;
+    if (a0 && a1)
+      __builtin_nontemporal_store(vv, reinterpret_cast<vdbl2*>(col + at));
+    else if (a0)
+      __builtin_nontemporal_store(vv.x, col + at);
+    else if (a1)
+      __builtin_nontemporal_store(vv.y, col + at + 1);
+    const int tail = r0 + TILE_ROWS - s + t;
+    if (SH && r == rt - 1 && t < LINE && tail < n) {
+      const int i = LINE - 1 - s + TILE_ROWS + t;
+      const double den = (ld_d[i] - sc[u]) - mm[u], rc = rcp_1nr(den);
+      double q = iv[u] * rc;
+      q = __builtin_fma(__builtin_fma(-q, den, iv[u]), rc, q);
+      __builtin_nontemporal_store(ld_z[i] * q, col + tail);
+    }
   }
 }
-
-// Waves of the address-ordered writer for a problem of order n: about
-// SWEEP_WAVES, a whole number m >= 1 of waves per position range.
-static int64_t sweep_waves(int64_t n) {
-  const int64_t wpc = (n + 2 * WAVE - 1) / (2 * WAVE);
-  const int64_t m = std::min<int64_t>(std::max<int64_t>(1, SWEEP_WAVES / wpc), (n + SWEEP_U - 1) / SWEEP_U);
-  return wpc * m;
+static int64_t tile_blocks(int64_t n, int64_t columns) {
+  return (n + TILE_ROWS - 1) / TILE_ROWS * ((columns + TILE_C - 1) / TILE_C);
 }
 
-// The eigenvector writer alone (single problem, a range of columns).
-template <int CB>
+// The eigenvector writer alone (single problem, a range of columns); launched
+// with VEC_PAD bytes of LDS, which leave 4 blocks per CU.
+constexpr size_t VEC_PAD = 28 << 10;
+template <bool SH>
 __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
   // beside the eigenvalue kernel of the next chunk its waves issue first, so
   // that the stores keep flowing while the sweeps take the remaining issue
   // slots; beside k_fix (the last chunk) they do not, since k_fix is latency-
   // bound and would starve
   if (v.prio) __builtin_amdgcn_s_setprio(3);
-  if (v.sweep)
-    vec_sweep(v, __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (VEC_T / WAVE) + threadIdx.x / WAVE)), v.sweep);
-  else
-    vec_block<CB>(blockIdx.x, v);
+  vec_tile<SH>(v, blockIdx.x);
 }
 
-// k_fix and the eigenvector writer in one launch: the first nfix blocks take
-// flagged eigenpairs from the queue (latency-bound work), the others write V
-// (HBM-bound), so the two overlap.
-template <int CB>
-__global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix) {
-  if (blockIdx.x < (unsigned)nfix)
+// k_fix and the eigenvector writer in one launch, so that the two overlap: the
+// first nfix blocks take flagged eigenpairs from the queue (latency-bound
+// work), then come the blocks that write V (HBM-bound), and the last ntail take
+// what is left of the queue when the writers run out.
+// Where the writers are more than the GPU's places few blocks go in front: 256
+// there hold a quarter of the places for little when few eigenpairs are flagged
+// (n = 8000, 185 us a call against 173 with 64 and 448; every eigenpair
+// flagged, 673 against 517).  Where all blocks are resident together the tail
+// only costs its launch (n = 300, 62 us a call against 59).
+constexpr int FIX_HEAD = 64, FIX_TAIL = 448, FIX_SMALL = 256;
+constexpr int64_t FIX_RESIDENT = 1024;  // 256 CUs, 4 blocks each
+constexpr int FIX_BATCH = 512;
+enum { VEC_BATCH, VEC_ALIGNED, VEC_SHIFTED };
+template <int KIND>
+__global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix, int ntail) {
+  if (blockIdx.x < (unsigned)nfix || blockIdx.x >= gridDim.x - ntail)
     fix_items(A);
-  else if (v.sweep)
-    vec_sweep(v, __builtin_amdgcn_readfirstlane((int)((blockIdx.x - nfix) * (VEC_T / WAVE) + threadIdx.x / WAVE)),
-              v.sweep);
+  else if (KIND == VEC_BATCH)
+    vec_block(blockIdx.x - nfix, v);
   else
-    vec_block<CB>(blockIdx.x - nfix, v);
+    vec_tile<KIND == VEC_SHIFTED>(v, blockIdx.x - nfix);
 }
 
 // ------------------------------------------------------- K_nu, remedies
@@ -2972,7 +2997,7 @@ static int64_t count_groups(int64_t nprob, const int64_t* offs, int cb) {
   return c;
 }
 static int batch_columns(int64_t nprob, const int64_t* offs) {
-  int cb = VEC_C_BATCH;
+  int cb = VEC_C;
   while (cb > 4 && count_groups(nprob, offs, cb) < VEC_BLOCKS) cb /= 2;
   return cb;
 }
@@ -3150,15 +3175,13 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   va.V = V;
   va.voffs = voffs;
   va.ldv = ldv;
-  const int64_t rtiles = (N + VEC_ROWS - 1) / VEC_ROWS;
-  va.cb = VEC_C_SINGLE;
-  while (va.cb > 4 && (N + va.cb - 1) / va.cb * rtiles < VEC_BLOCKS) va.cb /= 2;
   va.cbase = 0;
   va.cend = (int32_t)N;
   va.prio = 0;
-  // one problem whose columns all start 16-byte aligned: the address-ordered writer
-  va.sweep = (V && !persistent_grid && ((uintptr_t)V & 15) == 0 && (ldv & 1) == 0) ? (int32_t)sweep_waves(N) : 0;
-  const unsigned sweep_blocks = (unsigned)((va.sweep + VEC_T / WAVE - 1) / (VEC_T / WAVE));
+  va.n = (int32_t)N;
+  va.neg = rho_dev ? -1 : rho_host < 0;
+  // one problem: some column starts off a 128-byte line
+  const bool shift = ((uintptr_t)V & (8 * LINE - 1)) != 0 || ldv % LINE != 0;
   auto launch_eig = [&](unsigned grid, int g0, int occ) {
     A.g0 = g0;
     switch (occ) {
@@ -3178,16 +3201,15 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
                          dim3(FIXT), 0, st, A);
   };
   auto launch_vec = [&](int64_t cb, int64_t ce, hipStream_t s2, bool prio) {
-    const int64_t cg = (ce - cb + va.cb - 1) / va.cb;
-    const int64_t rt = (N + VEC_ROWS - 1) / VEC_ROWS;
     VArgs vb = va;
-    vb.groups = nullptr;
-    vb.ncolgroups = cg;
     vb.cbase = (int32_t)cb;
     vb.cend = (int32_t)ce;
     vb.prio = prio ? 1 : 0;
-    hipLaunchKernelGGL((k_vec<VEC_C_SINGLE>), dim3(vb.sweep ? sweep_blocks : (unsigned)(cg * rt)), dim3(VEC_T), 0, s2,
-                       vb);
+    const dim3 grid((unsigned)tile_blocks(N, ce - cb));
+    if (shift)
+      hipLaunchKernelGGL(k_vec<true>, grid, dim3(VEC_T), VEC_PAD, s2, vb);
+    else
+      hipLaunchKernelGGL(k_vec<false>, grid, dim3(VEC_T), VEC_PAD, s2, vb);
   };
 
   // A single problem with eigenvectors and opts.vwrite = K >= 2: the
@@ -3250,19 +3272,19 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
   if (V) {
     // k_fix overlapped with the eigenvector writer: a few blocks take the
     // flagged eigenpairs, the rest write every other column
-    const int nfix = persistent_grid ? 512 : 256;
     if (persistent_grid) {
       va.groups = (const int4*)(w + L.groups);
-      va.ncolgroups = ngroups;
-      hipLaunchKernelGGL((k_fixvec<VEC_C_BATCH>), dim3((unsigned)(nfix + ngroups)), dim3(VEC_T), 0, st, A, va, nfix);
+      hipLaunchKernelGGL(k_fixvec<VEC_BATCH>, dim3((unsigned)(FIX_BATCH + ngroups)), dim3(VEC_T), 0, st, A, va,
+                         FIX_BATCH, 0);
     } else {
-      const int64_t cg = (N + va.cb - 1) / va.cb;
-      const int64_t rt = (N + VEC_ROWS - 1) / VEC_ROWS;
-      va.groups = nullptr;
-      va.ncolgroups = cg;
-      hipLaunchKernelGGL((k_fixvec<VEC_C_SINGLE>), dim3(nfix + (va.sweep ? sweep_blocks : (unsigned)(cg * rt))),
-                         dim3(VEC_T), 0, st, A, va,
-                         nfix);
+      const int64_t tiles = tile_blocks(N, N);
+      const bool many = tiles > FIX_RESIDENT;
+      const int nfix = many ? FIX_HEAD : FIX_SMALL, ntail = many ? FIX_TAIL : 0;
+      const dim3 grid((unsigned)(nfix + tiles + ntail));
+      if (shift)
+        hipLaunchKernelGGL(k_fixvec<VEC_SHIFTED>, grid, dim3(VEC_T), 0, st, A, va, nfix, ntail);
+      else
+        hipLaunchKernelGGL(k_fixvec<VEC_ALIGNED>, grid, dim3(VEC_T), 0, st, A, va, nfix, ntail);
     }
   } else {
     unsigned fgrid = (unsigned)std::min<int64_t>(std::max<int64_t>(N, 1), 2048);
@@ -3333,7 +3355,7 @@ size_t dpr1_batched_workspace_size(int64_t nprob, const int64_t* offs_host) {
   for (int64_t p = 0; p < nprob; ++p)
     if (offs_host[p + 1] - offs_host[p] < 1) return 0;
   int64_t ntotal = offs_host[nprob];
-  return batch_bytes(layout_batch(nprob, ntotal, count_groups(nprob, offs_host, VEC_C_BATCH)),
+  return batch_bytes(layout_batch(nprob, ntotal, count_groups(nprob, offs_host, VEC_C)),
                      count_wide(nprob, offs_host));
 }
 
@@ -3352,7 +3374,7 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   }
   int64_t N = offs_host[nprob];
   if (N > (int64_t)INT32_MAX) return -2;
-  const Layout L0 = layout_batch(nprob, N, count_groups(nprob, offs_host, VEC_C_BATCH));
+  const Layout L0 = layout_batch(nprob, N, count_groups(nprob, offs_host, VEC_C));
   const int64_t nwide = count_wide(nprob, offs_host);
   if (work_bytes < batch_bytes(L0, nwide)) return -6;
   dpr1_opts o;
