@@ -64,116 +64,102 @@ __device__ __forceinline__ double rcp_nr(double x) {
   return __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
 }
 
-__device__ __forceinline__ double lane_value(double x, int lane) {
-  const int64_t b = __double_as_longlong(x);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
-}
-
-// V in address order: wave g keeps rows 64 E (g % wpc) .. + 64 E - 1 in
-// registers, E consecutive ones a lane, and writes the groups of ASM_U
-// consecutive columns g / wpc, g / wpc + m, ... (m waves per row range), the
-// next group's column constants loaded while the current one is written.  The
-// whole GPU's write front then moves through V as a fill's does, in 16-byte
-// streaming stores.  Bound by HBM writes; n = 32768: 1533 us in tiles of 1024
-// rows with 8-byte stores, 1365 so (1597 with a branch per column).
-// An odd ldv puts every other column's stores across 16-byte boundaries, which
-// the hardware takes and which beats one row a lane (n = 4099: 288 us a call
-// against 299).  CPLX: V is complex (interleaved re, im; element (i, c) at 2 (i
-// + c ldv)), an element fills 16 bytes and row i is multiplied by the phase of
-// z_i.
-constexpr int ASM_T = 256, ASM_U = 8, ASM_WAVES = 2048;
+// A block writes ASM_T E rows of ASM_C columns in 16-byte streaming stores, E
+// rows a thread (a complex element fills 16 bytes), and ends; blocks go down
+// the columns first, in memory order, 5 to a CU (ASM_LDS bytes of LDS each,
+// more than they use), which holds the GPU's write front together as the eigenvector
+// writer's tiles do.  A column's windows are shifted back to whole 128-byte
+// lines, by up to LINE - 1 rows; the block keeps what it needs of the rows
+// that it may meet in LDS, and the last row range also writes the rows behind its window.
+// Bound by HBM writes.  A call, against 2048 waves that loop over columns: n =
+// 32768 1890 us (1925), 32767 1853 (2845), 16000 665 (711), 16001 706 (893),
+// complex n = 4099 281 (293).  8 columns 2 to 5 % slower, 12 and 16 more.
+// CPLX: V is complex (interleaved re, im; element (i, c) at 2 (i + c ldv)) and
+// row i is multiplied by the phase of z_i.
+constexpr int ASM_T = 256, ASM_C = 6;
+constexpr size_t ASM_LDS = 30 << 10;
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
-typedef dbl2 dbl2u __attribute__((aligned(8)));
 
 template <bool CPLX>
-__global__ void __launch_bounds__(ASM_T) k_assemble(AsmArgs a, int64_t wpc, int64_t m) {
-  constexpr int E = CPLX ? 1 : 2;
-  const int lane = threadIdx.x & 63;
-  const int64_t g = (int64_t)blockIdx.x * (ASM_T / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int64_t n = a.n, r = g % wpc, i0 = 64 * E * r + E * lane;
-  const int64_t ngrp = (n + ASM_U - 1) / ASM_U;
-  if (g >= wpc * m) return;
-  double di[E], zi[E], ui[E], pr[E], pm[E];
-  int gi[E], pi[E];
+__global__ void __launch_bounds__(ASM_T) k_assemble(AsmArgs a, int rtiles) {
+  constexpr int E = CPLX ? 1 : 2, ROWS = ASM_T * E, LINE = 16 / (CPLX ? 2 : 1), NB = ROWS + 2 * LINE;
+  __shared__ double ld_d[NB], ld_z[NB], ld_u[NB];
+  __shared__ int2 ld_g[NB];
+  __shared__ dbl2 ld_p[CPLX ? NB : 1];
+  const int t = threadIdx.x, r = (int)(blockIdx.x % rtiles);
+  const int64_t n = a.n, r0 = (int64_t)r * ROWS, c0 = (int64_t)(blockIdx.x / rtiles) * ASM_C;
+  double sg[ASM_C], mu[ASM_C], ic[ASM_C], ub[ASM_C];
+  int grp[ASM_C], ct[ASM_C];
 #pragma unroll
-  for (int j = 0; j < E; ++j) {
-    const int64_t i = i0 + j;
-    const bool ok = i < n;
-    if (CPLX) {
-      pr[j] = ok ? a.ph[2 * i] : 0.0;
-      pm[j] = ok ? a.ph[2 * i + 1] : 0.0;
-    }
-    di[j] = ok ? a.d[i] : 0.0;
-    zi[j] = ok ? a.z[i] : 0.0;
-    ui[j] = ok ? a.ru[i] : 0.0;
-    gi[j] = ok ? a.rgrp[i] : -1;
-    pi[j] = ok ? a.rpos[i] : -1;
+  for (int u = 0; u < ASM_C; ++u) {
+    const int64_t c = min(c0 + u, n - 1);
+    sg[u] = a.csig[c];
+    mu[u] = a.cmu[c];
+    ic[u] = a.cic[c];
+    ub[u] = a.cub[c];
+    grp[u] = a.cgrp[c];
+    ct[u] = a.ct[c];
   }
-  // a group's constants in one load across the wave: lane u + 8 f holds field f
-  // of column q ASM_U + u
-  auto load = [&](int64_t q) {
-    const int f = lane / ASM_U;
-    const int64_t c = min(q * ASM_U + (lane & (ASM_U - 1)), n - 1);
-    double x = 0.0;
-    if (f == 0) x = a.csig[c];
-    else if (f == 1) x = a.cmu[c];
-    else if (f == 2) x = a.cic[c];
-    else if (f == 3) x = a.cub[c];
-    else if (f == 4) x = a.cgrp[c];
-    else if (f == 5) x = a.ct[c];
-    return x;
-  };
-  auto store = [&](int64_t c, const double* v) {
+  for (int i = t; i < NB - 1; i += ASM_T) {
+    const int64_t at = r0 - (LINE - 1) + i;
+    const bool in = at >= 0 && at < n;
+    ld_d[i] = in ? a.d[at] : 0.0;
+    ld_z[i] = in ? a.z[at] : 0.0;
+    ld_u[i] = in ? a.ru[at] : 0.0;
+    ld_g[i] = in ? int2{a.rgrp[at], a.rpos[at]} : int2{-2, 0};
+    if (CPLX) ld_p[i] = in ? *(const dbl2*)(a.ph + 2 * at) : dbl2{0.0, 0.0};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < ASM_C; ++u) {
+    if (c0 + u >= n) break;
+    double* col = a.V + (CPLX ? 2 : 1) * (c0 + u) * a.ldv;
+    const int s = (int)(((uintptr_t)col / (CPLX ? 16 : 8)) & (LINE - 1));
+    auto value = [&](int i) {
+      // mu / den with one residual correction, then the scaled norm; a row
+      // with z_i == 0 (deflated, or a zero member of a merged group) is
+      // exactly 0 whatever den is
+      const double den = (ld_d[i] - sg[u]) - mu[u];
+      const double rc = rcp_nr(den), z = ld_z[i];
+      double w = ic[u] * rc;
+      w = __builtin_fma(__builtin_fma(-w, den, ic[u]), rc, w);
+      double v = z != 0.0 ? z * w : 0.0;
+      if (grp[u] >= 0) {
+        // column ct of H = I - beta u u^T restricted to the group
+        const int2 g = ld_g[i];
+        v = g.x == grp[u] ? (g.y == ct[u] ? 1.0 : 0.0) - ub[u] * ld_u[i] : 0.0;
+      }
+      return v;
+    };
+    auto put = [&](int i, int64_t at, double v) {  // one row, entry i of LDS
+      if (at < 0 || at >= n) return;
+      if (CPLX) {
+        const dbl2 cv = {v * ld_p[i].x, v * ld_p[i].y};
+        __builtin_nontemporal_store(cv, (dbl2*)(col + 2 * at));
+      } else {
+        __builtin_nontemporal_store(v, col + at);
+      }
+    };
+    const int i = LINE - 1 - s + E * t;
+    const int64_t at = r0 - s + E * t;
+    const double v0 = value(i);
     if (CPLX) {
-      if (i0 < n) {
-        const dbl2 cv = {v[0] * pr[0], v[0] * pm[0]};
-        __builtin_nontemporal_store(cv, (dbl2*)(a.V + 2 * (c * a.ldv + i0)));
-      }
-    } else if (E == 2 && i0 + 1 < n) {
-      const dbl2 cv = {v[0], v[E - 1]};
-      __builtin_nontemporal_store(cv, (dbl2u*)(a.V + c * a.ldv + i0));
-    } else if (i0 < n) {
-      __builtin_nontemporal_store(v[0], a.V + c * a.ldv + i0);
-    }
-  };
-  double cur = g / wpc < ngrp ? load(g / wpc) : 0.0;
-  for (int64_t q = g / wpc; q < ngrp; q += m) {
-    const double nxt = q + m < ngrp ? load(q + m) : 0.0;
-    // every column's quotient first, then the few columns that are none: a
-    // branch per column around the quotients would keep them from overlapping
-    double v[ASM_U][E];
-#pragma unroll
-    for (int u = 0; u < ASM_U; ++u) {
-      const double sg = lane_value(cur, u), mu = lane_value(cur, ASM_U + u), ic = lane_value(cur, 2 * ASM_U + u);
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        // mu / den with one residual correction, then the scaled norm; a row
-        // with z_i == 0 (deflated, or a zero member of a merged group) is
-        // exactly 0 whatever den is
-        const double den = (di[j] - sg) - mu;
-        const double rc = rcp_nr(den);
-        double w = ic * rc;
-        w = __builtin_fma(__builtin_fma(-w, den, ic), rc, w);
-        v[u][j] = zi[j] != 0.0 ? zi[j] * w : 0.0;
+      put(i, at, v0);
+    } else {
+      const double v1 = value(i + 1);
+      const dbl2 v = {v0, v1};
+      if (at >= 0 && at + 1 < n) {
+        __builtin_nontemporal_store(v, (dbl2*)(col + at));
+      } else {
+        put(i, at, v0);
+        put(i + 1, at + 1, v1);
       }
     }
-#pragma unroll
-    for (int u = 0; u < ASM_U; ++u) {
-      const int h = (int)lane_value(cur, 4 * ASM_U + u);
-      if (h < 0) continue;
-      // column t of H = I - beta u u^T restricted to the group h
-      const int t = (int)lane_value(cur, 5 * ASM_U + u);
-      const double ub = lane_value(cur, 3 * ASM_U + u);
-#pragma unroll
-      for (int j = 0; j < E; ++j) v[u][j] = gi[j] == h ? (pi[j] == t ? 1.0 : 0.0) - ub * ui[j] : 0.0;
+    if (r == rtiles - 1 && t < LINE) {
+      const int q = LINE - 1 - s + ROWS + t;
+      put(q, r0 + ROWS - s + t, value(q));
     }
-#pragma unroll
-    for (int u = 0; u < ASM_U; ++u)
-      if (q * ASM_U + u < n) store(q * ASM_U + u, v[u]);
-    cur = nxt;
   }
 }
 
@@ -671,11 +657,10 @@ static int front_end(const double* d, const double* z, double rho, int64_t n, do
     a.cic = f64(L.cic);
     a.cub = f64(L.cub);
     a.V = V;
-    const int64_t span = CPLX ? 64 : 128;  // rows of a wave
-    const int64_t wpc = (n + span - 1) / span;
-    const int64_t per = std::min<int64_t>(std::max<int64_t>(1, ASM_WAVES / wpc), (n + ASM_U - 1) / ASM_U);
-    const dim3 grid((unsigned)((wpc * per + ASM_T / 64 - 1) / (ASM_T / 64)));
-    hipLaunchKernelGGL(k_assemble<CPLX>, grid, dim3(ASM_T), 0, st, a, wpc, per);
+    const int64_t span = CPLX ? ASM_T : 2 * ASM_T;  // rows of a block
+    const int64_t rtiles = (n + span - 1) / span, ctiles = (n + ASM_C - 1) / ASM_C;
+    hipLaunchKernelGGL(k_assemble<CPLX>, dim3((unsigned)(rtiles * ctiles)), dim3(ASM_T),
+                       ASM_LDS - (CPLX ? 48 * 272 : 32 * 544), st, a, (int)rtiles);
     GCHECK(hipGetLastError());
   }
   GCHECK(hipStreamSynchronize(st));
