@@ -2317,6 +2317,11 @@ constexpr int VEC_ROWS = 2048;
 // columns per block: 32 (64 measured 4-7 % slower on the 2048-problem mix and
 // on 4 problems of n = 16384, 16 no faster)
 constexpr int VEC_C = 32;
+// Fewer, VEC_C_MIN at least, where they would be more than VEC_ELEMS elements,
+// and in memory order, for the same reason as the tiles below: 300 problems of
+// n = 700 .. 800 647 us a call (686 in 32 columns, largest problems first), 64
+// of n = 1000 293 (311); twice the elements 670 and 306, half 696 and 300.
+constexpr int VEC_C_MIN = 4, VEC_ELEMS = 8192;
 // Where blocks of that many columns leave the GPU idle their width is halved,
 // to 4 at least, until VEC_BLOCKS run (a problem of n = 1501: 47 blocks of 32
 // columns took 54 us for 18 MB).
@@ -2376,7 +2381,9 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
     linv[threadIdx.x] = v.cinv[a];
     lskip[threadIdx.x] = v.vflag ? v.vflag[a] : 0;
   }
-  __syncthreads();
+  const bool skipping = __syncthreads_or(threadIdx.x < nc && v.vflag && v.vflag[M.off + c0 + threadIdx.x]);
+  typedef double vdbl2 __attribute__((ext_vector_type(2)));
+  constexpr int WE = 2 * WAVE;
   const int64_t ld = n, base = v.voffs[p];
   const int wv = wave_id(), lane = threadIdx.x % WAVE;
   constexpr int NW = VEC_T / WAVE;
@@ -2388,6 +2395,56 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
     const int64_t kolo = M.neg ? (int64_t)n - c0 - nc : c0;
     const int64_t S = base + kolo * n;
     const int len = nc * n;
+    if (n >= WE) {
+      // windows of 128 elements aligned to 1 KB, two elements per lane in one
+      // 16-byte store; a window meets two columns at most, and the wave keeps
+      // the column and position of its first element
+      const int skew = (int)(((uintptr_t)(V + S) >> 3) & (WE - 1));
+      int l0 = wv * WE - skew, q = l0 > 0 ? l0 / n : 0, pos0 = l0 - q * n;
+      const int dq = NW * WE / n, dr = NW * WE - dq * n;
+      auto value = [&](int x, bool& ok) {  // element x of the window's column or of the next
+        int c = q;
+        ok = l0 + x >= 0 && l0 + x < len;
+        int pos = pos0 + x;
+        if (pos >= n) {
+          pos -= n;
+          ++c;
+        }
+        pos = max(pos, 0);
+        c = min(c, nc - 1);
+        if (M.neg) c = nc - 1 - c;
+        if (skipping) ok = ok && !lskip[c];
+        const double w = linv[c];
+        const double den = (ld_d[pos] - lsig[c]) - lmu[c];
+        const double rc = rcp_1nr(den);
+        double qq = w * rc;
+        qq = __builtin_fma(__builtin_fma(-qq, den, w), rc, qq);  // corrected quotient
+        return ld_z[pos] * qq;
+      };
+      for (; l0 < len; l0 += NW * WE) {
+        bool a0, a1;
+        const double v0 = value(2 * lane, a0), v1 = value(2 * lane + 1, a1);
+        double* vp = V + S + l0 + 2 * lane;
+        if (a0 && a1) {
+          const vdbl2 vv = {v0, v1};
+          __builtin_nontemporal_store(vv, reinterpret_cast<vdbl2*>(vp));
+        } else if (a0) {
+          __builtin_nontemporal_store(v0, vp);
+        } else if (a1) {
+          __builtin_nontemporal_store(v1, vp + 1);
+        }
+        q += dq;
+        pos0 += dr;
+        if (pos0 >= n) {
+          pos0 -= n;
+          ++q;
+        } else if (pos0 < 0) {  // the first window started before the range
+          pos0 += n;
+          --q;
+        }
+      }
+      return;
+    }
     const int64_t Sal = S & ~(int64_t)(WAVE - 1);
     const int nwin = (int)((S + len - Sal + WAVE - 1) / WAVE);
     const float inv_n = 1.0f / (float)n;
@@ -2423,8 +2480,6 @@ __device__ void vec_block(unsigned bid, const VArgs& v) {
   // lane in one 16-byte store (the column's address set up once, then a plain
   // loop; a window's lane with only one element in the segment stores it
   // alone).
-  typedef double vdbl2 __attribute__((ext_vector_type(2)));
-  constexpr int WE = 2 * WAVE;
   for (int c = wv; c < nc; c += NW) {
     if (lskip[c]) continue;
     const int k = c0 + c;
@@ -2596,7 +2651,12 @@ __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
 // only costs its launch (n = 300, 62 us a call against 59).
 constexpr int FIX_HEAD = 64, FIX_TAIL = 448, FIX_SMALL = 256;
 constexpr int64_t FIX_RESIDENT = 1024;  // 256 CUs, 4 blocks each
-constexpr int FIX_BATCH = 512;
+// A batch of mean order BATCH_FEW or more: 300 problems of n = 700 .. 800 625 us
+// with BATCH_HEAD and BATCH_TAIL against 647 with 512 in front, 1024 of n = 16 ..
+// 2048 1394 against 1419; smaller ones have more flagged eigenpairs for the
+// elements they write (1000 of n = 130 .. 300 388 against 348).
+constexpr int FIX_BATCH = 512, BATCH_HEAD = 128, BATCH_TAIL = 384;
+constexpr int64_t BATCH_FEW = 320;
 enum { VEC_BATCH, VEC_ALIGNED, VEC_SHIFTED };
 template <int KIND>
 __global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix, int ntail) {
@@ -2988,11 +3048,16 @@ static double occ_margin(int oc) { return oc > 4 ? 0.96 : 1.0; }
 
 // Number of (problem, column group, row tile) blocks of the batched
 // eigenvector launch with cb columns each, and its columns per block.
+static int group_columns(int64_t np, int cb) {
+  while (cb > VEC_C_MIN && cb * std::min<int64_t>(np, VEC_ROWS) > VEC_ELEMS) cb /= 2;
+  return cb;
+}
 static int64_t count_groups(int64_t nprob, const int64_t* offs, int cb) {
   int64_t c = 0;
   for (int64_t p = 0; p < nprob; ++p) {
     const int64_t np = offs[p + 1] - offs[p];
-    c += ((np + cb - 1) / cb) * ((np + VEC_ROWS - 1) / VEC_ROWS);
+    const int g = group_columns(np, cb);
+    c += ((np + g - 1) / g) * ((np + VEC_ROWS - 1) / VEC_ROWS);
   }
   return c;
 }
@@ -3274,8 +3339,10 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     // flagged eigenpairs, the rest write every other column
     if (persistent_grid) {
       va.groups = (const int4*)(w + L.groups);
-      hipLaunchKernelGGL(k_fixvec<VEC_BATCH>, dim3((unsigned)(FIX_BATCH + ngroups)), dim3(VEC_T), 0, st, A, va,
-                         FIX_BATCH, 0);
+      const bool few = N >= BATCH_FEW * nprob;
+      const int nfix = few ? BATCH_HEAD : FIX_BATCH, ntail = few ? BATCH_TAIL : 0;
+      hipLaunchKernelGGL(k_fixvec<VEC_BATCH>, dim3((unsigned)(nfix + ngroups + ntail)), dim3(VEC_T), 0, st, A, va,
+                         nfix, ntail);
     } else {
       const int64_t tiles = tile_blocks(N, N);
       const bool many = tiles > FIX_RESIDENT;
@@ -3406,14 +3473,16 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   int64_t nitems = (int64_t)items.size();
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax);
   // blocks of the eigenvector kernel: (problem, first column, columns,
-  // first row), largest problems first
+  // first row), in memory order
   std::vector<int4> groups;
   const int cb = batch_columns(nprob, offs_host);
-  for (int32_t p : order) {
+  groups.reserve(count_groups(nprob, offs_host, cb));
+  for (int32_t p = 0; p < nprob; ++p) {
     const int64_t np = offs_host[p + 1] - offs_host[p];
-    for (int64_t c0 = 0; c0 < np; c0 += cb)
+    const int g = group_columns(np, cb);
+    for (int64_t c0 = 0; c0 < np; c0 += g)
       for (int64_t r0 = 0; r0 < np; r0 += VEC_ROWS)
-        groups.push_back(make_int4(p, (int)c0, (int)std::min<int64_t>(cb, np - c0), (int)r0));
+        groups.push_back(make_int4(p, (int)c0, (int)std::min<int64_t>(g, np - c0), (int)r0));
   }
   hipStream_t st = (hipStream_t)stream;
   HIPCHECK(hipMemcpyAsync((char*)work + L0.items, items.data(), sizeof(int4) * nitems, hipMemcpyHostToDevice, st));

@@ -73,3 +73,28 @@ def test_written_in_chunks(D, rho):
     ref = solve(D, d, z, rho, 8208, 0)[0]
     for ldv, shift, chunks in [(8208, 0, 3), (8197, 0, 3), (8198, 5, 8)]:
         assert np.array_equal(solve(D, d, z, rho, ldv, shift, chunks)[0], ref), (ldv, shift, chunks)
+
+
+@pytest.mark.parametrize("mean", ["small", "large"])
+def test_batch_blocks(D, mean):
+    """A batch's blocks: columns per block and windows at the orders where either changes, on both
+    sides of the rule for the blocks that finish flagged eigenpairs."""
+    import torch
+    sizes = [1, 2, 31, 32, 33, 126, 127, 128, 129, 255, 256, 257, 511, 512, 513]
+    if mean == "large":
+        sizes += [1023, 1025, 2047, 2048, 2049, 2300]
+    print(f"[tiles] batch {mean}", flush=True)
+    offs = np.concatenate([[0], np.cumsum(sizes)])
+    data = [W.uniform(n, 50 + n) for n in sizes]
+    d, z = (np.concatenate([x[i] for x in data]) for i in range(2))
+    rho = np.array([0.75 if i % 2 else -1.5 for i in range(len(sizes))])
+    b = D.Batch(offs, vectors=True)
+    r = b.solve(*(torch.tensor(x, dtype=torch.float64, device="cuda") for x in (d, z, rho)))
+    torch.cuda.synchronize()
+    idx, mu, xn = (x.cpu().numpy() for x in (r.shift_idx, r.mu, r.xnorm))
+    for p, n in enumerate(sizes):
+        s = slice(offs[p], offs[p + 1])
+        V = b.vblock(p).cpu().numpy()
+        dp, zp = d[s], z[s]
+        want = zp[:, None] / (((dp[:, None] - dp[idx[s]][None, :]) - mu[s][None, :]) * xn[s][None, :])
+        assert np.max(np.abs(V - want) / np.abs(want)) <= 4 * np.finfo(float).eps, n
