@@ -23,27 +23,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-FP64_PEAK_TFLOPS = 78.6   # MI355X FP64 vector (and matrix) peak
 HBM_PEAK_GBS = 8000.0
-
-# Algorithmic FP64 flops per (eigenvalue k, inner index j) pair, counted as the
-# peak counts them: a fused multiply-add is 2, an add, multiply or division 1
-# (the Newton refinement of the hardware reciprocal is not counted).
-FLOPS_SHIFT = 10          # (d_j - d_k) - tau (2), 1/den, t, t/den, 3 adds, fma for t/den^2 (2)
-FLOPS_TIP = 19            # TwoSum d_j - sigma (6), 1/dl, quotient + residual (7), compensated add (5)
-FLOPS_ROOT_MODEL = 14     # per pass: delta' (2), nu delta' - 1 (2), q, 1/q, t, 1/pp (2), tp, tp3, 3 adds
-FLOPS_ROOT_BISECT = 7     # per pass: delta' (2), nu delta' - 1 (2), q, 1/q, add
-FLOPS_FINAL = 20.375      # accurate last pass: delta', pp (4), q, 1/q, t, corrected quotient (4),
-                          # 1/pp (2), tp, tp3, tp4, 3 adds, and the sum of t: a tree over blocks
-                          # of eight (7/8) feeding a Neumaier sum (4/8)
-
-
-def flops_per_pair(root, passes_mean):
-    """Algorithmic flops per (k, j) pair done by the eigenvalue kernel (k_eig): the shift pass,
-    the tip, `passes_mean` plain root-finder passes and the accurate last pass (which also gives
-    ||x||)."""
-    per = FLOPS_ROOT_MODEL if root == 1 else FLOPS_ROOT_BISECT
-    return FLOPS_SHIFT + FLOPS_TIP + per * passes_mean + FLOPS_FINAL
 
 
 def log(msg):
@@ -136,7 +116,7 @@ def main():
     value = n / (ms_step / 1e3)
     # The same solves with the eigenvector write after the eigenvalue kernel (opts.vwrite = 1, the default),
     # timed with the library's events on the launch stream: the eigenvalue kernel is then one
-    # launch (the roofline's duration) and the second phase (k_fixvec + k_fixout) writes V alone.
+    # launch and the second phase (k_fixvec, the roofline's) writes V alone.
     seq = D.opts(root=args.root, split=base.split, main_passes=base.main_passes,
                  waves_per_simd=base.waves_per_simd, vwrite=1)
     step(seq)
@@ -150,28 +130,10 @@ def main():
     eig_ms = float(np.mean([e.eig_ms() for e in ev]))
     vec_ms = float(np.mean([e.vec_ms() for e in ev]))
     iters_mean = st["iters_sum"] / n
-    fpp = flops_per_pair(args.root, iters_mean)
-    achieved = fpp * n * n / (eig_ms / 1e3) / 1e12
     vec_gbs = n * n * 8 / (vec_ms / 1e3) / 1e9
     log(f"[bench] {ms_step:.3f} ms/step ({value:.4g} eigenpairs/s); with the write after the eigenvalue kernel "
-        f"{ms_seq:.3f} ms/step: k_eig {eig_ms:.3f} ms, k_fixvec+k_fixout {vec_ms:.3f} ms ({vec_gbs:.0f} GB/s); "
+        f"{ms_seq:.3f} ms/step: k_eig {eig_ms:.3f} ms, k_fixvec {vec_ms:.3f} ms ({vec_gbs:.0f} GB/s); "
         f"iters/eig {iters_mean:.2f}, stats {st}")
-
-    # HBM bytes of one k_eig launch from the FETCH_SIZE / WRITE_SIZE counters,
-    # scaled by the copy-kernel calibration; used only while the kernel
-    # sources are the ones the counters were taken on
-    # per launch shape (split, waves per SIMD, pass budget): the register
-    # budget changes what stays in registers and so the bytes moved
-    traffic = None
-    shape = f"{int(base.split)},{int(base.waves_per_simd) or 4},{int(base.main_passes) or 2}"
-    tf = os.path.join(ROOT, "profiles", f"k_eig_n{n}_traffic.txt")
-    if os.path.exists(tf):
-        try:
-            tj = json.load(open(tf))
-            if tj.get("source_sha") == source_sha() and tj.get("n") == n:
-                traffic = tj.get("shapes", {}).get(shape, {}).get("k_eig_bytes")
-        except Exception:
-            traffic = None
 
     result = {
         "metric": "eigenpairs/s FP64 at n=32768 + batched mix; fwd+bwd/s; % FP64 peak",
@@ -189,10 +151,11 @@ def main():
         "config": {"workload": f"single DPR1 n={n}, all eigenvalues + full V (FP64), d~U[-1,1] sorted, "
                                f"z~N(0,1)/sqrt(n), rho=1, seed 2",
                    "n": n, "root": "model" if args.root == 1 else "bisection", "tuning": tune},
-        "roofline": {"bound": "alu", "kernel": "k_eig", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS, "traffic": traffic,
-                     "flops_per_pair": fpp, "kernel_ms": eig_ms},
-        "v_write": {"kernel": "k_fixvec+k_fixout (V written after the eigenvalue kernel, k_fix's work beside it)",
+        # the step's longest kernel; its bytes are V's, written once and never read
+        "roofline": {"bound": "hbm", "kernel": "k_fixvec", "achieved": vec_gbs, "peak": HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": vec_gbs / HBM_PEAK_GBS, "traffic": n * n * 8, "kernel_ms": vec_ms,
+                     "k_eig_ms": eig_ms},
+        "v_write": {"kernel": "k_fixvec (V written after the eigenvalue kernel, k_fix's work beside it)",
                     "ms": vec_ms, "GB/s": vec_gbs, "frac_hbm": vec_gbs / HBM_PEAK_GBS,
                     "ms_per_step_sequential": ms_seq,
                     "note": ("value is timed with the tuned write: " + (
@@ -282,16 +245,6 @@ def copy_calibration(nbytes=1 << 30, reps=3):
     ms = (time.perf_counter() - t0) * 1e3 / reps
     print(json.dumps({"mode": "copy", "bytes_read": nbytes, "bytes_written": nbytes, "reps": reps,
                       "ms": ms, "GB/s": 2 * nbytes / (ms / 1e3) / 1e9}), flush=True)
-
-
-def source_sha():
-    """Hash of the sources k_eig is compiled from (its file, the double-double header, the ABI
-    header): the stored traffic record is used only while these are unchanged."""
-    import hashlib
-    h = hashlib.sha256()
-    for f in ("paper_1405_7537_amd/csrc/dpr1_kernels.hip", "paper_1405_7537_amd/csrc/dd.h", "include/dpr1.h"):
-        h.update(open(os.path.join(ROOT, f), "rb").read())
-    return h.hexdigest()[:16]
 
 
 def tuned(D, args, d, z, rho, vectors):

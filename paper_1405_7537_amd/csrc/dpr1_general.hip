@@ -21,9 +21,7 @@
 // components are those of eq. (eigenvecAi) evaluated on the original d and z,
 //   v_k[i] = z_i / (((d_i - sigma_k) - mu_k) ||x_k||),
 // because a member i of a merged group has d_i = the group's pole and carries
-// z_i = (w_i / ||w||) ||w||, and a deflated row has z_i = 0.  So each thread
-// keeps (d_i, z_i) of its row in registers and writes whole column segments
-// (coalesced, streaming stores), HBM-bound like the eigenvector writer.
+// z_i = (w_i / ||w||) ||w||, and a deflated row has z_i = 0.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -594,8 +594,8 @@ __device__ __forceinline__ void model_step(double m, double g, double Spz, doubl
 // directly), the block's level, the wide level.  The windows come from the
 // poles' positions alone, so any distribution is covered: where poles cluster
 // so that nothing is far, the window is the whole problem.  Bound by FP64
-// issue; measured at n = 32768 (uniform poles): k_far 72 us and k_eig 212 us
-// where the direct sums took 2520 us; the 2048-problem mix 383 and 1840 us
+// issue; measured at n = 32768 (uniform poles): k_far 72 us and k_eig 130 us
+// where the direct sums took 2520 us; the 2048-problem mix 390 and 740 us
 // against 3560 us.  Errors of lambda, mu, ||x|| and V against an extended-
 // precision root are those of the direct sums (rms over 26 distributions: mu
 // 1.3e-16 both, ||x|| 1.3e-16 against 1.7e-16).
@@ -2303,10 +2303,10 @@ __global__ void __launch_bounds__(FIXT, 4) k_fix(KArgs A) { fix_items(A); }
 
 // ------------------------------------------------------------------- vec
 // v_j = zeta_j w/(delta_j - mu), w = 1/||x|| (eq. eigenvecAi).  A block owns up
-// to CB columns of one problem over up to ROWS consecutive positions of each
-// column.  The (d_j, zeta_j) of those positions are staged in LDS once; each
-// wave then writes 64-element windows aligned to 512 bytes of V, so every
-// store instruction covers whole cache lines whatever the column's offset
+// to VEC_C columns of one problem over up to VEC_ROWS consecutive positions of
+// each column.  The (d_j, zeta_j) of those positions are staged in LDS once; each
+// wave then writes 128-element windows aligned to 1 KB of V (64 elements where
+// columns are shorter), so every store covers whole lines at any column offset
 // (a packed ragged batch puts most columns at odd offsets; misaligned
 // non-temporal stores write partial lines and halve the write bandwidth).
 // Only the first and last window of a column segment are partial.  The block
@@ -2314,8 +2314,7 @@ __global__ void __launch_bounds__(FIXT, 4) k_fix(KArgs A) { fix_items(A); }
 // plan.
 constexpr int VEC_T = 256;
 constexpr int VEC_ROWS = 2048;
-// columns per block: 32 (64 measured 4-7 % slower on the 2048-problem mix and
-// on 4 problems of n = 16384, 16 no faster)
+// most columns per block
 constexpr int VEC_C = 32;
 // Fewer, VEC_C_MIN at least, where they would be more than VEC_ELEMS elements,
 // and in memory order, for the same reason as the tiles below: 300 problems of

@@ -1,8 +1,9 @@
 // Host side of the reduction of Sec. 1 for one DPR1 problem: sort the poles
 // decreasingly, deflate a pole whose z_j is zero, merge each group of equal
 // poles by one Householder reflection (the reduced problem keeps the pole
-// once, with z = ||w||).  Used by the front end (dpr1_general.hip) and by the
-// divide-and-conquer driver (dpr1_tridiag.hip), one problem at a time.
+// once, with z = ||w||).  Used by the divide-and-conquer driver
+// (dpr1_tridiag.hip), one merge at a time; the front end does the same on the
+// GPU for one large problem.
 #pragma once
 
 #include <stdint.h>

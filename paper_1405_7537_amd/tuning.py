@@ -18,7 +18,7 @@ import tempfile
 
 import numpy as np
 
-VERSION = 4
+VERSION = 5
 
 
 def cache_path() -> str:
