@@ -12,14 +12,15 @@
 // goes down to leaves of at most 32 rows, which one kernel solves by Jacobi
 // rotations; all merges of one depth are done together:
 //   1. z of every merge: the row of a leaf's Q comes from that kernel; the row
-//      of a merged child's Q was formed by k_zrows when that child was merged, straight from its
-//      children's Q and its V, so it is on the host before that child's
-//      product (step 5) has finished;
+//      of a merged child's Q was formed by k_zrows when that child was merged,
+//      straight from its children's Q and its V, so it is on the host before
+//      that child's product (step 5) has finished;
 //   2. the host reduces each merge as in Sec. 1 (unsorted poles, equal poles,
 //      zero z_j: reduce.h), a z_j below 2^-300 max|z| counting as zero and
 //      poles within 8 eps max|d| merged like equal ones;
 //   3. one batched launch of the DPR1 solver (dpr1_eig_batched, eigenvalues
-//      and the shifted representation only) solves all reduced problems;
+//      and the shifted representation only) solves all reduced problems, and
+//      k_tri_columns orders their eigenvalues among the deflated ones;
 //   4. k_tri_assemble writes every merge's V (eq. (eigenvecAi) on the merge's
 //      own poles and z, unit and reflection columns);
 //   5. k_dgemm forms diag(Q1, Q2) V for every merge into the other Q buffer
@@ -436,6 +437,68 @@ __global__ void __launch_bounds__(TA_T) k_tri_assemble(const ANode* __restrict__
   }
 }
 
+// The columns of every merge of a depth and the new eigenvalues (block (x, p):
+// 256 columns of merge p): the eigenvalues of the reduced problem and the
+// columns of the reduction, both decreasing, the latter first among equal
+// values, so a column's place is its own index plus its rank in the other list.
+// On the solver's stream right behind the solve, so that the assembly and the
+// product need not wait for the host (a call: n = 4096 3615 us with the order
+// and the tables made on the host, 3300 so; n = 8192 15.3 ms and 14.6); the host
+// only reads the eigenvalues, for the next depth's reductions.  Bound by latency
+// (about 12 dependent loads, 5 us).  After a range report the solver's outputs are unspecified:
+// every index is bounded whatever they hold.
+struct MTab {
+  int32_t start, size;
+  int32_t roff, rcnt;  // the reduced problem's offset and order
+  int32_t soff, pad;   // offset of the reduction's columns
+};
+struct CSrc {
+  double val, ub;
+  int32_t kind, idx, t, pad;
+};
+__global__ void __launch_bounds__(256) k_tri_columns(const MTab* tab, const CSrc* csrc, const double* rd,
+                                                     const double* lamr, const int32_t* sidx, const double* mu,
+                                                     const double* xn, double* lamn, int32_t* ckind, int32_t* cidx,
+                                                     int32_t* ct, double* csig, double* cmu, double* cic,
+                                                     double* cub) {
+  const MTab m = tab[blockIdx.y];
+  const int t = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (t >= m.size) return;
+  const bool red = t < m.rcnt;
+  const int own = red ? t : t - m.rcnt;
+  const CSrc* src = csrc + m.soff;
+  const double* lam = lamr + m.roff;
+  const double v = red ? lam[own] : src[own].val;
+  int lo = 0, hi = red ? m.size - m.rcnt : m.rcnt;  // entries of the other list that come first
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    const double x = red ? src[mid].val : lam[mid];
+    if (red ? x >= v : x > v)
+      lo = mid + 1;
+    else
+      hi = mid;
+  }
+  const int64_t c = (int64_t)m.start + own + lo;
+  lamn[c] = v;
+  CSrc e = {0.0, 0.0, COL_REDUCED, own, 0, 0};
+  double sg = 0.0, u = 0.0, ic = 0.0;
+  if (red) {
+    const int64_t k = (int64_t)m.roff + own;
+    sg = rd[m.roff + min(max(sidx[k], 0), m.rcnt - 1)];
+    u = mu[k];
+    ic = 1.0 / xn[k];
+  } else {
+    e = src[own];
+  }
+  ckind[c] = e.kind;
+  cidx[c] = e.idx;
+  ct[c] = e.t;
+  csig[c] = sg;
+  cmu[c] = u;
+  cic[c] = ic;
+  cub[c] = e.ub;
+}
+
 // C (M x N, ldc) = A (M x K, lda) B (K x N, ldb), column-major, FP64.
 struct GDesc {
   const double* A;
@@ -546,7 +609,7 @@ static size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct TLayout {
-  size_t Qw, Vw, rd, rz, lamr, mur, xnr, sidx, infop, rhop, offsp, zl, dl, rgrp, rpos, ru, ckind, cidx, ct,
+  size_t Qw, Vw, rd, rz, lamr, mur, xnr, sidx, lamn, infop, rhop, offsp, mtab, csrc, zl, dl, rgrp, rpos, ru, ckind, cidx, ct,
       csig, cmu, cic, cub, anodes, atab, gdesc, gtab, zit, solver, total;
   int64_t maxV, maxAsm, maxTiles, maxNodes, maxZ;
   size_t solver_bytes;
@@ -594,14 +657,12 @@ static TLayout tlayout(int64_t n, const std::vector<Node>& nodes, int maxd) {
   L.mur = o; o = al(o + 8 * n);
   L.xnr = o; o = al(o + 8 * n);
   L.sidx = o; o = al(o + 4 * n);
+  L.lamn = o; o = al(o + 8 * n);
   L.infop = o; o = al(o + 4 * P);
   L.rhop = o; o = al(o + 8 * P);
   L.offsp = o; o = al(o + 8 * (P + 1));
-  L.zl = o; o = al(o + 8 * n);
-  L.dl = o; o = al(o + 8 * n);
-  L.rgrp = o; o = al(o + 4 * n);
-  L.rpos = o; o = al(o + 4 * n);
-  L.ru = o; o = al(o + 8 * n);
+  L.mtab = o; o = al(o + sizeof(MTab) * P);
+  L.csrc = o; o = al(o + sizeof(CSrc) * n);
   L.ckind = o; o = al(o + 4 * n);
   L.cidx = o; o = al(o + 4 * n);
   L.ct = o; o = al(o + 4 * n);
@@ -609,6 +670,11 @@ static TLayout tlayout(int64_t n, const std::vector<Node>& nodes, int maxd) {
   L.cmu = o; o = al(o + 8 * n);
   L.cic = o; o = al(o + 8 * n);
   L.cub = o; o = al(o + 8 * n);
+  L.zl = o; o = al(o + 8 * n);
+  L.dl = o; o = al(o + 8 * n);
+  L.rgrp = o; o = al(o + 4 * n);
+  L.rpos = o; o = al(o + 4 * n);
+  L.ru = o; o = al(o + 8 * n);
   L.anodes = o; o = al(o + sizeof(ANode) * P);
   L.atab = o; o = al(o + sizeof(int4) * std::max<int64_t>(L.maxAsm, 1));
   L.gdesc = o; o = al(o + sizeof(GDesc) * 2 * P);
@@ -658,11 +724,12 @@ static hipStream_t tri_aux_stream() {
 // use are freed after this) and release the event.
 struct TriDone {
   hipStream_t st, st2;
-  hipEvent_t ev = nullptr;
+  hipEvent_t ev = nullptr, solved = nullptr;
   ~TriDone() {
     (void)hipStreamSynchronize(st2);
     (void)hipStreamSynchronize(st);
     if (ev) (void)hipEventDestroy(ev);
+    if (solved) (void)hipEventDestroy(solved);
   }
 };
 
@@ -755,28 +822,29 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
   // the copies that use it have finished (the event waited for at the start of
   // a depth follows the previous depth's copies on the caller's stream; the
   // second stream is synchronised after each depth's solves)
-  std::vector<int32_t> hgrp(n, 0), hpos(n, 0), hkind(n, 0), hidx(n, 0), hct(n, 0);
-  std::vector<double> hz(n), hzr(n, 0.0), hru(n, 0.0), hsig(n, 0.0), hmu(n, 0.0), hic(n, 0.0), hub(n, 0.0);
+  std::vector<int32_t> hgrp(n, 0), hpos(n, 0);
+  std::vector<double> hz(n), hzr(n, 0.0), hru(n, 0.0);
   std::vector<ZItem> zit;
-  std::vector<double> rd, rz, lamr, mur, xnr, rhop;
-  std::vector<int32_t> sidx, infop;
+  std::vector<double> rd, rz, rhop;
+  std::vector<MTab> mtab;
+  std::vector<CSrc> csrc;
   std::vector<int64_t> offs;
   std::vector<ANode> anodes;
   std::vector<int4> atab, gtab;
   std::vector<GDesc> gdesc;
-  std::vector<fe::Col> all;
   std::vector<int64_t> roff, rcnt;  // per merge: offset and size of its reduced problem
   std::vector<std::vector<fe::Col>> mcols;
-  std::vector<double> hnew(n), hpole(n), gval(n);
+  std::vector<double> hpole(n), gval(n);
   std::vector<char> seen(n);
   fe::Scratch scr;
   dpr1_plan plan;
   // host mirrors of contiguous workspace regions, so that each region moves
-  // in one copy per depth: the solver's inputs [rd, offsp], its outputs
-  // [lamr, infop], and the merges' z and poles with the assembly, GEMM and
+  // in one copy per depth: the solver's inputs with the merges' table and the
+  // reduction's columns [rd, csrc], the new eigenvalues and reports [lamn,
+  // infop], and the merges' z and poles with the assembly, GEMM and
   // z-row arrays [zl, zit]
   const int64_t P = std::max<int64_t>(L.maxNodes, 1);
-  std::vector<char> mirA(L.offsp + 8 * (P + 1) - L.rd), mirB(L.infop + 4 * P - L.lamr), mirC(L.solver - L.zl);
+  std::vector<char> mirA(L.csrc + sizeof(CSrc) * n - L.rd), mirB(L.infop + 4 * P - L.lamn), mirC(L.solver - L.zl);
   auto put = [](std::vector<char>& mir, size_t base, size_t off, const void* src, size_t bytes) {
     if (bytes) memcpy(mir.data() + (off - base), src, bytes);
   };
@@ -784,6 +852,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
   if (!st2) return DPR1_EHIP;
   TriDone fin{st, st2};
   TCHECK(hipEventCreateWithFlags(&fin.ev, hipEventDisableTiming));
+  TCHECK(hipEventCreateWithFlags(&fin.solved, hipEventDisableTiming));
   bool zpending = false;  // rows of this depth's z in flight to hzr (event fin.ev)
 
   for (int D = maxd; D >= 0; --D) {
@@ -873,44 +942,50 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     const int64_t nprob = (int64_t)rhop.size();
     const int64_t mtot = (int64_t)rd.size();
 
-    // 3. one batched solve of the reduced problems
-    lamr.resize(mtot);
-    mur.resize(mtot);
-    xnr.resize(mtot);
-    sidx.resize(mtot);
+    // 3. one batched solve of the reduced problems, and every merge's columns
+    mtab.clear();
+    csrc.clear();
+    int64_t smax = 0;
+    for (size_t p = 0; p < lv.size(); ++p) {
+      mtab.push_back({(int32_t)lv[p]->start, (int32_t)lv[p]->size, (int32_t)roff[p], (int32_t)rcnt[p],
+                      (int32_t)csrc.size(), 0});
+      for (const fe::Col& q : mcols[p]) csrc.push_back({q.val, q.ub, q.kind, q.idx, q.t, 0});
+      smax = std::max(smax, lv[p]->size);
+    }
+    double* drd = (double*)(w + L.rd);
+    double* dlr = (double*)(w + L.lamr);
+    double* dmu = (double*)(w + L.mur);
+    double* dxn = (double*)(w + L.xnr);
+    int32_t* dsi = (int32_t*)(w + L.sidx);
     if (nprob > 0) {
-      infop.assign(nprob, 0);
       const int prc = dpr1_batched_plan(nprob, offs.data(), opts, &plan, w + L.solver, L.solver_bytes, (void*)st2);
       if (prc != DPR1_OK) return prc == DPR1_EHIP ? DPR1_EHIP : -10;
-      double* drd = (double*)(w + L.rd);
-      double* drz = (double*)(w + L.rz);
-      double* dlr = (double*)(w + L.lamr);
-      double* dmu = (double*)(w + L.mur);
-      double* dxn = (double*)(w + L.xnr);
-      int32_t* dsi = (int32_t*)(w + L.sidx);
-      int32_t* dinf = (int32_t*)(w + L.infop);
-      double* drho = (double*)(w + L.rhop);
-      int64_t* doffs = (int64_t*)(w + L.offsp);
-      put(mirA, L.rd, L.rd, rd.data(), 8 * mtot);
-      put(mirA, L.rd, L.rz, rz.data(), 8 * mtot);
-      put(mirA, L.rd, L.rhop, rhop.data(), 8 * nprob);
-      put(mirA, L.rd, L.offsp, offs.data(), 8 * (nprob + 1));
-      TCHECK(hipMemcpyAsync(w + L.rd, mirA.data(), L.offsp + 8 * (nprob + 1) - L.rd, hipMemcpyHostToDevice, st2));
-      const int rc = dpr1_eig_batched(&plan, doffs, drd, drz, drho, dlr, nullptr, nullptr, dsi, dmu, dxn, dinf,
-                                      nullptr, w + L.solver, L.solver_bytes, (void*)st2);
-      if (rc != DPR1_OK) return rc;
-      TCHECK(hipMemcpyAsync(mirB.data(), w + L.lamr, mirB.size(), hipMemcpyDeviceToHost, st2));
-      TCHECK(hipStreamSynchronize(st2));
-      memcpy(lamr.data(), mirB.data() + (L.lamr - L.lamr), 8 * mtot);
-      memcpy(mur.data(), mirB.data() + (L.mur - L.lamr), 8 * mtot);
-      memcpy(xnr.data(), mirB.data() + (L.xnr - L.lamr), 8 * mtot);
-      memcpy(sidx.data(), mirB.data() + (L.sidx - L.lamr), 4 * mtot);
-      memcpy(infop.data(), mirB.data() + (L.infop - L.lamr), 4 * nprob);
-      for (int32_t x : infop)
-        if (x != DPR1_INFO_OK) return tri_set_info(info, x, st);
     }
+    put(mirA, L.rd, L.rd, rd.data(), 8 * mtot);
+    put(mirA, L.rd, L.rz, rz.data(), 8 * mtot);
+    put(mirA, L.rd, L.rhop, rhop.data(), 8 * nprob);
+    put(mirA, L.rd, L.offsp, offs.data(), 8 * (nprob + 1));
+    put(mirA, L.rd, L.mtab, mtab.data(), sizeof(MTab) * mtab.size());
+    put(mirA, L.rd, L.csrc, csrc.data(), sizeof(CSrc) * csrc.size());
+    TCHECK(hipMemcpyAsync(w + L.rd, mirA.data(), L.csrc + sizeof(CSrc) * csrc.size() - L.rd, hipMemcpyHostToDevice,
+                          st2));
+    if (nprob > 0) {
+      const int rc = dpr1_eig_batched(&plan, (int64_t*)(w + L.offsp), drd, (double*)(w + L.rz),
+                                      (double*)(w + L.rhop), dlr, nullptr, nullptr, dsi, dmu, dxn,
+                                      (int32_t*)(w + L.infop), nullptr, w + L.solver, L.solver_bytes, (void*)st2);
+      if (rc != DPR1_OK) return rc;
+    }
+    // (the tables' last reader, the depth below's assembly, has finished: its
+    // z rows are on the host)
+    hipLaunchKernelGGL(k_tri_columns, dim3((unsigned)cdiv(smax, 256), (unsigned)lv.size()), dim3(256), 0, st2,
+                       (const MTab*)(w + L.mtab), (const CSrc*)(w + L.csrc), (const double*)drd, (const double*)dlr,
+                       (const int32_t*)dsi, (const double*)dmu, (const double*)dxn, (double*)(w + L.lamn),
+                       (int32_t*)ta.ckind, (int32_t*)ta.cidx, (int32_t*)ta.ct, (double*)ta.csig, (double*)ta.cmu,
+                       (double*)ta.cic, (double*)ta.cub);
+    TCHECK(hipGetLastError());
+    TCHECK(hipEventRecord(fin.solved, st2));
 
-    // 4. columns of every merge, the new eigenvalues, the assembly and GEMM tables
+    // 4. the assembly and GEMM tables
     put(mirC, L.zl, L.zl, hz.data(), 8 * n);     // z as reduced
     put(mirC, L.zl, L.dl, hpole.data(), 8 * n);  // the merges' poles (grouped)
     anodes.clear();
@@ -919,26 +994,9 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     gtab.clear();
     zit.clear();
     int64_t voff = 0;
-    hnew = hlam;
     for (size_t p = 0; p < lv.size(); ++p) {
       const Node& nd = *lv[p];
       const int64_t o = nd.start, s = nd.size;
-      fe::merge_cols(mcols[p], lamr.data() + roff[p], rcnt[p], all, &scr);
-      for (int64_t c = 0; c < s; ++c) {
-        const fe::Col& q = all[c];
-        hnew[o + c] = q.val;
-        hkind[o + c] = q.kind;
-        hidx[o + c] = q.idx;
-        hct[o + c] = q.t;
-        hub[o + c] = q.ub;
-        hsig[o + c] = hmu[o + c] = hic[o + c] = 0.0;
-        if (q.kind == COL_REDUCED) {
-          const int64_t k = roff[p] + q.idx;
-          hsig[o + c] = rd[roff[p] + sidx[k]];
-          hmu[o + c] = mur[k];
-          hic[o + c] = 1.0 / xnr[k];
-        }
-      }
       const int32_t q = (int32_t)anodes.size();
       anodes.push_back({o, s, voff});
       for (int32_t cg = 0; cg < (int32_t)cdiv(s, TA_CB); ++cg)
@@ -972,17 +1030,9 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     if (voff > L.maxV || (int64_t)atab.size() > L.maxAsm || (int64_t)gtab.size() > L.maxTiles ||
         (int64_t)zit.size() > L.maxZ)
       return -10;
-    hlam.swap(hnew);
     put(mirC, L.zl, L.rgrp, hgrp.data(), 4 * n);
     put(mirC, L.zl, L.rpos, hpos.data(), 4 * n);
     put(mirC, L.zl, L.ru, hru.data(), 8 * n);
-    put(mirC, L.zl, L.ckind, hkind.data(), 4 * n);
-    put(mirC, L.zl, L.cidx, hidx.data(), 4 * n);
-    put(mirC, L.zl, L.ct, hct.data(), 4 * n);
-    put(mirC, L.zl, L.csig, hsig.data(), 8 * n);
-    put(mirC, L.zl, L.cmu, hmu.data(), 8 * n);
-    put(mirC, L.zl, L.cic, hic.data(), 8 * n);
-    put(mirC, L.zl, L.cub, hub.data(), 8 * n);
     put(mirC, L.zl, L.anodes, anodes.data(), sizeof(ANode) * anodes.size());
     put(mirC, L.zl, L.atab, atab.data(), sizeof(int4) * atab.size());
     put(mirC, L.zl, L.gdesc, gdesc.data(), sizeof(GDesc) * gdesc.size());
@@ -996,6 +1046,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     int4* datab = (int4*)(w + L.atab);
     GDesc* dgdesc = (GDesc*)(w + L.gdesc);
     int4* dgtab = (int4*)(w + L.gtab);
+    TCHECK(hipStreamWaitEvent(st, fin.solved, 0));
     hipLaunchKernelGGL(k_tri_assemble, dim3((unsigned)atab.size()), dim3(TA_T), 0, st, danodes, datab, ta);
     TCHECK(hipGetLastError());
     // the parents' z rows (after the assembly, which reads this depth's z
@@ -1011,6 +1062,16 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     // 5. Q = diag(Q1, Q2) V for every merge
     hipLaunchKernelGGL(k_dgemm, dim3((unsigned)gtab.size()), dim3(GNT), 0, st, dgdesc, dgtab);
     TCHECK(hipGetLastError());
+    // the new eigenvalues, for the next depth, and the solve's reports
+    TCHECK(hipMemcpyAsync(mirB.data(), w + L.lamn, L.infop + 4 * nprob - L.lamn, hipMemcpyDeviceToHost, st2));
+    TCHECK(hipStreamSynchronize(st2));
+    for (int64_t p = 0; p < nprob; ++p) {
+      int32_t x;
+      memcpy(&x, mirB.data() + (L.infop - L.lamn) + 4 * p, 4);
+      if (x != DPR1_INFO_OK) return tri_set_info(info, x, st);
+    }
+    for (const Node* nd : lv)
+      memcpy(hlam.data() + nd->start, mirB.data() + 8 * nd->start, 8 * nd->size);
   }
   // the eigenvalues once, after the root merge (no kernel reads them)
   if (!nodes.empty()) TCHECK(hipMemcpyAsync(lambda, hlam.data(), 8 * n, hipMemcpyHostToDevice, st));
