@@ -61,11 +61,11 @@ struct Node {
 };
 
 // Blocks of at most LEAF rows are not split: k_leaf solves them (below), where
-// every entry of T is 0 or within 2^+-LEAF_EXP.  Beyond that the merges go down
-// to 1 x 1 blocks: their solver refuses what leaves its range (DPR1_INFO_RANGE
-// from about 2^-950 and 2^900 on), which rotations would answer.
+// every entry of T is 0 or within [LEAF_MIN, LEAF_MAX].  Beyond that the merges
+// go down to 1 x 1 blocks: their solver refuses what leaves its range
+// (DPR1_INFO_RANGE from about 2^-950 and 2^900 on), which rotations would answer.
 constexpr int64_t LEAF = 32;
-constexpr int LEAF_EXP = 450;
+constexpr double LEAF_MIN = 0x1p-450, LEAF_MAX = 0x1p450;
 struct Leaf {
   int32_t start, size, side, pad;
 };
@@ -776,7 +776,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
   // leaves: the diagonal after every split's modification (staged in lambda)
   bool ranged = true;
   auto in_range = [](double x) {
-    return x == 0.0 || (std::fabs(x) >= std::ldexp(1.0, -LEAF_EXP) && std::fabs(x) <= std::ldexp(1.0, LEAF_EXP));
+    return x == 0.0 || (std::fabs(x) >= LEAF_MIN && std::fabs(x) <= LEAF_MAX);
   };
   for (double x : ha) ranged = ranged && in_range(x);
   for (double x : hb) ranged = ranged && in_range(x);
@@ -798,9 +798,6 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
                      b, lambda, Q, ldq, Qw, n, zl);
   TCHECK(hipGetLastError());
   std::vector<double> hzleaf(n);
-  TCHECK(hipMemcpyAsync(hlam.data(), lambda, 8 * n, hipMemcpyDeviceToHost, st));
-  TCHECK(hipMemcpyAsync(hzleaf.data(), zl, 8 * n, hipMemcpyDeviceToHost, st));
-  TCHECK(hipStreamSynchronize(st));
 
   double* dl = (double*)(w + L.dl);
   TArgs ta;
@@ -849,11 +846,18 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     if (bytes) memcpy(mir.data() + (off - base), src, bytes);
   };
   hipStream_t st2 = tri_aux_stream();
-  if (!st2) return DPR1_EHIP;
+  if (!st2) {
+    (void)hipStreamSynchronize(st);  // the copies above read the host's arrays
+    return DPR1_EHIP;
+  }
   TriDone fin{st, st2};
   TCHECK(hipEventCreateWithFlags(&fin.ev, hipEventDisableTiming));
   TCHECK(hipEventCreateWithFlags(&fin.solved, hipEventDisableTiming));
   bool zpending = false;  // rows of this depth's z in flight to hzr (event fin.ev)
+  // the leaves' eigenvalues and z rows (the staging above is set up meanwhile)
+  TCHECK(hipMemcpyAsync(hlam.data(), lambda, 8 * n, hipMemcpyDeviceToHost, st));
+  TCHECK(hipMemcpyAsync(hzleaf.data(), zl, 8 * n, hipMemcpyDeviceToHost, st));
+  TCHECK(hipStreamSynchronize(st));
 
   for (int D = maxd; D >= 0; --D) {
     std::vector<const Node*> lv;
