@@ -37,6 +37,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <memory>
 #include <vector>
 
 #include "../../include/dpr1.h"
@@ -3455,6 +3456,7 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   // the queue, and the far-field records: item e's own record is e, the wide
   // level's lie behind the queue's
   std::vector<int4> items, witems;
+  items.reserve(N / WAVE + nprob);
   FarHdr hdr{0, nwide, (int64_t)(L0.total + al(8 * (size_t)FAR_REC * nwide))};
   const int64_t rec0 = N / WAVE + nprob;
   for (int32_t p : order) {
@@ -3473,31 +3475,30 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax);
   // blocks of the eigenvector kernel: (problem, first column, columns,
   // first row), in memory order
-  std::vector<int4> groups;
   const int cb = batch_columns(nprob, offs_host);
-  groups.reserve(count_groups(nprob, offs_host, cb));
+  const int64_t ngroups = count_groups(nprob, offs_host, cb);
+  // [far header, items, groups] in one copy: each from pageable memory costs
+  // some 15 us (a tridiagonal solve of n = 4096, a plan per depth, 3310 us with
+  // three, 3255 with one; n = 300 823 and 785)
+  const size_t h0 = L0.ctr + FAR_HDR, bytes = L0.groups + sizeof(int4) * ngroups - h0;
+  std::unique_ptr<char[]> mir(new char[bytes]);
+  memcpy(mir.get(), &hdr, sizeof hdr);
+  memcpy(mir.get() + (L0.items - h0), items.data(), sizeof(int4) * nitems);
+  int4* groups = (int4*)(mir.get() + (L0.groups - h0));
   for (int32_t p = 0; p < nprob; ++p) {
     const int64_t np = offs_host[p + 1] - offs_host[p];
     const int g = group_columns(np, cb);
     for (int64_t c0 = 0; c0 < np; c0 += g)
       for (int64_t r0 = 0; r0 < np; r0 += VEC_ROWS)
-        groups.push_back(make_int4(p, (int)c0, (int)std::min<int64_t>(g, np - c0), (int)r0));
+        *groups++ = make_int4(p, (int)c0, (int)std::min<int64_t>(g, np - c0), (int)r0);
   }
   hipStream_t st = (hipStream_t)stream;
-  // [far header, items, groups] in one copy: each from pageable memory costs
-  // some 15 us (a tridiagonal solve of n = 4096, a plan per depth, 3310 us with
-  // three, 3255 with one; n = 300 823 and 785)
-  const size_t h0 = L0.ctr + FAR_HDR;
-  std::vector<char> mir(L0.groups + sizeof(int4) * groups.size() - h0);
-  memcpy(mir.data(), &hdr, sizeof hdr);
-  memcpy(mir.data() + (L0.items - h0), items.data(), sizeof(int4) * nitems);
-  memcpy(mir.data() + (L0.groups - h0), groups.data(), sizeof(int4) * groups.size());
-  HIPCHECK(hipMemcpyAsync((char*)work + h0, mir.data(), mir.size(), hipMemcpyHostToDevice, st));
+  HIPCHECK(hipMemcpyAsync((char*)work + h0, mir.get(), bytes, hipMemcpyHostToDevice, st));
   if (nwide)
     HIPCHECK(hipMemcpyAsync((char*)work + hdr.wide_off, witems.data(), sizeof(int4) * nwide, hipMemcpyHostToDevice,
                             st));
   HIPCHECK(hipStreamSynchronize(st));
-  plan->ngroups = (int64_t)groups.size();
+  plan->ngroups = ngroups;
   plan->nprob = nprob;
   plan->ntotal = N;
   plan->nitems = nitems;
