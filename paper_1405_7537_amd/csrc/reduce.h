@@ -167,7 +167,8 @@ inline void reduce(const double* hd, const double* hz, int64_t n, bool zero_all,
 
 // Both lists are decreasing: merge the deflated/reflected columns with the
 // reduced eigenvalues lamr[0..m) (deflated and reflected first among equal
-// values).
+// values).  k_tri_columns and k_front_columns do this on the GPU; this form is
+// their reference in the host test.
 inline void merge_cols(const std::vector<Col>& cols, const double* lamr, int64_t m, std::vector<Col>& out,
                        Scratch* scratch = nullptr) {
   Scratch local;
