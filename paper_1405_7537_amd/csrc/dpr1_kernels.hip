@@ -42,10 +42,10 @@
 
 #include "../../include/dpr1.h"
 #include "dd.h"
+#include "far_sizes.h"
 
 namespace dpr1 {
 
-constexpr int WAVE = 64;
 constexpr int MAXW = 16;
 constexpr double GROW = 1.0 + 0x1p-40;
 
@@ -602,7 +602,6 @@ __device__ __forceinline__ void model_step(double m, double g, double Spz, doubl
 // 1.3e-16 both, ||x|| 1.3e-16 against 1.7e-16).
 constexpr int FAR_P = 48, FAR_Q = 24, FAR_ND = 26;
 constexpr double FAR_T = 2.5;
-constexpr int FAR_WIDE = 8;  // blocks of 64 eigenvalues that share a wide record
 // record: m_q (FAR_P), their low parts (FAR_Q), the moments of the
 // magnitudes sum zeta_j^2/|d_j - t| (FAR_ND), c, iR, the window a, b, and the
 // number of poles in the level
@@ -700,22 +699,6 @@ __device__ __forceinline__ void far_reduce(double (&h)[32], double (&l)[32], int
   } else {
     h[0] = h[0] + oh;
   }
-}
-
-constexpr int FAR_BLK = 256, FAR_SLICE = 2048, FAR_NSL_MAX = 1024;
-
-// Orders from which a problem has records, and from which it has the wide
-// level too.  Below FAR_MIN the near window of a block (about 2.5 times its
-// 64 poles) is most of the problem.
-constexpr int FAR_MIN = 384, FAR_MIN2 = 2048;
-static constexpr int64_t far_slices(int64_t n) {
-  const int64_t s = (n + FAR_SLICE - 1) / FAR_SLICE;
-  return s > FAR_NSL_MAX ? FAR_NSL_MAX : s;
-}
-// records of the wide level
-static constexpr int64_t far_wide_records(int64_t n) {
-  if (n < FAR_MIN2) return 0;
-  return ((n + WAVE - 1) / WAVE + FAR_WIDE - 1) / FAR_WIDE * far_slices(n);
 }
 
 // Moments of one (level, group, slice): the block's waves are dealt to the
@@ -3224,7 +3207,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     F.items = A.items;
     F.hdr = (const FarHdr*)(w + L.ctr + FAR_HDR);
     F.work = w;
-    const int64_t blocks = persistent_grid ? std::min<int64_t>(nitems, 2048) : nitems + far_wide_records(N);
+    const int64_t blocks = persistent_grid ? std::min<int64_t>(nitems, 2048) : far_grid(nitems + far_wide_records(N));
     hipLaunchKernelGGL(k_far, dim3((unsigned)blocks), dim3(FAR_BLK), 0, st, F);
   }
   HIPCHECK(hipGetLastError());
