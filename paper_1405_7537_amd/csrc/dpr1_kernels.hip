@@ -2929,7 +2929,7 @@ static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t
 
 // One problem: a record per block of 64 eigenvalues and the wide level's.
 static constexpr Layout layout_single(int64_t n) {
-  return layout(1, n, 0, 0, n < FAR_MIN ? 0 : (n + WAVE - 1) / WAVE + far_wide_records(n));
+  return layout(1, n, 0, 0, n < FAR_MIN ? 0 : (n + WAVE - 1) / WAVE + far_wide_room(n));
 }
 // A batch: records for the whole queue; its wide level lies behind.
 // Halving the columns of the writer's blocks at most doubles a count below
@@ -2945,7 +2945,7 @@ static size_t batch_bytes(const Layout& L, int64_t nwide) {
 }
 static int64_t count_wide(int64_t nprob, const int64_t* offs) {
   int64_t c = 0;
-  for (int64_t p = 0; p < nprob; ++p) c += far_wide_records(offs[p + 1] - offs[p]);
+  for (int64_t p = 0; p < nprob; ++p) c += far_wide_room(offs[p + 1] - offs[p]);
   return c;
 }
 

@@ -5,5 +5,7 @@ extern "C" {
 int64_t shim_far_blocks(int64_t n) {
   return dpr1::far_grid((n + dpr1::WAVE - 1) / dpr1::WAVE + dpr1::far_wide_records(n));
 }
+int64_t shim_far_records(int64_t n) { return dpr1::far_wide_records(n); }
+int64_t shim_far_room(int64_t n) { return dpr1::far_wide_room(n); }
 int64_t shim_far_block_threads(void) { return dpr1::FAR_BLK; }
 }
