@@ -2893,16 +2893,17 @@ __global__ void __launch_bounds__(FIXT) k_remedy(KArgs A) {
 
 // ===================================================================== host
 struct Layout {
-  size_t meta, sd, sz, pairs, z2lo, ii, mu, xs, lam, csig, cinv, fix, vflag, items, groups, part, ctr, far, total;
+  size_t meta, sd, sz, pairs, z2lo, ii, mu, xs, lam, csig, cinv, fix, vflag, items, groups, part, ctr, far, witems,
+      total;
 };
 
 static constexpr size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
-// nrec: far-field records.  A batch's list of wide items (and their records
-// past the queue's) follows L.total; its offset is in the header at FAR_HDR
-// behind the counters.
+// nrec: far-field records; nwide: entries of a batch's list of wide items, whose
+// offset is in the header at FAR_HDR behind the counters.
 constexpr size_t FAR_HDR = 128;
-static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t ngroups, int64_t nrec) {
+static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t ngroups, int64_t nrec,
+                               int64_t nwide) {
   Layout L{};
   size_t o = 0;
   L.meta = o; o = al(o + sizeof(Meta) * nprob);
@@ -2923,30 +2924,23 @@ static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t
   L.items = o; o = al(o + sizeof(int4) * nitems);
   L.groups = o; o = al(o + sizeof(int4) * ngroups);
   L.far = o; o = al(o + 8 * (size_t)FAR_REC * nrec);
+  L.witems = o; o = al(o + sizeof(int4) * nwide);
   L.total = o;
   return L;
 }
 
 // One problem: a record per block of 64 eigenvalues and the wide level's.
 static constexpr Layout layout_single(int64_t n) {
-  return layout(1, n, 0, 0, n < FAR_MIN ? 0 : (n + WAVE - 1) / WAVE + far_wide_room(n));
+  return layout(1, n, 0, 0, n < FAR_MIN ? 0 : (n + WAVE - 1) / WAVE + far_wide_room(n), 0);
 }
-// A batch: records for the whole queue; its wide level lies behind.
-// Halving the columns of the writer's blocks at most doubles a count below
-// VEC_BLOCKS, so 2 VEC_BLOCKS entries hold the table wherever it is not the one
-// of full blocks: the size grows with the problems and their number.
-static Layout layout_batch(int64_t nprob, int64_t N, int64_t ngroups) {
-  ngroups = std::max(ngroups, 2 * VEC_BLOCKS);
-  const int64_t nitems = N / WAVE + nprob;  // upper bound of sum ceil(n_p/64)
-  return layout(nprob, N, nitems, ngroups, nitems);
-}
-static size_t batch_bytes(const Layout& L, int64_t nwide) {
-  return L.total + al(8 * (size_t)FAR_REC * nwide) + al(sizeof(int4) * nwide);
-}
-static int64_t count_wide(int64_t nprob, const int64_t* offs) {
-  int64_t c = 0;
-  for (int64_t p = 0; p < nprob; ++p) c += far_wide_room(offs[p + 1] - offs[p]);
-  return c;
+// A batch, from what its plan holds.  The wide level's records lie behind the
+// queue's.  Halving the columns of the writer's blocks at most doubles a count
+// below VEC_BLOCKS, so 2 VEC_BLOCKS entries hold the table wherever it is not
+// the one of full blocks: the size grows with the problems and their number.
+static int64_t batch_items(int64_t nprob, int64_t N) { return N / WAVE + nprob; }  // >= sum ceil(n_p/64)
+static Layout layout_batch(int64_t nprob, int64_t N, int64_t nmax, int64_t ngroups) {
+  const int64_t nitems = batch_items(nprob, N), nwide = far_batch_wide(N, nmax);
+  return layout(nprob, N, nitems, std::max(ngroups, 2 * VEC_BLOCKS), far_batch_own(N, nmax, nitems) + nwide, nwide);
 }
 
 static void fill_opts(const dpr1_opts* in, dpr1_opts* o) {
@@ -3404,9 +3398,9 @@ size_t dpr1_batched_workspace_size(int64_t nprob, const int64_t* offs_host) {
   if (nprob < 1 || !offs_host || offs_host[0] != 0) return 0;
   for (int64_t p = 0; p < nprob; ++p)
     if (offs_host[p + 1] - offs_host[p] < 1) return 0;
-  int64_t ntotal = offs_host[nprob];
-  return batch_bytes(layout_batch(nprob, ntotal, count_groups(nprob, offs_host, VEC_C)),
-                     count_wide(nprob, offs_host));
+  int64_t nmax = 0;
+  for (int64_t p = 0; p < nprob; ++p) nmax = std::max(nmax, offs_host[p + 1] - offs_host[p]);
+  return layout_batch(nprob, offs_host[nprob], nmax, count_groups(nprob, offs_host, VEC_C)).total;
 }
 
 int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* opts, dpr1_plan* plan,
@@ -3424,9 +3418,8 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   }
   int64_t N = offs_host[nprob];
   if (N > (int64_t)INT32_MAX) return -2;
-  const Layout L0 = layout_batch(nprob, N, count_groups(nprob, offs_host, VEC_C));
-  const int64_t nwide = count_wide(nprob, offs_host);
-  if (work_bytes < batch_bytes(L0, nwide)) return -6;
+  const Layout L0 = layout_batch(nprob, N, nmax, count_groups(nprob, offs_host, VEC_C));
+  if (work_bytes < L0.total) return -6;
   dpr1_opts o;
   fill_opts(opts, &o);
   if (!occ_valid(o.waves_per_simd) || o.mode_b < 0 || o.mode_b > 3) return -3;
@@ -3439,9 +3432,9 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   // the queue, and the far-field records: item e's own record is e, the wide
   // level's lie behind the queue's
   std::vector<int4> items, witems;
-  items.reserve(N / WAVE + nprob);
-  FarHdr hdr{0, nwide, (int64_t)(L0.total + al(8 * (size_t)FAR_REC * nwide))};
-  const int64_t rec0 = N / WAVE + nprob;
+  items.reserve(batch_items(nprob, N));
+  FarHdr hdr{0, 0, (int64_t)L0.witems};
+  const int64_t rec0 = far_batch_own(N, nmax, batch_items(nprob, N));
   for (int32_t p : order) {
     const int64_t np = offs_host[p + 1] - offs_host[p];
     const int nsl = (int)far_slices(np);
@@ -3454,6 +3447,7 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
       items.push_back(make_int4(p, (int)k0, np >= FAR_MIN2 ? (int)(w0 + k0 / (FAR_WIDE * WAVE) * nsl) : -1, nsl));
     if (np >= FAR_MIN) hdr.nown = (int64_t)items.size();
   }
+  const int64_t nwide = hdr.nwide = (int64_t)witems.size();
   int64_t nitems = (int64_t)items.size();
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax);
   // blocks of the eigenvector kernel: (problem, first column, columns,
@@ -3505,7 +3499,7 @@ int dpr1_eig_batched(const dpr1_plan* plan, const int64_t* offs, const double* d
   if (V && !voffs) return -8;
   if (!info) return -12;
   if (!work) return -14;
-  const Layout L = layout_batch(plan->nprob, plan->ntotal, plan->ngroups);
+  const Layout L = layout_batch(plan->nprob, plan->ntotal, plan->nmax, plan->ngroups);
   if (work_bytes < L.total) return -15;
   return launch_solve(L, (char*)work, plan->nprob, plan->ntotal, plan->nmax, offs, 0, d, z, rho, 0.0, lambda, V, voffs, 0,
                       shift_idx, mu, xnorm, info, stats, plan->opts, plan->split, plan->nitems, plan->grid,

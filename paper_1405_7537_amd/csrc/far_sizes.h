@@ -41,6 +41,21 @@ static constexpr int64_t far_wide_room(int64_t n) {
                            std::max<int64_t>(FAR_FILL, FAR_WIDE * far_groups(n)));
 }
 
+// Room for the records of a batch of order sum N, largest order nmax and
+// `items` blocks of 64 eigenvalues, from what a plan holds, so that a solve can
+// check its workspace.  Own records: a problem of order np >= FAR_MIN has
+// ceil(np/64) <= np/64 + 63/64 <= 7 np/384 of them.  Wide level: one of order np
+// >= FAR_MIN2 has ceil(np/512) <= np/512 + 511/512 <= 5 np/2048 groups.
+static constexpr int64_t far_batch_own(int64_t N, int64_t nmax, int64_t items) {
+  return nmax < FAR_MIN ? 0 : std::min<int64_t>(items, 7 * N / 384);
+}
+static constexpr int64_t far_batch_wide(int64_t N, int64_t nmax) {
+  if (nmax < FAR_MIN2) return 0;
+  // no order has more slices than 32768 = 64 groups of 16
+  const int64_t s = std::min<int64_t>((nmax + FAR_SLICE - 1) / FAR_SLICE, 16);
+  return 5 * N * s / 2048;
+}
+
 // Blocks of k_far (FAR_BLK threads each), which loop over the records: one a
 // record up to FAR_GRID, far more than the GPU holds and far below the 2^32
 // threads that a launch may have.

@@ -7,5 +7,8 @@ int64_t shim_far_blocks(int64_t n) {
 }
 int64_t shim_far_records(int64_t n) { return dpr1::far_wide_records(n); }
 int64_t shim_far_room(int64_t n) { return dpr1::far_wide_room(n); }
+int64_t shim_far_min(void) { return dpr1::FAR_MIN; }
+int64_t shim_far_batch_own(int64_t N, int64_t nmax, int64_t items) { return dpr1::far_batch_own(N, nmax, items); }
+int64_t shim_far_batch_wide(int64_t N, int64_t nmax) { return dpr1::far_batch_wide(N, nmax); }
 int64_t shim_far_block_threads(void) { return dpr1::FAR_BLK; }
 }
