@@ -614,8 +614,9 @@ static int tile_of(int64_t n, int64_t nb) {
 }
 static BLayout blayout(int64_t n, int64_t nb) {
   BLayout L;
-  const int tb = tile_of(n, nb);
-  const int64_t nt = (n + tb - 1) / tb;
+  // partials for the smaller tile whichever runs: the size then grows with n
+  // and nb, and a workspace holds every smaller call too
+  const int64_t nt = (n + 63) / 64;
   size_t o = 0;
   L.X = o; o = al(o + sizeof(double) * n * n * nb);
   L.y = o; o = al(o + sizeof(double) * n * nb);

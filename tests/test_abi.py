@@ -185,3 +185,16 @@ def test_single_backward_argument_errors_need_no_gpu(lib):
     assert call(rb=None) == -15
     assert call(w=None) == -16
     assert call(wb=16) == -17
+
+
+def test_backward_workspace_grows_with_the_problem(lib):
+    """A workspace for the largest order and batch of a program holds its smaller calls: the size never falls."""
+    lib.dpr1_backward_workspace_size.argtypes = [ctypes.c_int64, ctypes.c_int64]
+    lib.dpr1_backward_workspace_size.restype = ctypes.c_size_t
+    size = lib.dpr1_backward_workspace_size
+    for nb in (1, 2, 3, 7, 40, 256, 1000):
+        sizes = [size(n, nb) for n in range(1, 4200)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), nb
+    for n in (1, 63, 64, 65, 128, 129, 300, 512, 1000, 1729):
+        sizes = [size(n, nb) for nb in range(1, 700)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), n
