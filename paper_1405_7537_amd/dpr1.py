@@ -8,6 +8,7 @@ present.
 from __future__ import annotations
 
 import ctypes as C
+import math
 import os
 
 import numpy as np
@@ -469,7 +470,7 @@ def _backward_batched(d, z, rho, shift_idx, mu, xnorm, V, lam_bar, V_bar, vb_row
     rc = lib().dpr1_eig_backward_strided(nb, n, _ptr(d), _ptr(z), _ptr(rho), _ptr(shift_idx), _ptr(mu),
                                          _ptr(xnorm), _ptr(V), n, _ptr(lam_bar), _ptr(V_bar), vb_row, vb_col,
                                          _ptr(d_bar), _ptr(z_bar), _ptr(rho_bar), _ptr(work), wb, _stream())
-    _rc(rc, "dpr1_eig_backward_batched")
+    _rc(rc, "dpr1_eig_backward_strided")
     return d_bar, z_bar, rho_bar
 
 
@@ -497,17 +498,20 @@ def backward(d, z, rho, shift_idx, mu, xnorm, V=None, lam_bar=None, V_bar=None, 
     for t in (d, z, shift_idx, mu, xnorm, lam_bar):
         if t is not None:
             assert t.is_contiguous() and t.device == dev
+    rho = float(rho)
+    if rho == 0.0 or not math.isfinite(rho):
+        _rc(-3, "dpr1_eig_backward")           # the strided entry takes rho on the device, where nothing checks it
     if V_bar is not None and V_bar.stride(1) == 1 and V_bar.stride(0) >= n and n > 1:
         # V_bar row by row (as autograd produces it): read in place
-        rho_t = torch.full((1,), float(rho), dtype=torch.float64, device=dev)
+        rho_t = torch.full((1,), rho, dtype=torch.float64, device=dev)
         rc = lib().dpr1_eig_backward_strided(1, n, _ptr(d), _ptr(z), _ptr(rho_t), _ptr(shift_idx), _ptr(mu),
                                              _ptr(xnorm), _ptr(Vc), ldv, _ptr(lam_bar), _ptr(V_bar),
                                              V_bar.stride(0), 1, _ptr(d_bar), _ptr(z_bar), _ptr(rho_bar),
                                              _ptr(work), wb, _stream())
-        _rc(rc, "dpr1_eig_backward")
+        _rc(rc, "dpr1_eig_backward_strided")
         return d_bar, z_bar, rho_bar
     Vbc, ldvb = colmajor(V_bar)
-    rc = lib().dpr1_eig_backward(_ptr(d), _ptr(z), float(rho), n, _ptr(shift_idx), _ptr(mu), _ptr(xnorm), _ptr(Vc),
+    rc = lib().dpr1_eig_backward(_ptr(d), _ptr(z), rho, n, _ptr(shift_idx), _ptr(mu), _ptr(xnorm), _ptr(Vc),
                                  ldv, _ptr(lam_bar), _ptr(Vbc), ldvb, _ptr(d_bar), _ptr(z_bar), _ptr(rho_bar),
                                  _ptr(work), wb, _stream())
     _rc(rc, "dpr1_eig_backward")

@@ -198,3 +198,18 @@ def test_backward_workspace_grows_with_the_problem(lib):
     for n in (1, 63, 64, 65, 128, 129, 300, 512, 1000, 1729):
         sizes = [size(n, nb) for nb in range(1, 700)]
         assert all(a <= b for a, b in zip(sizes, sizes[1:])), n
+
+
+@pytest.mark.parametrize("rho", [0.0, float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("rows", [True, False])
+def test_backward_refuses_rho_in_either_layout(rho, rows):
+    """backward() with V_bar row by row, as autograd hands it over, or column by column: rho = 0 and non-finite
+    ones are argument 3, before anything is launched."""
+    import torch
+
+    import paper_1405_7537_amd.dpr1 as D
+    n = 5
+    v = torch.ones(n, dtype=torch.float64)
+    M = torch.eye(n, dtype=torch.float64)
+    with pytest.raises(RuntimeError, match=r"dpr1_eig_backward failed: -3"):
+        D.backward(v, v, rho, torch.zeros(n, dtype=torch.int32), v, v, M.t(), v, M if rows else M.t())
