@@ -30,6 +30,8 @@
 #include <cstring>
 
 #include "../../include/dpr1.h"
+#define DPR1_HD __device__ __forceinline__
+#include "columns.h"
 
 namespace dpr1 {
 namespace gen {
@@ -473,9 +475,9 @@ __global__ void __launch_bounds__(FR) k_front_reduce(int64_t n, const double* d,
 }
 
 // The columns in decreasing order of their eigenvalues, those of the reduction
-// first among equal ones: both lists are decreasing, so a column's place is its
-// own index plus its rank in the other list.
-__global__ void __launch_bounds__(256) k_front_columns(int64_t n, int64_t m, FrontCols fc, const double* rd,
+// first among equal ones.
+__global__ void __launch_bounds__(256) k_front_columns(int64_t n, int64_t m, bool neg, FrontCols fc,
+                                                       const double* rd,
                                                        const double* lamr, const int32_t* sidx, const double* mu,
                                                        const double* xn, const int32_t* inf, double* lambda,
                                                        int32_t* info, bool vectors, int32_t* cgrp, int32_t* ct,
@@ -485,19 +487,9 @@ __global__ void __launch_bounds__(256) k_front_columns(int64_t n, int64_t m, Fro
   if (t == 0) info[0] = code;
   if (t >= n || code != 0) return;  // the solve left its outputs unspecified
   const bool red = t < m;
-  const int64_t own = red ? t : t - m, cnt = red ? n - m : m;
+  const int64_t own = red ? t : t - m;
   const double v = red ? lamr[own] : fc.val[own];
-  const double* other = red ? fc.val : lamr;
-  int64_t lo = 0, hi = cnt;  // entries of the other list that come first
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) / 2;
-    const double x = other[mid];
-    if (red ? x >= v : x > v)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  const int64_t c = own + lo;
+  const int64_t c = column_place(t, n, m, lamr, rd, neg, [&](int64_t q) { return fc.val[q]; });
   lambda[c] = v;
   if (!vectors) return;
   cgrp[c] = red ? -1 : fc.grp[own];
@@ -633,7 +625,7 @@ static int front_end(const double* d, const double* z, double rho, int64_t n, do
                             w + L.solver, dpr1_workspace_size(m), (void*)st);
     if (rc != DPR1_OK) return rc;
   }
-  hipLaunchKernelGGL(k_front_columns, rows, dim3(256), 0, st, n, m, fc, (const double*)rd, (const double*)f64(L.lamr),
+  hipLaunchKernelGGL(k_front_columns, rows, dim3(256), 0, st, n, m, rho < 0.0, fc, (const double*)rd, (const double*)f64(L.lamr),
                      (const int32_t*)i32(L.sidx), (const double*)f64(L.mu), (const double*)f64(L.xn),
                      (const int32_t*)i32(L.inf), lambda, info, V != nullptr, i32(L.cgrp), i32(L.ct), f64(L.csig),
                      f64(L.cmu), f64(L.cic), f64(L.cub));

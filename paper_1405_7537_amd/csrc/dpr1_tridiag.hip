@@ -44,6 +44,8 @@
 #include <vector>
 
 #include "../../include/dpr1.h"
+#define DPR1_HD __device__ __forceinline__
+#include "columns.h"
 #include "dd.h"
 #include "reduce.h"
 
@@ -439,8 +441,8 @@ __global__ void __launch_bounds__(TA_T) k_tri_assemble(const ANode* __restrict__
 
 // The columns of every merge of a depth and the new eigenvalues (block (x, p):
 // 256 columns of merge p): the eigenvalues of the reduced problem and the
-// columns of the reduction, both decreasing, the latter first among equal
-// values, so a column's place is its own index plus its rank in the other list.
+// columns of the reduction in decreasing order, the latter first among equal
+// values.
 // On the solver's stream right behind the solve, so that the assembly and the
 // product need not wait for the host (a call: n = 4096 3615 us with the order
 // and the tables made on the host, 3300 so; n = 8192 15.3 ms and 14.6); the host
@@ -450,7 +452,7 @@ __global__ void __launch_bounds__(TA_T) k_tri_assemble(const ANode* __restrict__
 struct MTab {
   int32_t start, size;
   int32_t roff, rcnt;  // the reduced problem's offset and order
-  int32_t soff, pad;   // offset of the reduction's columns
+  int32_t soff, neg;   // offset of the reduction's columns; beta < 0
 };
 struct CSrc {
   double val, ub;
@@ -469,16 +471,8 @@ __global__ void __launch_bounds__(256) k_tri_columns(const MTab* tab, const CSrc
   const CSrc* src = csrc + m.soff;
   const double* lam = lamr + m.roff;
   const double v = red ? lam[own] : src[own].val;
-  int lo = 0, hi = red ? m.size - m.rcnt : m.rcnt;  // entries of the other list that come first
-  while (lo < hi) {
-    const int mid = (lo + hi) / 2;
-    const double x = red ? src[mid].val : lam[mid];
-    if (red ? x >= v : x > v)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  const int64_t c = (int64_t)m.start + own + lo;
+  const int64_t c = m.start + column_place(t, m.size, m.rcnt, lam, rd + m.roff, m.neg != 0,
+                                           [&](int64_t q) { return src[q].val; });
   lamn[c] = v;
   CSrc e = {0.0, 0.0, COL_REDUCED, own, 0, 0};
   double sg = 0.0, u = 0.0, ic = 0.0;
@@ -952,7 +946,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
     int64_t smax = 0;
     for (size_t p = 0; p < lv.size(); ++p) {
       mtab.push_back({(int32_t)lv[p]->start, (int32_t)lv[p]->size, (int32_t)roff[p], (int32_t)rcnt[p],
-                      (int32_t)csrc.size(), 0});
+                      (int32_t)csrc.size(), hb[lv[p]->start + lv[p]->m - 1] < 0.0});
       for (const fe::Col& q : mcols[p]) csrc.push_back({q.val, q.ub, q.kind, q.idx, q.t, 0});
       smax = std::max(smax, lv[p]->size);
     }
