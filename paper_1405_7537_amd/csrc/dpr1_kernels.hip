@@ -585,7 +585,11 @@ __device__ __forceinline__ void model_step(double m, double g, double Spz, doubl
 // (Chebyshev expansion of 1/(D - x) on [-1, 1]; geometric in u).  A pole is
 // far when |D| >= FAR_T = 2.5, so |u| <= 1/4.79 and FAR_P = 48 orders leave
 // less than 2^-106 of the sum of magnitudes; orders below FAR_Q = 24 are
-// accumulated in double-double, the others (below 2^-54 of it) in binary64.
+// accumulated in double-double, the others (together below 2^-52 of it) in
+// binary64.  The tip takes all 48.  The shift test and the passes that only
+// steer take FAR_ND = 26: values to 2^-56, slopes to 2^-46 (worst at the end of
+// the interval away from a pole at the cut).  The accurate pass, whose slope
+// gives ||x||, takes FAR_NA = 31: values to 2^-68, slopes to 2^-57.
 // The moments cost about 450 instructions per pole and block instead of the
 // 64 x 71 of the direct sums, and what the eigenvalue kernel does per
 // eigenvalue no longer grows with n.  A second, wide level (FAR_WIDE blocks
@@ -600,7 +604,7 @@ __device__ __forceinline__ void model_step(double m, double g, double Spz, doubl
 // against 3560 us.  Errors of lambda, mu, ||x|| and V against an extended-
 // precision root are those of the direct sums (rms over 26 distributions: mu
 // 1.3e-16 both, ||x|| 1.3e-16 against 1.7e-16).
-constexpr int FAR_P = 48, FAR_Q = 24, FAR_ND = 26;
+constexpr int FAR_P = 48, FAR_Q = 24, FAR_ND = 26, FAR_NA = 31;
 constexpr double FAR_T = 2.5;
 // record: m_q (FAR_P), their low parts (FAR_Q), the moments of the
 // magnitudes sum zeta_j^2/|d_j - t| (FAR_ND), c, iR, the window a, b, and the
@@ -882,13 +886,13 @@ __global__ void __launch_bounds__(FAR_BLK, 2) k_far(FarArgs F) {
 
 // Values of an expansion held in LDS (the layout of a record) by Clenshaw's
 // recurrence, differentiated for the slopes.
-// The orders FAR_ND-1 .. 1 (26 - 1 = 5 x 5) run in fives, whose coefficients
-// are loaded together: one LDS latency per five steps.
-template <class F>
+// The orders P-1 .. 1 (26 - 1 = 5 x 5, 31 - 1 = 6 x 5) run in fives, whose
+// coefficients are loaded together: one LDS latency per five steps.
+template <int P, class F>
 __device__ __forceinline__ void far_orders(const double* cf, F&& step) {
-  static_assert((FAR_ND - 1) % 5 == 0, "orders in fives");
+  static_assert((P - 1) % 5 == 0, "orders in fives");
 #pragma unroll 1
-  for (int c = FAR_ND - 5; c >= 1; c -= 5) {
+  for (int c = P - 5; c >= 1; c -= 5) {
     double k[5];
 #pragma unroll
     for (int u = 0; u < 5; ++u) k[u] = cf[c + u];
@@ -933,13 +937,15 @@ __device__ __forceinline__ void far_eval(const double* cf, double x, double& f, 
   f2 = __builtin_fma(x, h1, p1 - h2);
   fa = __builtin_fma(x, m1, cf[FR_ABS] - m2);
 }
-// the divided difference f[x, y], and f', f''/2 and the third derivative / 6 at y
+// the divided difference f[x, y], and f', f''/2 and the third derivative / 6 at
+// y, from P orders
+template <int P>
 __device__ __forceinline__ void far_diff(const double* cf, double x, double y, double& fxy, double& f1, double& f2,
                                          double& f3) {
   const double x2 = 2.0 * x, y2 = 2.0 * y;
   double a1 = 0.0, a2 = 0.0, c1 = 0.0, c2 = 0.0;
   double b1 = 0.0, b2 = 0.0, p1 = 0.0, p2 = 0.0, h1 = 0.0, h2 = 0.0, g1 = 0.0, g2 = 0.0;
-  far_orders(cf, [&](double k) {
+  far_orders<P>(cf, [&](double k) {
     const double c0 = __builtin_fma(y2, c1, __builtin_fma(2.0, a1, -c2));
     const double a0 = __builtin_fma(x2, a1, k - a2);
     const double g0 = __builtin_fma(y2, g1, __builtin_fma(2.0, h1, -g2));
@@ -1002,6 +1008,11 @@ __device__ __forceinline__ dd far_value(const double* cf, dd x, double& fa) {
   fa = __builtin_fma(x.hi, m1, km - m2);
   return dd_add_same(dd_add_same(dd{kh, kl}, dd_neg(B2)), dd_mul(x, B1));
 }
+
+template <int P>
+struct Orders {
+  static constexpr int value = P;
+};
 
 // Expansions of one block: the levels that hold poles (their records in LDS,
 // FAR_REC doubles each) and the near window.
@@ -1421,7 +1432,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   // a divided difference of f, and zeta^2/pp^2, zeta^2 delta'/pp^3, zeta^2
   // delta'^2/pp^4 are its derivatives at lambda times powers of |mu|.  The
   // exterior eigenvalue takes its direct sums instead.
-  auto far_sums = [&](double m, double (&v)[4]) {
+  auto far_sums = [&](double m, double (&v)[4], auto orders) {
     v[0] = v[1] = v[2] = v[3] = 0.0;
     if (wv < FF.lev) {
       const double muv = s / m, am = fabs(muv);
@@ -1430,7 +1441,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
         const double ir = q[FR_IR], x = (sigma - q[FR_C]) * ir;
         const double y = interior ? __builtin_fma(muv, ir, x) : x;
         double fxy, f1, f2, f3;
-        far_diff(q, x, y, fxy, f1, f2, f3);
+        far_diff<orders.value>(q, x, y, fxy, f1, f2, f3);
         const double mi = am * ir, ms = muv * ir;  // in units of the half-width
         v[0] = __builtin_fma(fxy, mi, v[0]);
         v[1] = __builtin_fma(f1 * am, mi, v[1]);
@@ -1465,7 +1476,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
           S[0] += t;
         });
         double fs[4];
-        far_sums(m, fs);
+        far_sums(m, fs, Orders<FAR_ND>{});
         S[0] += fs[0];
         wg_sum<1>(S, W, wv, lane, red);
         ++iters;
@@ -1516,7 +1527,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
           S[2] = __builtin_fma(tp, u, S[2]);  // w_j/(m - xi_j)^3
         });
         double fs[4];
-        far_sums(m, fs);
+        far_sums(m, fs, Orders<FAR_ND>{});
         S[0] += fs[0];
         S[1] += fs[1];
         S[2] += fs[2];
@@ -1602,7 +1613,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   });
   {
     double fs[4];
-    far_sums(m, fs);
+    far_sums(m, fs, Orders<FAR_NA>{});
     neu(fs[0]);
     Sp[0] += fs[1];
     Sp[1] += fs[2];
