@@ -970,6 +970,42 @@ __device__ __forceinline__ void far_diff(const double* cf, double x, double y, d
   f2 = __builtin_fma(y, h1, p1 - h2);
   f3 = __builtin_fma(y, g1, h1 - g2);
 }
+// f[x, y] in double-double at double-doubles x, y, from FAR_NA orders: the
+// recurrence of far_diff for the accurate pass, whose sum is carried with its
+// rounding errors
+__device__ __forceinline__ dd far_pair(const double* cf, dd x, dd y) {
+  const double x2 = 2.0 * x.hi, y2 = 2.0 * y.hi;
+  double a1 = 0.0, a2 = 0.0, c1 = 0.0, c2 = 0.0;
+  double k[FAR_NA - FAR_Q];
+#pragma unroll
+  for (int u = 0; u < FAR_NA - FAR_Q; ++u) k[u] = cf[FAR_Q + u];
+#pragma unroll
+  for (int u = FAR_NA - FAR_Q - 1; u >= 0; --u) {
+    const double c0 = __builtin_fma(y2, c1, __builtin_fma(2.0, a1, -c2));
+    const double a0 = __builtin_fma(x2, a1, k[u] - a2);
+    a2 = a1;
+    a1 = a0;
+    c2 = c1;
+    c1 = c0;
+  }
+  const dd X2 = {x2, 2.0 * x.lo}, Y2 = {y2, 2.0 * y.lo};
+  dd A1 = {a1, 0.0}, A2 = {a2, 0.0}, C1 = {c1, 0.0}, C2 = {c2, 0.0};
+  double kh = cf[FAR_Q - 1], kl = cf[FR_LO + FAR_Q - 1];
+#pragma unroll 1
+  for (int q = FAR_Q - 1; q >= 1; --q) {
+    // the next order's coefficients while this one's are used
+    const double nh = cf[q - 1], nl = cf[FR_LO + q - 1];
+    const dd C0 = dd_add_same(dd_add_same(dd{2.0 * A1.hi, 2.0 * A1.lo}, dd_neg(C2)), dd_mul(Y2, C1));
+    const dd A0 = dd_add_same(dd_add_same(dd{kh, kl}, dd_neg(A2)), dd_mul(X2, A1));
+    A2 = A1;
+    A1 = A0;
+    C2 = C1;
+    C1 = C0;
+    kh = nh;
+    kl = nl;
+  }
+  return dd_add_same(dd_add_same(A1, dd_neg(C2)), dd_mul(y, C1));
+}
 // f in double-double at a double-double x, and the sum of magnitudes fa
 __device__ __forceinline__ dd far_value(const double* cf, dd x, double& fa) {
   const double x2 = 2.0 * x.hi;
@@ -1009,9 +1045,9 @@ __device__ __forceinline__ dd far_value(const double* cf, dd x, double& fa) {
   return dd_add_same(dd_add_same(dd{kh, kl}, dd_neg(B2)), dd_mul(x, B1));
 }
 
-template <int P>
-struct Orders {
-  static constexpr int value = P;
+template <bool B>
+struct Bool {
+  static constexpr bool value = B;
 };
 
 // Expansions of one block: the levels that hold poles (their records in LDS,
@@ -1071,20 +1107,40 @@ __device__ __forceinline__ Far far_load(const double* r0, const double* r1, int 
 // The exterior eigenvalue (k = 1) lies outside its block's interval: its sums
 // over the poles outside the near window are taken directly, the block's
 // threads along the poles.  All threads call it; every thread receives the
-// totals.  red: 5 doubles per wave.
+// totals.  COMP: v[0], v[1] are Neumaier partials, combined with TwoSum.  red: 5
+// doubles per wave.
+template <bool COMP>
 __device__ __forceinline__ void ext_total(double (&v)[5], int W, int wv, int lane, double* red) {
+  auto add = [](double (&a)[5], const double (&b)[5]) {
+    if (COMP) {
+      const dd t = two_sum(a[0], b[0]);
+      a[0] = t.hi;
+      a[1] = a[1] + b[1] + t.lo;
+    } else {
+      a[0] += b[0];
+      a[1] += b[1];
+    }
+    a[2] += b[2];
+    a[3] += b[3];
+    a[4] += b[4];
+  };
+  for (int o = 32; o > 0; o >>= 1) {
+    double x[5];
 #pragma unroll
-  for (int q = 0; q < 5; ++q)
-    for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o);
+    for (int q = 0; q < 5; ++q) x[q] = __shfl_xor(v[q], o);
+    add(v, x);
+  }
   __syncthreads();
   if (lane == 0)
     for (int q = 0; q < 5; ++q) red[5 * wv + q] = v[q];
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 5; ++q) {
-    double s = red[q];
-    for (int w = 1; w < W; ++w) s += red[5 * w + q];
-    v[q] = s;
+  for (int q = 0; q < 5; ++q) v[q] = red[q];
+  for (int w = 1; w < W; ++w) {
+    double x[5];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) x[q] = red[5 * w + q];
+    add(v, x);
   }
 }
 // f, f', f''/2 of the far poles at sigma + tau
@@ -1103,10 +1159,10 @@ __device__ __forceinline__ void ext_eval(const double* P, int n, const Far& F, d
     v[1] += t * r;
     v[2] = __builtin_fma(t * r, r, v[2]);
   }
-  ext_total(v, W, wv, lane, red);
+  ext_total<false>(v, W, wv, lane, red);
 }
 // the sums of a root-finder pass over the far poles at nu = m (s = 1):
-// sum zeta^2/(delta pp) (Neumaier partials of each thread), and those of
+// sum zeta^2/(delta pp) (Neumaier sum in v[0], v[1]), and those of
 // zeta^2/pp^2, zeta^2 delta/pp^3, zeta^2 delta^2/pp^4
 __device__ __forceinline__ void ext_sums(const double* P, int n, const Far& F, double sigma, double m, double (&v)[5],
                                          int W, int wv, int lane, double* red) {
@@ -1131,7 +1187,7 @@ __device__ __forceinline__ void ext_sums(const double* P, int n, const Far& F, d
     v[3] += tp3;
     v[4] = __builtin_fma(tp3, u, v[4]);
   }
-  ext_total(v, W, wv, lane, red);
+  ext_total<true>(v, W, wv, lane, red);
 }
 
 // One block of 64 eigenvalues (k0 .. k0+63) of problem p, W waves.  r0, r1: the
@@ -1431,19 +1487,35 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   // waves add 0): with mu = s/m, zeta^2/(delta' pp) = |mu| zeta^2/((d - sigma)(d - lambda)),
   // a divided difference of f, and zeta^2/pp^2, zeta^2 delta'/pp^3, zeta^2
   // delta'^2/pp^4 are its derivatives at lambda times powers of |mu|.  The
-  // exterior eigenvalue takes its direct sums instead.
-  auto far_sums = [&](double m, double (&v)[4], auto orders) {
-    v[0] = v[1] = v[2] = v[3] = 0.0;
-    if (wv < FF.lev) {
-      const double muv = s / m, am = fabs(muv);
-      for (int l = wv; l < FF.lev; l += W) {
-        const double* q = FF.cf + l * FAR_REC;
-        const double ir = q[FR_IR], x = (sigma - q[FR_C]) * ir;
+  // exterior eigenvalue takes its direct sums instead.  `last`: the accurate
+  // pass, where the first sum comes in double-double (its low part in v0l),
+  // as the near poles' does, and the slopes from more orders, each a wave's
+  // job (in one wave 2.5 % of a call at n = 32768, 4 % at 1501).
+  auto far_sums = [&](double m, double (&v)[4], double& v0l, auto last) {
+    constexpr bool LAST = decltype(last)::value;
+    v[0] = v[1] = v[2] = v[3] = v0l = 0.0;
+    const int jobs = LAST ? 2 * FF.lev : FF.lev;
+    if (wv < jobs) {
+      const dd ad = LAST ? dd_div(dd{1.0, 0.0}, dd{m, 0.0}) : dd{fabs(s / m), 0.0};
+      const double am = ad.hi, muv = s * am;
+      for (int l = wv; l < jobs; l += W) {
+        const bool pair = LAST && l >= FF.lev;
+        const double* q = FF.cf + (pair ? l - FF.lev : l) * FAR_REC;
+        const double ir = q[FR_IR];
+        if (pair) {
+          const dd X = dd_mul_d(two_sum(sigma, -q[FR_C]), ir), md = dd_mul_d(ad, ir);
+          const dd Y = interior ? dd_add(X, dd{s * md.hi, s * md.lo}) : X;
+          const dd t = dd_add_same(dd{v[0], v0l}, dd_mul(far_pair(q, X, Y), md));
+          v[0] = t.hi;
+          v0l = t.lo;
+          continue;
+        }
+        const double x = (sigma - q[FR_C]) * ir;
         const double y = interior ? __builtin_fma(muv, ir, x) : x;
-        double fxy, f1, f2, f3;
-        far_diff<orders.value>(q, x, y, fxy, f1, f2, f3);
         const double mi = am * ir, ms = muv * ir;  // in units of the half-width
-        v[0] = __builtin_fma(fxy, mi, v[0]);
+        double fxy, f1, f2, f3;
+        far_diff<LAST ? FAR_NA : FAR_ND>(q, x, y, fxy, f1, f2, f3);
+        if (!LAST) v[0] = __builtin_fma(fxy, mi, v[0]);
         v[1] = __builtin_fma(f1 * am, mi, v[1]);
         v[2] = __builtin_fma(__builtin_fma(ms, f2, f1) * am, am * mi, v[2]);
         v[3] = __builtin_fma(__builtin_fma(ms, __builtin_fma(ms, f3, 2.0 * f2), f1) * am, am * (am * mi), v[3]);
@@ -1454,7 +1526,8 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
       ext_sums(P, n, FF, lane_value(sigma, 0), lane_value(m, 0), e, W, wv, lane, er);
       if (lane == 0) {
         const bool first = wv == 0;
-        v[0] = first ? e[0] + e[1] : 0.0;
+        v[0] = first ? e[0] : 0.0;
+        v0l = first ? e[1] : 0.0;
         v[1] = first ? e[2] : 0.0;
         v[2] = first ? e[3] : 0.0;
         v[3] = first ? e[4] : 0.0;
@@ -1475,9 +1548,9 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
           if (seg == 1 && j == i) t = 0.0;
           S[0] += t;
         });
-        double fs[4];
-        far_sums(m, fs, Orders<FAR_ND>{});
-        S[0] += fs[0];
+        double fs[4], fl;
+        far_sums(m, fs, fl, Bool<false>{});
+        S[0] += fs[0] + fl;
         wg_sum<1>(S, W, wv, lane, red);
         ++iters;
       }
@@ -1526,9 +1599,9 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
           S[1] += tp;
           S[2] = __builtin_fma(tp, u, S[2]);  // w_j/(m - xi_j)^3
         });
-        double fs[4];
-        far_sums(m, fs, Orders<FAR_ND>{});
-        S[0] += fs[0];
+        double fs[4], fl;
+        far_sums(m, fs, fl, Bool<false>{});
+        S[0] += fs[0] + fl;
         S[1] += fs[1];
         S[2] += fs[2];
         wg_sum<3>(S, W, wv, lane, red);
@@ -1612,9 +1685,10 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
     Sp[2] = __builtin_fma(tp3, u, Sp[2]);               // zeta_j^2 delta'_j^2/pp^4
   });
   {
-    double fs[4];
-    far_sums(m, fs, Orders<FAR_NA>{});
+    double fs[4], fl;
+    far_sums(m, fs, fl, Bool<true>{});
     neu(fs[0]);
+    cc += fl;
     Sp[0] += fs[1];
     Sp[1] += fs[2];
     Sp[2] += fs[3];

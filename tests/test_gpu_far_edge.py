@@ -64,3 +64,43 @@ def test_norm_of_a_heavy_pole_beyond_the_cut(D):
         worst = max(worst, solve(D, dist, lane, frac, 1e-6, j)[1])
     print(f"  worst {worst:.2f} eps")
     assert worst <= 5.0
+
+
+@pytest.mark.parametrize("light", [5e-4, 1e-3])
+def test_mu_beside_a_heavy_pole_beyond_the_cut(D, light):
+    """The heavy pole is most of the secular sum and of its slope.  The expansions' part is exact to far below eps;
+    the light poles' corrected quotients (2 eps) are at most half of the slope: 1 eps; the root's last step and mu =
+    s/nu are rounded once each: 1 eps."""
+    worst = 0.0
+    for j, (dist, lane, frac) in enumerate(POINTS):
+        if light * 111 > 0.4 * min(frac, 1 - frac):  # (the gap's own poles would take most of the slope)
+            continue
+        print(f"[far edge] mu {light} {dist} lane {lane} at {frac}", flush=True)
+        worst = max(worst, solve(D, dist, lane, frac, light, j)[0])
+    print(f"  worst {worst:.2f} eps")
+    assert worst <= 2.0
+
+
+@pytest.mark.parametrize("n", [500, 1500, 3000])
+@pytest.mark.parametrize("near", [0.3, 0.1, 0.01])
+def test_exterior_eigenvalue(D, n, near):
+    """The exterior eigenvalue's far sums are direct, along the block's threads, and the poles near it lighter than
+    the far ones.  mu: the last step and s/nu rounded once each, 1 eps; the terms' errors, 2 eps each at most, average
+    over 100 or more: 0.3 eps."""
+    worst = 0.0
+    for seed in range(12):
+        rng = np.random.default_rng(seed)
+        d = np.sort(rng.uniform(-1.0, 1.0, n))[::-1].copy()
+        z = rng.uniform(0.5, 1.5, n)
+        z[:150] *= near
+        rho = 10.0 ** rng.uniform(-3, 1)
+        r = D.eig(d, z, rho, vectors=False)
+        mu = ld(float(r.mu[0]))
+        delta, z2, m = d.astype(ld) - ld(d[int(r.shift_idx[0])]), z.astype(ld) ** 2, mu
+        for _ in range(4):
+            t = z2 / (delta - m)
+            f, fp = 1 + ld(rho) * t.sum(), ld(rho) * (t / (delta - m)).sum()
+            m = m - m * f / (f + m * fp)
+        worst = max(worst, float(abs(mu - m) / abs(m) / EPS))
+    print(f"[far edge] exterior n={n} near={near} worst {worst:.2f} eps", flush=True)
+    assert worst <= 1.3
