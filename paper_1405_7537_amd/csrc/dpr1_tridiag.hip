@@ -101,10 +101,12 @@ static void modify_diag(std::vector<double>& a, const std::vector<double>& b, in
 
 // --------------------------------------------------------------- kernels
 // A leaf: all eigenpairs of a symmetric tridiagonal block T of at most LEAF
-// rows by Jacobi rotations in LDS.  Round robin order: 31 steps a sweep of 16
-// disjoint pairs; thread (i, j) of 16 x 16 carries the 2 x 2 block of pairs i
-// and j and two rows of V from one buffer to the other, so a step has one
-// barrier; every wave computes the 16 rotations for itself.  A step is bound by
+// rows by Jacobi rotations in LDS.  Round robin order: N - 1 steps a sweep of
+// N/2 disjoint pairs, N the rows rounded up to even (always 31 steps of 16
+// pairs, and sums over 32 rows below, took 60 us for a block of one row); thread
+// (i, j) of 16 x 16 carries the 2 x 2 block of pairs i and j and two rows of V
+// from one buffer to the other, so a step has one barrier; every wave computes
+// all rotations for itself.  A step is bound by
 // the latency of its rotation (tangent from the hardware's reciprocals, cosine
 // refined to full precision).  An element within 2^-56 ||T|| or 2^-32 of the
 // difference of its diagonal entries stays; a sweep without a rotation is the
@@ -127,21 +129,22 @@ __device__ __forceinline__ void leaf_add(dd& a, dd t) {
   a = fast_two_sum(y.hi, y.lo + (a.lo + t.lo));
 }
 // (V^T V)_ij - [i = j]
-__device__ __forceinline__ double leaf_gram(const double* V, int ld, int i, int j) {
+__device__ __forceinline__ double leaf_gram(const double* V, int ld, int s, int i, int j) {
   dd g = {i == j ? -1.0 : 0.0, 0.0};
-  for (int k = 0; k < LEAF; ++k) leaf_add(g, two_prod(V[k * ld + i], V[k * ld + j]));
+  for (int k = 0; k < s; ++k) leaf_add(g, two_prod(V[k * ld + i], V[k * ld + j]));
   return g.hi + g.lo;
 }
 
 __global__ void __launch_bounds__(256) k_leaf(const Leaf* leaves, const double* diag, const double* off, double* lam,
                                               double* Q, int64_t ldq, double* Qw, int64_t ldw, double* zl) {
-  constexpr int LD = LEAF + 1, NP = LEAF / 2, NR = LEAF - 1;
+  constexpr int LD = LEAF + 1, NP = LEAF / 2;
   __shared__ double As[2][LEAF * LD], Vs[2][LEAF * LD];
   __shared__ double ta[LEAF], tb[LEAF], ev[LEAF], sg[LEAF];
   __shared__ int rank[LEAF];
   static_assert(LEAF == 32, "256 threads are the 2 x 2 blocks of a block of 32 rows");
   const Leaf L = leaves[blockIdx.x];
   const int s = L.size, t = threadIdx.x;
+  const int np = (s + 1) / 2, nr = 2 * np - 1;  // pairs, steps of a sweep
   const int64_t o = L.start;
   if (t < LEAF) {
     ta[t] = t < s ? diag[o + t] : 0.0;
@@ -152,21 +155,22 @@ __global__ void __launch_bounds__(256) k_leaf(const Leaf* leaves, const double* 
   for (int k = 0; k < LEAF; ++k) norm = fmax(norm, fmax(fabs(ta[k]), fabs(tb[k])));
   const double tiny = 0x1p-56 * norm;
   for (int e = t; e < LEAF * LEAF; e += 256) {
-    const int i = e / LEAF, j = e % LEAF;  // rows s .. 31: zero, never rotated
+    const int i = e / LEAF, j = e % LEAF;  // row s of an odd block: zero, never rotated
     As[0][i * LD + j] = i == j ? ta[i] : (i == j + 1 ? tb[j] : (j == i + 1 ? tb[i] : 0.0));
     Vs[0][i * LD + j] = i == j ? 1.0 : 0.0;
   }
   __syncthreads();
-  const int bi = t / NP, bj = t % NP, lane0 = t & 48;
+  const int bi = min(t / NP, np - 1), bj = min(t % NP, np - 1), lane0 = t & 48;
+  const bool mine = t / NP < np && t % NP < np;
   int cur = 0;
   for (int sweep = 0; sweep < 20; ++sweep) {
     bool rotated = false;
-    for (int r = 0; r < NR; ++r) {
-      // pair u of step r: 0 and 31 - r, or u + r and 31 - u + r (1 .. 31 in a ring)
-      auto ring = [](int x) { return x >= NR ? x - NR + 1 : x + 1; };
+    for (int r = 0; r < nr; ++r) {
+      // pair u of step r: 0 and nr + r, or u + r and nr - u + r (1 .. nr in a ring)
+      auto ring = [&](int x) { return x >= nr ? x - nr + 1 : x + 1; };
       auto pair = [&](int u, int& p, int& q) {
         p = u == 0 ? 0 : ring(u - 1 + r);
-        q = ring(NR - 1 - u + r);
+        q = ring(nr - 1 - u + r);
       };
       int pi, qi, pj, qj;
       pair(bi, pi, qi);
@@ -176,7 +180,7 @@ __global__ void __launch_bounds__(256) k_leaf(const Leaf* leaves, const double* 
       const double app = A[pj * LD + pj], aqq = A[qj * LD + qj], apq = A[pj * LD + qj];
       const double x00 = A[pi * LD + pj], x01 = A[pi * LD + qj], x10 = A[qi * LD + pj], x11 = A[qi * LD + qj];
       const double v0 = V[bi * LD + pj], w0 = V[bi * LD + qj];
-      const double v1 = V[(bi + NP) * LD + pj], w1 = V[(bi + NP) * LD + qj];
+      const double v1 = V[(bi + np) * LD + pj], w1 = V[(bi + np) * LD + qj];
       double cj = 1.0, sj = 0.0;
       const double df = aqq - app;
       if (fabs(apq) > fmax(tiny, 0x1p-32 * fabs(df))) {
@@ -188,19 +192,21 @@ __global__ void __launch_bounds__(256) k_leaf(const Leaf* leaves, const double* 
         sj = tn * cj;
         rotated = true;
       }
-      const double ci = __shfl(cj, lane0 + bi % NP, 64), si = __shfl(sj, lane0 + bi % NP, 64);
+      const double ci = __shfl(cj, lane0 + bi, 64), si = __shfl(sj, lane0 + bi, 64);
       const double y00 = ci * x00 - si * x10, y01 = ci * x01 - si * x11;
       const double y10 = si * x00 + ci * x10, y11 = si * x01 + ci * x11;
       double* B = As[cur ^ 1];
       double* W = Vs[cur ^ 1];
-      B[pi * LD + pj] = cj * y00 - sj * y01;
-      B[pi * LD + qj] = sj * y00 + cj * y01;
-      B[qi * LD + pj] = cj * y10 - sj * y11;
-      B[qi * LD + qj] = sj * y10 + cj * y11;
-      W[bi * LD + pj] = cj * v0 - sj * w0;
-      W[bi * LD + qj] = sj * v0 + cj * w0;
-      W[(bi + NP) * LD + pj] = cj * v1 - sj * w1;
-      W[(bi + NP) * LD + qj] = sj * v1 + cj * w1;
+      if (mine) {
+        B[pi * LD + pj] = cj * y00 - sj * y01;
+        B[pi * LD + qj] = sj * y00 + cj * y01;
+        B[qi * LD + pj] = cj * y10 - sj * y11;
+        B[qi * LD + qj] = sj * y10 + cj * y11;
+        W[bi * LD + pj] = cj * v0 - sj * w0;
+        W[bi * LD + qj] = sj * v0 + cj * w0;
+        W[(bi + np) * LD + pj] = cj * v1 - sj * w1;
+        W[(bi + np) * LD + qj] = sj * v1 + cj * w1;
+      }
       cur ^= 1;
       __syncthreads();
     }
@@ -210,43 +216,46 @@ __global__ void __launch_bounds__(256) k_leaf(const Leaf* leaves, const double* 
   double* A = As[cur];
   double* E = As[cur ^ 1];
   double* V = Vs[cur];
-  if (t < LEAF) ev[t] = A[t * LD + t];
+  if (t < s) ev[t] = A[t * LD + t];
   __syncthreads();
-  for (int e = t; e < LEAF * LEAF; e += 256) {
+  for (int e = t; e < s * LEAF; e += 256) {
     const int k = e / LEAF, j = e % LEAF;
+    if (j >= s) continue;
     dd w = two_prod(ta[k], V[k * LD + j]);
     if (k > 0) leaf_add(w, two_prod(tb[k - 1], V[(k - 1) * LD + j]));
-    if (k + 1 < LEAF) leaf_add(w, two_prod(tb[k], V[(k + 1) * LD + j]));
+    if (k + 1 < s) leaf_add(w, two_prod(tb[k], V[(k + 1) * LD + j]));
     leaf_add(w, two_prod(-ev[j], V[k * LD + j]));
     A[k * LD + j] = w.hi + w.lo;
   }
   __syncthreads();
-  if (t < LEAF) {
+  if (t < s) {
     double c = 0.0;
-    for (int k = 0; k < LEAF; ++k) c = __builtin_fma(V[k * LD + t], A[k * LD + t], c);
+    for (int k = 0; k < s; ++k) c = __builtin_fma(V[k * LD + t], A[k * LD + t], c);
     ev[t] += c;  // v.v = 1 to some eps, and c is some eps ||T||
   }
   __syncthreads();
   double vmax = 0.0;
-  for (int j = 0; j < LEAF; ++j) vmax = fmax(vmax, fabs(ev[j]));
-  for (int e = t; e < LEAF * LEAF; e += 256) {
+  for (int j = 0; j < s; ++j) vmax = fmax(vmax, fabs(ev[j]));
+  for (int e = t; e < s * LEAF; e += 256) {
     const int i = e / LEAF, j = e % LEAF;
+    if (j >= s) continue;
     const double gap = ev[j] - ev[i];
     double x = 0.0;
     if (i != j && fabs(gap) > 0x1p-20 * vmax) {
-      for (int k = 0; k < LEAF; ++k) x = __builtin_fma(V[k * LD + i], A[k * LD + j], x);
+      for (int k = 0; k < s; ++k) x = __builtin_fma(V[k * LD + i], A[k * LD + j], x);
       x /= gap;
     } else {
-      x = -0.5 * leaf_gram(V, LD, i, j);
+      x = -0.5 * leaf_gram(V, LD, s, i, j);
     }
     E[i * LD + j] = x;
   }
   __syncthreads();
   double* U = Vs[cur ^ 1];
-  for (int e = t; e < LEAF * LEAF; e += 256) {
+  for (int e = t; e < s * LEAF; e += 256) {
     const int i = e / LEAF, j = e % LEAF;
+    if (j >= s) continue;
     double c = 0.0;
-    for (int k = 0; k < LEAF; ++k) c = __builtin_fma(V[i * LD + k], E[k * LD + j], c);
+    for (int k = 0; k < s; ++k) c = __builtin_fma(V[i * LD + k], E[k * LD + j], c);
     U[i * LD + j] = V[i * LD + j] + c;
   }
   V = U;
@@ -791,6 +800,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
   hipLaunchKernelGGL(k_leaf, dim3((unsigned)leaves.size()), dim3(256), 0, st, (const Leaf*)dleaves, (const double*)lambda,
                      b, lambda, Q, ldq, Qw, n, zl);
   TCHECK(hipGetLastError());
+  if (nodes.empty()) return tri_set_info(info, DPR1_INFO_OK, st);  // one block: lambda and Q are the leaf's
   std::vector<double> hzleaf(n);
 
   double* dl = (double*)(w + L.dl);
@@ -1072,7 +1082,7 @@ int dpr1_tridiag_eig(const double* a, const double* b, int64_t n, double* lambda
       memcpy(hlam.data() + nd->start, mirB.data() + 8 * nd->start, 8 * nd->size);
   }
   // the eigenvalues once, after the root merge (no kernel reads them)
-  if (!nodes.empty()) TCHECK(hipMemcpyAsync(lambda, hlam.data(), 8 * n, hipMemcpyHostToDevice, st));
+  TCHECK(hipMemcpyAsync(lambda, hlam.data(), 8 * n, hipMemcpyHostToDevice, st));
   // tri_set_info waits for the stream: the host staging above must outlive
   // its copies
   return tri_set_info(info, DPR1_INFO_OK, st);
