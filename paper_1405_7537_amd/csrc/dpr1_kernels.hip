@@ -886,13 +886,13 @@ __global__ void __launch_bounds__(FAR_BLK, 2) k_far(FarArgs F) {
 
 // Values of an expansion held in LDS (the layout of a record) by Clenshaw's
 // recurrence, differentiated for the slopes.
-// The orders P-1 .. 1 (26 - 1 = 5 x 5, 31 - 1 = 6 x 5) run in fives, whose
+// The orders P-1 .. L (26 - 1 = 5 x 5, 31 - 1 = 6 x 5) run in fives, whose
 // coefficients are loaded together: one LDS latency per five steps.
-template <int P, class F>
+template <int P, int L = 1, class F>
 __device__ __forceinline__ void far_orders(const double* cf, F&& step) {
-  static_assert((P - 1) % 5 == 0, "orders in fives");
+  static_assert((P - L) % 5 == 0, "orders in fives");
 #pragma unroll 1
-  for (int c = P - 5; c >= 1; c -= 5) {
+  for (int c = P - 5; c >= L; c -= 5) {
     double k[5];
 #pragma unroll
     for (int u = 0; u < 5; ++u) k[u] = cf[c + u];
@@ -972,27 +972,27 @@ __device__ __forceinline__ void far_diff(const double* cf, double x, double y, d
 }
 // f[x, y] in double-double at double-doubles x, y, from FAR_NA orders: the
 // recurrence of far_diff for the accurate pass, whose sum is carried with its
-// rounding errors
+// rounding errors.  The orders from FAR_QD on are below 2^-5 of f[x, y] (worst, a
+// pole at the cut seen from the block's other end), so binary64 there leaves 0.1
+// eps; the lower ones take the moments' low parts.  (All orders below FAR_Q in
+// double-double: 2 to 4 % of a batch's time.)
+constexpr int FAR_QD = 6;
 __device__ __forceinline__ dd far_pair(const double* cf, dd x, dd y) {
   const double x2 = 2.0 * x.hi, y2 = 2.0 * y.hi;
   double a1 = 0.0, a2 = 0.0, c1 = 0.0, c2 = 0.0;
-  double k[FAR_NA - FAR_Q];
-#pragma unroll
-  for (int u = 0; u < FAR_NA - FAR_Q; ++u) k[u] = cf[FAR_Q + u];
-#pragma unroll
-  for (int u = FAR_NA - FAR_Q - 1; u >= 0; --u) {
+  far_orders<FAR_NA, FAR_QD>(cf, [&](double k) {
     const double c0 = __builtin_fma(y2, c1, __builtin_fma(2.0, a1, -c2));
-    const double a0 = __builtin_fma(x2, a1, k[u] - a2);
+    const double a0 = __builtin_fma(x2, a1, k - a2);
     a2 = a1;
     a1 = a0;
     c2 = c1;
     c1 = c0;
-  }
+  });
   const dd X2 = {x2, 2.0 * x.lo}, Y2 = {y2, 2.0 * y.lo};
   dd A1 = {a1, 0.0}, A2 = {a2, 0.0}, C1 = {c1, 0.0}, C2 = {c2, 0.0};
-  double kh = cf[FAR_Q - 1], kl = cf[FR_LO + FAR_Q - 1];
+  double kh = cf[FAR_QD - 1], kl = cf[FR_LO + FAR_QD - 1];
 #pragma unroll 1
-  for (int q = FAR_Q - 1; q >= 1; --q) {
+  for (int q = FAR_QD - 1; q >= 1; --q) {
     // the next order's coefficients while this one's are used
     const double nh = cf[q - 1], nl = cf[FR_LO + q - 1];
     const dd C0 = dd_add_same(dd_add_same(dd{2.0 * A1.hi, 2.0 * A1.lo}, dd_neg(C2)), dd_mul(Y2, C1));
@@ -1490,7 +1490,7 @@ __device__ __forceinline__ void eig_block(const KArgs& A, int p, int k0, double*
   // exterior eigenvalue takes its direct sums instead.  `last`: the accurate
   // pass, where the first sum comes in double-double (its low part in v0l),
   // as the near poles' does, and the slopes from more orders, each a wave's
-  // job (in one wave 2.5 % of a call at n = 32768, 4 % at 1501).
+  // job.
   auto far_sums = [&](double m, double (&v)[4], double& v0l, auto last) {
     constexpr bool LAST = decltype(last)::value;
     v[0] = v[1] = v[2] = v[3] = v0l = 0.0;
