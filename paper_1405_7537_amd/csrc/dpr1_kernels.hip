@@ -2719,12 +2719,18 @@ __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
 // only costs its launch (n = 300, 62 us a call against 59).
 constexpr int FIX_HEAD = 64, FIX_TAIL = 448, FIX_SMALL = 256;
 constexpr int64_t FIX_RESIDENT = 1024;  // 256 CUs, 4 blocks each
-// A batch of mean order BATCH_FEW or more: 300 problems of n = 700 .. 800 625 us
-// with BATCH_HEAD and BATCH_TAIL against 647 with 512 in front, 1024 of n = 16 ..
-// 2048 1394 against 1419; smaller ones have more flagged eigenpairs for the
-// elements they write (1000 of n = 130 .. 300 388 against 348).
+// A batch: by the writer's blocks per 64 eigenvalues (4 for problems of n = 257
+// .. 512, 8 above, more where narrow blocks fill the GPU), since that is its
+// work against the flagged eigenpairs'.  512 blocks in front / BATCH_HEAD and
+// BATCH_TAIL, us, uniform (graded) poles: 1000 problems of n = 104 .. 156 208 /
+// 238 (202 / 234), 300 of n = 264 .. 396 270 / 304 (270 / 308), 200 of 480 264 /
+// 274 (335 / 348), 540 297 / 293 (384 / 380), 300 of n = 600 .. 900 625 / 603
+// (799 / 776), 10 of 1000 94 / 92 (132 / 130); 300 of n = 100 .. 700 257 / 285,
+// 1024 of n = 16 .. 2048 1304 / 1288.  The line lies at order 490 (256 graded
+// ones of 512 398 / 383), inside the orders of 4 blocks: so also by the mean
+// order.
 constexpr int FIX_BATCH = 512, BATCH_HEAD = 128, BATCH_TAIL = 384;
-constexpr int64_t BATCH_FEW = 320;
+constexpr int64_t BATCH_FEW = 6, BATCH_FEW_MEAN = 490;
 enum { VEC_BATCH, VEC_ALIGNED, VEC_SHIFTED };
 template <int KIND>
 __global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix, int ntail) {
@@ -3401,7 +3407,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     // flagged eigenpairs, the rest write every other column
     if (persistent_grid) {
       va.groups = (const int4*)(w + L.groups);
-      const bool few = N >= BATCH_FEW * nprob;
+      const bool few = WAVE * ngroups >= BATCH_FEW * N || N >= BATCH_FEW_MEAN * nprob;
       const int nfix = few ? BATCH_HEAD : FIX_BATCH, ntail = few ? BATCH_TAIL : 0;
       hipLaunchKernelGGL(k_fixvec<VEC_BATCH>, dim3((unsigned)(nfix + ngroups + ntail)), dim3(VEC_T), 0, st, A, va,
                          nfix, ntail);
