@@ -158,7 +158,8 @@ typedef struct dpr1_opts {
 
 void dpr1_default_opts(dpr1_opts* opts);
 
-/* Bytes of device workspace dpr1_eig needs for a problem of order n.       */
+/* Bytes of device workspace dpr1_eig needs for a problem of order n: about 190
+ * to 230 a row, never less for more rows.                                   */
 size_t dpr1_workspace_size(int64_t n);
 
 /* All eigenpairs of one DPR1 matrix (Alg. 1 for k = 1..n).
@@ -240,8 +241,8 @@ int dpr1_eig_batched(const dpr1_plan* plan, const int64_t* offs, const double* d
 
 /* Autotuning (not in the paper): the launch shape is chosen by measurement.
  * The candidates are the split W in {1, 2, 4, 8, 12, 16} (waves sharing one
- * block of 64 eigenvalues, i.e. W threads per eigenvalue; every wave's slice
- * of the inner sum keeps at least 64 terms), the register budget
+ * block of 64 eigenvalues, i.e. W threads per eigenvalue; n/W at least 64),
+ * the register budget
  * waves_per_simd in {4, 6, 8}, for the model iteration (root = 1) the pass
  * budget main_passes ({2, 3} single, {2, 3, 4} batched) and, for one problem
  * with eigenvectors at n >= 8192, the write vwrite in {0 (after the
@@ -353,7 +354,8 @@ int dpr1_eig_backward_strided(int64_t nbatch, int64_t n, const double* d, const 
  * Unlike the entry points above this one SYNCHRONISES the host with `stream`:
  * the reduction runs on the device, but the launches of the reduced solve
  * depend on the reduced problem's order, which the host reads back; it returns
- * when the work has finished.  It cannot be captured in a hipGraph.  Returns 0, -p for an invalid argument p, or DPR1_EHIP.         */
+ * when the work has finished.  It cannot be captured in a hipGraph.  Returns
+ * 0, -p for an invalid argument p, or DPR1_EHIP.                            */
 size_t dpr1_general_workspace_size(int64_t n);   /* also for dpr1_eig_hermitian */
 int dpr1_eig_general(const double* d, const double* z, double rho, int64_t n, double* lambda,
                      double* V, int64_t ldv, int32_t* info, const dpr1_opts* opts, void* work,
@@ -380,7 +382,8 @@ int dpr1_eig_hermitian(const double* d, const double* z, double rho, int64_t n, 
  * beta = b there: T = diag(T1 - beta e_m e_m^T, T2 - beta e_1 e_1^T)
  * + beta u u^T, u = e_m + e_{m+1}; the halves are solved recursively down to
  * blocks of at most 32 rows, solved by Jacobi rotations (where an entry is
- * neither 0 nor within 2^+-450: down to 1 x 1), and each merge is the DPR1 problem D = diag(Lambda1, Lambda2),
+ * neither 0 nor within 2^+-450: down to 1 x 1), and each merge is the DPR1
+ * problem D = diag(Lambda1, Lambda2),
  * z = [last row of Q1, first row of Q2], rho = beta, reduced as by
  * dpr1_eig_general (beta = 0 decouples the halves), solved for all merges
  * of one depth in one batched launch, and followed by Q = diag(Q1, Q2) V.

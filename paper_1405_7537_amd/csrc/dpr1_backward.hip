@@ -262,9 +262,9 @@ __global__ void __launch_bounds__(4 * TB, 4) k_gemm(GArgs g) {
     }
   }
 
-  // Epilogue (256 x 512: 20 % of the kernel's instructions beside the matrix
-  // cores; one V load per element in turn and IEEE quotients cost 90 us a
-  // product).  Accumulator element q of a lane holds row lane/16 + 4q,
+  // Epilogue (256 x 512: the matrix cores are busy 60 % of a product's time, other
+  // vector instructions, most of them this, 12 to 18 %; one V load per element in
+  // turn and IEEE quotients cost 90 us a product).  Accumulator element q of a lane holds row lane/16 + 4q,
   // column lane%16 of its 16x16 block (checked on gfx950 with a probe that
   // multiplies A(:,0) = 2^i by B(0,:) = 3^j).  The per-row and per-column
   // quantities of this tile are staged in LDS first; per-row / per-column

@@ -17,11 +17,11 @@
 //              From order FAR_MIN on only the poles near the block's
 //              eigenvalues are summed one by one; the others enter through
 //              expansions whose moments k_far has formed.
-//   k_far   -- moments of the far-field expansions, one per block of 64
-//              eigenvalues and (from FAR_MIN2) one per 512.
 //              Instances for 4, 6 and 8 waves per SIMD (register budgets);
 //              the split W, the budget and the pass count are options that
 //              dpr1_autotune / dpr1_batched_autotune choose by timing.
+//   k_far   -- moments of the far-field expansions, one per block of 64
+//              eigenvalues and (from FAR_MIN2) one per 512.
 //   k_fix   -- one 256-thread block at a time per flagged eigenpair: root
 //              search continued past k_eig's pass budget, double-double
 //              Newton polish, and the near-zero recomputation of eq. (gamma).
@@ -599,11 +599,11 @@ __device__ __forceinline__ void model_step(double m, double g, double Spz, doubl
 // directly), the block's level, the wide level.  The windows come from the
 // poles' positions alone, so any distribution is covered: where poles cluster
 // so that nothing is far, the window is the whole problem.  Bound by FP64
-// issue; measured at n = 32768 (uniform poles): k_far 72 us and k_eig 130 us
-// where the direct sums took 2520 us; the 2048-problem mix 390 and 740 us
-// against 3560 us.  Errors of lambda, mu, ||x|| and V against an extended-
-// precision root are those of the direct sums (rms over 26 distributions: mu
-// 1.3e-16 both, ||x|| 1.3e-16 against 1.7e-16).
+// issue; measured at n = 32768 (uniform poles): k_far 72 us and k_eig 126 us
+// where the direct sums took 2520 us; the 2048-problem mix 400 and 770 us
+// against 3560 us.  Errors against extended precision, all eigenvalues of 17
+// distributions, rms in eps: mu 0.30 to 0.49 (direct sums 0.36 to 0.76), ||x||
+// 0.45 to 0.57 (0.50 to 0.87).
 constexpr int FAR_P = 48, FAR_Q = 24, FAR_ND = 26, FAR_NA = 31;
 constexpr double FAR_T = 2.5;
 // record: m_q (FAR_P), their low parts (FAR_Q), the moments of the
@@ -1862,7 +1862,6 @@ __device__ __forceinline__ dd wave_sum_dd(dd a) {
   }
   return a;
 }
-// Neumaier partials of the lanes, combined in a fixed butterfly order
 
 // Block-wide sums over FIXT threads (4 waves) in a fixed order; every thread
 // receives the total.
@@ -1933,8 +1932,6 @@ __device__ __forceinline__ double block_sum_comp(double s, double c, double* sm)
   return S + C;
 }
 
-// One block of FIXT threads per flagged eigenpair at a time; the inner index
-// is strided over the block and every pass ends in a block-wide sum.
 // The four sums of a continued pass in one exchange: the Neumaier partials
 // (s, c) combined as in block_sum_comp (returned, its compensation in c) and
 // three plain sums a, b, e as in block_sum, with one pair of barriers instead
@@ -2101,6 +2098,8 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
   return cur;
 }
 
+// One block of FIXT threads per flagged eigenpair at a time; the inner index
+// is strided over the block and every pass ends in a block-wide sum.
 // Item e of the list: the n0 long items sit at the front, the others at the
 // back in reverse order.
 __device__ __forceinline__ int fix_slot(const KArgs& A, int n0, int e) {
@@ -2713,10 +2712,11 @@ __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
 // work), then come the blocks that write V (HBM-bound), and the last ntail take
 // what is left of the queue when the writers run out.
 // Where the writers are more than the GPU's places few blocks go in front: 256
-// there hold a quarter of the places for little when few eigenpairs are flagged
-// (n = 8000, 185 us a call against 173 with 64 and 448; every eigenpair
-// flagged, 673 against 517).  Where all blocks are resident together the tail
-// only costs its launch (n = 300, 62 us a call against 59).
+// there hold a quarter of the places for little when few eigenpairs are flagged.
+// Where all blocks are resident together the tail only costs its launch.  A call
+// with FIX_SMALL in front / FIX_HEAD and FIX_TAIL, us: n = 300 57 / 60, 1000 76 / 81,
+// 1400 77 / 82, 1700 83 / 83, 2000 89 / 88, 4000 107 / 103, 8000 181 / 169, 20000
+// 696 / 666; every eigenpair polished, 6000 472 / 361.
 constexpr int FIX_HEAD = 64, FIX_TAIL = 448, FIX_SMALL = 256;
 constexpr int64_t FIX_RESIDENT = 1024;  // 256 CUs, 4 blocks each
 // A batch: by the writer's blocks per 64 eigenvalues (4 for problems of n = 257
@@ -3096,9 +3096,9 @@ static int time_calls(F&& solve, int reps, hipStream_t st, double* ms) {
   return rc;
 }
 
-// Candidate splits for inner length nmax (the largest problem): W waves
-// share one block of 64 eigenvalues (W threads per eigenvalue), and every
-// wave's slice of the inner sum keeps at least 64 terms.  Candidate
+// Candidate splits for the largest order nmax: W waves share one block of 64
+// eigenvalues (W threads per eigenvalue), 64 poles of the problem or more each
+// (they split the near poles, which are fewer from order FAR_MIN on).  Candidate
 // occupancy variants of k_eig: 4, 6 and 8 waves per SIMD.
 static int split_candidates(int64_t nmax, int* out) {
   static const int cand[6] = {1, 2, 4, 8, 12, 16};

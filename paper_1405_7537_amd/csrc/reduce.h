@@ -33,6 +33,8 @@ struct Col {
 // s-th largest d (equal values keep their row order, -0 and +0 are equal).
 // LSD radix sort on order-preserving 64-bit keys, 11 bits a pass (a pass
 // whose digit is the same for every key is skipped); insertion sort up to 256.
+// For reduce without sorted runs: the host test's reference of k_front_sort's
+// order (the driver's merges have two sorted runs).
 inline void sort_decreasing(const double* d, int64_t n, std::vector<int64_t>& order) {
   if (n <= 256) {
     // small problems (the many merges near the leaves of a divide and
