@@ -2098,6 +2098,51 @@ __device__ double dd_polish(const double2* Z2v, const double* Zl, int n, int i, 
   return cur;
 }
 
+// The polish of the exterior eigenvalue (k = 1): mu = lambda_1 - d_1 from
+// rho sum zeta_j^2/(mu + (d_1 - d_j)) = 1, whose terms all have one sign, so
+// that nothing cancels whatever mu against the poles' spread.  (g cancels by
+// mu/spread: in double-double a ratio beyond 1e16 left any point of the bracket,
+// up to n times off.)  The reciprocal of the sum is concave in mu and close to linear
+// from mu = spread on: Newton's steps on it come from the left after the first, two or
+// three in all.  cur: the start; returns mu.
+__device__ double ext_polish(const double2* Z2v, const double* Zl, int n, double sigma, double zi2, double zz,
+                             double rho, double cur, int* steps, double* sm) {
+  double lo = rho * zi2 / GROW, hi = rho * zz * GROW;
+  if (!(cur > lo && cur < hi)) cur = fmid(lo, hi);
+  int pit;
+  for (pit = 0; pit < 100; ++pit) {
+    dd acc = {0.0, 0.0};
+    double s2 = 0.0, unused = 0.0;
+    fix_poles<4, true>(Z2v, Zl, n, [&](int, double dj, double z2, double z2l, bool in) {
+      const dd den = dd_add_same(two_sum(sigma, -dj), dd{cur, 0.0});
+      const double r = rcp_1nr(den.hi);
+      const double q1 = z2 * r;
+      double e = __builtin_fma(-q1, den.hi, z2);
+      e = __builtin_fma(-q1, den.lo, e + z2l);
+      if (!in) return;
+      acc = dd_add_same(acc, fast_two_sum(q1, e * r));
+      s2 += q1 * r;
+    });
+    acc = block_sum_polish(acc, s2, unused, sm);
+    const dd S = dd_mul_d(acc, rho), h = dd_add(S, dd{-1.0, 0.0});
+    if (h.hi == 0.0) break;
+    if (h.hi > 0.0) lo = cur; else hi = cur;
+    const double step = (S.hi / (rho * s2)) * (h.hi + h.lo);
+    double t = cur + step;
+    const bool last = fabs(step) <= 0x1p-36 * cur;
+    if (!(t >= lo && t <= hi)) {
+      if (adjacent(lo, hi)) break;
+      t = fmid(lo, hi);
+    } else if (last) {
+      cur = t;
+      break;
+    }
+    cur = t;
+  }
+  *steps = pit;
+  return cur;
+}
+
 // One block of FIXT threads per flagged eigenpair at a time; the inner index
 // is strided over the block and every pass ends in a block-wide sum.
 // Item e of the list: the n0 long items sit at the front, the others at the
@@ -2217,15 +2262,18 @@ __device__ void fix_items(const KArgs& A) {
     }
 
     if (pol) {
-      const dd bdd = {it.bhi, it.blo};
-      const double xm = (k > 0) ? 1.0 / (Dv[k - 1] - Dv[k]) : 0.0;
-      double cur = nu1;
-      if (!(cur > it.lo && cur < it.hi)) cur = nu0;
-      double last;
-      const double zjm = (k > 0) ? Zv[i == k ? k - 1 : k] : 0.0;
-      const double sw = (k > 0) ? fabs(zjm * xm) / fabs(zi) : 0.0;
-      cur = dd_polish(Z2v, Zl, n, i, s, sigma, zi, bdd, xm, sw, it.lo, it.hi, cur, false, &last, &pit, sm);
-      muv = s / cur;
+      if (k == 0) {
+        muv = ext_polish(Z2v, Zl, n, sigma, zi2, M.zz, rho, 1.0 / nu1, &pit, sm);
+      } else {
+        const dd bdd = {it.bhi, it.blo};
+        const double xm = 1.0 / (Dv[k - 1] - Dv[k]);
+        double cur = nu1;
+        if (!(cur > it.lo && cur < it.hi)) cur = nu0;
+        double last;
+        const double sw = fabs(Zv[i == k ? k - 1 : k] * xm) / fabs(zi);
+        cur = dd_polish(Z2v, Zl, n, i, s, sigma, zi, bdd, xm, sw, it.lo, it.hi, cur, false, &last, &pit, sm);
+        muv = s / cur;
+      }
       lam = sigma + muv;
       polished = true;
       if (A.nearzero > 0) {
