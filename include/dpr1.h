@@ -217,7 +217,8 @@ int dpr1_eig_noalloc(const double* d, const double* z, double rho, int64_t n, do
  *   batch with these host offsets (0 if the offsets are invalid).
  * dpr1_batched_plan: reads the host offsets (offs_host[0] = 0, sizes >= 1),
  *   builds the work queue and the launch shape, copies the queue into the
- *   workspace and synchronises `stream` (the only host->device copy and the
+ *   workspace (a large table of the eigenvector kernel's blocks is made there
+ *   by a kernel) and synchronises `stream` (the only host->device copy and the
  *   only synchronisation of the batched path).  The plan struct (host memory,
  *   caller-owned) is then passed to every solve of that batch shape; the
  *   solve can be repeated or captured in a hipGraph with the same workspace.

@@ -2745,6 +2745,31 @@ static int64_t tile_blocks(int64_t n, int64_t columns) {
 // The eigenvector writer alone (single problem, a range of columns); launched
 // with VEC_PAD bytes of LDS, which leave 4 blocks per CU.
 constexpr size_t VEC_PAD = 28 << 10;
+// The writer's table of a batch, in memory order, from an entry a problem:
+// (its first block, columns a block, order).  Made and copied by the host it was
+// most of a large plan, us: the 2048-problem mix (100 000 blocks) 300 against
+// 117, one problem of n = 32768 143 / 26, 8 of 8000 85 / 26; 256 of 512 (8192
+// blocks) 30 / 30, and below a kernel costs more than it saves (100 of 300 17 /
+// 22, 64 of 64 15 / 21): PLAN_HOST.
+constexpr int64_t PLAN_HOST = 8192;
+__global__ void __launch_bounds__(256) k_plan_groups(int nprob, int ngroups, const int4* __restrict__ prob,
+                                                     int4* __restrict__ groups) {
+  const int e = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (e >= ngroups) return;
+  int lo = 0, hi = nprob - 1;  // the last problem whose first block is not behind e
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (prob[mid].x <= e)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  const int4 q = prob[lo];
+  const int rt = (q.z + VEC_ROWS - 1) / VEC_ROWS, l = e - q.x;
+  const int c0 = l / rt * q.y, r0 = l % rt * VEC_ROWS;
+  groups[e] = make_int4(lo, c0, min(q.y, q.z - c0), r0);
+}
+
 template <bool SH>
 __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
   // beside the eigenvalue kernel of the next chunk its waves issue first, so
@@ -3032,8 +3057,8 @@ __global__ void __launch_bounds__(FIXT) k_remedy(KArgs A) {
 
 // ===================================================================== host
 struct Layout {
-  size_t meta, sd, sz, pairs, z2lo, ii, mu, xs, lam, csig, cinv, fix, vflag, items, groups, part, ctr, far, witems,
-      total;
+  size_t meta, sd, sz, pairs, z2lo, ii, mu, xs, lam, csig, cinv, fix, vflag, prob, items, witems, groups, part, ctr,
+      far, total;
 };
 
 static constexpr size_t al(size_t x) { return (x + 255) & ~size_t(255); }
@@ -3059,11 +3084,12 @@ static constexpr Layout layout(int64_t nprob, int64_t N, int64_t nitems, int64_t
   L.fix = o; o = al(o + sizeof(FixItem) * N);
   L.vflag = o; o = al(o + N);
   L.part = o; o = al(o + 3 * sizeof(double) * PREP_MAX_SPLIT);
-  L.ctr = o; o = al(o + FAR_HDR + sizeof(FarHdr));  // the plan's header, queue and groups: one copy
+  L.ctr = o; o = al(o + FAR_HDR + sizeof(FarHdr));  // the plan's header, problems, queue and wide items: one copy
+  L.prob = o; o = al(o + (nitems ? sizeof(int4) * nprob : 0));
   L.items = o; o = al(o + sizeof(int4) * nitems);
+  L.witems = o; o = al(o + sizeof(int4) * nwide);
   L.groups = o; o = al(o + sizeof(int4) * ngroups);
   L.far = o; o = al(o + 8 * (size_t)FAR_REC * nrec);
-  L.witems = o; o = al(o + sizeof(int4) * nwide);
   L.total = o;
   return L;
 }
@@ -3168,18 +3194,22 @@ static int group_columns(int64_t np, int cb) {
   while (cb > VEC_C_MIN && cb * std::min<int64_t>(np, VEC_ROWS) > VEC_ELEMS) cb /= 2;
   return cb;
 }
+static int64_t group_blocks(int64_t np, int g) {  // (g a power of two: a plan may have many problems)
+  return ((np + g - 1) >> __builtin_ctz(g)) * ((np + VEC_ROWS - 1) / VEC_ROWS);
+}
 static int64_t count_groups(int64_t nprob, const int64_t* offs, int cb) {
   int64_t c = 0;
   for (int64_t p = 0; p < nprob; ++p) {
     const int64_t np = offs[p + 1] - offs[p];
-    const int g = group_columns(np, cb);
-    c += ((np + g - 1) / g) * ((np + VEC_ROWS - 1) / VEC_ROWS);
+    c += group_blocks(np, group_columns(np, cb));
   }
   return c;
 }
-static int batch_columns(int64_t nprob, const int64_t* offs) {
+// The columns of a batch's blocks; full: the number of full ones, which becomes
+// the number of blocks.
+static int batch_columns(int64_t nprob, const int64_t* offs, int64_t& full) {
   int cb = VEC_C;
-  while (cb > 4 && count_groups(nprob, offs, cb) < VEC_BLOCKS) cb /= 2;
+  while (cb > 4 && full < VEC_BLOCKS) full = count_groups(nprob, offs, cb /= 2);
   return cb;
 }
 
@@ -3557,7 +3587,8 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   }
   int64_t N = offs_host[nprob];
   if (N > (int64_t)INT32_MAX) return -2;
-  const Layout L0 = layout_batch(nprob, N, nmax, count_groups(nprob, offs_host, VEC_C));
+  int64_t ngroups = count_groups(nprob, offs_host, VEC_C);
+  const Layout L0 = layout_batch(nprob, N, nmax, ngroups);
   if (work_bytes < L0.total) return -6;
   dpr1_opts o;
   fill_opts(opts, &o);
@@ -3565,9 +3596,10 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   // longest-processing-time order: larger problems first
   std::vector<int32_t> order(nprob);
   for (int64_t p = 0; p < nprob; ++p) order[p] = (int32_t)p;
-  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+  const auto larger = [&](int32_t a, int32_t b) {
     return offs_host[a + 1] - offs_host[a] > offs_host[b + 1] - offs_host[b];
-  });
+  };
+  if (!std::is_sorted(order.begin(), order.end(), larger)) std::stable_sort(order.begin(), order.end(), larger);
   // the queue, and the far-field records: item e's own record is e, the wide
   // level's lie behind the queue's
   std::vector<int4> items, witems;
@@ -3576,7 +3608,7 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   const int64_t rec0 = far_batch_own(N, nmax, batch_items(nprob, N));
   for (int32_t p : order) {
     const int64_t np = offs_host[p + 1] - offs_host[p];
-    const int nsl = (int)far_slices(np);
+    const int nsl = np >= FAR_MIN2 ? (int)far_slices(np) : 1;
     const int64_t w0 = rec0 + (int64_t)witems.size();
     if (np >= FAR_MIN2)
       for (int64_t k0 = 0; k0 < np; k0 += FAR_WIDE * WAVE)
@@ -3589,31 +3621,42 @@ int dpr1_batched_plan(int64_t nprob, const int64_t* offs_host, const dpr1_opts* 
   const int64_t nwide = hdr.nwide = (int64_t)witems.size();
   int64_t nitems = (int64_t)items.size();
   int W = o.split > 0 ? std::min(o.split, MAXW) : pick_split(nitems, nmax);
-  // blocks of the eigenvector kernel: (problem, first column, columns,
-  // first row), in memory order
-  const int cb = batch_columns(nprob, offs_host);
-  const int64_t ngroups = count_groups(nprob, offs_host, cb);
-  // [far header, items, groups] in one copy: each from pageable memory costs
-  // some 15 us (a tridiagonal solve of n = 4096, a plan per depth, 3310 us with
-  // three, 3255 with one; n = 300 823 and 785)
-  const size_t h0 = L0.ctr + FAR_HDR, bytes = L0.groups + sizeof(int4) * ngroups - h0;
+  // the eigenvector kernel's blocks
+  const int cb = batch_columns(nprob, offs_host, ngroups);
+  const bool on_host = ngroups <= PLAN_HOST;
+  // [far header, problems, items, wide items, groups] in one copy: each from
+  // pageable memory costs some 15 us (a tridiagonal solve of n = 4096, a plan
+  // per depth, 3310 us with three, 3255 with one; n = 300 823 and 785)
+  const size_t h0 = L0.ctr + FAR_HDR;
+  const size_t bytes = (on_host ? L0.groups + sizeof(int4) * ngroups
+                        : nwide ? L0.witems + sizeof(int4) * nwide
+                                : L0.items + sizeof(int4) * nitems) - h0;
   std::unique_ptr<char[]> mir(new char[bytes]);
   memcpy(mir.get(), &hdr, sizeof hdr);
   memcpy(mir.get() + (L0.items - h0), items.data(), sizeof(int4) * nitems);
-  int4* groups = (int4*)(mir.get() + (L0.groups - h0));
+  if (nwide) memcpy(mir.get() + (L0.witems - h0), witems.data(), sizeof(int4) * nwide);
+  int4* prob = (int4*)(mir.get() + (L0.prob - h0));
+  int4* groups = (int4*)(mir.get() + (on_host ? L0.groups - h0 : 0));
+  int64_t g0 = 0;
   for (int32_t p = 0; p < nprob; ++p) {
     const int64_t np = offs_host[p + 1] - offs_host[p];
     const int g = group_columns(np, cb);
-    for (int64_t c0 = 0; c0 < np; c0 += g)
-      for (int64_t r0 = 0; r0 < np; r0 += VEC_ROWS)
-        *groups++ = make_int4(p, (int)c0, (int)std::min<int64_t>(g, np - c0), (int)r0);
+    if (on_host) {
+      for (int64_t c0 = 0; c0 < np; c0 += g)
+        for (int64_t r0 = 0; r0 < np; r0 += VEC_ROWS)
+          *groups++ = make_int4(p, (int)c0, (int)std::min<int64_t>(g, np - c0), (int)r0);
+    } else {
+      prob[p] = make_int4((int)g0, g, (int)np, 0);
+      g0 += group_blocks(np, g);
+    }
   }
   hipStream_t st = (hipStream_t)stream;
   HIPCHECK(hipMemcpyAsync((char*)work + h0, mir.get(), bytes, hipMemcpyHostToDevice, st));
-  if (nwide)
-    HIPCHECK(hipMemcpyAsync((char*)work + hdr.wide_off, witems.data(), sizeof(int4) * nwide, hipMemcpyHostToDevice,
-                            st));
-  HIPCHECK(hipStreamSynchronize(st));
+  if (!on_host && ngroups <= INT32_MAX)  // beyond (64 kB a block) no V fits any memory
+    hipLaunchKernelGGL(k_plan_groups, dim3((unsigned)((ngroups + 255) / 256)), dim3(256), 0, st, (int)nprob,
+                       (int)ngroups, (const int4*)((char*)work + L0.prob), (int4*)((char*)work + L0.groups));
+  const bool launched = hipGetLastError() == hipSuccess;
+  if (hipStreamSynchronize(st) != hipSuccess || !launched) return DPR1_EHIP;
   plan->ngroups = ngroups;
   plan->nprob = nprob;
   plan->ntotal = N;
