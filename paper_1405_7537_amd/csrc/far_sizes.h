@@ -21,7 +21,7 @@ constexpr int FAR_MIN = 384, FAR_MIN2 = 2048;
 // Slices are there to fill the GPU: 2048 poles each, but no more than make
 // FAR_FILL records in all, or 8 a group where the groups alone are many.  With
 // a slice per 2048 poles whatever the order the records were n^2/2^20 (n = 10^6:
-// 798 bytes of workspace a row for them); so they are at most 8 a group above
+// 795 bytes of workspace a row for them); so they are at most 8 a group above
 // n = 65536, 13 bytes a row.
 constexpr int64_t FAR_FILL = 1024;
 static constexpr int64_t far_groups(int64_t n) {
