@@ -2792,18 +2792,24 @@ __global__ void __launch_bounds__(VEC_T) k_vec(VArgs v) {
 // 696 / 666; every eigenpair polished, 6000 472 / 361.
 constexpr int FIX_HEAD = 64, FIX_TAIL = 448, FIX_SMALL = 256;
 constexpr int64_t FIX_RESIDENT = 1024;  // 256 CUs, 4 blocks each
-// A batch: by the writer's blocks per 64 eigenvalues (4 for problems of n = 257
-// .. 512, 8 above, more where narrow blocks fill the GPU), since that is its
-// work against the flagged eigenpairs'.  512 blocks in front / BATCH_HEAD and
-// BATCH_TAIL, us, uniform (graded) poles: 1000 problems of n = 104 .. 156 208 /
-// 238 (202 / 234), 300 of n = 264 .. 396 270 / 304 (270 / 308), 200 of 480 264 /
-// 274 (335 / 348), 540 297 / 293 (384 / 380), 300 of n = 600 .. 900 625 / 603
-// (799 / 776), 10 of 1000 94 / 92 (132 / 130); 300 of n = 100 .. 700 257 / 285,
-// 1024 of n = 16 .. 2048 1304 / 1288.  The line lies at order 490 (256 graded
-// ones of 512 398 / 383), inside the orders of 4 blocks: so also by the mean
-// order.
+// A batch: few blocks in front where its flagged eigenpairs are few (at least one
+// a problem, the exterior one) or little against what the writer has to do, for
+// which its blocks per 64 eigenvalues stand where they are full ones (4 for
+// problems of n = 257 .. 512, 8 above); the line lies at order 490, inside the
+// orders of 4 blocks, so also by the mean order.  512 blocks in front /
+// BATCH_HEAD and BATCH_TAIL, us (graded poles in brackets): 400 problems of n = 64
+// 72 / 86, 100 of 200 82 / 103, 1000 of n = 104 .. 156 208 / 238 (202 / 234), 200 of
+// 300 158 / 207, 300 of n = 264 .. 396 270 / 304 (270 / 308), 200 of 480 264 / 274
+// (335 / 348), 256 of 512 (398 / 383), 200 of 540 297 / 293 (384 / 380), 300 of n =
+// 600 .. 900 625 / 603 (799 / 776); 30 of 200 65 / 62, 30 of 300 72 / 69, 40 of 300
+// 73 / 77, 10 of 1000 94 / 92 (132 / 130); 300 of n = 100 .. 700 257 / 285, 1024 of n = 16 .. 2048
+// 1304 / 1288.
 constexpr int FIX_BATCH = 512, BATCH_HEAD = 128, BATCH_TAIL = 384;
-constexpr int64_t BATCH_FEW = 6, BATCH_FEW_MEAN = 490;
+constexpr int64_t BATCH_FEW = 6, BATCH_FEW_MEAN = 490, BATCH_FEW_PROB = 32;
+static bool batch_few(int64_t nprob, int64_t N, int64_t ngroups) {
+  return nprob <= BATCH_FEW_PROB || N >= BATCH_FEW_MEAN * nprob ||
+         (ngroups > 2 * VEC_BLOCKS && WAVE * ngroups >= BATCH_FEW * N);
+}
 enum { VEC_BATCH, VEC_ALIGNED, VEC_SHIFTED };
 template <int KIND>
 __global__ void __launch_bounds__(VEC_T, 4) k_fixvec(KArgs A, VArgs v, int nfix, int ntail) {
@@ -3485,7 +3491,7 @@ static int launch_solve(const Layout& L, char* w, int64_t nprob, int64_t N, int6
     // flagged eigenpairs, the rest write every other column
     if (persistent_grid) {
       va.groups = (const int4*)(w + L.groups);
-      const bool few = WAVE * ngroups >= BATCH_FEW * N || N >= BATCH_FEW_MEAN * nprob;
+      const bool few = batch_few(nprob, N, ngroups);
       const int nfix = few ? BATCH_HEAD : FIX_BATCH, ntail = few ? BATCH_TAIL : 0;
       hipLaunchKernelGGL(k_fixvec<VEC_BATCH>, dim3((unsigned)(nfix + ngroups + ntail)), dim3(VEC_T), 0, st, A, va,
                          nfix, ntail);
